@@ -20,6 +20,7 @@ _LIB_PATH = os.path.join(_HERE, "libsar.so")
 _SOURCES = {
     "sar_api.hip": [],
     "attn_simple.hip": [],
+    "attn_f32_mfma.hip": [],
     "attn_mfma_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
     "attn_mfma_cols.hip": [],
     "attn_mfma_cols_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],

@@ -143,7 +143,7 @@ sar_status attn_core_fwd(const sar_attn_desc* desc, const void* q, const void* k
     e = sar::launch_attn_fwd_mfma(P, q, k, v, o, lse, (hipStream_t)stream);
   } else {
     if ((st = check_simple_limits(P)) != SAR_OK) return st;
-    e = sar::launch_attn_fwd_simple(P, desc->dtype == SAR_BF16, q, k, v, o, lse, nullptr, nullptr, nullptr, (hipStream_t)stream);
+    e = sar::launch_attn_fwd_f32(P, desc->dtype == SAR_BF16, q, k, v, o, lse, (hipStream_t)stream);
   }
   return e == hipSuccess ? SAR_OK : hip_fail(e, "attn_core_fwd launch");
 }
@@ -211,8 +211,7 @@ static sar_status bwd_recompute_impl(const char* who, const sar_attn_desc* desc,
       e = sar::launch_attn_bwd_mfma(P, q, k, v, o, lse, d_o, dq, dk, dv, (float*)workspace, passes, (hipStream_t)stream);
   } else {
     if ((st = check_simple_limits(P)) != SAR_OK) return st;
-    e = sar::launch_attn_bwd_simple(P, desc->dtype == SAR_BF16, q, k, v, o, lse, d_o, dq, dk, dv, (float*)workspace, nullptr, nullptr, nullptr, passes,
-                                    (hipStream_t)stream);
+    e = sar::launch_attn_bwd_f32(P, desc->dtype == SAR_BF16, q, k, v, o, lse, d_o, dq, dk, dv, (float*)workspace, passes, (hipStream_t)stream);
   }
   return e == hipSuccess ? SAR_OK : hip_fail(e, who);
 }
@@ -295,8 +294,7 @@ sar_status attn_core_bwd_stored(const sar_attn_desc* desc, const void* q, const 
     e = sar::launch_attn_bwd_stored_mfma(P, q, k, v, o, d_o, Pst, Mst, Dst, dq, dk, dv, (float*)workspace, (hipStream_t)stream);
   } else {
     if ((st = check_simple_limits(P)) != SAR_OK) return st;
-    e = sar::launch_attn_bwd_simple(P, desc->dtype == SAR_BF16, q, k, v, nullptr, nullptr, d_o, dq, dk, dv, (float*)workspace, Pst, Mst, Dst, 3,
-                                    (hipStream_t)stream);
+    e = sar::launch_attn_bwd_simple(P, desc->dtype == SAR_BF16, k, v, q, d_o, dq, dk, dv, (float*)workspace, Pst, Mst, Dst, (hipStream_t)stream);
   }
   return e == hipSuccess ? SAR_OK : hip_fail(e, "attn_core_bwd_stored launch");
 }

@@ -37,14 +37,17 @@ struct RowsParams {
   uint64_t offset;
 };
 
-// attn_simple.hip: one-wave-per-row kernels in plain fp32 arithmetic, any d % 4 == 0 up to 256; also the
-// stored-activation baseline (P, M, D written / read).
+// attn_f32_mfma.hip: fp32 matrix instructions, any d % 4 == 0 up to 256: the fp32 dtype, and bf16 that attn_mfma_*.hip do not cover.
+// passes: bit 0 = row pass (dq, writes delta), bit 1 = column pass (dk, dv, reads delta)
+hipError_t launch_attn_fwd_f32(const AttnParams& P, bool bf16, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st);
+hipError_t launch_attn_bwd_f32(const AttnParams& P, bool bf16, const void* q, const void* k, const void* v, const void* o, const float* lse,
+                               const void* dO, void* dq, void* dk, void* dv, float* delta, int passes, hipStream_t st);
+
+// attn_simple.hip: the stored-activation baseline (P, M, D written / read) with one wave per row, any d % 4 == 0 up to 256
 hipError_t launch_attn_fwd_simple(const AttnParams& P, bool bf16, const void* q, const void* k, const void* v, void* o, float* lse,
                                   void* Pst, uint8_t* Mst, void* Dst, hipStream_t st);
-// passes: bit 0 = row pass (dq, writes delta), bit 1 = column pass (dk, dv, reads delta)
-hipError_t launch_attn_bwd_simple(const AttnParams& P, bool bf16, const void* q, const void* k, const void* v, const void* o,
-                                  const float* lse, const void* dO, void* dq, void* dk, void* dv, float* delta,
-                                  const void* Pst, const uint8_t* Mst, const void* Dst, int passes, hipStream_t st);
+hipError_t launch_attn_bwd_simple(const AttnParams& P, bool bf16, const void* k, const void* v, const void* q, const void* dO, void* dq, void* dk, void* dv,
+                                  float* delta, const void* Pst, const uint8_t* Mst, const void* Dst, hipStream_t st);
 size_t attn_simple_lds_bytes(int s);
 
 // attn_mfma_rows.hip (forward, dQ pass) and attn_mfma_cols.hip (dK/dV pass): bf16 MFMA kernels, d in {64, 96, 128, 160}

@@ -108,6 +108,28 @@ def test_fp32_shapes(s, b, a, t, rank, d, p, std, outlier):
     assert np.max(np.abs(got["lse"] - ref["lse"]) / (1.0 + np.abs(ref["lse"]))) < 1e-5
 
 
+@pytest.mark.parametrize("dtype,s,d,p,causal,scale", [
+    ("f32", 8, 4, 0.1, 1, None), ("f32", 24, 20, 0.1, 1, None), ("f32", 32, 32, 0.0, 0, None), ("f32", 40, 36, 0.1, 1, None),    # one or two tiles of 32
+    ("f32", 128, 96, 0.1, 1, None), ("f32", 136, 100, 0.25, 0, None), ("f32", 168, 160, 0.1, 1, None),                           # one tile per wave, one more, two
+    ("f32", 104, 196, 0.1, 1, None), ("f32", 72, 228, 0.1, 0, None), ("f32", 256, 256, 0.1, 1, None),                            # widest heads
+    ("f32", 104, 64, 0.1, 1, -0.2), ("f32", 72, 64, 0.1, 0, 0.0),                                                                # any sign of the score scale
+    ("bf16", 72, 8, 0.1, 1, None), ("bf16", 168, 72, 0.1, 1, None), ("bf16", 136, 256, 0.0, 0, None)])
+def test_fp32_matrix_instruction_kernels(dtype, s, d, p, causal, scale):
+    """The kernels on fp32 matrix instructions where they can go wrong: sequences that end inside a tile of 32, with fewer tiles
+    than waves and one more, head dimensions that are no multiple of 8 or 32, the smallest and the largest, bf16 head
+    dimensions that the bf16 kernels leave to them.  Tolerances: those of the other tests of either dtype."""
+    from gpu_util import run_attn
+    sh = oracle.AttnShape(s=s, b=2, a=4, h=4 * d, t=2, rank=1, p=p, seed=77, offset=(1 << 32) - 50, causal=causal, **({} if scale is None else {"scale": scale}))
+    q, k, v, do = attn_inputs(s, 2, 2, d, dtype, seed=5)
+    print(f"{dtype} s={s} d={d} p={p} causal={causal} scale={scale}", flush=True)
+    got = run_attn(sh, dtype, q, k, v, do)
+    if dtype == "bf16":
+        return _check_bf16_heads("f32-mfma", sh, q, k, v, do, got, range(4))
+    ref = _oracle(sh, q, k, v, do)
+    _check("f32-mfma", got, ref, dtype, ["o", "dq", "dk", "dv"])
+    assert np.max(np.abs(got["lse"] - ref["lse"]) / (1.0 + np.abs(ref["lse"]))) < 1e-5
+
+
 @pytest.mark.parametrize("two_pass", [False, True])
 @pytest.mark.parametrize("d", [64, 96, 128, 160])
 @pytest.mark.parametrize("s,b,A,p,std,causal", [(200, 2, 2, 0.1, None, 1), (328, 1, 3, 0.25, 1.0, 1), (200, 1, 2, 0.1, None, 0), (264, 1, 1, 0.0, 1.0, 0),
