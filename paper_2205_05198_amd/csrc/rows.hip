@@ -37,6 +37,149 @@ template <> struct Vec8<float> {
   }
 };
 
+// 8 consecutive elements as they lie in memory: what a thread holds of a load in flight
+template <typename T> struct Raw8;
+template <> struct Raw8<uint16_t> {
+  uint4 u;
+  __device__ __forceinline__ void load(const uint16_t* p) { u = *reinterpret_cast<const uint4*>(p); }
+  // converted afresh from here on: otherwise the compiler keeps the eight floats of an earlier get() in registers
+  __device__ __forceinline__ void pin() { asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w)); }
+  __device__ __forceinline__ void get(float (&f)[8]) const {
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      f[2 * e] = __uint_as_float(w[e] << 16);
+      f[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
+    }
+  }
+};
+template <> struct Raw8<float> {
+  float4 a, b;
+  __device__ __forceinline__ void load(const float* p) { a = *reinterpret_cast<const float4*>(p); b = *reinterpret_cast<const float4*>(p + 4); }
+  __device__ __forceinline__ void pin() { asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w), "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w)); }
+  __device__ __forceinline__ void get(float (&f)[8]) const {
+    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+  }
+};
+
+// ---------------------------------------------------------------------------------------------------
+// Elementwise passes that also sum every column (bias gradients).  A workgroup of 256 threads owns a block of 8 L columns, L =
+// 2^lg lanes of 8 elements to a row segment, 256 / L segments; its rows are split, split + nsplit, ... in groups of 256 / L, so
+// that all workgroups together walk through the tensor as one contiguous window.  Column sums: registers, then LDS across the
+// segments, then (nsplit > 1) partial sums that colsum_finish_kernel adds.
+//
+// Bound: HBM.  Four workgroups a CU, one row of a thread at a time, measured best or within 1 % of it over bias-GeLU backward of
+// 8192 x 3072 and 2048 x 10240 and bias-dropout backward of 1024 x 6144, 256 and 4096 x 20480 (four rows
+// of a thread in flight and two workgroups a CU: up to 6 % slower for bias-GeLU, equal for bias-dropout).
+// ---------------------------------------------------------------------------------------------------
+constexpr int kColGroups = 1024;  // workgroups to aim at
+struct ColPlan {
+  int lg, ncb, nsplit;  // lanes of a row segment (log2), column blocks, row splits
+};
+static inline ColPlan col_plan(int64_t rows, int64_t h, int nt = 256) {
+  const int64_t nchunk = h >> 3;
+  ColPlan p{3, 0, 1};
+  // Narrow blocks of all rows, with no partial sums and no second launch (2.4 us): at most four trips of a thread, or enough
+  // blocks to fill the chip (LayerNorm backward of 256 x 20480: 12.8 us, split 15.8).
+  if (rows <= nt / 2 || (nchunk >= 1536 && rows <= 512)) {
+    p.ncb = (int)((nchunk + 7) / 8);
+    return p;
+  }
+  for (int lg = 6; lg >= 3; --lg) {  // the widest segment that leaves at most an eighth of the lanes without work
+    const int64_t L = 1 << lg, used = (nchunk + L - 1) / L * L;
+    if (used - nchunk <= nchunk / 8) { p.lg = lg; break; }
+  }
+  const int64_t L = 1 << p.lg;
+  p.ncb = (int)((nchunk + L - 1) / L);
+  const int64_t nseg = nt >> p.lg, most = (rows + nseg - 1) / nseg;
+  // up to four trips of a thread cost less than the launch that adds partial sums
+  p.nsplit = most <= 4 ? 1 : (int)(most * p.ncb <= kColGroups ? most : kColGroups / p.ncb > 1 ? kColGroups / p.ncb : 1);
+  return p;
+}
+
+// op: In (what a row segment loads), column(col) (per column, before the rows), load(row, col), apply(in, row, col, sums)
+template <int NT, typename Op>
+__device__ __forceinline__ void colsum_block(Op& op, int64_t rows, int64_t h, const ColPlan& pl, int block, float (&acc)[Op::kSums][8]) {
+  const int cb = block % pl.ncb, split = block / pl.ncb;
+  const int seg = threadIdx.x >> pl.lg, nseg = NT >> pl.lg;
+  const int64_t chunk = (int64_t)cb << pl.lg | (threadIdx.x & ((1 << pl.lg) - 1));
+#pragma unroll
+  for (int s = 0; s < Op::kSums; ++s)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[s][e] = 0.f;
+  if (chunk >= (h >> 3)) return;
+  const int64_t col = chunk << 3, step = (int64_t)pl.nsplit * nseg;
+  op.column(col);
+  for (int64_t r = (int64_t)split * nseg + seg; r < rows; r += step) op.apply(op.load(r, col), r, col, acc);
+}
+// sums over the segments of a workgroup; the column block's sums go to out[s] + column (a split's partial sums or the result)
+template <int NT, int S>
+__device__ __forceinline__ void colsum_store(const float (&acc)[S][8], float* sb, int64_t h, const ColPlan& pl, int block, float* const (&out)[S]) {
+  const int cb = block % pl.ncb, nseg = NT >> pl.lg, width = 8 << pl.lg;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sb[8 * threadIdx.x + e] = acc[s][e];
+    __syncthreads();
+    for (int c = threadIdx.x; c < width; c += NT) {
+      float t = 0.f;
+      for (int q = 0; q < nseg; ++q) t += sb[q * width + c];
+      const int64_t cc = (int64_t)cb * width + c;
+      if (cc < h) out[s][cc] = t;
+    }
+  }
+}
+template <typename Op>
+__global__ __launch_bounds__(256) void colsum_kernel(Op op, int64_t rows, int64_t h, float* __restrict__ out, ColPlan pl) {
+  __shared__ __attribute__((aligned(16))) float sb[8 * 256];
+  float acc[1][8];
+  colsum_block<256>(op, rows, h, pl, blockIdx.x, acc);
+  float* const dst[1] = {out + (int64_t)(blockIdx.x / pl.ncb) * h};
+  colsum_store<256, 1>(acc, sb, h, pl, blockIdx.x, dst);
+}
+
+// part[nsplit][ncol] -> sums of columns 0 .. h-1 to out0, of the rest to out1.  32 columns a workgroup (8 lanes of 4), 32 groups
+// of splits, four loads in flight each (one thread a column, one load after the other: 11.4 us for 43 splits of 3072 columns).
+__global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restrict__ part, int nsplit, int64_t ncol, int64_t h, float* __restrict__ out0,
+                                                           float* __restrict__ out1) {
+  __shared__ __attribute__((aligned(16))) float4 sb[32][8];
+  const int l = threadIdx.x & 7, g = threadIdx.x >> 3;
+  const int64_t c = (int64_t)blockIdx.x * 32 + 4 * l;
+  float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c < ncol)
+#pragma unroll 4
+    for (int q = g; q < nsplit; q += 32) {
+      const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)q * ncol + c);
+      t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+    }
+  sb[g][l] = t;
+  __syncthreads();
+  if (g == 0 && c < ncol) {
+    for (int q = 1; q < 32; ++q) {
+      const float4 v = sb[q][l];
+      t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+    }
+    float* o = c < h ? out0 + c : out1 + (c - h);  // the caller's array: aligned to a float only
+    o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
+  }
+}
+static hipError_t launch_colsum_finish(const float* part, int nsplit, int64_t ncol, int64_t h, float* out0, float* out1, hipStream_t st) {
+  hipLaunchKernelGGL(colsum_finish_kernel, dim3((unsigned)((ncol + 31) / 32)), dim3(256), 0, st, part, nsplit, ncol, h, out0, out1);
+  return hipGetLastError();
+}
+template <typename Op>
+static hipError_t launch_colsum(const Op& op, int64_t rows, int64_t h, float* out, float* ws, hipStream_t st) {
+  const ColPlan pl = col_plan(rows, h);
+  hipLaunchKernelGGL((colsum_kernel<Op>), dim3((unsigned)(pl.ncb * pl.nsplit)), dim3(256), 0, st, op, rows, h, pl.nsplit == 1 ? out : ws, pl);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || pl.nsplit == 1 ? e : launch_colsum_finish(ws, pl.nsplit, h, h, out, nullptr, st);
+}
+static inline size_t colsum_workspace_bytes(int64_t rows, int64_t h) {
+  const ColPlan pl = col_plan(rows, h);
+  return pl.nsplit > 1 ? (size_t)pl.nsplit * (size_t)h * sizeof(float) : 0;
+}
+
 // block-wide sum of two values; every thread gets the totals.  red must hold 2 * 16 floats.
 __device__ __forceinline__ void block_sum2(float& a, float& b, float* red) {
   a = wave_sum(a);
@@ -100,122 +243,216 @@ __global__ __launch_bounds__(1024) void ln_fwd_kernel(RowsParams P, const T* __r
 }
 
 // ---------------------------------------------------------------------------------------------------
-// LayerNorm backward, one launch with two kinds of workgroups (dgamma / dbeta do not depend on the row sums, so
-// nothing orders the two kinds):
-//   blockIdx <  rows: one row, kept in registers: c1 = mean_c(g), c2 = mean_c(g xhat) with g = dy*gamma, then
-//                     dx = rstd (g - c1 - xhat c2);
-//   blockIdx >= rows: a slab of kLnSlab columns and a contiguous range of rows (kLnSlab/8 lanes cover one row segment,
-//                     8 blockDim/kLnSlab segments per trip): dgamma = sum_r dy xhat, dbeta = sum_r dy of the slab, summed in
-//                     registers, across the lanes of a wave, then across waves in LDS.  The second read of x and dy
-//                     comes out of the caches: the row workgroups stream the same bytes at the same time.
-// part[split][0][h] = dgamma partial, part[split][1][h] = dbeta partial (or the final arrays if there is 1 split).
+// LayerNorm backward: c1 = mean_c(g), c2 = mean_c(g xhat) of a row with g = dy*gamma, dx = rstd (g - c1 - xhat c2);
+// dgamma = sum_r dy xhat, dbeta = sum_r dy.  Two forms:
+//   few rows:  one launch with two kinds of workgroups (dgamma / dbeta do not depend on the row sums, so nothing orders them):
+//              blockIdx <  rows: one row, kept in registers: dx;
+//              blockIdx >= rows: a block of columns and a split of the rows, as in colsum_kernel: dgamma, dbeta.
+//              x and dy are read twice, the second time mostly out of the caches;
+//   many rows: G workgroups that walk through the rows together, each with the dgamma, dbeta sums of its rows in registers:
+//              x and dy are read once, and 2 G rows of fp32 partial sums are written and read back.
+// Bound: HBM and, below about 20 MB a tensor, the two or three memory round trips of a launch.  us before (896 threads a
+// row workgroup, slabs of 64 columns, always two reads) and now: 256 x 20480 15.3 -> 12.8, 512 x 12288 17.5 -> 12.8,
+// 1024 x 6144 18.3 -> 15.5, 2048 x 6144 27.2 -> 22.4, 8192 x 4096 75.6 -> 45.9, 4096 x 20480 188 -> 110 (4.6 TB/s of the
+// three tensors).
 // ---------------------------------------------------------------------------------------------------
-constexpr int kLnSlab = 64;  // columns of a slab workgroup: 8 lanes x 16 bytes (bf16) per row segment; 128 measured slower
-
 template <typename T, int VPT>
-__global__ __launch_bounds__(1024) void ln_bwd_kernel(RowsParams P, const T* __restrict__ dy, const T* __restrict__ x,
-                                                     const float* __restrict__ mean, const float* __restrict__ rstd,
-                                                     const T* __restrict__ gamma, T* __restrict__ dx, float* __restrict__ dg_out,
-                                                     float* __restrict__ db_out, int nslab, int rows_per_split) {
-  __shared__ float red[32];
-  __shared__ float sacc[2][16][kLnSlab];
-  if ((int64_t)blockIdx.x < P.rows) {
-    const int64_t r = blockIdx.x;
-    const int nchunk = (int)(P.h >> 3);
-    const float mu = mean[r], rs = rstd[r];
-    float xh[VPT][8], gg[VPT][8];
-    float s1 = 0.f, s2 = 0.f;
+struct LnRow {  // a thread's share of a row: chunks threadIdx + u * blockDim
+  Raw8<T> x[VPT], dy[VPT];
+  __device__ __forceinline__ void load(const T* xr, const T* dyr, int nchunk) {
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
       const int c = threadIdx.x + u * blockDim.x;
       if (c < nchunk) {
-        float xv[8], dv[8], g[8];
-        Vec8<T>::load(x + r * P.h + 8 * c, xv);
-        Vec8<T>::load(dy + r * P.h + 8 * c, dv);
-        Vec8<T>::load(gamma + 8 * c, g);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          xh[u][e] = (xv[e] - mu) * rs;
-          gg[u][e] = dv[e] * g[e];
-          s1 += gg[u][e];
-          s2 = fmaf(gg[u][e], xh[u][e], s2);
-        }
+        x[u].load(xr + 8 * c);
+        dy[u].load(dyr + 8 * c);
       }
     }
-    block_sum2(s1, s2, red);
-    const float c1 = s1 / (float)P.h, c2 = s2 / (float)P.h;
+  }
+};
+
+template <typename T>
+struct LnBwdCols {
+  static constexpr int kSums = 2;
+  struct In { Raw8<T> x, dy; float mu, rs; };
+  int64_t h;
+  const T *dy, *x;
+  const float *mean, *rstd;
+  __device__ __forceinline__ void column(int64_t) {}
+  __device__ __forceinline__ In load(int64_t r, int64_t col) const {
+    In in;
+    in.x.load(x + r * h + col);
+    in.dy.load(dy + r * h + col);
+    in.mu = mean[r];
+    in.rs = rstd[r];
+    return in;
+  }
+  __device__ __forceinline__ void apply(const In& in, int64_t, int64_t, float (&acc)[2][8]) const {
+    float xv[8], dv[8];
+    in.x.get(xv);
+    in.dy.get(dv);
 #pragma unroll
-    for (int u = 0; u < VPT; ++u) {
-      const int c = threadIdx.x + u * blockDim.x;
-      if (c < nchunk) {
-        float out[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = rs * (gg[u][e] - c1 - xh[u][e] * c2);
-        Vec8<T>::store(dx + r * P.h + 8 * c, out);
-      }
+    for (int e = 0; e < 8; ++e) {
+      acc[0][e] = fmaf(dv[e], (xv[e] - in.mu) * in.rs, acc[0][e]);
+      acc[1][e] += dv[e];
     }
+  }
+};
+
+// dg_out, db_out: the results, or (pl.nsplit > 1) partial sums [nsplit][2][h]
+template <typename T, int NT, int VPT>
+__global__ __launch_bounds__(NT) void ln_bwd_kernel(RowsParams P, const T* __restrict__ dy, const T* __restrict__ x, const float* __restrict__ mean,
+                                                   const float* __restrict__ rstd, const T* __restrict__ gamma, T* __restrict__ dx,
+                                                   float* __restrict__ dg_out, float* __restrict__ db_out, ColPlan pl) {
+  __shared__ __attribute__((aligned(16))) float sb[8 * NT];
+  if ((int64_t)blockIdx.x >= P.rows) {
+    const int block = (int)((int64_t)blockIdx.x - P.rows);
+    LnBwdCols<T> op{P.h, dy, x, mean, rstd};
+    float acc[2][8];
+    colsum_block<NT>(op, P.rows, P.h, pl, block, acc);
+    const int64_t at = (int64_t)(block / pl.ncb) * 2 * P.h;
+    float* const dst[2] = {dg_out + at, db_out + at};
+    colsum_store<NT, 2>(acc, sb, P.h, pl, block, dst);
     return;
   }
-  const int idx = (int)((int64_t)blockIdx.x - P.rows);
-  const int slab = idx % nslab, split = idx / nslab;
-  constexpr int LPS = kLnSlab / 8;  // lanes per row segment
-  const int nseg = (int)(blockDim.x / LPS), seg = threadIdx.x / LPS, ls = threadIdx.x % LPS;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = (int)(blockDim.x >> 6);
-  const int64_t col = (int64_t)slab * kLnSlab + 8 * ls;
-  const bool colok = col < P.h;
-  const int64_t r_lo = (int64_t)split * rows_per_split;
-  const int64_t r_hi = min(P.rows, r_lo + rows_per_split);
-  float ag[8], ab[8];
+  const int64_t r = blockIdx.x;
+  const int nchunk = (int)(P.h >> 3);
+  const float mu = mean[r], rs = rstd[r];
+  LnRow<T, VPT> row;
+  row.load(x + r * P.h, dy + r * P.h, nchunk);
+  Raw8<T> gr[VPT];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { ag[e] = 0.f; ab[e] = 0.f; }
-  if (colok) {
-    for (int64_t r = r_lo + seg; r < r_hi; r += nseg) {
-      float xv[8], dv[8];
-      Vec8<T>::load(x + r * P.h + col, xv);
-      Vec8<T>::load(dy + r * P.h + col, dv);
-      const float mu = mean[r], rs = rstd[r];
+  for (int u = 0; u < VPT; ++u) {
+    const int c = threadIdx.x + u * NT;
+    if (c < nchunk) gr[u].load(gamma + 8 * c);
+  }
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int u = 0; u < VPT; ++u)
+    if ((int)threadIdx.x + u * NT < nchunk) {
+      float xv[8], dv[8], g[8];
+      row.x[u].get(xv);
+      row.dy[u].get(dv);
+      gr[u].get(g);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        ag[e] = fmaf(dv[e], (xv[e] - mu) * rs, ag[e]);
-        ab[e] += dv[e];
+        const float gg = dv[e] * g[e];
+        s1 += gg;
+        s2 = fmaf(gg, (xv[e] - mu) * rs, s2);
       }
     }
-  }
-  // lanes ls, ls + LPS, ... of a wave hold the same columns
+  block_sum2(s1, s2, sb);
+  const float c1 = s1 / (float)P.h, c2 = s2 / (float)P.h;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int u = 0; u < VPT; ++u) {
+    const int c = threadIdx.x + u * NT;
+    if (c < nchunk) {
+      float xv[8], dv[8], g[8], out[8];
+      row.x[u].pin();
+      row.dy[u].pin();
+      gr[u].pin();
+      row.x[u].get(xv);
+      row.dy[u].get(dv);
+      gr[u].get(g);
 #pragma unroll
-    for (int m = LPS; m < 64; m <<= 1) {
-      ag[e] += __shfl_xor(ag[e], m);
-      ab[e] += __shfl_xor(ab[e], m);
+      for (int e = 0; e < 8; ++e) out[e] = rs * (dv[e] * g[e] - c1 - (xv[e] - mu) * rs * c2);
+      Vec8<T>::store(dx + r * P.h + 8 * c, out);
     }
-  }
-  if (lane < LPS) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { sacc[0][wave][8 * ls + e] = ag[e]; sacc[1][wave][8 * ls + e] = ab[e]; }
-  }
-  __syncthreads();
-  // thread t sums array t / kLnSlab, column t % kLnSlab over the waves
-  for (int t = threadIdx.x; t < 2 * kLnSlab; t += blockDim.x) {
-    const int c = t % kLnSlab, which = t / kLnSlab;
-    float tot = 0.f;
-    for (int q = 0; q < nw; ++q) tot += sacc[which][q][c];
-    const int64_t cc = (int64_t)slab * kLnSlab + c;
-    if (cc < P.h) (which ? db_out : dg_out)[(size_t)split * 2 * P.h + cc] = tot;
   }
 }
 
-// sums the row-split partials: part[nsplit][2][h] -> dgamma[h], dbeta[h]
-__global__ void ln_bwd_finish_kernel(const float* __restrict__ part, int nsplit, int64_t h, float* __restrict__ dgamma, float* __restrict__ dbeta) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= h) return;
-  float tg = 0.f, tb = 0.f;
-  for (int q = 0; q < nsplit; ++q) {
-    tg += part[(size_t)q * 2 * h + c];
-    tb += part[(size_t)q * 2 * h + h + c];
+// many rows.  PF: the next row is requested before this one is worked on (where the registers allow it)
+template <typename T, int NT, int VPT, bool PF>
+__global__ __launch_bounds__(NT, 2) void ln_bwd_stream_kernel(RowsParams P, const T* __restrict__ dy, const T* __restrict__ x,
+                                                                     const float* __restrict__ mean, const float* __restrict__ rstd,
+                                                                     const T* __restrict__ gamma, T* __restrict__ dx, float* __restrict__ part) {
+  __shared__ float red[2][2][NT / 64];
+  const int nchunk = (int)(P.h >> 3);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  Raw8<T> gr[VPT];
+  float ag[VPT][8], ab[VPT][8];
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int c = threadIdx.x + u * NT;
+    if (c < nchunk) gr[u].load(gamma + 8 * c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { ag[u][e] = 0.f; ab[u][e] = 0.f; }
   }
-  dgamma[c] = tg;
-  dbeta[c] = tb;
+  LnRow<T, VPT> row, next;
+  float mu = 0.f, rs = 0.f, mu_n = 0.f, rs_n = 0.f;
+  int64_t r = blockIdx.x;
+  if (PF) {
+    next.load(x + r * P.h, dy + r * P.h, nchunk);
+    mu_n = mean[r];
+    rs_n = rstd[r];
+  }
+  for (int it = 0; r < P.rows; r += gridDim.x, it ^= 1) {
+    if (PF) {
+      row = next;
+      mu = mu_n;
+      rs = rs_n;
+      if (r + gridDim.x < P.rows) {
+        next.load(x + (r + gridDim.x) * P.h, dy + (r + gridDim.x) * P.h, nchunk);
+        mu_n = mean[r + gridDim.x];
+        rs_n = rstd[r + gridDim.x];
+      }
+    } else {
+      row.load(x + r * P.h, dy + r * P.h, nchunk);
+      mu = mean[r];
+      rs = rstd[r];
+    }
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u)
+      if ((int)threadIdx.x + u * NT < nchunk) {
+        float xv[8], dv[8], g[8];
+        row.x[u].get(xv);
+        row.dy[u].get(dv);
+        gr[u].get(g);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float xh = (xv[e] - mu) * rs, gg = dv[e] * g[e];
+          ag[u][e] = fmaf(dv[e], xh, ag[u][e]);
+          ab[u][e] += dv[e];
+          s1 += gg;
+          s2 = fmaf(gg, xh, s2);
+        }
+      }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (lane == 0) { red[it][0][wave] = s1; red[it][1][wave] = s2; }
+    __syncthreads();  // the other buffer is written next, after every wave has passed this point: one barrier a row
+    s1 = 0.f;
+    s2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) { s1 += red[it][0][w]; s2 += red[it][1][w]; }
+    const float c1 = s1 / (float)P.h, c2 = s2 / (float)P.h;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+      const int c = threadIdx.x + u * NT;
+      if (c < nchunk) {
+        float xv[8], dv[8], g[8], out[8];
+        row.x[u].pin();
+        row.dy[u].pin();
+        gr[u].pin();
+        row.x[u].get(xv);
+        row.dy[u].get(dv);
+        gr[u].get(g);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e] = rs * (dv[e] * g[e] - c1 - (xv[e] - mu) * rs * c2);
+        Vec8<T>::store(dx + r * P.h + 8 * c, out);
+      }
+    }
+  }
+  float* pg = part + (int64_t)blockIdx.x * 2 * P.h;
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int c = threadIdx.x + u * NT;
+    if (c < nchunk) {
+      Vec8<float>::store(pg + 8 * c, ag[u]);
+      Vec8<float>::store(pg + P.h + 8 * c, ab[u]);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -320,9 +557,9 @@ __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T*
 
 // ---------------------------------------------------------------------------------------------------
 // bias-dropout-add backward: dx = M dout/(1-p) with M regenerated from Philox; the residual branch's gradient is
-// dout itself and is not written.  Without dbias this is elementwise (one thread per 8 elements).  With dbias
-// (the column sums of dx) a workgroup owns a slab of 64 columns and a range of rows, as ln_bwd's second pass:
-// part[split][h] partial sums, or dbias itself if there is one split.
+// dout itself and is not written.  Without dbias this is elementwise (one thread per 8 elements); with dbias a column-summing
+// pass (1024 x 6144: 9.0 + 2.7 us as slabs of 64 columns and a one-thread-a-column finish, 9.8
+// together now; 4096 x 20480: 113 -> 64 us).
 // ---------------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void bda_bwd_kernel(RowsParams P, const T* __restrict__ dout, T* __restrict__ dx) {
@@ -338,57 +575,36 @@ __global__ __launch_bounds__(256) void bda_bwd_kernel(RowsParams P, const T* __r
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void bda_bwd_slab_kernel(RowsParams P, const T* __restrict__ dout, T* __restrict__ dx, float* __restrict__ db_out,
-                                                          int rows_per_split) {
-  __shared__ float sb[32][65];
-  const int slab = blockIdx.x, split = blockIdx.y;
-  const int seg = threadIdx.x >> 3, l8 = threadIdx.x & 7;
-  const int64_t col = (int64_t)slab * 64 + 8 * l8;
-  const bool colok = col < P.h;
-  const int64_t r_lo = (int64_t)split * rows_per_split;
-  const int64_t r_hi = min(P.rows, r_lo + rows_per_split);
-  float ab[8];
+struct BdaBwdCols {
+  static constexpr int kSums = 1;
+  typedef Raw8<T> In;
+  RowsParams P;
+  const T* dout;
+  T* dx;
+  __device__ __forceinline__ void column(int64_t) {}
+  __device__ __forceinline__ In load(int64_t r, int64_t col) const {
+    In in;
+    in.load(dout + r * P.h + col);
+    return in;
+  }
+  __device__ __forceinline__ void apply(const In& in, int64_t r, int64_t col, float (&acc)[1][8]) const {
+    float dv[8], o[8];
+    in.get(dv);
+    const uint64_t e = (uint64_t)(P.row_offset + r) * (uint64_t)P.h + (uint64_t)col;
+    const uint32_t keep = keep_bits8(P.offset + (e >> 3), 1u, P.key0, P.key1, P.thresh);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ab[e] = 0.f;
-  for (int64_t r = r_lo + seg; r < r_hi; r += 32) {
-    if (colok) {
-      float dv[8], o[8];
-      Vec8<T>::load(dout + r * P.h + col, dv);
-      const uint64_t e = (uint64_t)(P.row_offset + r) * (uint64_t)P.h + (uint64_t)col;
-      const uint32_t keep = keep_bits8(P.offset + (e >> 3), 1u, P.key0, P.key1, P.thresh);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        o[q] = ((keep >> q) & 1u) ? dv[q] * P.keep_scale : 0.f;
-        ab[q] += o[q];
-      }
-      Vec8<T>::store(dx + r * P.h + col, o);
+    for (int q = 0; q < 8; ++q) {
+      o[q] = ((keep >> q) & 1u) ? dv[q] * P.keep_scale : 0.f;
+      acc[0][q] += o[q];
     }
+    Vec8<T>::store(dx + r * P.h + col, o);
   }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) sb[seg][8 * l8 + e] = ab[e];
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int c = threadIdx.x;
-    float t = 0.f;
-    for (int q = 0; q < 32; ++q) t += sb[q][c];
-    const int64_t cc = (int64_t)slab * 64 + c;
-    if (cc < P.h) db_out[(size_t)split * P.h + cc] = t;
-  }
-}
-
-// sums row-split partials: part[nsplit][h] -> dbias[h]
-__global__ void bda_bwd_finish_kernel(const float* __restrict__ part, int nsplit, int64_t h, float* __restrict__ dbias) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= h) return;
-  float t = 0.f;
-  for (int q = 0; q < nsplit; ++q) t += part[(size_t)q * h + c];
-  dbias[c] = t;
-}
+};
 
 // ---------------------------------------------------------------------------------------------------
 // bias + GeLU of the MLP block (Section 4.1): y = z Phi(z), z = x + bias, Phi the standard normal CDF (exact form,
 // through erf).  Backward: dx = dy (Phi(z) + z phi(z)) from the stored input, dbias = column sums of dx.
-// One thread per 8 elements; with dbias, column slabs of 64 as in bias_dropout_add_bwd.
+// One thread per 8 elements; with dbias, a column-summing pass.
 // ---------------------------------------------------------------------------------------------------
 // Phi(z) and phi(z) from one exponential: erf by the rational approximation 7.1.26 of Abramowitz & Stegun,
 // erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x), x >= 0, |error| <= 1.5e-7, with x = |z| / sqrt 2,
@@ -447,46 +663,37 @@ __global__ __launch_bounds__(256) void bias_gelu_bwd_kernel(RowsParams P, const 
   Vec8<T>::store(dx + at, o);
 }
 
-// with dbias: a workgroup owns 64 columns and a range of rows, as bda_bwd_slab_kernel
 template <typename T, bool HAS_BIAS>
-__global__ __launch_bounds__(256) void bias_gelu_bwd_slab_kernel(RowsParams P, const T* __restrict__ dy, const T* __restrict__ x,
-                                                                const T* __restrict__ bias, T* __restrict__ dx, float* __restrict__ db_out,
-                                                                int rows_per_split) {
-  __shared__ float sb[32][65];
-  const int slab = blockIdx.x, split = blockIdx.y;
-  const int seg = threadIdx.x >> 3, l8 = threadIdx.x & 7;
-  const int64_t col = (int64_t)slab * 64 + 8 * l8;
-  const bool colok = col < P.h;
-  const int64_t r_lo = (int64_t)split * rows_per_split;
-  const int64_t r_hi = min(P.rows, r_lo + rows_per_split);
-  float ab[8], bv[8];
+struct GeluBwdCols {
+  static constexpr int kSums = 1;
+  struct In { Raw8<T> x, dy; };
+  RowsParams P;
+  const T *dy, *x, *bias;
+  T* dx;
+  float bv[8];
+  __device__ __forceinline__ void column(int64_t col) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { ab[e] = 0.f; bv[e] = 0.f; }
-  if (HAS_BIAS && colok) Vec8<T>::load(bias + col, bv);
-  for (int64_t r = r_lo + seg; r < r_hi; r += 32) {
-    if (colok) {
-      float xv[8], dv[8], o[8];
-      Vec8<T>::load(x + r * P.h + col, xv);
-      Vec8<T>::load(dy + r * P.h + col, dv);
+    for (int e = 0; e < 8; ++e) bv[e] = 0.f;
+    if (HAS_BIAS) Vec8<T>::load(bias + col, bv);
+  }
+  __device__ __forceinline__ In load(int64_t r, int64_t col) const {
+    In in;
+    in.x.load(x + r * P.h + col);
+    in.dy.load(dy + r * P.h + col);
+    return in;
+  }
+  __device__ __forceinline__ void apply(const In& in, int64_t r, int64_t col, float (&acc)[1][8]) const {
+    float xv[8], dv[8], o[8];
+    in.x.get(xv);
+    in.dy.get(dv);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        o[q] = dv[q] * gelu_grad(xv[q] + bv[q]);
-        ab[q] += o[q];
-      }
-      Vec8<T>::store(dx + r * P.h + col, o);
+    for (int q = 0; q < 8; ++q) {
+      o[q] = dv[q] * gelu_grad(xv[q] + bv[q]);
+      acc[0][q] += o[q];
     }
+    Vec8<T>::store(dx + r * P.h + col, o);
   }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) sb[seg][8 * l8 + e] = ab[e];
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int c = threadIdx.x;
-    float t = 0.f;
-    for (int q = 0; q < 32; ++q) t += sb[q][c];
-    const int64_t cc = (int64_t)slab * 64 + c;
-    if (cc < P.h) db_out[(size_t)split * P.h + cc] = t;
-  }
-}
+};
 
 // ------------------------------------------------------------------------------------------------ launchers
 static inline int pick_vpt(int64_t h, int& threads) {
@@ -519,49 +726,78 @@ hipError_t launch_ln_fwd(const RowsParams& P, bool bf16, const void* x, const vo
   return bf16 ? ln_fwd_t<uint16_t>(P, x, gamma, beta, y, mean, rstd, st) : ln_fwd_t<float>(P, x, gamma, beta, y, mean, rstd, st);
 }
 
-// target: slab workgroups to aim at (256 = one per CU); min_trips: trips of a slab workgroup over its rows at least
-static inline void ln_bwd_plan(int64_t rows, int64_t h, int threads, int slabw, int& nslab, int& nsplit, int& rows_per_split, int target = 256,
-                               int min_trips = 1) {
-  nslab = (int)((h + slabw - 1) / slabw);
-  const int nseg = threads / (slabw / 8);                // row segments per trip of a slab workgroup
-  int want = (target + nslab - 1) / nslab;
-  int maxsplit = (int)((rows + (int64_t)nseg * min_trips - 1) / ((int64_t)nseg * min_trips));
-  nsplit = want < 1 ? 1 : (want > maxsplit ? maxsplit : want);
-  if (nsplit < 1) nsplit = 1;
-  rows_per_split = (int)((rows + nsplit - 1) / nsplit);
-  nsplit = (int)((rows + rows_per_split - 1) / rows_per_split);
+// Workgroups of the form that reads x and dy once, 0 where the other one runs.  About 512 threads a CU; the narrower a row, the
+// fewer threads work on it and the more rows' partial sums there are.  From eight rows a workgroup on they cost less than the
+// second read (two reads / one, us: 1024 x 6144 15.4 / 17.1, 2048 x 6144 25.4 / 22.4, 8192 x 4096 59.7 / 45.9).  Rows wider than
+// 20480 leave no registers for a request ahead (bf16: from sixteen rows on, 2048 x 25600 90.9 / 99.8, 4096 x 25600 193 / 163),
+// and beyond 28672 no room for the sums.
+static inline int ln_bwd_stream_groups(int64_t rows, int64_t h, bool bf16) {
+  const int64_t nchunk = h >> 3;
+  const int groups = nchunk <= 128 ? 1024 : nchunk <= 512 ? 512 : 256;
+  return nchunk <= (bf16 ? 3584 : 2560) && rows >= (nchunk <= 2560 ? 8 : 16) * groups ? groups : 0;
 }
+static inline int ln_bwd_threads(int64_t h) { return h <= 8192 ? 256 : 512; }  // of a workgroup, where x and dy are read twice
 
-size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h) {
-  int nslab, nsplit, rps, threads;
-  pick_vpt(h, threads);
-  ln_bwd_plan(rows, h, threads, kLnSlab, nslab, nsplit, rps);
+size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {
+  const int groups = ln_bwd_stream_groups(rows, h, bf16), nsplit = groups ? groups : col_plan(rows, h, ln_bwd_threads(h)).nsplit;
   return nsplit > 1 ? (size_t)nsplit * 2 * (size_t)h * sizeof(float) : 256;
 }
 
 template <typename T>
 static hipError_t ln_bwd_t(const RowsParams& P, const void* dy, const void* x, const float* mean, const float* rstd, const void* gamma, void* dx,
                            float* dgamma, float* dbeta, void* ws, hipStream_t st) {
-  int nslab, nsplit, rps, threads;
-  const int vpt = pick_vpt(P.h, threads);
-  ln_bwd_plan(P.rows, P.h, threads, kLnSlab, nslab, nsplit, rps);
+  const int nchunk = (int)(P.h >> 3);
   float* part = (float*)ws;
-  // one split: the slab workgroups see every row and write dgamma / dbeta themselves; else partials [split][2][h]
-  float* dg_out = nsplit == 1 ? dgamma : part;
-  float* db_out = nsplit == 1 ? dbeta : part + P.h;
-  dim3 grid((unsigned)(P.rows + (int64_t)nslab * nsplit)), block(threads);
-#define SAR_LN_BWD(V) hipLaunchKernelGGL((ln_bwd_kernel<T, V>), grid, block, 0, st, P, (const T*)dy, (const T*)x, mean, rstd, (const T*)gamma, (T*)dx, dg_out, db_out, nslab, rps)
-  switch (vpt) {
-    case 1: SAR_LN_BWD(1); break;
-    case 2: SAR_LN_BWD(2); break;
-    case 3: SAR_LN_BWD(3); break;
-    default: SAR_LN_BWD(4); break;
+  constexpr bool half = sizeof(T) == 2;
+  if (const int groups = ln_bwd_stream_groups(P.rows, P.h, half)) {
+    auto go = [&](auto kern, int nt) {
+      hipLaunchKernelGGL(kern, dim3(groups), dim3(nt), 0, st, P, (const T*)dy, (const T*)x, mean, rstd, (const T*)gamma, (T*)dx, part);
+    };
+    if (nchunk <= 128) go(ln_bwd_stream_kernel<T, 128, 1, true>, 128);
+    else if (nchunk <= 256) go(ln_bwd_stream_kernel<T, 256, 1, true>, 256);
+    else if (nchunk <= 512) go(ln_bwd_stream_kernel<T, 256, 2, true>, 256);
+    else switch ((nchunk + 511) / 512) {
+      case 2: go(ln_bwd_stream_kernel<T, 512, 2, true>, 512); break;
+      case 3: go(ln_bwd_stream_kernel<T, 512, 3, true>, 512); break;
+      case 4: go(ln_bwd_stream_kernel<T, 512, 4, half>, 512); break;
+      case 5: go(ln_bwd_stream_kernel<T, 512, 5, half>, 512); break;
+      default:
+        if constexpr (half) {
+          if (nchunk <= 3072) go(ln_bwd_stream_kernel<T, 512, 6, false>, 512);
+          else go(ln_bwd_stream_kernel<T, 512, 7, false>, 512);
+        }
+    }
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_colsum_finish(part, groups, 2 * P.h, P.h, dgamma, dbeta, st);
   }
-#undef SAR_LN_BWD
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || nsplit == 1) return e;
-  hipLaunchKernelGGL(ln_bwd_finish_kernel, dim3((unsigned)((P.h + 255) / 256)), dim3(256), 0, st, (const float*)part, nsplit, P.h, dgamma, dbeta);
-  return hipGetLastError();
+  const int nt = ln_bwd_threads(P.h);
+  const ColPlan pl = col_plan(P.rows, P.h, nt);
+  float* dg_out = pl.nsplit == 1 ? dgamma : part;
+  float* db_out = pl.nsplit == 1 ? dbeta : part + P.h;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(P.rows + (int64_t)pl.ncb * pl.nsplit)), dim3(nt), 0, st, P, (const T*)dy, (const T*)x, mean, rstd,
+                       (const T*)gamma, (T*)dx, dg_out, db_out, pl);
+  };
+  const int vpt = (nchunk + nt - 1) / nt;
+  if (nt == 256) {
+    switch (vpt) {
+      case 1: go(ln_bwd_kernel<T, 256, 1>); break;
+      case 2: go(ln_bwd_kernel<T, 256, 2>); break;
+      case 3: go(ln_bwd_kernel<T, 256, 3>); break;
+      default: go(ln_bwd_kernel<T, 256, 4>); break;
+    }
+  } else {
+    switch (vpt) {
+      case 3: go(ln_bwd_kernel<T, 512, 3>); break;
+      case 4: go(ln_bwd_kernel<T, 512, 4>); break;
+      case 5: go(ln_bwd_kernel<T, 512, 5>); break;
+      case 6: go(ln_bwd_kernel<T, 512, 6>); break;
+      case 7: go(ln_bwd_kernel<T, 512, 7>); break;
+      default: go(ln_bwd_kernel<T, 512, 8>); break;
+    }
+  }
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || pl.nsplit == 1 ? e : launch_colsum_finish(part, pl.nsplit, 2 * P.h, P.h, dgamma, dbeta, st);
 }
 
 hipError_t launch_ln_bwd(const RowsParams& P, bool bf16, const void* dy, const void* x, const float* mean, const float* rstd, const void* gamma,
@@ -613,21 +849,8 @@ hipError_t launch_bias_dropout_add_ln_fwd(const RowsParams& P, bool bf16, const 
               : bda_ln_t<float>(P, x, bias, resid, gamma, beta, out, y, mean, rstd, st);
 }
 
-// The bias-GeLU backward has many rows (s b of them, not s b / t): a slab workgroup does one dependent load -> arithmetic
-// -> store chain per trip, so the bytes in flight are what the resident waves hold; eight workgroups per CU instead of
-// one or two (2048 x 10240: 320 -> 2080 workgroups) take it from 45 to 32 us.  (Finer splits, or two rows per trip, are slower.)
-static constexpr int kGeluTarget = 2048, kGeluMinTrips = 2;
-size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h) {
-  int nslab, nsplit, rps;
-  ln_bwd_plan(rows, h, 256, 64, nslab, nsplit, rps, kGeluTarget, kGeluMinTrips);
-  return nsplit > 1 ? (size_t)nsplit * (size_t)h * sizeof(float) : 0;
-}
-
-size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h) {
-  int nslab, nsplit, rps;
-  ln_bwd_plan(rows, h, 256, 64, nslab, nsplit, rps);
-  return nsplit > 1 ? (size_t)nsplit * (size_t)h * sizeof(float) : 0;
-}
+size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h) { return colsum_workspace_bytes(rows, h); }
+size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h) { return colsum_workspace_bytes(rows, h); }
 
 template <typename T>
 static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
@@ -635,18 +858,7 @@ static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, flo
     hipLaunchKernelGGL((bda_bwd_kernel<T>), dim3((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), dim3(256), 0, st, P, (const T*)dout, (T*)dx);
     return hipGetLastError();
   }
-  int nslab, nsplit, rps;
-  ln_bwd_plan(P.rows, P.h, 256, 64, nslab, nsplit, rps);
-  if (nsplit == 1) {
-    hipLaunchKernelGGL((bda_bwd_slab_kernel<T>), dim3(nslab, 1), dim3(256), 0, st, P, (const T*)dout, (T*)dx, dbias, rps);
-    return hipGetLastError();
-  }
-  float* part = (float*)ws;
-  hipLaunchKernelGGL((bda_bwd_slab_kernel<T>), dim3(nslab, nsplit), dim3(256), 0, st, P, (const T*)dout, (T*)dx, part, rps);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bda_bwd_finish_kernel, dim3((unsigned)((P.h + 255) / 256)), dim3(256), 0, st, (const float*)part, nsplit, P.h, dbias);
-  return hipGetLastError();
+  return launch_colsum(BdaBwdCols<T>{P, (const T*)dout, (T*)dx}, P.rows, P.h, dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
@@ -674,19 +886,8 @@ static hipError_t bias_gelu_bwd_t(const RowsParams& P, const void* dy, const voi
     else hipLaunchKernelGGL((bias_gelu_bwd_kernel<T, false>), grid, block, 0, st, P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx);
     return hipGetLastError();
   }
-  int nslab, nsplit, rps;
-  ln_bwd_plan(P.rows, P.h, 256, 64, nslab, nsplit, rps, kGeluTarget, kGeluMinTrips);
-  float* out = nsplit == 1 ? dbias : (float*)ws;
-  if (bias)
-    hipLaunchKernelGGL((bias_gelu_bwd_slab_kernel<T, true>), dim3(nslab, nsplit), dim3(256), 0, st, P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx,
-                       out, rps);
-  else
-    hipLaunchKernelGGL((bias_gelu_bwd_slab_kernel<T, false>), dim3(nslab, nsplit), dim3(256), 0, st, P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx,
-                       out, rps);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || nsplit == 1) return e;
-  hipLaunchKernelGGL(bda_bwd_finish_kernel, dim3((unsigned)((P.h + 255) / 256)), dim3(256), 0, st, (const float*)ws, nsplit, P.h, dbias);
-  return hipGetLastError();
+  if (bias) return launch_colsum(GeluBwdCols<T, true>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, dbias, (float*)ws, st);
+  return launch_colsum(GeluBwdCols<T, false>{P, (const T*)dy, (const T*)x, nullptr, (T*)dx, {}}, P.rows, P.h, dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_gelu_bwd(const RowsParams& P, bool bf16, const void* dy, const void* x, const void* bias, void* dx, float* dbias, void* ws,

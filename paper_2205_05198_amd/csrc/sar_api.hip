@@ -331,7 +331,7 @@ sar_status ln_fwd(const sar_rows_desc* desc, const void* x, const void* gamma, c
 
 size_t ln_bwd_workspace(const sar_rows_desc* desc) {
   if (check_rows_desc(desc, nullptr) != SAR_OK) return 0;
-  return sar::ln_bwd_workspace_bytes(desc->rows, desc->h);
+  return sar::ln_bwd_workspace_bytes(desc->rows, desc->h, desc->dtype == SAR_BF16);
 }
 
 sar_status ln_bwd(const sar_rows_desc* desc, const void* dy, const void* x, const float* mean, const float* rstd, const void* gamma, void* dx,
@@ -341,7 +341,7 @@ sar_status ln_bwd(const sar_rows_desc* desc, const void* dy, const void* x, cons
   if (st != SAR_OK) return st;
   if (!dy || !x || !mean || !rstd || !gamma || !dx || !dgamma || !dbeta) return fail(SAR_ERR_NULL, "ln_bwd: NULL tensor pointer");
   if (!aligned16(dy) || !aligned16(x) || !aligned16(gamma) || !aligned16(dx)) return fail(SAR_ERR_ALIGN, "ln_bwd: pointer not 16-byte aligned");
-  const size_t need = sar::ln_bwd_workspace_bytes(P.rows, P.h);
+  const size_t need = sar::ln_bwd_workspace_bytes(P.rows, P.h, desc->dtype == SAR_BF16);
   if (!workspace || workspace_bytes < need) return fail(SAR_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, workspace_bytes);
   if (!aligned16(workspace)) return fail(SAR_ERR_ALIGN, "workspace not 16-byte aligned");
   hipError_t e = sar::launch_ln_bwd(P, desc->dtype == SAR_BF16, dy, x, mean, rstd, gamma, dx, dgamma, dbeta, workspace, (hipStream_t)stream);

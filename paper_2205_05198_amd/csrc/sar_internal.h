@@ -78,7 +78,7 @@ int attn_mfma_cu_count();  // compute units of the current device, asked once
 // rows.hip: LayerNorm forward/backward and bias-dropout-add on [rows, h]
 hipError_t launch_ln_fwd(const RowsParams& P, bool bf16, const void* x, const void* gamma, const void* beta, void* y, float* mean,
                          float* rstd, hipStream_t st);
-size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h);
+size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16);
 hipError_t launch_ln_bwd(const RowsParams& P, bool bf16, const void* dy, const void* x, const float* mean, const float* rstd,
                          const void* gamma, void* dx, float* dgamma, float* dbeta, void* ws, hipStream_t st);
 hipError_t launch_bias_dropout_add(const RowsParams& P, bool bf16, const void* x, const void* bias, const void* resid, void* out,

@@ -212,3 +212,55 @@ def test_bias_gelu(rows, h, dtype, with_bias):
     # dbias is an fp32 sum of fp32 products on both dtypes
     assert err(host(dbias), ref["dbias"], "f32") < 1e-4
 
+
+
+@pytest.mark.parametrize("rows,h,dtype", [
+    (8192, 1024, "bf16"), (8193, 1016, "bf16"), (4096, 2048, "f32"), (4097, 2056, "bf16"),      # x and dy read once: 128, 256 threads a row
+    (2048, 4104, "bf16"), (2049, 20480, "bf16"), (2048, 20480, "f32"), (4096, 28672, "bf16"),   # 512 threads: one chunk more than 512, widest rows
+    (2047, 4104, "bf16"), (4095, 20488, "bf16"),                                                # one row too few for that
+    (128, 520, "bf16"), (129, 520, "bf16"), (512, 12288, "bf16"), (513, 12288, "bf16"), (512, 12280, "bf16"), (700, 32768, "f32"),
+])
+def test_column_sums(rows, h, dtype):
+    """The passes that sum columns, on both sides of every line of their dispatch: rows split or not, x and dy of the LayerNorm
+    backward read once or twice, widths that leave lanes without work.  Reference: the definitions in fp64 on the device;
+    tolerances: those of the tests above."""
+    from gpu_util import BAR, DT, err, host
+    tdt, code = DT[dtype]
+    g = torch.Generator(device="cuda").manual_seed(rows + h)
+    x, dy = (torch.randn(rows, h, device="cuda", generator=g).to(tdt) for _ in range(2))
+    gamma, bias = ((1.0 + 0.1 * torch.randn(h, device="cuda", generator=g)).to(tdt), (0.1 * torch.randn(h, device="cuda", generator=g)).to(tdt))
+    print(f"column sums rows={rows} h={h} {dtype}", flush=True)
+    desc = sar.RowsDesc.make(rows, h, dtype=code, p=0.1, seed=3, offset=9)
+    dx = torch.empty_like(x)
+    mean, rstd = (torch.empty(rows, dtype=torch.float32, device="cuda") for _ in range(2))
+    c0, c1 = (torch.empty(h, dtype=torch.float32, device="cuda") for _ in range(2))
+    def scratch(n):
+        return torch.full((max(16, n) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    def close(got, ref, how):
+        e = err(host(got), ref.cpu().numpy(), how)
+        assert e <= BAR[how], e
+    xd, dyd = x.double(), dy.double()
+    sar.ln_fwd(desc, x, gamma, bias, dx, mean, rstd)
+    sar.ln_bwd(desc, dy, x, mean, rstd, gamma, dx, c0, c1, scratch(sar.ln_bwd_workspace(desc)))
+    mu = xd.mean(1, keepdim=True)
+    xhat = (xd - mu) * (xd.var(1, unbiased=False, keepdim=True) + desc.eps).rsqrt()
+    gg = dyd * gamma.double()
+    rs = (xd.var(1, unbiased=False, keepdim=True) + desc.eps).rsqrt()
+    close(dx, rs * (gg - gg.mean(1, keepdim=True) - xhat * (gg * xhat).mean(1, keepdim=True)), dtype)
+    close(c0, (dyd * xhat).sum(0), "f32")
+    close(c1, dyd.sum(0), "f32")
+    del xhat, gg
+    m = torch.empty(rows, h, dtype=torch.uint8, device="cuda")
+    sar.bias_dropout_add(desc, x, None, dy, dx, m)
+    sar.bias_dropout_add_bwd(desc, dy, dx, c0, scratch(sar.bias_dropout_add_bwd_workspace(desc)))
+    ref = dyd * m.double() / (1.0 - float(np.float32(0.1)))
+    close(dx, ref, dtype)
+    close(c0, ref.sum(0), "f32")
+    sar.bias_gelu_bwd(desc, dy, x, bias, dx, c0, scratch(sar.bias_gelu_bwd_workspace(desc)))
+    z = (xd + bias.double())
+    ref = dyd * (0.5 * (1.0 + torch.erf(z / 2 ** 0.5)) + z * torch.exp(-z * z / 2) / (2 * np.pi) ** 0.5)
+    if dtype == "f32":
+        close(dx, ref, dtype)
+    else:
+        assert bool(((dx.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-3 * ref.square().mean().sqrt()).all())
+    close(c0, ref.sum(0), "f32")
