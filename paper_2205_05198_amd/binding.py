@@ -21,6 +21,7 @@ _SOURCES = {
     "sar_api.hip": [],
     "attn_simple.hip": [],
     "attn_f32_mfma.hip": [],
+    "attn_f32_mfma_bf16.hip": [],
     "attn_mfma_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
     "attn_mfma_cols.hip": [],
     "attn_mfma_cols_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],

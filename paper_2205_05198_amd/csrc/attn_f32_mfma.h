@@ -1,0 +1,575 @@
+// Attention core with selective recomputation (Section 5) on the fp32 matrix instructions: the fp32 dtype, and bf16 inputs whose
+// head dimension or score scale the bf16 kernels do not cover.  Any head dimension d % 4 == 0 up to 256.
+//
+// Every contraction is v_mfma_f32_{32x32x2,16x16x4}_f32: fp32 inputs, fp32 accumulation.  M = 32 or 16; lane = M*hh + li:
+//   A: lane holds row li, k = hh     B: lane holds column li, k = hh
+//   D: lane holds column li; M = 32: rows 8*g + 4*hh + r in acc[4*g + r]; M = 16: rows 4*hh + r in acc[r]
+// A result tile is directly the B operand of a second product whose k runs over its rows: each register supplies one k for every
+// hh, so neither the probabilities nor dS ever change layout, and which rows those are is only a matter of which rows of the
+// other operand a lane reads.
+//
+// One M = 32 instruction takes 64 cycles of its SIMD for 256 bytes of either operand, so operands come straight from global
+// memory (L1 / L2) without staging: rows as 16-byte pieces along the head dimension (4 consecutive k of one row per lane), and
+// columns as coalesced reads along the head dimension.  A workgroup owns M query rows (forward, row pass) or M keys (column
+// pass), keeps their operands in LDS, and its four waves take every fourth 32-wide tile of the other dimension; they meet once,
+// at the end, to add their partial results in a fixed order.  No barrier inside the tile loop.  Bound: the fp32 matrix rate.
+// Measured at s = 1024, 24 heads of 64, causal, against the plain one-wave-per-row kernels that these replace: forward and
+// backward together 2538 -> 175 us (83 TFLOP/s of the nine contractions executed, of the 154 that a large product reaches).
+#pragma once
+#include <type_traits>
+#include "sar_device.h"
+#include "sar_internal.h"
+
+namespace sar {
+namespace {
+
+constexpr float kLog2eF = 1.4426950408889634f, kLn2F = 0.6931471805599453f;
+constexpr float kLazyF = 60.0f;  // the running reference exponent moves only when a row maximum grew by > 2^60
+constexpr int NWF = 4;           // waves of a workgroup
+constexpr int kTileF = 32;       // width of a step along the other dimension
+
+template <int M> struct Geo;
+template <> struct Geo<32> {
+  typedef float16_t acc_t;
+  static constexpr int HH = 2, SUB = 1, NV = 16;  // lanes along k, result tiles of a step, values of a step per lane
+  static __device__ __forceinline__ acc_t mfma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+  // scores with keys in rows: the key of the tile that operand row m (of result tile t) stands for, and the key of value e of a lane:
+  // a lane's values 8 c .. 8 c + 7 are 8 consecutive keys (one Philox call)
+  static __device__ __forceinline__ int key_of_row(int, int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1); }
+  static __device__ __forceinline__ int key_of_value(int e, int hh) { return 16 * (e >> 3) + 8 * hh + (e & 7); }
+  // scores with query rows in rows, in their natural order
+  static __device__ __forceinline__ int row_of_row(int, int m) { return m; }
+  static __device__ __forceinline__ int row_of_value(int e, int hh) { return 8 * (e >> 2) + 4 * hh + (e & 3); }
+};
+template <> struct Geo<16> {
+  typedef float4_t acc_t;
+  static constexpr int HH = 4, SUB = 2, NV = 8;
+  static __device__ __forceinline__ acc_t mfma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int key_of_row(int t, int m) { return 8 * (m >> 2) + 4 * t + (m & 3); }
+  static __device__ __forceinline__ int key_of_value(int e, int hh) { return 8 * hh + e; }
+  static __device__ __forceinline__ int row_of_row(int t, int m) { return 16 * t + m; }
+  static __device__ __forceinline__ int row_of_value(int e, int hh) { return 16 * (e >> 2) + 4 * hh + (e & 3); }
+};
+
+__device__ __forceinline__ float4_t load4(const float* p) { return *reinterpret_cast<const float4_t*>(p); }
+__device__ __forceinline__ float4_t load4(const uint16_t* p) {
+  const uint2 u = *reinterpret_cast<const uint2*>(p);
+  float4_t f = {__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+  return f;
+}
+
+// over the lanes that hold one column
+template <int M>
+__device__ __forceinline__ float column_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  if (M == 16) v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return v;
+}
+template <int M>
+__device__ __forceinline__ float column_sum(float v) {
+  v += __shfl_xor(v, 32, 64);
+  if (M == 16) v += __shfl_xor(v, 16, 64);
+  return v;
+}
+
+// CT = column tiles of M that cover the head dimension.  Column m of an M-wide operand or result stands for the CT consecutive
+// elements col_start(m) .. + CT - 1 of a row (tile ct of the CT matrix products takes the ct-th of them), so that a lane reads
+// and writes runs of CT elements.  Where M CT > d the last runs overlap: those elements are computed and written twice, equal.
+template <int CT>
+__device__ __forceinline__ int col_start(int m, int d) { return min(CT * m, d - CT); }
+
+template <int CT>
+__device__ __forceinline__ void load_cols(const float* p, float (&f)[CT]) {
+  struct __attribute__((packed, aligned(4))) run { float v[CT]; };
+  const run r = *reinterpret_cast<const run*>(p);
+#pragma unroll
+  for (int e = 0; e < CT; ++e) f[e] = r.v[e];
+}
+template <int CT>
+__device__ __forceinline__ void load_cols(const uint16_t* p, float (&f)[CT]) {
+#pragma unroll
+  for (int e = 0; e < CT; ++e) f[e] = bf16_to_f32(p[e]);
+}
+
+// Rows of a tensor in LDS, as fp32, zero beyond the head dimension; DT = 32-wide pieces that cover it, pitch 32 DT + 4
+template <int M, int DT, typename T>
+__device__ __forceinline__ void rows_to_lds(float* dst, const T* g, int64_t gstride, int rows_valid, int d) {
+  for (int c = threadIdx.x; c < M * 8 * DT; c += 64 * NWF) {
+    const int r = c / (8 * DT), x = 4 * (c - r * 8 * DT);
+    float4_t f = {0.f, 0.f, 0.f, 0.f};
+    if (x < d) f = load4(g + (int64_t)min(r, rows_valid - 1) * gstride + x);
+    *reinterpret_cast<float4_t*>(dst + r * (32 * DT + 4) + x) = f;
+  }
+}
+
+// Operands that come from global memory are requested this far ahead of the matrix instruction that reads them (in floats per
+// lane; a float is one instruction's worth, 64 cycles at M = 32), in rings of registers.
+constexpr int kAheadF = 16;
+constexpr int rows_ahead(int n, int nv) { return kAheadF / n < 2 ? 2 : kAheadF / n > nv ? nv : kAheadF / n; }  // n: floats of a row per lane
+
+// Row operands: pieces of 4 consecutive elements (4 (HH j + hh)) of one row per lane.  Pieces beyond the head dimension repeat the
+// last one; the other operand is zero there.
+constexpr int kRingF = kAheadF / 4;
+template <int M, int DT, typename T>
+__device__ __forceinline__ float4_t load_piece(const T* row, int j, int hh, int d) {
+  constexpr int W = 4 * Geo<M>::HH;
+  return load4(row + (W * (j + 1) <= 32 * (DT - 1) ? W * j + 4 * hh : min(W * j + 4 * hh, d - 4)));  // d > 32 (DT - 1)
+}
+template <int M, int DT, typename T>
+__device__ __forceinline__ void ring_start(float4_t (&ring)[kRingF], const T* row, const T* next, int hh, int d) {
+  constexpr int NP = 8 * DT / Geo<M>::HH;
+#pragma unroll
+  for (int j = 0; j < kRingF; ++j) ring[j] = j < NP ? load_piece<M, DT>(row, j, hh, d) : load_piece<M, DT>(next, j - NP, hh, d);
+}
+// M x M product over the head dimension of the row in `ring` / `row` and rows in LDS.  The ring is refilled with the rest of
+// `row`, then with the first pieces of `next` (its pieces past the row after `next` with those of `after`).  R0: ring slot of this
+// row's piece 0.
+template <int M, int DT, int R0, typename T>
+__device__ __forceinline__ typename Geo<M>::acc_t dot_tile(float4_t (&ring)[kRingF], const T* row, const T* next, const T* after, const float* lds_row, int hh,
+                                                           int d) {
+  constexpr int NP = 8 * DT / Geo<M>::HH, W = 4 * Geo<M>::HH;
+  typename Geo<M>::acc_t acc;
+#pragma unroll
+  for (int e = 0; e < Geo<M>::NV / Geo<M>::SUB; ++e) acc[e] = 0.f;
+  int off = 0;
+  asm volatile("" : "+v"(off));  // the reads of LDS stay in the tile loop: hoisted out of it they would hold 16 DT registers
+  lds_row += off;
+  float4_t b = *reinterpret_cast<const float4_t*>(lds_row);
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const float4_t a = ring[(R0 + j) % kRingF], bj = b;
+    if (j + 1 < NP) b = *reinterpret_cast<const float4_t*>(lds_row + W * (j + 1));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc = Geo<M>::mfma(a[u], bj[u], acc);
+    asm volatile("" : "+v"(acc));  // in this place: left alone, the products sink below all of the loads
+    const int n = j + kRingF;  // piece that takes this slot
+    ring[(R0 + j) % kRingF] = n < NP ? load_piece<M, DT>(row, n, hh, d) : n < 2 * NP ? load_piece<M, DT>(next, n - NP, hh, d) : load_piece<M, DT>(after, n - 2 * NP, hh, d);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return acc;
+}
+
+// sum over the four waves of acc (one row of the output per lane li), times mul, to rows 0 .. rows_valid - 1 of out.
+// buf: NWF * M * (8 CT + 4) floats at M = 32 (eight columns m at a time), NWF * M * (16 CT + 4) at M = 16; the waves' order is fixed.
+template <int M, int CT>
+constexpr int merge_pitch() { return (M == 32 ? 8 : 16) * CT + 4; }
+template <int M, int CT, typename T>
+__device__ __forceinline__ void merge_store(const typename Geo<M>::acc_t (&acc)[CT], float* buf, int wave, int li, int hh, float mul, T* out, int64_t gstride,
+                                            int rows_valid, int d) {
+  constexpr int PITCH = merge_pitch<M, CT>(), NG = M == 32 ? 4 : 1, MM = M / NG;  // MM: columns m of a round
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    __syncthreads();
+    float* w = buf + (wave * M + li) * PITCH + 4 * hh * CT;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) w[r * CT + ct] = acc[ct][4 * g + r];
+    __syncthreads();
+    const int row = threadIdx.x / MM, m = threadIdx.x % MM;  // 256 threads = M x MM
+    float s[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) s[ct] = buf[row * PITCH + m * CT + ct];
+    for (int q = 1; q < NWF; ++q)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) s[ct] += buf[(q * M + row) * PITCH + m * CT + ct];
+    if (row < rows_valid) {
+      T* o = out + (int64_t)row * gstride + col_start<CT>(MM * g + m, d);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) Elem<T>::store(o + ct, s[ct] * mul);
+    }
+  }
+}
+
+// Work of workgroup blockIdx: heaviest first, every other round of 256 (one workgroup a CU) the other way round, so that a CU that
+// gets one of each round gets about the same work as the next (s = 1024, 24 heads, 768 workgroups: 196 -> 175 us for the whole
+// forward and backward).
+__device__ __forceinline__ int work_index() {
+  const int b = blockIdx.x >> 8, c = blockIdx.x & 255, last = min(255, (int)gridDim.x - 1 - (b << 8));
+  return (b << 8) + ((b & 1) ? last - c : c);
+}
+
+// waves that share a SIMD: what the accumulators and the prefetched operands leave room for
+constexpr int waves_rows(int M, int DT) { return M == 16 ? (DT <= 2 ? 4 : DT <= 4 ? 3 : 2) : DT <= 2 ? 3 : 2; }
+constexpr int waves_cols(int M, int DT) { return M == 16 ? (DT <= 2 ? 3 : 2) : DT <= 4 ? 2 : 1; }
+
+// ---------------------------------------------------------------------------------------------------
+// forward: O, LSE of M query rows.  S^T = K Q^T (keys in rows), softmax along a lane's registers, O^T += V^T P^T.
+// ---------------------------------------------------------------------------------------------------
+template <int M, int DT, bool DROP, typename T>
+__global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kernel(AttnParams P, const T* __restrict__ q, const T* __restrict__ k,
+                                                                                 const T* __restrict__ v, T* __restrict__ o, float* __restrict__ lse) {
+  typedef Geo<M> G;
+  constexpr int QP = 32 * DT + 4, CT = 32 * DT / M, NV = G::NV;
+  __shared__ __attribute__((aligned(16))) float Qs[M * QP];
+  __shared__ __attribute__((aligned(16))) float buf[NWF * M * merge_pitch<M, CT>()];
+  __shared__ float ml[2][NWF][M];
+  const int N = P.b * P.A, nrb = (P.s + M - 1) / M, wi = work_index();
+  const int rb = nrb - 1 - wi / N;  // heaviest row blocks first
+  const int bn = wi % N, beta = bn / P.A, n = bn % P.A;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & (M - 1), hh = lane / M;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a;
+  const int i0 = M * rb, i = i0 + li, i_ld = min(i, P.s - 1);
+  const int jlim = P.causal ? i : P.s - 1;
+  const int ntile = (P.causal ? min(i0 + M, P.s) : P.s) / kTileF + ((P.causal ? min(i0 + M, P.s) : P.s) % kTileF != 0);
+  rows_to_lds<M, DT>(Qs, q + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  const uint64_t rowG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s + (uint64_t)i_ld) * (uint64_t)(P.s >> 3);
+  const float sc2 = P.scale * kLog2eF;
+  const T* kg = k + base;
+  const T* vg = v + base + col_start<CT>(li, P.d);
+  auto krow = [&](int jt, int t) __attribute__((always_inline)) { return kg + (int64_t)min(kTileF * jt + G::key_of_row(t, li), P.s - 1) * P.stride_s; };
+  typename G::acc_t oacc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] = 0.f;
+  float m_ref = -1.0e30f, l_run = 0.f;
+  float4_t ring[kRingF];
+  ring_start<M, DT>(ring, krow(wave, 0), krow(wave, G::SUB - 1), hh, P.d);
+  __syncthreads();
+  const float* qrow = Qs + li * QP + 4 * hh;
+  constexpr int VA = rows_ahead(CT, NV);
+  for (int jt = wave; jt < ntile; jt += NWF) {
+    const int j0 = kTileF * jt;
+    auto vrow = [&](int e) __attribute__((always_inline)) { return vg + (int64_t)min(j0 + G::key_of_value(e, hh), P.s - 1) * P.stride_s; };
+    float vf[VA][CT];
+#pragma unroll
+    for (int e = 0; e < VA; ++e) load_cols<CT>(vrow(e), vf[e]);
+    float st[NV];
+    if constexpr (M == 32) {
+      const float16_t s0 = dot_tile<M, DT, 0>(ring, krow(jt, 0), krow(jt + NWF, 0), krow(jt + NWF, 0), qrow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < NV; ++e) st[e] = s0[e] * sc2;
+    } else {
+      const float4_t s0 = dot_tile<M, DT, 0>(ring, krow(jt, 0), krow(jt, 1), krow(jt + NWF, 0), qrow, hh, P.d);
+      const float4_t s1 = dot_tile<M, DT, (2 * DT) % kRingF>(ring, krow(jt, 1), krow(jt + NWF, 0), krow(jt + NWF, 1), qrow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { st[e] = s0[e] * sc2; st[4 + e] = s1[e] * sc2; }
+    }
+    float mt = -1.0e30f;
+    if (jt == ntile - 1) {  // keys beyond jlim (above the diagonal, or past the end) are masked
+#pragma unroll
+      for (int e = 0; e < NV; ++e)
+        if (j0 + G::key_of_value(e, hh) > jlim) st[e] = -INFINITY;
+    }
+#pragma unroll
+    for (int e = 0; e < NV; ++e) mt = fmaxf(mt, st[e]);
+    mt = column_max<M>(mt);
+    if (__builtin_amdgcn_ballot_w64(mt > m_ref + kLazyF) != 0) {
+      const float m_new = fmaxf(m_ref, mt), corr = __builtin_amdgcn_exp2f(m_ref - m_new);
+      m_ref = m_new;
+      l_run *= corr;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] *= corr;
+    }
+#pragma unroll
+    for (int c = 0; c < NV / 8; ++c) {
+      uint32_t keep = 0xffu;
+      if (DROP) keep = keep_bits8(rowG + (uint64_t)((j0 + G::key_of_value(8 * c, hh)) >> 3), 0u, P.key0, P.key1, P.thresh);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int e = 8 * c + x;
+        const float pe = __builtin_amdgcn_exp2f(st[e] - m_ref);
+        l_run += pe;
+        const float pd = !DROP || ((keep >> x) & 1u) ? pe : 0.f;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) oacc[ct] = G::mfma(vf[e % VA][ct], pd, oacc[ct]);
+        asm volatile("" : "+v"(oacc[0]));
+        if (e + VA < NV) load_cols<CT>(vrow(e + VA), vf[e % VA]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  const float l_tot = column_sum<M>(l_run);
+  if (hh == 0) { ml[0][wave][li] = m_ref; ml[1][wave][li] = l_tot; }
+  __syncthreads();
+  float m = ml[0][0][li], l = 0.f;
+  for (int w = 1; w < NWF; ++w) m = fmaxf(m, ml[0][w][li]);
+  for (int w = 0; w < NWF; ++w) l = fmaf(ml[1][w][li], __builtin_amdgcn_exp2f(ml[0][w][li] - m), l);
+  const float wgt = __builtin_amdgcn_exp2f(m_ref - m) * P.keep_scale / l;
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] *= wgt;
+  if (wave == 0 && hh == 0 && i < P.s) lse[(size_t)bn * P.s + i] = (m + __builtin_amdgcn_logf(l)) * kLn2F;
+  merge_store<M, CT>(oacc, buf, wave, li, hh, 1.f, o + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// backward, row pass: delta_i = dO_i . O_i and dQ_i = alpha sum_j dS_ij K_j of M query rows.
+// ---------------------------------------------------------------------------------------------------
+template <int M, int DT, bool DROP, typename T>
+__global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32_kernel(AttnParams P, const T* __restrict__ q, const T* __restrict__ k,
+                                                                                      const T* __restrict__ v, const T* __restrict__ o,
+                                                                                      const float* __restrict__ lse, const T* __restrict__ dO,
+                                                                                      T* __restrict__ dq, float* __restrict__ delta) {
+  typedef Geo<M> G;
+  constexpr int QP = 32 * DT + 4, CT = 32 * DT / M, NV = G::NV, TPR = 64 * NWF / M;  // TPR: threads a row in the delta sums
+  __shared__ __attribute__((aligned(16))) float Qs[M * QP], Gs[M * QP];
+  __shared__ __attribute__((aligned(16))) float buf[NWF * M * merge_pitch<M, CT>()];
+  __shared__ float part[M][TPR];
+  const int N = P.b * P.A, nrb = (P.s + M - 1) / M, wi = work_index();
+  const int rb = nrb - 1 - wi / N;
+  const int bn = wi % N, beta = bn / P.A, n = bn % P.A;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & (M - 1), hh = lane / M;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a;
+  const int i0 = M * rb, i = i0 + li, i_ld = min(i, P.s - 1);
+  const int jlim = P.causal ? i : P.s - 1;
+  const int ntile = ((P.causal ? min(i0 + M, P.s) : P.s) + kTileF - 1) / kTileF;
+  rows_to_lds<M, DT>(Qs, q + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  rows_to_lds<M, DT>(Gs, dO + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  const T* kg = k + base;
+  const T* vg = v + base;
+  const T* kc = k + base + col_start<CT>(li, P.d);
+  auto rowat = [&](int jt, int t) __attribute__((always_inline)) { return (int64_t)min(kTileF * jt + G::key_of_row(t, li), P.s - 1) * P.stride_s; };
+  float4_t ring[kRingF];
+  ring_start<M, DT>(ring, kg + rowat(wave, 0), (M == 32 ? vg : kg) + rowat(wave, G::SUB - 1), hh, P.d);
+  __syncthreads();
+  {
+    const int r = threadIdx.x / TPR, tr = threadIdx.x % TPR;
+    const T* orow = o + base + (int64_t)min(i0 + r, P.s - 1) * P.stride_s;
+    float a = 0.f;
+    for (int x = 4 * tr; x < P.d; x += 4 * TPR) {
+      const float4_t f = load4(orow + x);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a = fmaf(f[u], Gs[r * QP + x + u], a);
+    }
+    part[r][tr] = a;
+  }
+  __syncthreads();
+  float dl = 0.f;
+#pragma unroll
+  for (int tr = 0; tr < TPR; ++tr) dl += part[li][tr];
+  if (wave == 0 && hh == 0 && i < P.s) delta[(size_t)bn * P.s + i] = dl;
+  const float lse2 = lse[(size_t)bn * P.s + i_ld] * kLog2eF;
+  const uint64_t rowG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s + (uint64_t)i_ld) * (uint64_t)(P.s >> 3);
+  const float sc2 = P.scale * kLog2eF;
+  typename G::acc_t acc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int e = 0; e < NV / G::SUB; ++e) acc[ct][e] = 0.f;
+  const float *qrow = Qs + li * QP + 4 * hh, *grow = Gs + li * QP + 4 * hh;
+  constexpr int CA = rows_ahead(CT, NV);
+  for (int jt = wave; jt < ntile; jt += NWF) {
+    const int j0 = kTileF * jt;
+    auto crow = [&](int e) __attribute__((always_inline)) { return kc + (int64_t)min(j0 + G::key_of_value(e, hh), P.s - 1) * P.stride_s; };
+    float cf[CA][CT], st[NV], dd[NV];
+    if constexpr (M == 32) {
+      const float16_t s0 = dot_tile<M, DT, 0>(ring, kg + rowat(jt, 0), vg + rowat(jt, 0), vg + rowat(jt, 0), qrow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < CA; ++e) load_cols<CT>(crow(e), cf[e]);
+      const float16_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, vg + rowat(jt, 0), kg + rowat(jt + NWF, 0), kg + rowat(jt + NWF, 0), grow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < NV; ++e) { st[e] = s0[e]; dd[e] = d0[e]; }
+    } else {
+      const float4_t s0 = dot_tile<M, DT, 0>(ring, kg + rowat(jt, 0), kg + rowat(jt, 1), vg + rowat(jt, 0), qrow, hh, P.d);
+      const float4_t s1 = dot_tile<M, DT, (2 * DT) % kRingF>(ring, kg + rowat(jt, 1), vg + rowat(jt, 0), vg + rowat(jt, 1), qrow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < CA; ++e) load_cols<CT>(crow(e), cf[e]);
+      const float4_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, vg + rowat(jt, 0), vg + rowat(jt, 1), kg + rowat(jt + NWF, 0), grow, hh, P.d);
+      const float4_t d1 = dot_tile<M, DT, (6 * DT) % kRingF>(ring, vg + rowat(jt, 1), kg + rowat(jt + NWF, 0), kg + rowat(jt + NWF, 1), grow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { st[e] = s0[e]; st[4 + e] = s1[e]; dd[e] = d0[e]; dd[4 + e] = d1[e]; }
+    }
+#pragma unroll
+    for (int e = 0; e < NV; ++e) st[e] = fmaf(st[e], sc2, -lse2);
+    if (jt == ntile - 1) {
+#pragma unroll
+      for (int e = 0; e < NV; ++e)
+        if (j0 + G::key_of_value(e, hh) > jlim) st[e] = -INFINITY;
+    }
+#pragma unroll
+    for (int c = 0; c < NV / 8; ++c) {
+      uint32_t keep = 0xffu;
+      if (DROP) keep = keep_bits8(rowG + (uint64_t)((j0 + G::key_of_value(8 * c, hh)) >> 3), 0u, P.key0, P.key1, P.thresh);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int e = 8 * c + x;
+        const float pe = __builtin_amdgcn_exp2f(st[e]);
+        const float dp = !DROP || ((keep >> x) & 1u) ? dd[e] * P.keep_scale : 0.f;
+        const float ds = pe * (dp - dl);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[ct] = G::mfma(cf[e % CA][ct], ds, acc[ct]);
+        asm volatile("" : "+v"(acc[0]));
+        if (e + CA < NV) load_cols<CT>(crow(e + CA), cf[e % CA]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  merge_store<M, CT>(acc, buf, wave, li, hh, P.scale, dq + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// backward, column pass: dK_j = alpha sum_i dS_ij q_i, dV_j = sum_i D_ij dO_i of M keys.  Scores the other way round, S = Q K^T:
+// a lane owns one key, its registers are query rows, so D and dS are again B operands as they are.  One Philox call covers 8
+// consecutive keys of a row = 8 lanes: each of the 8 lanes draws an eighth of the calls of the lane's rows and all read one
+// another's bits.
+// ---------------------------------------------------------------------------------------------------
+// keep decisions of value E from the lane of the group of eight that drew its row
+template <int E, int CALLS>
+__device__ __forceinline__ bool kept(uint32_t mine, int li) {
+  return ((uint32_t)__builtin_amdgcn_ds_swizzle((int)mine, ((E / CALLS) << 5) | 0x18) >> (8 * (E % CALLS) + (li & 7))) & 1u;
+}
+template <int M, int DT, bool DROP, typename T>
+__global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32_kernel(AttnParams P, const T* __restrict__ q, const T* __restrict__ k,
+                                                                                      const T* __restrict__ v, const float* __restrict__ lse,
+                                                                                      const T* __restrict__ dO, const float* __restrict__ delta,
+                                                                                      T* __restrict__ dk, T* __restrict__ dv) {
+  typedef Geo<M> G;
+  constexpr int QP = 32 * DT + 4, CT = 32 * DT / M, NV = G::NV, CALLS = NV / 8;
+  __shared__ __attribute__((aligned(16))) float Ks[M * QP], Vs[M * QP];
+  __shared__ __attribute__((aligned(16))) float buf[NWF * M * merge_pitch<M, CT>()];
+  const int N = P.b * P.A, nt = (P.s + kTileF - 1) / kTileF, wi = work_index();
+  const int kb = wi / N;  // key block 0 sweeps the most rows: heaviest first
+  const int bn = wi % N, beta = bn / P.A, n = bn % P.A;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & (M - 1), hh = lane / M;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a;
+  const int j0 = M * kb, j = j0 + li;
+  const int it0 = P.causal ? j0 / kTileF : 0;
+  rows_to_lds<M, DT>(Ks, k + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+  rows_to_lds<M, DT>(Vs, v + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+  const T* qg = q + base;
+  const T* gg = dO + base;
+  const int cs = col_start<CT>(li, P.d);
+  const float* lse_h = lse + (size_t)bn * P.s;
+  const float* delta_h = delta + (size_t)bn * P.s;
+  const uint64_t headG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s) * (uint64_t)(P.s >> 3) +
+                         (uint64_t)((j0 + (li & ~7)) >> 3);
+  const float sc2 = P.scale * kLog2eF;
+  typename G::acc_t ka[CT], va[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int e = 0; e < NV / G::SUB; ++e) { ka[ct][e] = 0.f; va[ct][e] = 0.f; }
+  auto rowat = [&](int it, int t) __attribute__((always_inline)) { return (int64_t)min(kTileF * it + G::row_of_row(t, li), P.s - 1) * P.stride_s; };
+  float4_t ring[kRingF];
+  ring_start<M, DT>(ring, qg + rowat(it0 + wave, 0), (M == 32 ? gg : qg) + rowat(it0 + wave, G::SUB - 1), hh, P.d);
+  __syncthreads();
+  const float *krow = Ks + li * QP + 4 * hh, *vrow = Vs + li * QP + 4 * hh;
+  constexpr int CA = rows_ahead(2 * CT, NV);
+  for (int it = it0 + wave; it < nt; it += NWF) {
+    const int i0 = kTileF * it;
+    // rows past the end get probability 0 (what they read is clamped)
+    auto row_of = [&](int e) __attribute__((always_inline)) { return (int64_t)min(i0 + G::row_of_value(e, hh), P.s - 1) * P.stride_s + cs; };
+    float gc[CA][CT], qc[CA][CT], st[NV], dd[NV];
+    auto start_cols = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int e = 0; e < CA; ++e) {
+        load_cols<CT>(gg + row_of(e), gc[e]);
+        load_cols<CT>(qg + row_of(e), qc[e]);
+      }
+    };
+    if constexpr (M == 32) {
+      const float16_t s0 = dot_tile<M, DT, 0>(ring, qg + rowat(it, 0), gg + rowat(it, 0), gg + rowat(it, 0), krow, hh, P.d);
+      start_cols();
+      const float16_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, gg + rowat(it, 0), qg + rowat(it + NWF, 0), qg + rowat(it + NWF, 0), vrow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < NV; ++e) { st[e] = s0[e]; dd[e] = d0[e]; }
+    } else {
+      const float4_t s0 = dot_tile<M, DT, 0>(ring, qg + rowat(it, 0), qg + rowat(it, 1), gg + rowat(it, 0), krow, hh, P.d);
+      const float4_t s1 = dot_tile<M, DT, (2 * DT) % kRingF>(ring, qg + rowat(it, 1), gg + rowat(it, 0), gg + rowat(it, 1), krow, hh, P.d);
+      start_cols();
+      const float4_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, gg + rowat(it, 0), gg + rowat(it, 1), qg + rowat(it + NWF, 0), vrow, hh, P.d);
+      const float4_t d1 = dot_tile<M, DT, (6 * DT) % kRingF>(ring, gg + rowat(it, 1), qg + rowat(it + NWF, 0), qg + rowat(it + NWF, 1), vrow, hh, P.d);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { st[e] = s0[e]; st[4 + e] = s1[e]; dd[e] = d0[e]; dd[4 + e] = d1[e]; }
+    }
+    float4_t dl[NV / 4];
+#pragma unroll
+    for (int g = 0; g < NV / 4; ++g) {
+      const int ib = min(i0 + G::row_of_value(4 * g, hh), P.s - 4);  // s % 8 == 0: a group of four rows is inside or outside as a whole
+      const float4_t ls = *reinterpret_cast<const float4_t*>(lse_h + ib);
+      dl[g] = *reinterpret_cast<const float4_t*>(delta_h + ib);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) st[4 * g + r] = fmaf(st[4 * g + r], sc2, -(ls[r] * kLog2eF));
+    }
+    if ((P.causal && i0 < j0 + M) || i0 + kTileF > P.s) {
+#pragma unroll
+      for (int e = 0; e < NV; ++e) {
+        const int i = i0 + G::row_of_value(e, hh);
+        if ((P.causal && j > i) || i >= P.s) st[e] = -INFINITY;
+      }
+    }
+    uint32_t mine = 0;
+    if (DROP) {
+#pragma unroll
+      for (int y = 0; y < CALLS; ++y) {
+        const int i = i0 + G::row_of_value(CALLS * (li & 7) + y, hh);
+        mine |= keep_bits8(headG + (uint64_t)i * (uint64_t)(P.s >> 3), 0u, P.key0, P.key1, P.thresh) << (8 * y);
+      }
+    }
+#define SAR_ROW(E)                                                                                                          \
+  if constexpr (E < NV) {                                                                                                   \
+    const bool keep = !DROP || kept<E, CALLS>(mine, li);                                                                    \
+    const float pe = __builtin_amdgcn_exp2f(st[E]);                                                                         \
+    const float pd = keep ? pe * P.keep_scale : 0.f, dp = keep ? dd[E] * P.keep_scale : 0.f;                                \
+    const float ds = pe * (dp - dl[(E) >> 2][(E) & 3]);                                                                     \
+    _Pragma("unroll") for (int ct = 0; ct < CT; ++ct) {                                                                     \
+      va[ct] = G::mfma(gc[(E) % CA][ct], pd, va[ct]);                                                                       \
+      ka[ct] = G::mfma(qc[(E) % CA][ct], ds, ka[ct]);                                                                       \
+    }                                                                                                                       \
+    asm volatile("" : "+v"(va[0]), "+v"(ka[0]));                                                                            \
+    if constexpr ((E) + CA < NV) {                                                                                          \
+      load_cols<CT>(gg + row_of((E) + CA), gc[(E) % CA]);                                                                   \
+      load_cols<CT>(qg + row_of((E) + CA), qc[(E) % CA]);                                                                   \
+    }                                                                                                                       \
+    __builtin_amdgcn_sched_barrier(0);                                                                                      \
+  }
+    SAR_ROW(0) SAR_ROW(1) SAR_ROW(2) SAR_ROW(3) SAR_ROW(4) SAR_ROW(5) SAR_ROW(6) SAR_ROW(7)
+    SAR_ROW(8) SAR_ROW(9) SAR_ROW(10) SAR_ROW(11) SAR_ROW(12) SAR_ROW(13) SAR_ROW(14) SAR_ROW(15)
+#undef SAR_ROW
+  }
+  merge_store<M, CT>(va, buf, wave, li, hh, 1.f, dv + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+  merge_store<M, CT>(ka, buf, wave, li, hh, P.scale, dk + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+}
+
+// M = 16 where M = 32 leaves less than two workgroups a CU: twice the workgroups with half the work each start sooner and spread a
+// causal triangle better (us, forward and backward, M = 32 / 16: s = 128, 2 heads of 64 25.3 / 18.0; s = 1024, 8 heads of 128
+// 189 / 136; from there on equal, 512 x 64 heads 134 / 136, or slower for twice the operand reads, 1024 x 24 heads 175 / 186).
+inline bool narrow(const AttnParams& P) { return (int64_t)((P.s + 31) / 32) * P.b * P.A < 512; }
+
+template <int M, int DT, typename T>
+hipError_t fwd_dt(const AttnParams& P, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st) {
+  const dim3 grid((unsigned)((P.s + M - 1) / M * P.b * P.A)), block(64 * NWF);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)q, (const T*)k, (const T*)v, (T*)o, lse); };
+  if (P.thresh != 0) go(attn_fwd_f32_kernel<M, DT, true, T>);
+  else go(attn_fwd_f32_kernel<M, DT, false, T>);
+  return hipGetLastError();
+}
+
+template <int M, int DT, typename T>
+hipError_t bwd_dt(const AttnParams& P, const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, void* dk,
+                  void* dv, float* delta, int passes, hipStream_t st) {
+  const dim3 grid((unsigned)((P.s + M - 1) / M * P.b * P.A)), block(64 * NWF);
+  if (passes & 1) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)q, (const T*)k, (const T*)v, (const T*)o, lse, (const T*)dO, (T*)dq, delta); };
+    if (P.thresh != 0) go(attn_bwd_rows_f32_kernel<M, DT, true, T>);
+    else go(attn_bwd_rows_f32_kernel<M, DT, false, T>);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (passes & 2) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)q, (const T*)k, (const T*)v, lse, (const T*)dO, (const float*)delta, (T*)dk, (T*)dv); };
+    if (P.thresh != 0) go(attn_bwd_cols_f32_kernel<M, DT, true, T>);
+    else go(attn_bwd_cols_f32_kernel<M, DT, false, T>);
+  }
+  return hipGetLastError();
+}
+
+// f(M, DT) with the constants that the shape asks for
+template <typename F>
+hipError_t by_shape(const AttnParams& P, F&& f) {
+#define SAR_DT(N) case N: return narrow(P) ? f(std::integral_constant<int, 16>{}, std::integral_constant<int, N>{}) : f(std::integral_constant<int, 32>{}, std::integral_constant<int, N>{});
+  switch ((P.d + 31) / 32) {
+    SAR_DT(1) SAR_DT(2) SAR_DT(3) SAR_DT(4) SAR_DT(5) SAR_DT(6) SAR_DT(7) SAR_DT(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef SAR_DT
+}
+
+}  // namespace
+}  // namespace sar

@@ -114,14 +114,17 @@ def test_fp32_shapes(s, b, a, t, rank, d, p, std, outlier):
     ("f32", 104, 196, 0.1, 1, None), ("f32", 72, 228, 0.1, 0, None), ("f32", 256, 256, 0.1, 1, None),                            # widest heads
     ("f32", 104, 64, 0.1, 1, -0.2), ("f32", 72, 64, 0.1, 0, 0.0),                                                                # any sign of the score scale
     ("bf16", 72, 8, 0.1, 1, None), ("bf16", 168, 72, 0.1, 1, None), ("bf16", 136, 256, 0.0, 0, None)])
-def test_fp32_matrix_instruction_kernels(dtype, s, d, p, causal, scale):
-    """The kernels on fp32 matrix instructions where they can go wrong: sequences that end inside a tile of 32, with fewer tiles
+@pytest.mark.parametrize("heads", [2, 128])
+def test_fp32_matrix_instruction_kernels(dtype, s, d, p, causal, scale, heads):
+    """The kernels on fp32 matrix instructions, in blocks of 16 rows (few heads) and of 32 (many), where they can go wrong: sequences that end inside a tile of 32, with fewer tiles
     than waves and one more, head dimensions that are no multiple of 8 or 32, the smallest and the largest, bf16 head
     dimensions that the bf16 kernels leave to them.  Tolerances: those of the other tests of either dtype."""
     from gpu_util import run_attn
-    sh = oracle.AttnShape(s=s, b=2, a=4, h=4 * d, t=2, rank=1, p=p, seed=77, offset=(1 << 32) - 50, causal=causal, **({} if scale is None else {"scale": scale}))
-    q, k, v, do = attn_inputs(s, 2, 2, d, dtype, seed=5)
-    print(f"{dtype} s={s} d={d} p={p} causal={causal} scale={scale}", flush=True)
+    b = 2 if heads == 2 else 512 // ((s + 31) // 32) // heads + 1
+    sh = oracle.AttnShape(s=s, b=b, a=2 * heads, h=2 * heads * d, t=2, rank=1, p=p, seed=77, offset=(1 << 32) - 50, causal=causal,
+                          **({} if scale is None else {"scale": scale}))
+    q, k, v, do = attn_inputs(s, b, heads, d, dtype, seed=5)
+    print(f"{dtype} s={s} d={d} p={p} causal={causal} scale={scale} b={b} heads={heads}", flush=True)
     got = run_attn(sh, dtype, q, k, v, do)
     if dtype == "bf16":
         return _check_bf16_heads("f32-mfma", sh, q, k, v, do, got, range(4))
