@@ -7,7 +7,7 @@
 
 namespace sar {
 
-// form of the column pass at d = 128, 160 and s % 64 == 0: -1 = the library's choice; 0 plain, 1 software-pipelined,
+// form of the column pass: -1 = the library's choice; 0 plain, 1 software-pipelined,
 // 2 producer / consumer waves, 3 the same with persistent workgroups (forced forms fall back where they do not exist: 1 to
 // the plain one, 3 to 2)
 static std::atomic<int> g_force_form{-1};
@@ -21,13 +21,17 @@ hipError_t launch_attn_bwd_dkdv_mfma_split(const AttnParams& P, const void* q, c
 // the form that runs: 0 plain, 1 software-pipelined, 2 producer / consumer (3: forced persistent)
 template <int D>
 static int dkdv_form(const AttnParams& P, const uint16_t* ds_ws) {
-  if (P.s % 64 != 0) return 0;
   const int force = g_force_form.load();
-  if (force >= 0) return (D < 128 && force == 1) ? 0 : force;  // the software-pipelined form exists for d = 128, 160 only
-  // d = 64 (22B shard): 101.5 against 107.1 us with the dS stores of the once-form, 90.2 against 86.2 without
-  if (D < 128) return ds_ws ? 2 : 0;
-  // measured (once-form, us): 530B shard 78.6 / 80.2 / 69.6, 175B 70.4 / 60.5 / 48.1, 1T 98.3 / - / 90.0 for forms 0 / 1 / 2
-  return 2;
+  if (force >= 0) return force == 1 && (D < 128 || P.s % 64 != 0) ? 0 : force;  // the software-pipelined form: d = 128, 160 and full tiles only
+  // measured (once-form, us): 530B shard 78.6 / 80.2 / 69.6, 175B 70.4 / 60.5 / 48.1, 1T 98.3 / - / 90.0 for forms 0 / 1 / 2;
+  // s = 1000, 24 heads, whole backward, forms 0 / 2: d = 128 54.6 / 40.2, d = 160 63.5 / 45.0 (without the tiles 54.0 / 45.2, 59.8 / 50.9)
+  if (D >= 128 || (ds_ws && P.s % 64 == 0)) return 2;
+  // Without dropout, or without the tiles to store, two plain workgroups on a CU are as good once the launch keeps both busy.
+  // Whole backward at d = 64, forms 0 / 2, us: s = 2048, 12 heads, causal 58.5 / 47.5; no mask, s = 1000, 24 heads (384
+  // workgroups) 42.4 / 44.2; s = 2048, 64 heads 301 / 302 and (p = 0.1, persistent) 376 / 366; s = 1000, 24 heads, causal,
+  // p = 0.1, with tiles 37.9 / 30.5.  d = 96: 71.0 / 63.0, 52.1 / 55.6, 397 / 414, 481 / 474, 48.1 / 35.9.
+  const int64_t blocks = (int64_t)((P.s + 63) / 64) * P.b * P.A;
+  return P.thresh != 0 || blocks <= (P.causal ? 2 : 1) * attn_mfma_cu_count() ? 2 : 0;
 }
 
 // persistent workgroups in the producer / consumer form: -1 the launcher decides by shape, 0 / 1 forced

@@ -15,14 +15,15 @@
 //                          issues every direct-to-LDS load of the workgroup.
 // The consumer works one tile behind the producer; (Q, dO) tiles live in three stages: tile m is loaded during step m-1, read
 // by the producer in step m and by the consumer in step m+1.  One workgroup barrier per step.
-// Needs s % 64 == 0.  Everything is in vector registers (compiled with -amdgpu-mfma-vgpr-form): no copies out of
+// RAG: s is no multiple of 64 (the last tile's loads are clamped to the last row, and its rows and keys past the end get
+// probability 0).  Everything is in vector registers (compiled with -amdgpu-mfma-vgpr-form): no copies out of
 // accumulation registers.
 #pragma once
 #include "attn_mfma_cols_kernel.h"
 
 namespace sar {
 
-template <int D, bool DROP, bool WDS, bool PERS = false>
+template <int D, bool DROP, bool WDS, bool PERS, bool RAG>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                                     const uint16_t* __restrict__ v, const float* __restrict__ lse,
                                                                     const uint16_t* __restrict__ dO, const float* __restrict__ delta,
@@ -34,7 +35,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
   __shared__ float lse_s[NST][BI], delta_s[NST][BI];
 
   const int N = P.b * P.A;
-  const int nb = P.s / BN;
+  const int nb = RAG ? (P.s + BN - 1) / BN : P.s / BN;
   // Which key blocks this workgroup takes.  Plain: one, block blockIdx / N (key block 0 sweeps the most rows: heaviest
   // first).  PERS: the grid is R x N workgroups (R x N <= number of CUs) and workgroup (wq, head) takes its head's key blocks
   // wq, 2R-1-wq, 2R+wq, 4R-1-wq, ...: a heavy block, then a light one; the next block's K, V and first (Q, dO) tile are
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
   const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a;
   const int gstride = (int)P.stride_s;
   int jw0 = kb * BN + kgp * 32;  // first key of this pair
-  const int nit = P.s / BI;
+  const int nit = RAG ? nb : P.s / BI;
   int it0 = P.causal ? kb : 0;
   // (Q, dO) tile m of the current key block lives in stage (m - it0 + off) % NST; its K and V blocks are staged where tile
   // it0 + 1 will go; its output tiles go where its last tile was
@@ -69,8 +70,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
     kvmap.init(w, lane, gstride, true);
     {
       uint16_t* Kst = smem + stage_of(it0 + 1) * 2 * TILE;
-      dma_tile<D>(kvmap, k + base + (int64_t)(kb * BN) * gstride, Kst, w);
-      dma_tile<D>(kvmap, v + base + (int64_t)(kb * BN) * gstride, Kst + TILE, w);
+      if (RAG && kb == nb - 1) {
+        dma_tile_ragged<D>(kvmap, k + base + (int64_t)(kb * BN) * gstride, Kst, w, lane, gstride, P.s - kb * BN);
+        dma_tile_ragged<D>(kvmap, v + base + (int64_t)(kb * BN) * gstride, Kst + TILE, w, lane, gstride, P.s - kb * BN);
+      } else {
+        dma_tile<D>(kvmap, k + base + (int64_t)(kb * BN) * gstride, Kst, w);
+        dma_tile<D>(kvmap, v + base + (int64_t)(kb * BN) * gstride, Kst + TILE, w);
+      }
       dma_wait();
       __syncthreads();  // the K and V blocks are staged
     }
@@ -136,11 +142,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (P.causal && m == kb) {  // the diagonal tile: keys j > i get probability exp2(-inf) = 0
+      // the diagonal tile: keys j > i get probability exp2(-inf) = 0; RAG: rows and keys past the end as well
+      if ((P.causal && m == kb) || (RAG && (m == nit - 1 || kb == nb - 1))) {
         asm volatile("" ::: "memory");  // keep this a branch: all other tiles skip it
+        const int jlim = RAG ? (i >= P.s ? -1 : P.causal ? i : P.s - 1) : i;  // last key that row i attends to
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          if (jw0 + 16 * (e >> 3) + 8 * hh + (e & 7) > i) st[e] = -INFINITY;
+          if (jw0 + 16 * (e >> 3) + 8 * hh + (e & 7) > jlim) st[e] = -INFINITY;
       }
       // Q = P / (1-p) comes straight out of the exponential (log2 of the scale folded into the row's LSE term), so that
       // D = M Q is one select and dS = P (dD M / (1-p) - delta) = D dD - Q delta (1-p) two more operations per element.
@@ -199,8 +207,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
     const int so = stage_of(nit - 1);
     if (has_next) {
       uint16_t* Kst = smem + ((so + 2) % NST) * 2 * TILE;
-      dma_tile<D>(kvmap, k + base + (int64_t)(kb_n * BN) * gstride, Kst, w);
-      dma_tile<D>(kvmap, v + base + (int64_t)(kb_n * BN) * gstride, Kst + TILE, w);
+      if (RAG && kb_n == nb - 1) {
+        dma_tile_ragged<D>(kvmap, k + base + (int64_t)(kb_n * BN) * gstride, Kst, w, lane, gstride, P.s - kb_n * BN);
+        dma_tile_ragged<D>(kvmap, v + base + (int64_t)(kb_n * BN) * gstride, Kst + TILE, w, lane, gstride, P.s - kb_n * BN);
+      } else {
+        dma_tile<D>(kvmap, k + base + (int64_t)(kb_n * BN) * gstride, Kst, w);
+        dma_tile<D>(kvmap, v + base + (int64_t)(kb_n * BN) * gstride, Kst + TILE, w);
+      }
     }
     __syncthreads();  // the consumers are done with the last tile
     if (has_next) dma_wait();
@@ -214,17 +227,24 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
     }  // key blocks
   } else {
     // ---- consumer ----
-    DmaMap<D> map;
+    DmaMap<D> map, last;  // last: RAG, the last tile's offsets
     map.init(w, lane, gstride, false);
+    if constexpr (RAG) last.init(w, lane, gstride, false, P.s - (nit - 1) * BI);
     auto fetch_to = [&](int it, int round, int sg) __attribute__((always_inline)) {  // rounds 0 .. 2 PER - 1 of tile `it`, into stage sg
       constexpr int PER = DmaMap<D>::PER;
       uint16_t* dst = smem + sg * 2 * TILE;
-      if (round < PER) dma_one<D>(map, qg + (int64_t)(it * BI) * gstride, dst, w, round);
+      if constexpr (RAG) {
+        const int u = round < PER ? round : round - PER, l = w + 4 * u;
+        const uint16_t* src = (round < PER ? qg : dog) + (int64_t)(it * BI) * gstride;
+        if (u < PER - 1 || l < DmaMap<D>::NL)
+          dma16(src, it == nit - 1 ? last.goff[u] : map.goff[u], lds_addr(dst + (round < PER ? 0 : TILE)) + 1024u * (uint32_t)l);
+      } else if (round < PER) dma_one<D>(map, qg + (int64_t)(it * BI) * gstride, dst, w, round);
       else dma_one<D>(map, dog + (int64_t)(it * BI) * gstride, dst + TILE, w, round - PER);
     };
     auto fetch_stats_to = [&](int it, int sg) __attribute__((always_inline)) {  // one float per row, straight into LDS
-      dma4(lse + (size_t)bn * P.s + it * BI + lane, lds_addr(lse_s[sg]));
-      dma4(delta + (size_t)bn * P.s + it * BI + lane, lds_addr(delta_s[sg]));
+      const int r = RAG ? min(lane, P.s - 1 - it * BI) : lane;
+      dma4(lse + (size_t)bn * P.s + it * BI + r, lds_addr(lse_s[sg]));
+      dma4(delta + (size_t)bn * P.s + it * BI + r, lds_addr(delta_s[sg]));
     };
     auto fetch = [&](int it, int round) __attribute__((always_inline)) { fetch_to(it, round, stage_of(it)); };
     auto fetch_stats = [&](int it) __attribute__((always_inline)) { fetch_stats_to(it, stage_of(it)); };

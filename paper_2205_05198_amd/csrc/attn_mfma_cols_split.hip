@@ -1,16 +1,17 @@
 // bf16 attention core, backward column pass (dK, dV) in its producer / consumer form (two waves per SIMD, each within
-// 256 vector registers; compiled WITH -amdgpu-mfma-vgpr-form): every head dimension of the matrix-core path, s % 64 == 0.
+// 256 vector registers; compiled WITH -amdgpu-mfma-vgpr-form): every head dimension of the matrix-core path.
 #define SAR_COLS_ACC "v"
 #include "attn_mfma_cols_split.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace sar {
 
 template <int D>
 static hipError_t bwd_dkdv_split_d(const AttnParams& P, const void* q, const void* k, const void* v, const float* lse, const void* dO, const float* delta,
                                    void* dk, void* dv, uint16_t* ds_ws, int pers, hipStream_t st) {
-  const int N = P.b * P.A, nb = P.s / 64;
+  const int N = P.b * P.A, nb = (P.s + 63) / 64;
   // Persistent workgroups (each takes several key blocks of its head, a heavy one then a light one, and overlaps a block's
   // start with the end of the one before): needs (key blocks at a time) x (heads) workgroups within the CU count; chosen
   // when every workgroup then gets at least two key blocks.
@@ -22,27 +23,26 @@ static hipError_t bwd_dkdv_split_d(const AttnParams& P, const void* q, const voi
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, lse,
                        (const uint16_t*)dO, delta, (uint16_t*)dk, (uint16_t*)dv, ds_ws);
   };
-  if (use_pers) {
+  auto with = [&](auto rag, auto persistent) {
+    constexpr bool PERS = decltype(persistent)::value, RAG = decltype(rag)::value;
     if (ds_ws) {
-      if (P.thresh != 0) go(attn_bwd_dkdv_split_kernel<D, true, true, true>);
-      else go(attn_bwd_dkdv_split_kernel<D, false, true, true>);
+      if (P.thresh != 0) go(attn_bwd_dkdv_split_kernel<D, true, true, PERS, RAG>);
+      else go(attn_bwd_dkdv_split_kernel<D, false, true, PERS, RAG>);
     } else {
-      if (P.thresh != 0) go(attn_bwd_dkdv_split_kernel<D, true, false, true>);
-      else go(attn_bwd_dkdv_split_kernel<D, false, false, true>);
+      if (P.thresh != 0) go(attn_bwd_dkdv_split_kernel<D, true, false, PERS, RAG>);
+      else go(attn_bwd_dkdv_split_kernel<D, false, false, PERS, RAG>);
     }
-  } else if (ds_ws) {
-    if (P.thresh != 0) go(attn_bwd_dkdv_split_kernel<D, true, true>);
-    else go(attn_bwd_dkdv_split_kernel<D, false, true>);
-  } else {
-    if (P.thresh != 0) go(attn_bwd_dkdv_split_kernel<D, true, false>);
-    else go(attn_bwd_dkdv_split_kernel<D, false, false>);
-  }
+  };
+  if (P.s % 64 != 0) {
+    if (use_pers) with(std::true_type(), std::true_type());
+    else with(std::true_type(), std::false_type());
+  } else if (use_pers) with(std::false_type(), std::true_type());
+  else with(std::false_type(), std::false_type());
   return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd_dkdv_mfma_split(const AttnParams& P, const void* q, const void* k, const void* v, const float* lse, const void* dO,
                                            const float* delta, void* dk, void* dv, uint16_t* ds_ws, int pers, hipStream_t st) {
-  if (P.s % 64 != 0) return hipErrorInvalidValue;
   switch (P.d) {
     case 64: return bwd_dkdv_split_d<64>(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, pers, st);
     case 96: return bwd_dkdv_split_d<96>(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, pers, st);

@@ -274,6 +274,24 @@ def test_column_pass_pipelined_and_plain(d, s, b, A, p, causal, two_pass, pipe):
     _check_bf16_heads(f"cols-pipe{pipe}", sh, q, k, v, do, got, range(b * A))
 
 
+@pytest.mark.parametrize("pers", [2, 3])
+@pytest.mark.parametrize("two_pass", [False, True])
+@pytest.mark.parametrize("d,s,b,A,p,causal", [(160, 328, 3, 44, 0.1, 1), (160, 8, 1, 2, 0.1, 1), (64, 200, 2, 66, 0.1, 0), (96, 136, 1, 3, 0.25, 1), (128, 440, 1, 132, 0.0, 1),
+                                              (128, 120, 1, 2, 0.1, 0), (64, 56, 1, 2, 0.0, 0), (96, 72, 2, 66, 0.1, 1)])
+def test_column_pass_producer_consumer_ragged(d, s, b, A, p, causal, two_pass, pers):
+    """The producer / consumer column pass on sequences that end inside a tile: the last (Q, dO) tile and the last key block are
+    fetched with clamped rows, and their rows and keys past the end have probability 0 in every tile they meet.  Plain (2)
+    and persistent (3: 132 heads, a workgroup comes to the ragged key block after others), one to seven tiles."""
+    import paper_2205_05198_amd as sar
+    from gpu_util import run_attn
+    sar.sar_test_force_variants(-1, -1, -1, pers)
+    sh = oracle.AttnShape(s=s, b=b, a=A, h=A * d, p=p, seed=79, offset=(1 << 32) - 777, causal=causal)
+    q, k, v, do = attn_inputs(s, b, A, d, "bf16", seed=41)
+    print(f"column pass ragged form={pers} d={d} s={s} b={b} A={A} causal={causal} p={p} two_pass={two_pass}", flush=True)
+    got = run_attn(sh, "bf16", q, k, v, do, two_pass=two_pass)
+    _check_bf16_heads(f"cols-ragged{pers}", sh, q, k, v, do, got, sorted({0, 1, b * A // 2, b * A - 1}))
+
+
 def test_bf16_generic_path_other_head_dim():
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=72, b=1, a=2, h=2 * 40, p=0.1, seed=3)
