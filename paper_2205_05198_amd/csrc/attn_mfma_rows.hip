@@ -542,10 +542,6 @@ __global__ __launch_bounds__(LW ? 512 : 256) void attn_bwd_dq_mfma_kernel(AttnPa
 
 bool attn_mfma_supported(int d) { return d == 64 || d == 96 || d == 128 || d == 160; }
 
-// 128-row workgroups pay when there are more of them than CUs (256 on this chip), so that the heaviest one does not set the pace,
-// and at the largest head dimension only (measured at d = 160: -19 % at s = 4096, -20 % at s = 8192, -21 % without the
-// mask, -14 % for 20 heads, -20 % for 32 heads; +14 % at the 16-head s = 2048 shape with its 256 workgroups; at d = 128
-// +4 % and +10 % with 768 and 384 workgroups, at d = 96 +9 % with 512).
 // sar_test_force_variants (tests, measurements) overrides the choice.
 static std::atomic<int> g_force_fwd128{-1}, g_force_fwdlw{-1}, g_force_dqlw{-1};  // -1: the library chooses; 0 / 1: forced
 void attn_mfma_force_variants(int fwd128, int fwdlw, int dqlw) {
@@ -567,78 +563,72 @@ int attn_mfma_cu_count() {
 
 static int cu_count() { return attn_mfma_cu_count(); }
 
-static bool fwd_use_128(const AttnParams& P) {
-  if (P.s < 128) return false;
-  const int f = g_force_fwd128.load();
-  if (f == 0 || f == 1) return f == 1;
-  const int64_t wgs = (int64_t)((P.s + 127) / 128) * P.b * P.A;
-  const int cus = cu_count();
-  return P.d >= 160 && (P.causal ? wgs > cus : wgs >= cus);
+// Form of the forward by shape; us at s, heads (b * a/t), p = 0 / 0.1, from one sweep of every form.  w64, w128: workgroups of 64
+// and of 128 rows.
+//   128-row workgroups (one a CU), no mask: a round of them costs about 5/3 (d = 160) or 2 (d = 128) rounds of 64-row workgroups
+//     with loader waves, so they pay where that saves rounds: d = 160, s = 2048, 12 heads 60.4 / 60.9 -> 42.2 / 50.3, s = 1000, 24
+//     heads 31.9 / 33.1 -> 24.6 / 28.9, but s = 1736, 24 heads (two rounds against three) 75.9 / 91.2 -> 75.4 / 77.2 without
+//     them; d = 128, s = 2048, 64 heads 187 / 209 -> 157 / 192, s = 1000, 24 heads 23.9 / 28.6 -> 21.6 / 26.0.
+//     Causal, d = 160: more of them than CUs, so that the heaviest does not set the pace (-19 % at s = 4096, -20 % at s = 8192;
+//     +14 % with 256 workgroups).
+//     d = 64 without mask and dropout, 1024 workgroups of 64 rows or more: 2048 x 64 heads 107 -> 89 (loader waves 95).
+//   loader waves: d = 64: 1736 x 24 heads, causal 20.0 / 26.3 (producer / consumer pairs) -> 18.3 / 24.4, 2048 x 64 57.6 /
+//     74.1 -> 52.4 / 69.4, without the mask 107.6 / 138.8 -> 95.3 / 128.7, 512 x 128 18.5 / 22.5 -> 17.3 / 20.7.  d = 96, where three
+//     workgroups without them share a CU: only while a CU gets one (1024 x 8, causal 12.8 / 16.1 -> 10.6 / 13.9), or under the
+//     mask two (2048 x 12 23.9 / 29.7 -> 21.5 / 24.1; without the mask 32.5 / 44.5 -> 44.4 / 46.6).  d = 128, causal: not once
+//     two workgroups a CU are exceeded (1736 x 24 33.3 / 38.7 -> 29.0 / 35.4 without; 2048 x 12 23.7 / 26.2 -> 28.6 / 33.6).  d = 64, causal,
+//     no dropout: not from four workgroups a CU on (2048 x 64 49.6 against 52.4).
+//   persistent workgroups: every one gets two row blocks or more, d >= 128; below that under the mask and with exactly as many
+//     blocks as two a CU (4096 x 8: d = 64 29.8 / 44.9 -> 29.1 / 41.3, d = 96 41.0 / 49.3 -> 39.5 / 47.2; with more blocks than
+//     that 1736 x 24 18.3 / 24.4 -> 22.2 / 31.5).
+enum class FwdForm { Plain, Loaders, Split, Persistent, Rows128 };
+template <int D>
+static FwdForm fwd_form(const AttnParams& P) {
+  const int cus = cu_count(), N = P.b * P.A, nrb = (P.s + 63) / 64;
+  const int64_t w64 = (int64_t)nrb * N, w128 = (int64_t)((P.s + 127) / 128) * N;
+  const int64_t rounds64 = (w64 + cus - 1) / cus, rounds128 = (w128 + cus - 1) / cus;
+  const int f128 = P.s < 128 ? 0 : g_force_fwd128.load();
+  const bool bare = P.thresh == 0 && w64 >= 4 * (int64_t)cus;
+  bool use128 = f128 == 1;
+  if (f128 < 0) {
+    if (P.causal) use128 = D == 160 && w128 > cus;
+    else use128 = D == 160 ? 5 * rounds128 <= 3 * rounds64 : D == 128 ? 2 * rounds128 <= rounds64 : D == 64 && bare;
+  }
+  if (use128) return FwdForm::Rows128;
+  int lw = g_force_fwdlw.load();
+  const bool forced = lw >= 0;
+  if (!forced) {
+    if (D == 64) lw = !(bare && P.causal);
+    else if (D == 96) lw = w64 <= (P.causal ? 2 : 1) * (int64_t)cus;
+    else lw = !(D == 128 && P.causal && w64 > 2 * (int64_t)cus);
+  }
+  if (lw == 0) return FwdForm::Plain;
+  if (lw == 2) return FwdForm::Split;
+  // a grid of (row blocks at a time) x (heads) within the CU count
+  const bool two = N <= cus && nrb >= 2 * std::min(nrb, cus / N);
+  if (forced ? lw == 3 && N <= cus : two && (D >= 128 || (P.causal && w64 <= 2 * (int64_t)cus))) return FwdForm::Persistent;
+  return FwdForm::Loaders;
 }
 
 template <int D>
 static hipError_t fwd_d(const AttnParams& P, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st) {
-  if (fwd_use_128(P)) {
-    const int N128 = P.b * P.A, nrb128 = (P.s + 127) / 128;
-    if (P.thresh != 0)
-      hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, true, 4>), dim3((unsigned)(nrb128 * N128)), dim3(512), 0, st, P, (const uint16_t*)q,
-                         (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
-    else
-      hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, false, 4>), dim3((unsigned)(nrb128 * N128)), dim3(512), 0, st, P, (const uint16_t*)q,
-                         (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
-    return hipGetLastError();
-  }
   const int N = P.b * P.A, nrb = (P.s + 63) / 64;
-  {
-    // loader waves: measured -10 % at d = 160 (530B shard), -9 % at d = 128 (175B), -8 % at d = 64, +15 % at d = 96 (22B
-    // shard: three 4-wave workgroups share a CU there and fill each other's stalls).
-    const int lw = g_force_fwdlw.load();
-    // producer / consumer pairs: measured against the tile-fetching waves -16 % at d = 64 (22B shard), +2 % at d = 160,
-    // +12 % at d = 128: where the head dimension is small the matrix and LDS work that moves to the second wave is a larger
-    // share of a step, at d >= 128 the vector work that stays is the step
-    if (lw == 2 || (lw < 0 && D == 64)) {
-      if (P.thresh != 0)
-        hipLaunchKernelGGL((attn_fwd_split_kernel<D, true>), dim3((unsigned)(nrb * N)), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k,
-                           (const uint16_t*)v, (uint16_t*)o, lse);
-      else
-        hipLaunchKernelGGL((attn_fwd_split_kernel<D, false>), dim3((unsigned)(nrb * N)), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k,
-                           (const uint16_t*)v, (uint16_t*)o, lse);
-      return hipGetLastError();
+  auto go = [&](auto kern, int blocks, int threads) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks * N)), dim3((unsigned)threads), 0, st, P, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v,
+                       (uint16_t*)o, lse);
+    return hipGetLastError();
+  };
+  auto with = [&](auto drop) {  // p = 0: every element is kept, the variants that draw no random numbers
+    constexpr bool DROP = decltype(drop)::value;
+    switch (fwd_form<D>(P)) {
+      case FwdForm::Rows128: return go(attn_fwd_mfma_kernel<D, DROP, 4>, (P.s + 127) / 128, 512);
+      case FwdForm::Split: return go(attn_fwd_split_kernel<D, DROP>, nrb, 512);
+      case FwdForm::Persistent: return go(attn_fwd_pers_kernel<D, DROP>, std::min(nrb, cu_count() / N), 512);
+      case FwdForm::Loaders: return go(attn_fwd_mfma_kernel<D, DROP, 2, true>, nrb, 512);
+      default: return go(attn_fwd_mfma_kernel<D, DROP, 2>, nrb, 256);
     }
-    const bool use_lw = (lw == 0 || lw == 1 || lw == 3) ? lw != 0 : D != 96;
-    // persistent form of the same kernel (each workgroup works through a list of row blocks and overlaps a block's start with
-    // the end of the one before): needs a grid of (row blocks at a time) x (heads) within the CU count; chosen when every
-    // workgroup then gets at least two row blocks (measured at s = 2048: 16 heads of 160 -5 % .. -2.5 %; 12 heads of 128, where
-    // 21 of the 32 blocks of a head start at once and only some workgroups get a second one, +1 %); forced by 3
-    const int cus = cu_count();
-    const bool pers = use_lw && N <= cus && (lw == 3 || (lw < 0 && nrb >= 2 * std::min(nrb, cus / N)));
-    if (pers) {
-      const int R = std::min(nrb, cus / N);
-      if (P.thresh != 0)
-        hipLaunchKernelGGL((attn_fwd_pers_kernel<D, true>), dim3((unsigned)(R * N)), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k,
-                           (const uint16_t*)v, (uint16_t*)o, lse);
-      else
-        hipLaunchKernelGGL((attn_fwd_pers_kernel<D, false>), dim3((unsigned)(R * N)), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k,
-                           (const uint16_t*)v, (uint16_t*)o, lse);
-      return hipGetLastError();
-    }
-    if (use_lw) {
-      if (P.thresh != 0)
-        hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, true, 2, true>), dim3((unsigned)(nrb * N)), dim3(512), 0, st, P, (const uint16_t*)q,
-                           (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
-      else
-        hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, false, 2, true>), dim3((unsigned)(nrb * N)), dim3(512), 0, st, P, (const uint16_t*)q,
-                           (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
-      return hipGetLastError();
-    }
-  }
-  if (P.thresh != 0)
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, true, 2>), dim3((unsigned)(nrb * N)), dim3(256), 0, st, P, (const uint16_t*)q, (const uint16_t*)k,
-                       (const uint16_t*)v, (uint16_t*)o, lse);
-  else  // every element is kept: the variant that draws no random numbers
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, false, 2>), dim3((unsigned)(nrb * N)), dim3(256), 0, st, P, (const uint16_t*)q, (const uint16_t*)k,
-                       (const uint16_t*)v, (uint16_t*)o, lse);
-  return hipGetLastError();
+  };
+  return P.thresh != 0 ? with(std::true_type()) : with(std::false_type());
 }
 
 hipError_t launch_attn_fwd_mfma(const AttnParams& P, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st) {
