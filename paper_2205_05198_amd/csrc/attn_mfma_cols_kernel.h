@@ -1,12 +1,7 @@
-// bf16 attention core, backward column pass (dK, dV) on gfx950 matrix cores: the kernel, included by the two translation
-// units that instantiate it.  See attn_mfma_rows.hip for the tile layouts shared by the three kernels.
-//   attn_mfma_cols.hip        d = 128, 160: compiled WITHOUT -amdgpu-mfma-vgpr-form.  One wave per SIMD; the two accumulator
-//                             sets (2 x d/32 x 16 registers) live in accumulation registers (AGPRs) so that the 256 vector
-//                             registers stay free for operands.                                   SAR_COLS_ACC = "a"
-//   attn_mfma_cols_small.hip  d = 64, 96: compiled WITH it.  Two workgroups per CU, i.e. 256 registers per wave; a kernel that
-//                             uses no AGPRs gets all of them as vector registers (otherwise the file is split 128 + 128) and
-//                             the matrix instructions write where the vector arithmetic reads (22B shard -4.5 %, d = 64
-//                             -16 %).                                                               SAR_COLS_ACC = "v"
+// bf16 attention core, backward column pass (dK, dV) on gfx950 matrix cores: the plain kernel, for head dimensions 64 and 96.  Two
+// workgroups per CU, i.e. 256 registers per wave; compiled with -amdgpu-mfma-vgpr-form: a kernel that uses no AGPRs gets all
+// of them as vector registers (otherwise the file is split 128 + 128) and the matrix instructions write where the vector
+// arithmetic reads (22B shard -4.5 %, d = 64 -16 %).  See attn_mfma_rows.hip for the tile layouts shared by the kernels.
 #pragma once
 #include "attn_mfma_common.h"
 
@@ -30,15 +25,11 @@ __device__ __forceinline__ void ds_store2(uint16_t* base, int lane, bf16x8_t a, 
 // DROP = false is the p = 0 variant: no random numbers are drawn at all.
 // Up to d = 96 two workgroups fit a CU (LDS), if the compiler keeps a wave within half the register file: second
 // argument = waves per SIMD.
-// EVEN: s is a multiple of 64, every query tile is full.  Then the loads of the next (Q, dO) block are dealt out one
-// per pair of score-tile matrix instructions instead of all at the top of the step: the L1 accepts one wave-wide
-// load per 16 cycles per CU, a pair of 32x32x16 instructions keeps a SIMD busy for 64, so four waves that each issue
-// one load per pair never queue behind each other (issued back to back, all four sit through all 44 loads).
 // WDS: the bf16 dS tiles are also written to ds_ws (layout: ds_tile_index / kDsTileElems of sar_internal.h; inside a tile
 // wave (kgp, is) owns two runs of 1 KB, one per 16-key group c, 16 bytes per lane), for the pass that forms dQ = alpha dS K
 // from them without recomputing anything.
-template <int D, bool DROP, bool EVEN, bool WDS = false>
-__global__ __launch_bounds__(256, D <= 96 ? 2 : 1) void attn_bwd_dkdv_mfma_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+template <int D, bool DROP, bool WDS>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_mfma_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                                 const uint16_t* __restrict__ v, const float* __restrict__ lse,
                                                                 const uint16_t* __restrict__ dO, const float* __restrict__ delta,
                                                                 uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, uint16_t* __restrict__ ds_ws) {
@@ -125,15 +116,8 @@ __global__ __launch_bounds__(256, D <= 96 ? 2 : 1) void attn_bwd_dkdv_mfma_kerne
     if constexpr (WDS) dma_wait_keep<2>();
     else dma_wait();
     __syncthreads();  // ... and everybody's; nobody reads the other stage any more
-    // EVEN: the first round of the next block's loads; the last step fetches its own block again (into the stage
-    // that nobody reads any more) so that the step has one path
-    const int inx = min(it + 1, nit - 1) * BI;
     uint16_t* nxt = stages + ((it + 1) & 1) * 2 * TILE;
-    if constexpr (EVEN) {
-      dma_one<D>(map, qg + (int64_t)inx * gstride, nxt, wave, 0);
-      dma_one<D>(map, dog + (int64_t)inx * gstride, nxt + TILE, wave, 0);
-      if (wave == 0) load_stats(inx, (it + 1) & 1);
-    } else if (it + 1 < nit) {  // next tile's loads fly while this one is computed
+    if (it + 1 < nit) {  // next tile's loads fly while this one is computed
       const int left = P.s - (i0 + BI);
       if (left >= BI) {
         dma_tile<D>(map, qg + (int64_t)(i0 + BI) * gstride, nxt, wave);
@@ -149,22 +133,13 @@ __global__ __launch_bounds__(256, D <= 96 ? 2 : 1) void attn_bwd_dkdv_mfma_kerne
     const float* lse_c = lse_s[it & 1];
     const float* delta_c = delta_s[it & 1];
     const int i0w = i0 + 32 * is;  // this wave's 32 rows
-    // i0w + 31 < jw0 (the upper right quarter of the diagonal tile): every row precedes this wave's keys.  EVEN: the
-    // wave runs the tile fully masked rather than skipping it (its share of the loads sits inside)
-    if (EVEN || !P.causal || i0w + 31 >= jw0) {
+    // i0w + 31 < jw0 (the upper right quarter of the diagonal tile): every row precedes this wave's keys.
+    if (!P.causal || i0w + 31 >= jw0) {
       const bool diag = P.causal && (i0w < jw0 + 31);
       float16_t st, dd;
 #pragma unroll
       for (int e = 0; e < 16; ++e) { st[e] = 0.f; dd[e] = 0.f; }
-      if constexpr (EVEN) {  // loads between the matrix instructions: keep the accumulators where they are around them
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          asm volatile("" : "+" SAR_COLS_ACC(dkacc[dt]));
-          asm volatile("" : "+" SAR_COLS_ACC(dvacc[dt]));
-        }
-      }
-      // The operand reads run kAhead pairs of matrix instructions ahead, written out: the loads below are opaque
-      // memory operations to the compiler, which therefore never moves an LDS read up across one of them, and a
+      // The operand reads run kAhead pairs of matrix instructions ahead, written out: a
       // read issued right before its matrix instruction leaves the whole LDS latency exposed, KC times.
       constexpr int kAhead = 2;
       bf16x8_t ka[kAhead], qa[kAhead], va[kAhead], da[kAhead];
@@ -185,19 +160,6 @@ __global__ __launch_bounds__(256, D <= 96 ? 2 : 1) void attn_bwd_dkdv_mfma_kerne
           va[kc % kAhead] = ld_frag(vw + 16 * (kc + kAhead)), da[kc % kAhead] = ld_frag(drow + 16 * (kc + kAhead));
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (EVEN) {  // rounds 1 .. PER-1 of the Q tile, then of the dO tile
-          constexpr int PER = DmaMap<D>::PER;
-          static_assert(2 * (PER - 1) <= KC, "more load rounds than pairs of matrix instructions");
-          if (1 + kc < PER) dma_one<D>(map, qg + (int64_t)inx * gstride, nxt, wave, 1 + kc);
-          else if (2 + kc - PER < PER) dma_one<D>(map, dog + (int64_t)inx * gstride, nxt + TILE, wave, 2 + kc - PER);
-        }
-      }
-      if constexpr (EVEN) {
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          asm volatile("" : "+" SAR_COLS_ACC(dkacc[dt]));
-          asm volatile("" : "+" SAR_COLS_ACC(dvacc[dt]));
-        }
       }
       const int i = i0w + li;
       const float lse2 = lse_c[32 * is + li] * kLog2e, dl = delta_c[32 * is + li];
@@ -259,16 +221,15 @@ __global__ __launch_bounds__(256, D <= 96 ? 2 : 1) void attn_bwd_dkdv_mfma_kerne
       ds_tile += ds_step;
       if (P.causal) ds_step += kDsTileElems;
     }
-    // Keep the loop-carried accumulators in the accumulation registers (AGPRs) across the back-edge; without
-    // this the compiler copies all of them to VGPRs and back on every trip.
+    // Keep the loop-carried accumulators in vector registers across the back-edge.
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
-      asm volatile("" : "+" SAR_COLS_ACC(dkacc[dt]));
-      asm volatile("" : "+" SAR_COLS_ACC(dvacc[dt]));
+      asm volatile("" : "+v"(dkacc[dt]));
+      asm volatile("" : "+v"(dvacc[dt]));
     }
   }
   // ---- sum the two row halves, scale, store ----
-  dma_wait();  // EVEN: the last step's loads still target the stages that the exchange buffers overlap
+  dma_wait();
   __syncthreads();
   // each wave of a pair gives one accumulator set away and finishes the other: the upper half completes dV, the lower dK
   float* mg = reinterpret_cast<float*>(smem) + kgp * (64 * 32 * DT);
@@ -295,23 +256,11 @@ static hipError_t bwd_dkdv_d(const AttnParams& P, const void* q, const void* k, 
     hipLaunchKernelGGL(kern, dim3((unsigned)(nb * N)), dim3(256), 0, st, P, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, lse,
                        (const uint16_t*)dO, delta, (uint16_t*)dk, (uint16_t*)dv, ds_ws);
   };
-  // interleaved loads pay at d = 160 only (530B shard -3 %, 1T -6 %, s = 4096 -3 %; d = 128 unchanged; d = 96, where two
-  // workgroups share a CU and fill each other's stalls anyway, +2 %)
-  constexpr bool kInterleave = D >= 160;
-  const bool even = kInterleave && P.s % 64 == 0;
   if (ds_ws) {
-    if (P.thresh != 0) {
-      if (even) go(attn_bwd_dkdv_mfma_kernel<D, true, kInterleave, true>);
-      else go(attn_bwd_dkdv_mfma_kernel<D, true, false, true>);
-    } else {
-      if (even) go(attn_bwd_dkdv_mfma_kernel<D, false, kInterleave, true>);
-      else go(attn_bwd_dkdv_mfma_kernel<D, false, false, true>);
-    }
-  } else if (P.thresh != 0) {
-    if (even) go(attn_bwd_dkdv_mfma_kernel<D, true, kInterleave>);
-    else go(attn_bwd_dkdv_mfma_kernel<D, true, false>);
+    if (P.thresh != 0) go(attn_bwd_dkdv_mfma_kernel<D, true, true>);
+    else go(attn_bwd_dkdv_mfma_kernel<D, false, true>);
   } else {
-    if (even) go(attn_bwd_dkdv_mfma_kernel<D, false, kInterleave>);
+    if (P.thresh != 0) go(attn_bwd_dkdv_mfma_kernel<D, true, false>);
     else go(attn_bwd_dkdv_mfma_kernel<D, false, false>);
   }
   return hipGetLastError();

@@ -1,6 +1,5 @@
 // bf16 attention core, backward column pass (dK, dV): head dimensions 64 and 96 (two workgroups per CU, everything in
 // vector registers; compiled WITH -amdgpu-mfma-vgpr-form).
-#define SAR_COLS_ACC "v"
 #include "attn_mfma_cols_kernel.h"
 
 namespace sar {

@@ -1,6 +1,5 @@
 // bf16 attention core, backward column pass (dK, dV) in its producer / consumer form (two waves per SIMD, each within
 // 256 vector registers; compiled WITH -amdgpu-mfma-vgpr-form): every head dimension of the matrix-core path.
-#define SAR_COLS_ACC "v"
 #include "attn_mfma_cols_split.h"
 
 #include <algorithm>

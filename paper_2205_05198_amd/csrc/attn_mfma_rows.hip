@@ -25,7 +25,6 @@
 #include "attn_mfma_common.h"
 #include <atomic>
 #include <type_traits>
-#include "attn_mfma_fwd_split.h"
 #include "attn_mfma_fwd_pers.h"
 
 namespace sar {
@@ -572,7 +571,7 @@ static int cu_count() { return attn_mfma_cu_count(); }
 //     Causal, d = 160: more of them than CUs, so that the heaviest does not set the pace (-19 % at s = 4096, -20 % at s = 8192;
 //     +14 % with 256 workgroups).
 //     d = 64 without mask and dropout, 1024 workgroups of 64 rows or more: 2048 x 64 heads 107 -> 89 (loader waves 95).
-//   loader waves: d = 64: 1736 x 24 heads, causal 20.0 / 26.3 (producer / consumer pairs) -> 18.3 / 24.4, 2048 x 64 57.6 /
+//   loader waves: d = 64: against the producer / consumer pairs that ran there before, 1736 x 24 heads, causal 20.0 / 26.3 -> 18.3 / 24.4, 2048 x 64 57.6 /
 //     74.1 -> 52.4 / 69.4, without the mask 107.6 / 138.8 -> 95.3 / 128.7, 512 x 128 18.5 / 22.5 -> 17.3 / 20.7.  d = 96, where three
 //     workgroups without them share a CU: only while a CU gets one (1024 x 8, causal 12.8 / 16.1 -> 10.6 / 13.9), or under the
 //     mask two (2048 x 12 23.9 / 29.7 -> 21.5 / 24.1; without the mask 32.5 / 44.5 -> 44.4 / 46.6).  d = 128, causal: not once
@@ -581,7 +580,7 @@ static int cu_count() { return attn_mfma_cu_count(); }
 //   persistent workgroups: every one gets two row blocks or more, d >= 128; below that under the mask and with exactly as many
 //     blocks as two a CU (4096 x 8: d = 64 29.8 / 44.9 -> 29.1 / 41.3, d = 96 41.0 / 49.3 -> 39.5 / 47.2; with more blocks than
 //     that 1736 x 24 18.3 / 24.4 -> 22.2 / 31.5).
-enum class FwdForm { Plain, Loaders, Split, Persistent, Rows128 };
+enum class FwdForm { Plain, Loaders, Persistent, Rows128 };
 template <int D>
 static FwdForm fwd_form(const AttnParams& P) {
   const int cus = cu_count(), N = P.b * P.A, nrb = (P.s + 63) / 64;
@@ -603,7 +602,6 @@ static FwdForm fwd_form(const AttnParams& P) {
     else lw = !(D == 128 && P.causal && w64 > 2 * (int64_t)cus);
   }
   if (lw == 0) return FwdForm::Plain;
-  if (lw == 2) return FwdForm::Split;
   // a grid of (row blocks at a time) x (heads) within the CU count
   const bool two = N <= cus && nrb >= 2 * std::min(nrb, cus / N);
   if (forced ? lw == 3 && N <= cus : two && (D >= 128 || (P.causal && w64 <= 2 * (int64_t)cus))) return FwdForm::Persistent;
@@ -622,7 +620,6 @@ static hipError_t fwd_d(const AttnParams& P, const void* q, const void* k, const
     constexpr bool DROP = decltype(drop)::value;
     switch (fwd_form<D>(P)) {
       case FwdForm::Rows128: return go(attn_fwd_mfma_kernel<D, DROP, 4>, (P.s + 127) / 128, 512);
-      case FwdForm::Split: return go(attn_fwd_split_kernel<D, DROP>, nrb, 512);
       case FwdForm::Persistent: return go(attn_fwd_pers_kernel<D, DROP>, std::min(nrb, cu_count() / N), 512);
       case FwdForm::Loaders: return go(attn_fwd_mfma_kernel<D, DROP, 2, true>, nrb, 512);
       default: return go(attn_fwd_mfma_kernel<D, DROP, 2>, nrb, 256);
