@@ -579,7 +579,10 @@ static int cu_count() { return attn_mfma_cu_count(); }
 //     no dropout: not from four workgroups a CU on (2048 x 64 49.6 against 52.4).
 //   persistent workgroups: every one gets two row blocks or more, d >= 128; below that under the mask and with exactly as many
 //     blocks as two a CU (4096 x 8: d = 64 29.8 / 44.9 -> 29.1 / 41.3, d = 96 41.0 / 49.3 -> 39.5 / 47.2; with more blocks than
-//     that 1736 x 24 18.3 / 24.4 -> 22.2 / 31.5).
+//     that 1736 x 24 18.3 / 24.4 -> 22.2 / 31.5).  d >= 128, causal, also from one and a half blocks a workgroup on while a head
+//     has 16 blocks at most, where a workgroup's start is a large part of its time (1000 x 24: d = 128 14.9 / 16.9 -> 14.0 /
+//     16.6, d = 160 18.3 / 19.9 -> 17.3 / 18.4; 512 x 48 11.5 / 12.9 -> 10.8 / 12.0; but 1000 x 20 13.1 / 15.3 -> 13.4 / 15.6 and 2048 x 12
+//     23.8 / 27.1 -> 24.1 / 27.4).
 enum class FwdForm { Plain, Loaders, Persistent, Rows128 };
 template <int D>
 static FwdForm fwd_form(const AttnParams& P) {
@@ -604,7 +607,8 @@ static FwdForm fwd_form(const AttnParams& P) {
   if (lw == 0) return FwdForm::Plain;
   // a grid of (row blocks at a time) x (heads) within the CU count
   const bool two = N <= cus && nrb >= 2 * std::min(nrb, cus / N);
-  if (forced ? lw == 3 && N <= cus : two && (D >= 128 || (P.causal && w64 <= 2 * (int64_t)cus))) return FwdForm::Persistent;
+  const bool small = D >= 128 && P.causal && N <= cus && nrb <= 16 && 2 * w64 >= 3 * (int64_t)cus;
+  if (forced ? lw == 3 && N <= cus : small || (two && (D >= 128 || (P.causal && w64 <= 2 * (int64_t)cus)))) return FwdForm::Persistent;
   return FwdForm::Loaders;
 }
 

@@ -217,11 +217,13 @@ def test_forward_persistent_workgroups(d, s, b, A, causal, p):
 
 
 @pytest.mark.parametrize("d,s,b,A,p,causal", [(64, 136, 4, 86, 0.0, 1), (64, 264, 2, 103, 0.0, 0), (96, 72, 2, 64, 0.1, 1), (96, 328, 1, 85, 0.1, 1), (128, 136, 4, 43, 0.1, 1),
-                                              (128, 200, 1, 100, 0.0, 0), (160, 200, 1, 100, 0.1, 0), (160, 264, 2, 66, 0.1, 0)])
+                                              (128, 200, 1, 100, 0.0, 0), (160, 200, 1, 100, 0.1, 0), (160, 264, 2, 66, 0.1, 0),
+                                              (128, 328, 1, 65, 0.1, 1), (160, 456, 2, 25, 0.0, 1)])
 def test_forward_form_by_shape(d, s, b, A, p, causal):
     """The forward as the library chooses it, on both sides of the lines between its forms on 256 compute units: without loader
     waves (64: more than four workgroups a CU without dropout; 128: more than two under the mask), 128-row workgroups (64 bare;
-    128, 160 where they save a round), loader waves, persistent workgroups at d = 96; every sequence ends inside a tile."""
+    128, 160 where they save a round), loader waves, persistent workgroups (96; 128, 160 with some
+    workgroups at two row blocks and the rest at one); every sequence ends inside a tile."""
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=s, b=b, a=A, h=A * d, p=p, seed=80, offset=(1 << 32) - 999, causal=causal)
     q, k, v, do = attn_inputs(s, b, A, d, "bf16", seed=43)
