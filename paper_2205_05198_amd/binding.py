@@ -14,7 +14,7 @@ _CSRC = os.path.join(_HERE, "csrc")
 _LIB_PATH = os.path.join(_HERE, "libsar.so")
 # source file -> extra hipcc flags.  -amdgpu-mfma-vgpr-form keeps matrix-core accumulators in the VGPR file: with the
 # default heuristics the compiler parks them in AGPRs and copies all of them through VGPRs on every trip of the tile
-# loops.  The dK/dV pass needs both register files (2 accumulator sets) and pins its accumulators to AGPRs itself.
+# loops.
 # The iterative-ilp scheduling strategy interleaves the Philox integer work with the matrix-core chains of the
 # row-block kernels a little better than the default (about 5 % on the dQ pass, measured).
 _SOURCES = {

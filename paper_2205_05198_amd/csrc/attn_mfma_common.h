@@ -1,4 +1,4 @@
-// Shared pieces of the bf16 matrix-core attention kernels (attn_mfma_rows.hip, attn_mfma_cols.hip, attn_mfma_stored.hip): MFMA wrapper,
+// Shared pieces of the bf16 matrix-core attention kernels (attn_mfma_rows.hip, attn_mfma_cols_*.h, attn_mfma_dsgemm.hip, attn_mfma_stored.hip): MFMA wrapper,
 // LDS operand loads, direct global -> LDS tile loads, output staging.
 #pragma once
 #include "sar_device.h"
