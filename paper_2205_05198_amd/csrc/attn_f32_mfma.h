@@ -58,6 +58,8 @@ __device__ __forceinline__ float4_t load4(const uint16_t* p) {
   return f;
 }
 
+__device__ __forceinline__ bool finite(float f) { return (__float_as_uint(f) & 0x7f800000u) != 0x7f800000u; }
+
 // over the lanes that hold one column
 template <int M>
 __device__ __forceinline__ float column_max(float v) {
@@ -152,12 +154,14 @@ __device__ __forceinline__ typename Geo<M>::acc_t dot_tile(float4_t (&ring)[kRin
 
 // sum over the four waves of acc (one row of the output per lane li), times mul, to rows 0 .. rows_valid - 1 of out.
 // buf: NWF * M * (8 CT + 4) floats at M = 32 (eight columns m at a time), NWF * M * (16 CT + 4) at M = 16; the waves' order is fixed.
+// A wave stores M / NWF consecutive rows, whole, from merge_row_of_wave on.  Returns whether this thread stored a value that is not finite.
 template <int M, int CT>
 constexpr int merge_pitch() { return (M == 32 ? 8 : 16) * CT + 4; }
 template <int M, int CT, typename T>
-__device__ __forceinline__ void merge_store(const typename Geo<M>::acc_t (&acc)[CT], float* buf, int wave, int li, int hh, float mul, T* out, int64_t gstride,
+__device__ __forceinline__ bool merge_store(const typename Geo<M>::acc_t (&acc)[CT], float* buf, int wave, int li, int hh, float mul, T* out, int64_t gstride,
                                             int rows_valid, int d) {
   constexpr int PITCH = merge_pitch<M, CT>(), NG = M == 32 ? 4 : 1, MM = M / NG;  // MM: columns m of a round
+  bool odd = false;
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     __syncthreads();
@@ -177,9 +181,65 @@ __device__ __forceinline__ void merge_store(const typename Geo<M>::acc_t (&acc)[
     if (row < rows_valid) {
       T* o = out + (int64_t)row * gstride + col_start<CT>(MM * g + m, d);
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) Elem<T>::store(o + ct, s[ct] * mul);
+      for (int ct = 0; ct < CT; ++ct) {
+        const float y = s[ct] * mul;
+        odd |= !finite(y);
+        Elem<T>::store(o + ct, y);
+      }
     }
   }
+  return odd;
+}
+
+// Pairs (i, j) that the mask excludes, and rows past the end, have probability 0 and take part in the matrix products of a tile all the
+// same: 0 x infinity and 0 x NaN would reach outputs that the definition keeps them from.  A wave that has stored a value which is not
+// finite therefore looks at the operands of its tiles with excluded pairs, and where one of those is not finite either, it computes
+// the rows it stored again from the definition, over the allowed pairs only.  Finite results cost one compare each.
+__device__ __forceinline__ bool wave_any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
+template <int M>
+__device__ __forceinline__ int merge_row_of_wave(int wave) { return wave * (M / NWF); }  // the first; they are consecutive
+template <typename T>
+__device__ __forceinline__ bool any_odd(const T* g, int64_t gstride, int r0, int r1, int d) {  // this lane's share of rows r0 .. r1 - 1
+  bool odd = false;
+  for (int c = threadIdx.x & 63; c < (r1 - r0) * (d / 4); c += 64) {
+    const float4_t f = load4(g + (int64_t)(r0 + c / (d / 4)) * gstride + 4 * (c % (d / 4)));
+    odd |= !(finite(f[0]) && finite(f[1]) && finite(f[2]) && finite(f[3]));
+  }
+  return odd;
+}
+template <typename T>
+__device__ __forceinline__ float dot_rows(const T* a, const T* b, int d) {
+  float acc = 0.f;
+  for (int x = 0; x < d; x += 4) {
+    const float4_t fa = load4(a + x), fb = load4(b + x);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc = fmaf(fa[u], fb[u], acc);
+  }
+  return acc;
+}
+// out = mul sum_{j = lo}^{hi - 1} weight(j) src_j; a lane draws the weight of every 64th j
+template <typename T, typename W>
+__device__ __forceinline__ void plain_row(W&& weight, int lo, int hi, const T* src, int64_t gstride, int d, float mul, T* out) {
+  const int lane = threadIdx.x & 63;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int c0 = lo; c0 < hi; c0 += 64) {
+    const float mine = c0 + lane < hi ? weight(c0 + lane) : 0.f;
+    for (int y = 0; y < min(64, hi - c0); ++y) {
+      const float w = __shfl(mine, y, 64);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (lane + 64 * c < d) acc[c] = fmaf(w, Elem<T>::load(src + (int64_t)(c0 + y) * gstride + lane + 64 * c), acc[c]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (lane + 64 * c < d) Elem<T>::store(out + lane + 64 * c, acc[c] * mul);
+}
+// dropout decision of a single pair
+template <bool DROP>
+__device__ __forceinline__ bool kept_pair(const AttnParams& P, int beta, int n, int i, int j) {
+  return !DROP || keep_bit1((((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s + (uint64_t)i) * (uint64_t)P.s + (uint64_t)j, P.offset,
+                            0u, P.key0, P.key1, P.thresh);
 }
 
 // Work of workgroup blockIdx: heaviest first, every other round of 256 (one workgroup a CU) the other way round, so that a CU that
@@ -294,8 +354,20 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] *= wgt;
-  if (wave == 0 && hh == 0 && i < P.s) lse[(size_t)bn * P.s + i] = (m + __builtin_amdgcn_logf(l)) * kLn2F;
-  merge_store<M, CT>(oacc, buf, wave, li, hh, 1.f, o + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  const float lse_i = (m + __builtin_amdgcn_logf(l)) * kLn2F;
+  if (wave == 0 && hh == 0 && i < P.s) lse[(size_t)bn * P.s + i] = lse_i;
+  const bool odd = merge_store<M, CT>(oacc, buf, wave, li, hh, 1.f, o + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  if ((P.causal || P.s % kTileF) && wave_any(odd)) {
+    const int j0 = kTileF * (ntile - 1), r0 = i0 + merge_row_of_wave<M>(wave);
+    if (wave_any(any_odd(v + base, P.stride_s, j0, min(j0 + kTileF, P.s), P.d)))
+      for (int r = r0; r < min(r0 + M / NWF, P.s); ++r) {
+        const float lse_r = __shfl(lse_i, r - i0, 64);
+        plain_row([&](int j) __attribute__((always_inline)) {
+          const float pe = __builtin_amdgcn_exp2f((dot_rows(q + base + (int64_t)r * P.stride_s, k + base + (int64_t)j * P.stride_s, P.d) * P.scale - lse_r) * kLog2eF);
+          return kept_pair<DROP>(P, beta, n, r, j) ? pe * P.keep_scale : 0.f;
+        }, 0, P.causal ? r + 1 : P.s, v + base, P.stride_s, P.d, 1.f, o + base + (int64_t)r * P.stride_s);
+      }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -400,7 +472,19 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
       }
     }
   }
-  merge_store<M, CT>(acc, buf, wave, li, hh, P.scale, dq + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  const bool odd = merge_store<M, CT>(acc, buf, wave, li, hh, P.scale, dq + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
+  if ((P.causal || P.s % kTileF) && wave_any(odd)) {
+    const int j0 = kTileF * (ntile - 1), j1 = min(j0 + kTileF, P.s), r0 = i0 + merge_row_of_wave<M>(wave);
+    if (wave_any(any_odd(kg, P.stride_s, j0, j1, P.d) || any_odd(vg, P.stride_s, j0, j1, P.d)))
+      for (int r = r0; r < min(r0 + M / NWF, P.s); ++r) {
+        const float dl_r = __shfl(dl, r - i0, 64), lse_r = lse[(size_t)bn * P.s + r];
+        plain_row([&](int j) __attribute__((always_inline)) {
+          const float pe = __builtin_amdgcn_exp2f((dot_rows(q + base + (int64_t)r * P.stride_s, kg + (int64_t)j * P.stride_s, P.d) * P.scale - lse_r) * kLog2eF);
+          const float dp = dot_rows(dO + base + (int64_t)r * P.stride_s, vg + (int64_t)j * P.stride_s, P.d) * P.keep_scale;
+          return pe * ((kept_pair<DROP>(P, beta, n, r, j) ? dp : 0.f) - dl_r);
+        }, 0, P.causal ? r + 1 : P.s, kg, P.stride_s, P.d, P.scale, dq + base + (int64_t)r * P.stride_s);
+      }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -523,8 +607,26 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
     SAR_ROW(8) SAR_ROW(9) SAR_ROW(10) SAR_ROW(11) SAR_ROW(12) SAR_ROW(13) SAR_ROW(14) SAR_ROW(15)
 #undef SAR_ROW
   }
-  merge_store<M, CT>(va, buf, wave, li, hh, 1.f, dv + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
-  merge_store<M, CT>(ka, buf, wave, li, hh, P.scale, dk + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+  bool odd = merge_store<M, CT>(va, buf, wave, li, hh, 1.f, dv + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+  odd |= merge_store<M, CT>(ka, buf, wave, li, hh, P.scale, dk + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
+  if ((P.causal || P.s % kTileF) && wave_any(odd)) {
+    auto odd_rows = [&](int it) {  // of a tile with excluded pairs
+      const int r0 = kTileF * it, r1 = min(r0 + kTileF, P.s), r = r0 + lane;
+      return any_odd(qg, P.stride_s, r0, r1, P.d) || any_odd(gg, P.stride_s, r0, r1, P.d) || (r < r1 && !(finite(lse_h[r]) && finite(delta_h[r])));
+    };
+    const int c0 = j0 + merge_row_of_wave<M>(wave);
+    if (wave_any((P.causal && odd_rows(it0)) || (P.s % kTileF && odd_rows(nt - 1))))
+      for (int c = c0; c < min(c0 + M / NWF, P.s); ++c) {
+        const T *kc = k + base + (int64_t)c * P.stride_s, *vc = v + base + (int64_t)c * P.stride_s;
+        auto prob = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f((dot_rows(qg + (int64_t)i * P.stride_s, kc, P.d) * P.scale - lse_h[i]) * kLog2eF); };
+        plain_row([&](int i) __attribute__((always_inline)) { return kept_pair<DROP>(P, beta, n, i, c) ? prob(i) * P.keep_scale : 0.f; }, P.causal ? c : 0, P.s, gg, P.stride_s,
+                  P.d, 1.f, dv + base + (int64_t)c * P.stride_s);
+        plain_row([&](int i) __attribute__((always_inline)) {
+          const float dp = dot_rows(gg + (int64_t)i * P.stride_s, vc, P.d) * P.keep_scale;
+          return prob(i) * ((kept_pair<DROP>(P, beta, n, i, c) ? dp : 0.f) - delta_h[i]);
+        }, P.causal ? c : 0, P.s, qg, P.stride_s, P.d, P.scale, dk + base + (int64_t)c * P.stride_s);
+      }
+  }
 }
 
 // M = 16 where M = 32 leaves less than two workgroups a CU: twice the workgroups with half the work each start sooner and spread a
