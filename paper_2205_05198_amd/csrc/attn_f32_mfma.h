@@ -24,7 +24,9 @@ namespace sar {
 namespace {
 
 constexpr float kLog2eF = 1.4426950408889634f, kLn2F = 0.6931471805599453f;
-constexpr float kLazyF = 60.0f;  // the running reference exponent moves only when a row maximum grew by > 2^60
+// The running reference of a row's exponentials moves only when its maximum grew by more than this (2^8): terms and their sums stay far
+// from the end of the range.  It starts at the type's lowest value, which is below or equal to every score.
+constexpr float kLazyF = 5.5f, kLowestF = -3.40282347e38f;
 constexpr int NWF = 4;           // waves of a workgroup
 constexpr int kTileF = 32;       // width of a step along the other dimension
 
@@ -59,6 +61,14 @@ __device__ __forceinline__ float4_t load4(const uint16_t* p) {
 }
 
 __device__ __forceinline__ bool finite(float f) { return (__float_as_uint(f) & 0x7f800000u) != 0x7f800000u; }
+
+// Scores stay in natural units until a difference of two is taken: score() rounds to the same value in the forward and in both
+// backward passes, so that a score's distance from its row's log-sum-exp keeps the row's precision at any size of the scores.
+__device__ __forceinline__ float score(float dot, float scale) {
+#pragma clang fp contract(off)
+  return dot * scale;
+}
+__device__ __forceinline__ float exp_diff(float a, float b) { return __builtin_amdgcn_exp2f((a - b) * kLog2eF); }
 
 // over the lanes that hold one column
 template <int M>
@@ -275,7 +285,6 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
   const int ntile = (P.causal ? min(i0 + M, P.s) : P.s) / kTileF + ((P.causal ? min(i0 + M, P.s) : P.s) % kTileF != 0);
   rows_to_lds<M, DT>(Qs, q + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
   const uint64_t rowG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s + (uint64_t)i_ld) * (uint64_t)(P.s >> 3);
-  const float sc2 = P.scale * kLog2eF;
   const T* kg = k + base;
   const T* vg = v + base + col_start<CT>(li, P.d);
   auto krow = [&](int jt, int t) __attribute__((always_inline)) { return kg + (int64_t)min(kTileF * jt + G::key_of_row(t, li), P.s - 1) * P.stride_s; };
@@ -284,7 +293,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] = 0.f;
-  float m_ref = -1.0e30f, l_run = 0.f;
+  float m_ref = kLowestF, l_run = 0.f;
   float4_t ring[kRingF];
   ring_start<M, DT>(ring, krow(wave, 0), krow(wave, G::SUB - 1), hh, P.d);
   __syncthreads();
@@ -300,14 +309,14 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
     if constexpr (M == 32) {
       const float16_t s0 = dot_tile<M, DT, 0>(ring, krow(jt, 0), krow(jt + NWF, 0), krow(jt + NWF, 0), qrow, hh, P.d);
 #pragma unroll
-      for (int e = 0; e < NV; ++e) st[e] = s0[e] * sc2;
+      for (int e = 0; e < NV; ++e) st[e] = score(s0[e], P.scale);
     } else {
       const float4_t s0 = dot_tile<M, DT, 0>(ring, krow(jt, 0), krow(jt, 1), krow(jt + NWF, 0), qrow, hh, P.d);
       const float4_t s1 = dot_tile<M, DT, (2 * DT) % kRingF>(ring, krow(jt, 1), krow(jt + NWF, 0), krow(jt + NWF, 1), qrow, hh, P.d);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { st[e] = s0[e] * sc2; st[4 + e] = s1[e] * sc2; }
+      for (int e = 0; e < 4; ++e) { st[e] = score(s0[e], P.scale); st[4 + e] = score(s1[e], P.scale); }
     }
-    float mt = -1.0e30f;
+    float mt = kLowestF;
     if (jt == ntile - 1) {  // keys beyond jlim (above the diagonal, or past the end) are masked
 #pragma unroll
       for (int e = 0; e < NV; ++e)
@@ -317,7 +326,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
     for (int e = 0; e < NV; ++e) mt = fmaxf(mt, st[e]);
     mt = column_max<M>(mt);
     if (__builtin_amdgcn_ballot_w64(mt > m_ref + kLazyF) != 0) {
-      const float m_new = fmaxf(m_ref, mt), corr = __builtin_amdgcn_exp2f(m_ref - m_new);
+      const float m_new = fmaxf(m_ref, mt), corr = exp_diff(m_ref, m_new);
       m_ref = m_new;
       l_run *= corr;
 #pragma unroll
@@ -332,7 +341,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
 #pragma unroll
       for (int x = 0; x < 8; ++x) {
         const int e = 8 * c + x;
-        const float pe = __builtin_amdgcn_exp2f(st[e] - m_ref);
+        const float pe = exp_diff(st[e], m_ref);
         l_run += pe;
         const float pd = !DROP || ((keep >> x) & 1u) ? pe : 0.f;
 #pragma unroll
@@ -348,13 +357,13 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
   __syncthreads();
   float m = ml[0][0][li], l = 0.f;
   for (int w = 1; w < NWF; ++w) m = fmaxf(m, ml[0][w][li]);
-  for (int w = 0; w < NWF; ++w) l = fmaf(ml[1][w][li], __builtin_amdgcn_exp2f(ml[0][w][li] - m), l);
-  const float wgt = __builtin_amdgcn_exp2f(m_ref - m) * P.keep_scale / l;
+  for (int w = 0; w < NWF; ++w) l = fmaf(ml[1][w][li], exp_diff(ml[0][w][li], m), l);
+  const float wgt = exp_diff(m_ref, m) * P.keep_scale / l;
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] *= wgt;
-  const float lse_i = (m + __builtin_amdgcn_logf(l)) * kLn2F;
+  const float lse_i = m + __builtin_amdgcn_logf(l) * kLn2F;
   if (wave == 0 && hh == 0 && i < P.s) lse[(size_t)bn * P.s + i] = lse_i;
   const bool odd = merge_store<M, CT>(oacc, buf, wave, li, hh, 1.f, o + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
   if ((P.causal || P.s % kTileF) && wave_any(odd)) {
@@ -363,7 +372,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
       for (int r = r0; r < min(r0 + M / NWF, P.s); ++r) {
         const float lse_r = __shfl(lse_i, r - i0, 64);
         plain_row([&](int j) __attribute__((always_inline)) {
-          const float pe = __builtin_amdgcn_exp2f((dot_rows(q + base + (int64_t)r * P.stride_s, k + base + (int64_t)j * P.stride_s, P.d) * P.scale - lse_r) * kLog2eF);
+          const float pe = exp_diff(score(dot_rows(q + base + (int64_t)r * P.stride_s, k + base + (int64_t)j * P.stride_s, P.d), P.scale), lse_r);
           return kept_pair<DROP>(P, beta, n, r, j) ? pe * P.keep_scale : 0.f;
         }, 0, P.causal ? r + 1 : P.s, v + base, P.stride_s, P.d, 1.f, o + base + (int64_t)r * P.stride_s);
       }
@@ -416,9 +425,8 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
 #pragma unroll
   for (int tr = 0; tr < TPR; ++tr) dl += part[li][tr];
   if (wave == 0 && hh == 0 && i < P.s) delta[(size_t)bn * P.s + i] = dl;
-  const float lse2 = lse[(size_t)bn * P.s + i_ld] * kLog2eF;
+  const float lse_i = lse[(size_t)bn * P.s + i_ld];
   const uint64_t rowG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s + (uint64_t)i_ld) * (uint64_t)(P.s >> 3);
-  const float sc2 = P.scale * kLog2eF;
   typename G::acc_t acc[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
@@ -448,7 +456,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
       for (int e = 0; e < 4; ++e) { st[e] = s0[e]; st[4 + e] = s1[e]; dd[e] = d0[e]; dd[4 + e] = d1[e]; }
     }
 #pragma unroll
-    for (int e = 0; e < NV; ++e) st[e] = fmaf(st[e], sc2, -lse2);
+    for (int e = 0; e < NV; ++e) st[e] = score(st[e], P.scale);
     if (jt == ntile - 1) {
 #pragma unroll
       for (int e = 0; e < NV; ++e)
@@ -461,7 +469,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
 #pragma unroll
       for (int x = 0; x < 8; ++x) {
         const int e = 8 * c + x;
-        const float pe = __builtin_amdgcn_exp2f(st[e]);
+        const float pe = exp_diff(st[e], lse_i);
         const float dp = !DROP || ((keep >> x) & 1u) ? dd[e] * P.keep_scale : 0.f;
         const float ds = pe * (dp - dl);
 #pragma unroll
@@ -477,9 +485,9 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
     const int j0 = kTileF * (ntile - 1), j1 = min(j0 + kTileF, P.s), r0 = i0 + merge_row_of_wave<M>(wave);
     if (wave_any(any_odd(kg, P.stride_s, j0, j1, P.d) || any_odd(vg, P.stride_s, j0, j1, P.d)))
       for (int r = r0; r < min(r0 + M / NWF, P.s); ++r) {
-        const float dl_r = __shfl(dl, r - i0, 64), lse_r = lse[(size_t)bn * P.s + r];
+        const float dl_r = __shfl(dl, r - i0, 64), lse_r = __shfl(lse_i, r - i0, 64);
         plain_row([&](int j) __attribute__((always_inline)) {
-          const float pe = __builtin_amdgcn_exp2f((dot_rows(q + base + (int64_t)r * P.stride_s, kg + (int64_t)j * P.stride_s, P.d) * P.scale - lse_r) * kLog2eF);
+          const float pe = exp_diff(score(dot_rows(q + base + (int64_t)r * P.stride_s, kg + (int64_t)j * P.stride_s, P.d), P.scale), lse_r);
           const float dp = dot_rows(dO + base + (int64_t)r * P.stride_s, vg + (int64_t)j * P.stride_s, P.d) * P.keep_scale;
           return pe * ((kept_pair<DROP>(P, beta, n, r, j) ? dp : 0.f) - dl_r);
         }, 0, P.causal ? r + 1 : P.s, kg, P.stride_s, P.d, P.scale, dq + base + (int64_t)r * P.stride_s);
@@ -523,7 +531,6 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
   const float* delta_h = delta + (size_t)bn * P.s;
   const uint64_t headG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s) * (uint64_t)(P.s >> 3) +
                          (uint64_t)((j0 + (li & ~7)) >> 3);
-  const float sc2 = P.scale * kLog2eF;
   typename G::acc_t ka[CT], va[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
@@ -569,7 +576,7 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
       const float4_t ls = *reinterpret_cast<const float4_t*>(lse_h + ib);
       dl[g] = *reinterpret_cast<const float4_t*>(delta_h + ib);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) st[4 * g + r] = fmaf(st[4 * g + r], sc2, -(ls[r] * kLog2eF));
+      for (int r = 0; r < 4; ++r) st[4 * g + r] = score(st[4 * g + r], P.scale) - ls[r];
     }
     if ((P.causal && i0 < j0 + M) || i0 + kTileF > P.s) {
 #pragma unroll
@@ -589,7 +596,7 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
 #define SAR_ROW(E)                                                                                                          \
   if constexpr (E < NV) {                                                                                                   \
     const bool keep = !DROP || kept<E, CALLS>(mine, li);                                                                    \
-    const float pe = __builtin_amdgcn_exp2f(st[E]);                                                                         \
+    const float pe = __builtin_amdgcn_exp2f(st[E] * kLog2eF);                                                               \
     const float pd = keep ? pe * P.keep_scale : 0.f, dp = keep ? dd[E] * P.keep_scale : 0.f;                                \
     const float ds = pe * (dp - dl[(E) >> 2][(E) & 3]);                                                                     \
     _Pragma("unroll") for (int ct = 0; ct < CT; ++ct) {                                                                     \
@@ -618,7 +625,7 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
     if (wave_any((P.causal && odd_rows(it0)) || (P.s % kTileF && odd_rows(nt - 1))))
       for (int c = c0; c < min(c0 + M / NWF, P.s); ++c) {
         const T *kc = k + base + (int64_t)c * P.stride_s, *vc = v + base + (int64_t)c * P.stride_s;
-        auto prob = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f((dot_rows(qg + (int64_t)i * P.stride_s, kc, P.d) * P.scale - lse_h[i]) * kLog2eF); };
+        auto prob = [&](int i) __attribute__((always_inline)) { return exp_diff(score(dot_rows(qg + (int64_t)i * P.stride_s, kc, P.d), P.scale), lse_h[i]); };
         plain_row([&](int i) __attribute__((always_inline)) { return kept_pair<DROP>(P, beta, n, i, c) ? prob(i) * P.keep_scale : 0.f; }, P.causal ? c : 0, P.s, gg, P.stride_s,
                   P.d, 1.f, dv + base + (int64_t)c * P.stride_s);
         plain_row([&](int i) __attribute__((always_inline)) {

@@ -1,6 +1,6 @@
 """GPU: the attention core in fp32 (and bf16 of head dimensions that the bf16 kernels leave to the same kernels) on inputs that hold
 an infinity, a NaN, or scores at the end of the type's range.  A pair (i, j) that the mask excludes takes no part in anything: a value that
-is not finite reaches exactly the outputs that the definition, evaluated over the allowed pairs only, gives it, and as the same infinity."""
+is not finite reaches exactly the outputs that the definition, evaluated over the allowed pairs only, gives it, and as the same infinity.  Large finite scores keep their precision."""
 import numpy as np
 import pytest
 
@@ -97,3 +97,34 @@ def test_uninitialised_tail_of_a_causal_sequence():
     ref, mag = _definition(sh, q, k, v, do, [(0, 0), (0, 1)])
     assert np.all(np.abs(got["o"] - ref["o"])[:67] <= 1e-4 * mag["o"][:67]) and np.all(np.isnan(got["o"][67:]))
     assert np.max(np.abs(got["lse"] - ref["lse"])[:, :, :67]) < 1e-4
+
+
+@pytest.mark.parametrize("heads", [2, 64])
+@pytest.mark.parametrize("d,scale,top,causal", [(64, None, 58, 1), (96, None, 58, 1), (64, 1.0, 62, 1), (64, None, 58, 0), (64, -0.125, 58, 1), (32, None, 50, 1)])
+def test_scores_at_the_end_of_the_range(d, scale, top, causal, heads):
+    """Finite scores of one sign in a row, far below -1e30 or far above 1e30: every row attends to one key (a sum of several exponentials
+    would not show in a log-sum-exp of that size); a causal row 0 has no other."""
+    s = 72
+    sh = _case("f32", s, d, 0.1, causal, heads, scale)
+    q, k, v, do = attn_inputs(s, sh.b, sh.A, d, "f32", seed=13)
+    q[..., 0], q[..., 1:] = -2.0 ** top, 0.0
+    q[40::3, ..., 0] = 2.0 ** top
+    k[..., 0] = (2.0 ** top * (1.0 + (np.arange(s) * 29 % s) / 128.0))[:, None, None]
+    print(f"scores of 2^{2 * top} d={d} scale={scale} causal={causal} heads={sh.b * heads}", flush=True)
+    _compare("range", sh, "f32", q, k, v, do)
+
+
+@pytest.mark.parametrize("d,heads", [(64, 2), (96, 2), (64, 64)])
+def test_precision_of_large_scores(d, heads):
+    """Scores up to some 300, a row's softmax spread over few keys.  A probability exp(score - LSE) carries one rounding of the score and
+    one of the LSE, each uniform within 2^-17 where they lie between 128 and 256 as most row maxima do: sqrt 2 x 2^-17 / sqrt 3 = 6.2e-6
+    of dV in the 2-norm, less what cancels in rows with a single key.  Measured 3.4e-6 to 3.8e-6."""
+    s = 512
+    sh = oracle.AttnShape(s=s, b=1, a=heads, h=heads * d, p=0.0, seed=5)
+    q, k, v, do = attn_inputs(s, 1, heads, d, "f32", seed=14, qk_std=8.0)
+    from gpu_util import run_attn
+    got = run_attn(sh, "f32", q, k, v, do)
+    ref = oracle.attn_bwd(sh, q, k, v, do)["dv"]
+    e = float(np.linalg.norm(got["dv"] - ref) / np.linalg.norm(ref))
+    print(f"large scores d={d} heads={heads}: dV error {e:.2e}", flush=True)
+    assert e <= 2 ** 0.5 * 2.0 ** -17 / 3 ** 0.5
