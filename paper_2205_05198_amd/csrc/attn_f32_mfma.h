@@ -121,7 +121,7 @@ constexpr int kAheadF = 16;
 constexpr int rows_ahead(int n, int nv) { return kAheadF / n < 2 ? 2 : kAheadF / n > nv ? nv : kAheadF / n; }  // n: floats of a row per lane
 
 // Row operands: pieces of 4 consecutive elements (4 (HH j + hh)) of one row per lane.  Pieces beyond the head dimension repeat the
-// last one; the other operand is zero there.
+// last one; the other operand is zero there (an infinity in the last piece makes a score NaN then, which the end of the kernels mends).
 constexpr int kRingF = kAheadF / 4;
 template <int M, int DT, typename T>
 __device__ __forceinline__ float4_t load_piece(const T* row, int j, int hh, int d) {
@@ -204,7 +204,8 @@ __device__ __forceinline__ bool merge_store(const typename Geo<M>::acc_t (&acc)[
 // Pairs (i, j) that the mask excludes, and rows past the end, have probability 0 and take part in the matrix products of a tile all the
 // same: 0 x infinity and 0 x NaN would reach outputs that the definition keeps them from.  A wave that has stored a value which is not
 // finite therefore looks at the operands of its tiles with excluded pairs, and where one of those is not finite either, it computes
-// the rows it stored again from the definition, over the allowed pairs only.  Finite results cost one compare each.
+// the rows it stored again from the definition, over the allowed pairs only.  Where the head dimension is no multiple of 32 the products
+// have excluded elements in every tile: there it computes them again whatever the operands are.  Finite results cost one compare each.
 __device__ __forceinline__ bool wave_any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
 template <int M>
 __device__ __forceinline__ int merge_row_of_wave(int wave) { return wave * (M / NWF); }  // the first; they are consecutive
@@ -366,15 +367,20 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
   const float lse_i = m + __builtin_amdgcn_logf(l) * kLn2F;
   if (wave == 0 && hh == 0 && i < P.s) lse[(size_t)bn * P.s + i] = lse_i;
   const bool odd = merge_store<M, CT>(oacc, buf, wave, li, hh, 1.f, o + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
-  if ((P.causal || P.s % kTileF) && wave_any(odd)) {
+  if (wave_any(odd)) {
     const int j0 = kTileF * (ntile - 1), r0 = i0 + merge_row_of_wave<M>(wave);
-    if (wave_any(any_odd(v + base, P.stride_s, j0, min(j0 + kTileF, P.s), P.d)))
+    if (P.d % 32 || ((P.causal || P.s % kTileF) && wave_any(any_odd(v + base, P.stride_s, j0, min(j0 + kTileF, P.s), P.d))))
       for (int r = r0; r < min(r0 + M / NWF, P.s); ++r) {
-        const float lse_r = __shfl(lse_i, r - i0, 64);
-        plain_row([&](int j) __attribute__((always_inline)) {
-          const float pe = exp_diff(score(dot_rows(q + base + (int64_t)r * P.stride_s, k + base + (int64_t)j * P.stride_s, P.d), P.scale), lse_r);
-          return kept_pair<DROP>(P, beta, n, r, j) ? pe * P.keep_scale : 0.f;
-        }, 0, P.causal ? r + 1 : P.s, v + base, P.stride_s, P.d, 1.f, o + base + (int64_t)r * P.stride_s);
+        const int end = P.causal ? r + 1 : P.s;
+        auto scored = [&](int j) __attribute__((always_inline)) { return score(dot_rows(q + base + (int64_t)r * P.stride_s, k + base + (int64_t)j * P.stride_s, P.d), P.scale); };
+        float mx = -INFINITY, sum = 0.f;
+        for (int j = lane; j < end; j += 64) mx = fmaxf(mx, scored(j));
+        mx = wave_max(mx);
+        for (int j = lane; j < end; j += 64) sum += exp_diff(scored(j), mx);
+        const float lse_r = mx + __builtin_amdgcn_logf(wave_sum(sum)) * kLn2F;
+        if (lane == 0) lse[(size_t)bn * P.s + r] = lse_r;
+        plain_row([&](int j) __attribute__((always_inline)) { return kept_pair<DROP>(P, beta, n, r, j) ? exp_diff(scored(j), lse_r) * P.keep_scale : 0.f; }, 0, end, v + base,
+                  P.stride_s, P.d, 1.f, o + base + (int64_t)r * P.stride_s);
       }
   }
 }
@@ -481,9 +487,9 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
     }
   }
   const bool odd = merge_store<M, CT>(acc, buf, wave, li, hh, P.scale, dq + base + (int64_t)i0 * P.stride_s, P.stride_s, P.s - i0, P.d);
-  if ((P.causal || P.s % kTileF) && wave_any(odd)) {
+  if (wave_any(odd)) {
     const int j0 = kTileF * (ntile - 1), j1 = min(j0 + kTileF, P.s), r0 = i0 + merge_row_of_wave<M>(wave);
-    if (wave_any(any_odd(kg, P.stride_s, j0, j1, P.d) || any_odd(vg, P.stride_s, j0, j1, P.d)))
+    if (P.d % 32 || ((P.causal || P.s % kTileF) && wave_any(any_odd(kg, P.stride_s, j0, j1, P.d) || any_odd(vg, P.stride_s, j0, j1, P.d))))
       for (int r = r0; r < min(r0 + M / NWF, P.s); ++r) {
         const float dl_r = __shfl(dl, r - i0, 64), lse_r = __shfl(lse_i, r - i0, 64);
         plain_row([&](int j) __attribute__((always_inline)) {
@@ -616,13 +622,13 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
   }
   bool odd = merge_store<M, CT>(va, buf, wave, li, hh, 1.f, dv + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
   odd |= merge_store<M, CT>(ka, buf, wave, li, hh, P.scale, dk + base + (int64_t)j0 * P.stride_s, P.stride_s, P.s - j0, P.d);
-  if ((P.causal || P.s % kTileF) && wave_any(odd)) {
+  if (wave_any(odd)) {
     auto odd_rows = [&](int it) {  // of a tile with excluded pairs
       const int r0 = kTileF * it, r1 = min(r0 + kTileF, P.s), r = r0 + lane;
       return any_odd(qg, P.stride_s, r0, r1, P.d) || any_odd(gg, P.stride_s, r0, r1, P.d) || (r < r1 && !(finite(lse_h[r]) && finite(delta_h[r])));
     };
     const int c0 = j0 + merge_row_of_wave<M>(wave);
-    if (wave_any((P.causal && odd_rows(it0)) || (P.s % kTileF && odd_rows(nt - 1))))
+    if (P.d % 32 || wave_any((P.causal && odd_rows(it0)) || (P.s % kTileF && odd_rows(nt - 1))))
       for (int c = c0; c < min(c0 + M / NWF, P.s); ++c) {
         const T *kc = k + base + (int64_t)c * P.stride_s, *vc = v + base + (int64_t)c * P.stride_s;
         auto prob = [&](int i) __attribute__((always_inline)) { return exp_diff(score(dot_rows(qg + (int64_t)i * P.stride_s, kc, P.d), P.scale), lse_h[i]); };

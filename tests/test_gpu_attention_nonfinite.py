@@ -86,6 +86,19 @@ def test_excluded_pairs_take_no_part(dtype, s, d, p, causal, where, heads):
         _compare(f"{where}[{row}]={value}", sh, dtype, t["q"], t["k"], t["v"], t["do"])
 
 
+@pytest.mark.parametrize("heads", [2, 64])
+@pytest.mark.parametrize("dtype,s,d", [("f32", 40, 36), ("f32", 72, 80), ("f32", 40, 100), ("bf16", 72, 40)])
+def test_infinity_in_the_last_element_of_a_head(dtype, s, d, heads):
+    """Head dimensions that are no multiple of 32: the operand pieces past the end of a row are loads of its last one.  K = -infinity in the
+    last element, met by positive elements of Q, gives that key probability 0 and leaves all but its own row of scores finite."""
+    sh = _case(dtype, s, d, 0.1, 1, heads)
+    q, k, v, do = attn_inputs(s, sh.b, sh.A, d, dtype, seed=15)
+    q[..., d - 1], k[..., d - 1] = np.abs(q[..., d - 1]), np.abs(k[..., d - 1])
+    k[9, sh.b - 1, 1, d - 1] = -np.inf
+    print(f"last element {dtype} s={s} d={d} heads={sh.b * heads}", flush=True)
+    _compare("last element", sh, dtype, q, k, v, do)
+
+
 def test_uninitialised_tail_of_a_causal_sequence():
     """A sequence padded with NaN to a multiple of 8: the rows before the padding keep their O and LSE."""
     from gpu_util import run_attn
