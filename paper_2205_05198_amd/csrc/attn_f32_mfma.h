@@ -53,12 +53,18 @@ template <> struct Geo<16> {
   static __device__ __forceinline__ int row_of_value(int e, int hh) { return 16 * (e >> 2) + 4 * hh + (e & 3); }
 };
 
-__device__ __forceinline__ float4_t load4(const float* p) { return *reinterpret_cast<const float4_t*>(p); }
-__device__ __forceinline__ float4_t load4(const uint16_t* p) {
-  const uint2 u = *reinterpret_cast<const uint2*>(p);
-  float4_t f = {__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
-  return f;
-}
+// Operands in flight are held as they lie in memory and converted where they are used: a conversion next to the load waits for it.
+__device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+template <typename T> struct Raw4;  // 4 consecutive elements
+template <> struct Raw4<float> { typedef float4_t type; };
+template <> struct Raw4<uint16_t> { typedef uint2 type; };
+__device__ __forceinline__ float4_t raw_load4(const float* p) { return *reinterpret_cast<const float4_t*>(p); }
+__device__ __forceinline__ uint2 raw_load4(const uint16_t* p) { return *reinterpret_cast<const uint2*>(p); }
+__device__ __forceinline__ float4_t get4(float4_t r) { return r; }
+__device__ __forceinline__ float4_t get4(uint2 r) { return float4_t{lo_f32(r.x), hi_f32(r.x), lo_f32(r.y), hi_f32(r.y)}; }
+template <typename T>
+__device__ __forceinline__ float4_t load4(const T* p) { return get4(raw_load4(p)); }
 
 __device__ __forceinline__ bool finite(float f) { return (__float_as_uint(f) & 0x7f800000u) != 0x7f800000u; }
 
@@ -91,27 +97,55 @@ __device__ __forceinline__ float column_sum(float v) {
 template <int CT>
 __device__ __forceinline__ int col_start(int m, int d) { return min(CT * m, d - CT); }
 
+template <typename T, int CT> struct Cols;  // such a run in flight
+template <int CT> struct Cols<float, CT> {
+  struct __attribute__((packed, aligned(4))) run { float v[CT]; } r;
+  __device__ __forceinline__ void load(const float* p) { r = *reinterpret_cast<const run*>(p); }
+  __device__ __forceinline__ float get(int e) const { return r.v[e]; }
+};
+template <int CT> struct Cols<uint16_t, CT> {  // d % 8 == 0: a run of even length starts at an even element
+  struct __attribute__((packed, aligned(CT % 2 ? 2 : 4))) run { uint32_t v[CT / 2 ? CT / 2 : 1]; } r;
+  uint16_t last;
+  __device__ __forceinline__ void load(const uint16_t* p) {
+    if (CT > 1) r = *reinterpret_cast<const run*>(p);
+    if (CT % 2) last = p[CT - 1];
+  }
+  __device__ __forceinline__ float get(int e) const { return CT % 2 && e == CT - 1 ? bf16_to_f32(last) : e % 2 ? hi_f32(r.v[e / 2]) : lo_f32(r.v[e / 2]); }
+};
+
 template <int CT>
-__device__ __forceinline__ void load_cols(const float* p, float (&f)[CT]) {
-  struct __attribute__((packed, aligned(4))) run { float v[CT]; };
-  const run r = *reinterpret_cast<const run*>(p);
+__device__ __forceinline__ void store_cols(float* p, const float (&f)[CT]) {
 #pragma unroll
-  for (int e = 0; e < CT; ++e) f[e] = r.v[e];
+  for (int e = 0; e < CT; ++e) p[e] = f[e];
 }
 template <int CT>
-__device__ __forceinline__ void load_cols(const uint16_t* p, float (&f)[CT]) {
+__device__ __forceinline__ void store_cols(uint16_t* p, const float (&f)[CT]) {
+  if constexpr (CT % 2 == 0) {
+    struct __attribute__((packed, aligned(4))) run { uint32_t v[CT / 2]; } r;
 #pragma unroll
-  for (int e = 0; e < CT; ++e) f[e] = bf16_to_f32(p[e]);
+    for (int e = 0; e < CT / 2; ++e) r.v[e] = pack_bf16x2(f[2 * e], f[2 * e + 1]);
+    *reinterpret_cast<run*>(p) = r;
+  } else {
+#pragma unroll
+    for (int e = 0; e < CT; ++e) p[e] = f32_to_bf16(f[e]);
+  }
 }
 
 // Rows of a tensor in LDS, as fp32, zero beyond the head dimension; DT = 32-wide pieces that cover it, pitch 32 DT + 4
 template <int M, int DT, typename T>
 __device__ __forceinline__ void rows_to_lds(float* dst, const T* g, int64_t gstride, int rows_valid, int d) {
-  for (int c = threadIdx.x; c < M * 8 * DT; c += 64 * NWF) {
-    const int r = c / (8 * DT), x = 4 * (c - r * 8 * DT);
-    float4_t f = {0.f, 0.f, 0.f, 0.f};
-    if (x < d) f = load4(g + (int64_t)min(r, rows_valid - 1) * gstride + x);
-    *reinterpret_cast<float4_t*>(dst + r * (32 * DT + 4) + x) = f;
+  constexpr int N = M * 8 * DT, U = (N + 64 * NWF - 1) / (64 * NWF);  // all loads of a thread in flight at once
+  typename Raw4<T>::type f[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int c = threadIdx.x + 64 * NWF * u, r = c / (8 * DT), x = 4 * (c - r * 8 * DT);
+    f[u] = raw_load4(g + (int64_t)min(r, rows_valid - 1) * gstride + min(x, d - 4));
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int c = threadIdx.x + 64 * NWF * u, r = c / (8 * DT), x = 4 * (c - r * 8 * DT);
+    if (c < N) *reinterpret_cast<float4_t*>(dst + r * (32 * DT + 4) + x) = x < d ? get4(f[u]) : float4_t{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -124,12 +158,12 @@ constexpr int rows_ahead(int n, int nv) { return kAheadF / n < 2 ? 2 : kAheadF /
 // last one; the other operand is zero there (an infinity in the last piece makes a score NaN then, which the end of the kernels mends).
 constexpr int kRingF = kAheadF / 4;
 template <int M, int DT, typename T>
-__device__ __forceinline__ float4_t load_piece(const T* row, int j, int hh, int d) {
+__device__ __forceinline__ typename Raw4<T>::type load_piece(const T* row, int j, int hh, int d) {
   constexpr int W = 4 * Geo<M>::HH;
-  return load4(row + (W * (j + 1) <= 32 * (DT - 1) ? W * j + 4 * hh : min(W * j + 4 * hh, d - 4)));  // d > 32 (DT - 1)
+  return raw_load4(row + (W * (j + 1) <= 32 * (DT - 1) ? W * j + 4 * hh : min(W * j + 4 * hh, d - 4)));  // d > 32 (DT - 1)
 }
 template <int M, int DT, typename T>
-__device__ __forceinline__ void ring_start(float4_t (&ring)[kRingF], const T* row, const T* next, int hh, int d) {
+__device__ __forceinline__ void ring_start(typename Raw4<T>::type (&ring)[kRingF], const T* row, const T* next, int hh, int d) {
   constexpr int NP = 8 * DT / Geo<M>::HH;
 #pragma unroll
   for (int j = 0; j < kRingF; ++j) ring[j] = j < NP ? load_piece<M, DT>(row, j, hh, d) : load_piece<M, DT>(next, j - NP, hh, d);
@@ -138,7 +172,7 @@ __device__ __forceinline__ void ring_start(float4_t (&ring)[kRingF], const T* ro
 // `row`, then with the first pieces of `next` (its pieces past the row after `next` with those of `after`).  R0: ring slot of this
 // row's piece 0.
 template <int M, int DT, int R0, typename T>
-__device__ __forceinline__ typename Geo<M>::acc_t dot_tile(float4_t (&ring)[kRingF], const T* row, const T* next, const T* after, const float* lds_row, int hh,
+__device__ __forceinline__ typename Geo<M>::acc_t dot_tile(typename Raw4<T>::type (&ring)[kRingF], const T* row, const T* next, const T* after, const float* lds_row, int hh,
                                                            int d) {
   constexpr int NP = 8 * DT / Geo<M>::HH, W = 4 * Geo<M>::HH;
   typename Geo<M>::acc_t acc;
@@ -148,9 +182,13 @@ __device__ __forceinline__ typename Geo<M>::acc_t dot_tile(float4_t (&ring)[kRin
   asm volatile("" : "+v"(off));  // the reads of LDS stay in the tile loop: hoisted out of it they would hold 16 DT registers
   lds_row += off;
   float4_t b = *reinterpret_cast<const float4_t*>(lds_row);
+  constexpr bool kConvert = sizeof(T) == 2;  // the next piece is converted beside this piece's products
+  float4_t a_next;
+  if (kConvert) a_next = get4(ring[R0 % kRingF]);
 #pragma unroll
   for (int j = 0; j < NP; ++j) {
-    const float4_t a = ring[(R0 + j) % kRingF], bj = b;
+    const float4_t a = kConvert ? a_next : get4(ring[(R0 + j) % kRingF]), bj = b;
+    if (kConvert && j + 1 < NP) a_next = get4(ring[(R0 + j + 1) % kRingF]);
     if (j + 1 < NP) b = *reinterpret_cast<const float4_t*>(lds_row + W * (j + 1));
 #pragma unroll
     for (int u = 0; u < 4; ++u) acc = Geo<M>::mfma(a[u], bj[u], acc);
@@ -192,10 +230,10 @@ __device__ __forceinline__ bool merge_store(const typename Geo<M>::acc_t (&acc)[
       T* o = out + (int64_t)row * gstride + col_start<CT>(MM * g + m, d);
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        const float y = s[ct] * mul;
-        odd |= !finite(y);
-        Elem<T>::store(o + ct, y);
+        s[ct] *= mul;
+        odd |= !finite(s[ct]);
       }
+      store_cols<CT>(o, s);
     }
   }
   return odd;
@@ -295,7 +333,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
 #pragma unroll
     for (int e = 0; e < NV / G::SUB; ++e) oacc[ct][e] = 0.f;
   float m_ref = kLowestF, l_run = 0.f;
-  float4_t ring[kRingF];
+  typename Raw4<T>::type ring[kRingF];
   ring_start<M, DT>(ring, krow(wave, 0), krow(wave, G::SUB - 1), hh, P.d);
   __syncthreads();
   const float* qrow = Qs + li * QP + 4 * hh;
@@ -303,9 +341,9 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
   for (int jt = wave; jt < ntile; jt += NWF) {
     const int j0 = kTileF * jt;
     auto vrow = [&](int e) __attribute__((always_inline)) { return vg + (int64_t)min(j0 + G::key_of_value(e, hh), P.s - 1) * P.stride_s; };
-    float vf[VA][CT];
+    Cols<T, CT> vf[VA];
 #pragma unroll
-    for (int e = 0; e < VA; ++e) load_cols<CT>(vrow(e), vf[e]);
+    for (int e = 0; e < VA; ++e) vf[e].load(vrow(e));
     float st[NV];
     if constexpr (M == 32) {
       const float16_t s0 = dot_tile<M, DT, 0>(ring, krow(jt, 0), krow(jt + NWF, 0), krow(jt + NWF, 0), qrow, hh, P.d);
@@ -346,9 +384,9 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_fwd_f32_kern
         l_run += pe;
         const float pd = !DROP || ((keep >> x) & 1u) ? pe : 0.f;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) oacc[ct] = G::mfma(vf[e % VA][ct], pd, oacc[ct]);
+        for (int ct = 0; ct < CT; ++ct) oacc[ct] = G::mfma(vf[e % VA].get(ct), pd, oacc[ct]);
         asm volatile("" : "+v"(oacc[0]));
-        if (e + VA < NV) load_cols<CT>(vrow(e + VA), vf[e % VA]);
+        if (e + VA < NV) vf[e % VA].load(vrow(e + VA));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -412,7 +450,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
   const T* vg = v + base;
   const T* kc = k + base + col_start<CT>(li, P.d);
   auto rowat = [&](int jt, int t) __attribute__((always_inline)) { return (int64_t)min(kTileF * jt + G::key_of_row(t, li), P.s - 1) * P.stride_s; };
-  float4_t ring[kRingF];
+  typename Raw4<T>::type ring[kRingF];
   ring_start<M, DT>(ring, kg + rowat(wave, 0), (M == 32 ? vg : kg) + rowat(wave, G::SUB - 1), hh, P.d);
   __syncthreads();
   {
@@ -443,11 +481,12 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
   for (int jt = wave; jt < ntile; jt += NWF) {
     const int j0 = kTileF * jt;
     auto crow = [&](int e) __attribute__((always_inline)) { return kc + (int64_t)min(j0 + G::key_of_value(e, hh), P.s - 1) * P.stride_s; };
-    float cf[CA][CT], st[NV], dd[NV];
+    Cols<T, CT> cf[CA];
+    float st[NV], dd[NV];
     if constexpr (M == 32) {
       const float16_t s0 = dot_tile<M, DT, 0>(ring, kg + rowat(jt, 0), vg + rowat(jt, 0), vg + rowat(jt, 0), qrow, hh, P.d);
 #pragma unroll
-      for (int e = 0; e < CA; ++e) load_cols<CT>(crow(e), cf[e]);
+      for (int e = 0; e < CA; ++e) cf[e].load(crow(e));
       const float16_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, vg + rowat(jt, 0), kg + rowat(jt + NWF, 0), kg + rowat(jt + NWF, 0), grow, hh, P.d);
 #pragma unroll
       for (int e = 0; e < NV; ++e) { st[e] = s0[e]; dd[e] = d0[e]; }
@@ -455,7 +494,7 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
       const float4_t s0 = dot_tile<M, DT, 0>(ring, kg + rowat(jt, 0), kg + rowat(jt, 1), vg + rowat(jt, 0), qrow, hh, P.d);
       const float4_t s1 = dot_tile<M, DT, (2 * DT) % kRingF>(ring, kg + rowat(jt, 1), vg + rowat(jt, 0), vg + rowat(jt, 1), qrow, hh, P.d);
 #pragma unroll
-      for (int e = 0; e < CA; ++e) load_cols<CT>(crow(e), cf[e]);
+      for (int e = 0; e < CA; ++e) cf[e].load(crow(e));
       const float4_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, vg + rowat(jt, 0), vg + rowat(jt, 1), kg + rowat(jt + NWF, 0), grow, hh, P.d);
       const float4_t d1 = dot_tile<M, DT, (6 * DT) % kRingF>(ring, vg + rowat(jt, 1), kg + rowat(jt + NWF, 0), kg + rowat(jt + NWF, 1), grow, hh, P.d);
 #pragma unroll
@@ -479,9 +518,9 @@ __global__ __launch_bounds__(64 * NWF, waves_rows(M, DT)) void attn_bwd_rows_f32
         const float dp = !DROP || ((keep >> x) & 1u) ? dd[e] * P.keep_scale : 0.f;
         const float ds = pe * (dp - dl);
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[ct] = G::mfma(cf[e % CA][ct], ds, acc[ct]);
+        for (int ct = 0; ct < CT; ++ct) acc[ct] = G::mfma(cf[e % CA].get(ct), ds, acc[ct]);
         asm volatile("" : "+v"(acc[0]));
-        if (e + CA < NV) load_cols<CT>(crow(e + CA), cf[e % CA]);
+        if (e + CA < NV) cf[e % CA].load(crow(e + CA));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -543,7 +582,7 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
 #pragma unroll
     for (int e = 0; e < NV / G::SUB; ++e) { ka[ct][e] = 0.f; va[ct][e] = 0.f; }
   auto rowat = [&](int it, int t) __attribute__((always_inline)) { return (int64_t)min(kTileF * it + G::row_of_row(t, li), P.s - 1) * P.stride_s; };
-  float4_t ring[kRingF];
+  typename Raw4<T>::type ring[kRingF];
   ring_start<M, DT>(ring, qg + rowat(it0 + wave, 0), (M == 32 ? gg : qg) + rowat(it0 + wave, G::SUB - 1), hh, P.d);
   __syncthreads();
   const float *krow = Ks + li * QP + 4 * hh, *vrow = Vs + li * QP + 4 * hh;
@@ -552,12 +591,22 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
     const int i0 = kTileF * it;
     // rows past the end get probability 0 (what they read is clamped)
     auto row_of = [&](int e) __attribute__((always_inline)) { return (int64_t)min(i0 + G::row_of_value(e, hh), P.s - 1) * P.stride_s + cs; };
-    float gc[CA][CT], qc[CA][CT], st[NV], dd[NV];
+    Cols<T, CT> gc[CA], qc[CA];
+    float st[NV], dd[NV];
     auto start_cols = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int e = 0; e < CA; ++e) {
-        load_cols<CT>(gg + row_of(e), gc[e]);
-        load_cols<CT>(qg + row_of(e), qc[e]);
+        gc[e].load(gg + row_of(e));
+        qc[e].load(qg + row_of(e));
+      }
+    };
+    float4_t dl[NV / 4], ls[NV / 4];
+    auto start_stats = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int g = 0; g < NV / 4; ++g) {
+        const int ib = min(i0 + G::row_of_value(4 * g, hh), P.s - 4);  // s % 8 == 0: a group of four rows is inside or outside as a whole
+        ls[g] = *reinterpret_cast<const float4_t*>(lse_h + ib);
+        dl[g] = *reinterpret_cast<const float4_t*>(delta_h + ib);
       }
     };
     if constexpr (M == 32) {
@@ -566,7 +615,9 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
       const float16_t d0 = dot_tile<M, DT, (4 * DT) % kRingF>(ring, gg + rowat(it, 0), qg + rowat(it + NWF, 0), qg + rowat(it + NWF, 0), vrow, hh, P.d);
 #pragma unroll
       for (int e = 0; e < NV; ++e) { st[e] = s0[e]; dd[e] = d0[e]; }
+      start_stats();
     } else {
+      start_stats();
       const float4_t s0 = dot_tile<M, DT, 0>(ring, qg + rowat(it, 0), qg + rowat(it, 1), gg + rowat(it, 0), krow, hh, P.d);
       const float4_t s1 = dot_tile<M, DT, (2 * DT) % kRingF>(ring, qg + rowat(it, 1), gg + rowat(it, 0), gg + rowat(it, 1), krow, hh, P.d);
       start_cols();
@@ -575,15 +626,8 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
 #pragma unroll
       for (int e = 0; e < 4; ++e) { st[e] = s0[e]; st[4 + e] = s1[e]; dd[e] = d0[e]; dd[4 + e] = d1[e]; }
     }
-    float4_t dl[NV / 4];
 #pragma unroll
-    for (int g = 0; g < NV / 4; ++g) {
-      const int ib = min(i0 + G::row_of_value(4 * g, hh), P.s - 4);  // s % 8 == 0: a group of four rows is inside or outside as a whole
-      const float4_t ls = *reinterpret_cast<const float4_t*>(lse_h + ib);
-      dl[g] = *reinterpret_cast<const float4_t*>(delta_h + ib);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) st[4 * g + r] = score(st[4 * g + r], P.scale) - ls[r];
-    }
+    for (int e = 0; e < NV; ++e) st[e] = score(st[e], P.scale) - ls[e >> 2][e & 3];
     if ((P.causal && i0 < j0 + M) || i0 + kTileF > P.s) {
 #pragma unroll
       for (int e = 0; e < NV; ++e) {
@@ -606,13 +650,13 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
     const float pd = keep ? pe * P.keep_scale : 0.f, dp = keep ? dd[E] * P.keep_scale : 0.f;                                \
     const float ds = pe * (dp - dl[(E) >> 2][(E) & 3]);                                                                     \
     _Pragma("unroll") for (int ct = 0; ct < CT; ++ct) {                                                                     \
-      va[ct] = G::mfma(gc[(E) % CA][ct], pd, va[ct]);                                                                       \
-      ka[ct] = G::mfma(qc[(E) % CA][ct], ds, ka[ct]);                                                                       \
+      va[ct] = G::mfma(gc[(E) % CA].get(ct), pd, va[ct]);                                                                   \
+      ka[ct] = G::mfma(qc[(E) % CA].get(ct), ds, ka[ct]);                                                                   \
     }                                                                                                                       \
     asm volatile("" : "+v"(va[0]), "+v"(ka[0]));                                                                            \
     if constexpr ((E) + CA < NV) {                                                                                          \
-      load_cols<CT>(gg + row_of((E) + CA), gc[(E) % CA]);                                                                   \
-      load_cols<CT>(qg + row_of((E) + CA), qc[(E) % CA]);                                                                   \
+      gc[(E) % CA].load(gg + row_of((E) + CA));                                                                             \
+      qc[(E) % CA].load(qg + row_of((E) + CA));                                                                             \
     }                                                                                                                       \
     __builtin_amdgcn_sched_barrier(0);                                                                                      \
   }
