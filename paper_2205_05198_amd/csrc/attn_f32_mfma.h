@@ -686,10 +686,138 @@ __global__ __launch_bounds__(64 * NWF, waves_cols(M, DT)) void attn_bwd_cols_f32
   }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Short sequences (s <= 64), one wave a row (forward, row pass) or a key (column pass): a lane holds the pair with the other index
+// lane % KP, KP the power of two from s on, and every KP-th lane shares its products over the head dimension.  The kernels above spend
+// themselves on the products of a 16 x 32 tile that is mostly padding, one matrix instruction after the other.
+// ---------------------------------------------------------------------------------------------------
+struct Few {
+  int lane, kp, other;
+  __device__ __forceinline__ explicit Few(int s) : lane(threadIdx.x & 63), kp(s <= 8 ? 8 : s <= 16 ? 16 : s <= 32 ? 32 : 64), other(lane & (kp - 1)) {}
+  // a . b of this lane's pair; a: the wave's row, b: the lane's
+  template <typename T>
+  __device__ __forceinline__ float dot(const T* a, const T* b, int d) const {
+    float acc = 0.f;
+#pragma unroll 4
+    for (int x = 4 * (lane / kp); x < d; x += 4 * (64 / kp)) {
+      const float4_t fa = load4(a + x), fb = load4(b + x);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = fmaf(fa[u], fb[u], acc);
+    }
+    for (int o = kp; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+    return acc;
+  }
+  // out = mul sum_{y = lo}^{hi - 1} w(y) src_y, w in lane y
+  template <typename T>
+  __device__ __forceinline__ void sum(float w, int lo, int hi, const T* src, int64_t gstride, int d, float mul, T* out) const {
+    const int x = 4 * lane, xl = min(x, d - 4);  // d <= 256; every lane stays active: its weight is read by the others
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int y = lo; y < hi; ++y) {
+      const float wy = __shfl(w, y, 64);
+      const float4_t f = load4(src + (int64_t)y * gstride + xl);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] = fmaf(wy, f[u], acc[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] *= mul;
+    if (x < d) store_cols<4>(out + x, acc);
+  }
+};
+template <bool DROP, typename T>
+__global__ __launch_bounds__(64 * NWF) void attn_fwd_few_kernel(AttnParams P, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                               T* __restrict__ o, float* __restrict__ lse) {
+  const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * NWF + (threadIdx.x >> 6));
+  if (w >= P.b * P.A * P.s) return;
+  const int bn = w / P.s, i = w % P.s, beta = bn / P.A, n = bn % P.A, end = P.causal ? i + 1 : P.s;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a, row = base + (int64_t)i * P.stride_s;
+  const Few f(P.s);
+  const float dot = f.dot(q + row, k + base + (int64_t)min(f.other, end - 1) * P.stride_s, P.d), st = f.other < end ? score(dot, P.scale) : -INFINITY;
+  const float m = wave_max(st), pe = f.other < end ? exp_diff(st, m) : 0.f, l = wave_sum(f.lane < f.kp ? pe : 0.f);
+  if (f.lane == 0) lse[w] = m + __builtin_amdgcn_logf(l) * kLn2F;
+  f.sum(kept_pair<DROP>(P, beta, n, i, f.other) ? pe / l * P.keep_scale : 0.f, 0, end, v + base, P.stride_s, P.d, 1.f, o + row);
+}
+template <bool DROP, typename T>
+__global__ __launch_bounds__(64 * NWF) void attn_bwd_rows_few_kernel(AttnParams P, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                                    const T* __restrict__ o, const float* __restrict__ lse, const T* __restrict__ dO,
+                                                                    T* __restrict__ dq, float* __restrict__ delta) {
+  const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * NWF + (threadIdx.x >> 6));
+  if (w >= P.b * P.A * P.s) return;
+  const int bn = w / P.s, i = w % P.s, beta = bn / P.A, n = bn % P.A, end = P.causal ? i + 1 : P.s;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a, row = base + (int64_t)i * P.stride_s;
+  const Few f(P.s);
+  float dl = 0.f;
+  for (int x = 4 * f.lane; x < P.d; x += 256) {
+    const float4_t a = load4(o + row + x), b = load4(dO + row + x);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dl = fmaf(a[u], b[u], dl);
+  }
+  const int64_t other = base + (int64_t)min(f.other, end - 1) * P.stride_s;
+  const float st = score(f.dot(q + row, k + other, P.d), P.scale), dd = f.dot(dO + row, v + other, P.d);
+  dl = wave_sum(dl);
+  if (f.lane == 0) delta[w] = dl;
+  const float ds = exp_diff(st, lse[w]) * ((kept_pair<DROP>(P, beta, n, i, f.other) ? dd * P.keep_scale : 0.f) - dl);
+  f.sum(ds, 0, end, k + base, P.stride_s, P.d, P.scale, dq + row);
+}
+template <bool DROP, typename T>
+__global__ __launch_bounds__(64 * NWF) void attn_bwd_cols_few_kernel(AttnParams P, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                                    const float* __restrict__ lse, const T* __restrict__ dO, const float* __restrict__ delta,
+                                                                    T* __restrict__ dk, T* __restrict__ dv) {
+  const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * NWF + (threadIdx.x >> 6));
+  if (w >= P.b * P.A * P.s) return;
+  const int bn = w / P.s, j = w % P.s, beta = bn / P.A, n = bn % P.A, lo = P.causal ? j : 0;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a, col = base + (int64_t)j * P.stride_s;
+  const Few f(P.s);
+  const int i = min(max(f.other, lo), P.s - 1);
+  const int64_t other = base + (int64_t)i * P.stride_s;
+  const float ls = lse[bn * P.s + i], dl = delta[bn * P.s + i];
+  const float pe = exp_diff(score(f.dot(k + col, q + other, P.d), P.scale), ls), dd = f.dot(v + col, dO + other, P.d);
+  const bool keep = kept_pair<DROP>(P, beta, n, i, j);
+  f.sum(keep ? pe * P.keep_scale : 0.f, lo, P.s, dO + base, P.stride_s, P.d, 1.f, dv + col);
+  f.sum(pe * ((keep ? dd * P.keep_scale : 0.f) - dl), lo, P.s, q + base, P.stride_s, P.d, P.scale, dk + col);
+}
+
 // M = 16 where M = 32 leaves less than two workgroups a CU: twice the workgroups with half the work each start sooner and spread a
 // causal triangle better (us, forward and backward, M = 32 / 16: s = 128, 2 heads of 64 25.3 / 18.0; s = 1024, 8 heads of 128
-// 189 / 136; from there on equal, 512 x 64 heads 134 / 136, or slower for twice the operand reads, 1024 x 24 heads 175 / 186).
-inline bool narrow(const AttnParams& P) { return (int64_t)((P.s + 31) / 32) * P.b * P.A < 512; }
+// 189 / 136; from there on equal, 512 x 64 heads 134 / 136, or slower for twice the operand reads, 1024 x 24 heads 175 / 186), and
+// where half of a block of 32 rows would be padding.
+inline bool narrow(const AttnParams& P) { return P.s <= 16 || (int64_t)((P.s + 31) / 32) * P.b * P.A < 512; }
+
+// One wave a row: s <= 8 (backward, us, before / here: fp32, 1 head of 256 27.9 / 12.4, 2048 heads of 256 449 / 88, 2048 of 4 44.8 / 25.7); up to
+// s = 16 from head dimension 64 on, and 24 from 192 on, while there is at most one workgroup a CU (s = 16, 16 heads: d = 64
+// 12.3 / 11.8, 128 16.8 / 13.7, 256 29.5 / 19.1; d = 32 10.5 / 10.5; s = 24, 16 heads of 256 29.3 / 28.5, of 128 16.7 / 19.9; s = 16, 256 heads of
+// 64 12.6 / 20.9).
+inline bool few(const AttnParams& P) {
+  if (P.s <= 8) return true;
+  return (int64_t)P.s * P.b * P.A <= NWF * (int64_t)attn_mfma_cu_count() && P.s <= (P.d >= 192 ? 24 : P.d >= 64 ? 16 : 8);
+}
+
+template <typename T>
+hipError_t fwd_few(const AttnParams& P, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st) {
+  const dim3 grid((unsigned)((P.s * P.b * P.A + NWF - 1) / NWF)), block(64 * NWF);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)q, (const T*)k, (const T*)v, (T*)o, lse); };
+  if (P.thresh != 0) go(attn_fwd_few_kernel<true, T>);
+  else go(attn_fwd_few_kernel<false, T>);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t bwd_few(const AttnParams& P, const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, void* dk,
+                   void* dv, float* delta, int passes, hipStream_t st) {
+  const dim3 grid((unsigned)((P.s * P.b * P.A + NWF - 1) / NWF)), block(64 * NWF);
+  if (passes & 1) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)q, (const T*)k, (const T*)v, (const T*)o, lse, (const T*)dO, (T*)dq, delta); };
+    if (P.thresh != 0) go(attn_bwd_rows_few_kernel<true, T>);
+    else go(attn_bwd_rows_few_kernel<false, T>);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (passes & 2) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)q, (const T*)k, (const T*)v, lse, (const T*)dO, (const float*)delta, (T*)dk, (T*)dv); };
+    if (P.thresh != 0) go(attn_bwd_cols_few_kernel<true, T>);
+    else go(attn_bwd_cols_few_kernel<false, T>);
+  }
+  return hipGetLastError();
+}
 
 template <int M, int DT, typename T>
 hipError_t fwd_dt(const AttnParams& P, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st) {

@@ -133,6 +133,24 @@ def test_fp32_matrix_instruction_kernels(dtype, s, d, p, causal, scale, heads):
     assert np.max(np.abs(got["lse"] - ref["lse"]) / (1.0 + np.abs(ref["lse"]))) < 1e-5
 
 
+@pytest.mark.parametrize("dtype,s,d,p,causal", [("f32", 8, 4, 0.1, 1), ("f32", 8, 256, 0.0, 0), ("bf16", 8, 8, 0.1, 0), ("f32", 16, 64, 0.1, 1), ("f32", 16, 60, 0.1, 1),
+                                                 ("f32", 16, 100, 0.1, 0), ("bf16", 16, 72, 0.1, 1), ("f32", 24, 192, 0.1, 1), ("bf16", 24, 256, 0.0, 0), ("f32", 24, 188, 0.1, 1)])
+@pytest.mark.parametrize("heads", [1, 3, 128])
+def test_short_sequences_one_wave_a_row(dtype, s, d, p, causal, heads):
+    """Sequences of at most 24: one wave a row, or the matrix-instruction kernels where there are many rows or a small head; rows that do
+    not fill the last workgroup, head dimensions that leave lanes without a piece or do not divide among them."""
+    from gpu_util import run_attn
+    sh = oracle.AttnShape(s=s, b=1, a=2 * heads, h=2 * heads * d, t=2, rank=1, p=p, seed=77, offset=(1 << 32) - 50, causal=causal)
+    q, k, v, do = attn_inputs(s, 1, heads, d, dtype, seed=6)
+    print(f"short {dtype} s={s} d={d} p={p} causal={causal} heads={heads}", flush=True)
+    got = run_attn(sh, dtype, q, k, v, do)
+    if dtype == "bf16":
+        return _check_bf16_heads("short", sh, q, k, v, do, got, range(heads))
+    ref = _oracle(sh, q, k, v, do)
+    _check("short", got, ref, dtype, ["o", "dq", "dk", "dv"])
+    assert np.max(np.abs(got["lse"] - ref["lse"]) / (1.0 + np.abs(ref["lse"]))) < 1e-5
+
+
 @pytest.mark.parametrize("two_pass", [False, True])
 @pytest.mark.parametrize("d", [64, 96, 128, 160])
 @pytest.mark.parametrize("s,b,A,p,std,causal", [(200, 2, 2, 0.1, None, 1), (328, 1, 3, 0.25, 1.0, 1), (200, 1, 2, 0.1, None, 0), (264, 1, 1, 0.0, 1.0, 0),

@@ -72,13 +72,14 @@ def _case(dtype, s, d, p, causal, heads, scale=None):
 
 @pytest.mark.parametrize("heads", [2, 64])
 @pytest.mark.parametrize("where", ["q", "k", "v", "do"])
-@pytest.mark.parametrize("dtype,s,d,p,causal", [("f32", 72, 64, 0.1, 1), ("f32", 104, 96, 0.0, 1), ("f32", 40, 32, 0.1, 0), ("bf16", 72, 40, 0.1, 1), ("f32", 72, 128, 0.0, 0)])
+@pytest.mark.parametrize("dtype,s,d,p,causal", [("f32", 72, 64, 0.1, 1), ("f32", 104, 96, 0.0, 1), ("f32", 40, 32, 0.1, 0), ("bf16", 72, 40, 0.1, 1), ("f32", 72, 128, 0.0, 0),
+                                                 ("f32", 8, 64, 0.1, 1), ("bf16", 16, 72, 0.1, 1)])
 def test_excluded_pairs_take_no_part(dtype, s, d, p, causal, where, heads):
     """One element of one tensor is not finite: inside a 32-wide tile that the diagonal crosses, and in the last row, which the
     clamped loads past the end repeat."""
     sh = _case(dtype, s, d, p, causal, heads)
     base = dict(zip(("q", "k", "v", "do"), attn_inputs(s, sh.b, sh.A, d, dtype, seed=11)))
-    for row, value in ((5, np.nan), (37, np.inf), (s - 1, -np.inf), (s - 1, np.nan)):
+    for row, value in ((5, np.nan), (min(37, s - 2), np.inf), (s - 1, -np.inf), (s - 1, np.nan)):
         t = dict(base)
         t[where] = base[where].copy()
         t[where][row, sh.b - 1, 1, d // 2] = value
