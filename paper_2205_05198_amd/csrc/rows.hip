@@ -68,39 +68,40 @@ template <> struct Raw8<float> {
 // that all workgroups together walk through the tensor as one contiguous window.  Column sums: registers, then LDS across the
 // segments, then (nsplit > 1) partial sums that colsum_finish_kernel adds.
 //
-// Bound: HBM.  Four workgroups a CU, one row of a thread at a time, measured best or within 1 % of it over bias-GeLU backward of
-// 8192 x 3072 and 2048 x 10240 and bias-dropout backward of 1024 x 6144, 256 and 4096 x 20480 (four rows
-// of a thread in flight and two workgroups a CU: up to 6 % slower for bias-GeLU, equal for bias-dropout).
+// Bound: HBM.  One row of a thread at a time; the width of a segment is a template constant where the pass is a kernel of its own (as an
+// argument it costs 0.2 us of the 5 that 256 rows take).
 // ---------------------------------------------------------------------------------------------------
-constexpr int kColGroups = 1024;  // workgroups to aim at
 struct ColPlan {
   int lg, ncb, nsplit;  // lanes of a row segment (log2), column blocks, row splits
 };
-static inline ColPlan col_plan(int64_t rows, int64_t h, int nt = 256) {
+// one: lanes (log2) of a segment where a column block takes all of its rows, with no partial sums and no second launch (2.5 to 4 us); 0: rows
+// split over about `groups` workgroups.  Segments of 16 lanes then (bias-dropout backward, us, 8 / 16 / 64 lanes: bf16 8192 x 3072 19.7 / 19.3 /
+// 20.5, fp32 4096 x 8192 - / 43.5 / 50.3), 32 on the widest rows, and 64 where the pass's tensors together do not fit the last-level cache
+// (bf16 4096 x 20480 - / 65.8 / 62.0; bias-GeLU backward of bf16 8192 x 8192 - / 87 / 80).
+static inline ColPlan col_plan(int64_t rows, int64_t h, int64_t esz, int one, int groups, int tensors, int nt = 256) {
   const int64_t nchunk = h >> 3;
-  ColPlan p{3, 0, 1};
-  // Narrow blocks of all rows, with no partial sums and no second launch (2.4 us): at most four trips of a thread, or enough
-  // blocks to fill the chip (LayerNorm backward of 256 x 20480: 12.8 us, split 15.8).
-  if (rows <= nt / 2 || (nchunk >= 1536 && rows <= 512)) {
-    p.ncb = (int)((nchunk + 7) / 8);
+  ColPlan p{one, 0, 1};
+  if (one) {
+    p.ncb = (int)((nchunk + (1 << one) - 1) >> one);
     return p;
   }
-  for (int lg = 6; lg >= 3; --lg) {  // the widest segment that leaves at most an eighth of the lanes without work
-    const int64_t L = 1 << lg, used = (nchunk + L - 1) / L * L;
-    if (used - nchunk <= nchunk / 8) { p.lg = lg; break; }
+  const bool large = rows * h * esz * tensors > 288000000;
+  for (p.lg = large ? 6 : nchunk > 2560 ? 5 : 4; p.lg > 3; --p.lg) {  // the widest that leaves at most an eighth of the lanes without work
+    const int64_t L = 1 << p.lg, used = (nchunk + L - 1) / L * L;
+    if (used - nchunk <= nchunk / 8) break;
   }
-  const int64_t L = 1 << p.lg;
-  p.ncb = (int)((nchunk + L - 1) / L);
-  const int64_t nseg = nt >> p.lg, most = (rows + nseg - 1) / nseg;
-  // up to four trips of a thread cost less than the launch that adds partial sums
-  p.nsplit = most <= 4 ? 1 : (int)(most * p.ncb <= kColGroups ? most : kColGroups / p.ncb > 1 ? kColGroups / p.ncb : 1);
+  p.ncb = (int)((nchunk + (1 << p.lg) - 1) >> p.lg);
+  const int64_t nseg = nt >> p.lg, most = (rows + nseg - 1) / nseg, want = (large ? 1024 : groups) / p.ncb;  // no more than are resident at once
+  p.nsplit = (int)(want < 1 ? 1 : want < most ? want : most);
   return p;
 }
+// Rows up to which one split pays, given those measured on rows whose last block is full: in a block with idle lanes a trip can take twice as long
+// (bias-dropout backward of 512 x 520 10.2 us in one split, 7.7 in several, of 512 x 1024 6.2, 7.6).
+static inline int64_t one_split_rows(int64_t h, int64_t full) { return (h >> 3) % 8 == 0 ? full : 128; }
 
 // op: In (what a row segment loads), column(col) (per column, before the rows), load(row, col), apply(in, row, col, sums)
 template <int NT, typename Op>
-__device__ __forceinline__ void colsum_block(Op& op, int64_t rows, int64_t h, const ColPlan& pl, int block, float (&acc)[Op::kSums][8]) {
-  const int cb = block % pl.ncb, split = block / pl.ncb;
+__device__ __forceinline__ void colsum_block(Op& op, int64_t rows, int64_t h, const ColPlan& pl, int cb, int split, float (&acc)[Op::kSums][8]) {
   const int seg = threadIdx.x >> pl.lg, nseg = NT >> pl.lg;
   const int64_t chunk = (int64_t)cb << pl.lg | (threadIdx.x & ((1 << pl.lg) - 1));
 #pragma unroll
@@ -114,28 +115,32 @@ __device__ __forceinline__ void colsum_block(Op& op, int64_t rows, int64_t h, co
 }
 // sums over the segments of a workgroup; the column block's sums go to out[s] + column (a split's partial sums or the result)
 template <int NT, int S>
-__device__ __forceinline__ void colsum_store(const float (&acc)[S][8], float* sb, int64_t h, const ColPlan& pl, int block, float* const (&out)[S]) {
-  const int cb = block % pl.ncb, nseg = NT >> pl.lg, width = 8 << pl.lg;
+__device__ __forceinline__ void colsum_store(const float (&acc)[S][8], float* sb, int64_t h, const ColPlan& pl, int cb, float* const (&out)[S]) {
+  const int nseg = NT >> pl.lg, width = 8 << pl.lg;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    __syncthreads();
+    if (s) __syncthreads();
 #pragma unroll
     for (int e = 0; e < 8; ++e) sb[8 * threadIdx.x + e] = acc[s][e];
     __syncthreads();
     for (int c = threadIdx.x; c < width; c += NT) {
-      float t = 0.f;
-      for (int q = 0; q < nseg; ++q) t += sb[q * width + c];
+      float t[4] = {0.f, 0.f, 0.f, 0.f};  // nseg is a multiple of 4
+#pragma unroll 2
+      for (int q = 0; q < nseg; q += 4)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) t[x] += sb[(q + x) * width + c];
       const int64_t cc = (int64_t)cb * width + c;
-      if (cc < h) out[s][cc] = t;
+      if (cc < h) out[s][cc] = (t[0] + t[1]) + (t[2] + t[3]);
     }
   }
 }
-template <typename Op>
+template <typename Op, int LG>
 __global__ __launch_bounds__(256) void colsum_kernel(Op op, int64_t rows, int64_t h, float* __restrict__ out, ColPlan pl) {
+  pl.lg = LG;
   __shared__ __attribute__((aligned(16))) float sb[8 * 256];
   float acc[1][8];
-  colsum_block<256>(op, rows, h, pl, blockIdx.x, acc);
-  float* const dst[1] = {out + (int64_t)(blockIdx.x / pl.ncb) * h};
+  colsum_block<256>(op, rows, h, pl, blockIdx.x, blockIdx.y, acc);
+  float* const dst[1] = {out + (int64_t)blockIdx.y * h};
   colsum_store<256, 1>(acc, sb, h, pl, blockIdx.x, dst);
 }
 
@@ -169,16 +174,18 @@ static hipError_t launch_colsum_finish(const float* part, int nsplit, int64_t nc
   return hipGetLastError();
 }
 template <typename Op>
-static hipError_t launch_colsum(const Op& op, int64_t rows, int64_t h, float* out, float* ws, hipStream_t st) {
-  const ColPlan pl = col_plan(rows, h);
-  hipLaunchKernelGGL((colsum_kernel<Op>), dim3((unsigned)(pl.ncb * pl.nsplit)), dim3(256), 0, st, op, rows, h, pl.nsplit == 1 ? out : ws, pl);
+static hipError_t launch_colsum(const Op& op, int64_t rows, int64_t h, const ColPlan& pl, float* out, float* ws, hipStream_t st) {
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)pl.ncb, (unsigned)pl.nsplit), dim3(256), 0, st, op, rows, h, pl.nsplit == 1 ? out : ws, pl); };
+  switch (pl.lg) {
+    case 3: go(colsum_kernel<Op, 3>); break;
+    case 4: go(colsum_kernel<Op, 4>); break;
+    case 5: go(colsum_kernel<Op, 5>); break;
+    default: go(colsum_kernel<Op, 6>); break;
+  }
   const hipError_t e = hipGetLastError();
   return e != hipSuccess || pl.nsplit == 1 ? e : launch_colsum_finish(ws, pl.nsplit, h, h, out, nullptr, st);
 }
-static inline size_t colsum_workspace_bytes(int64_t rows, int64_t h) {
-  const ColPlan pl = col_plan(rows, h);
-  return pl.nsplit > 1 ? (size_t)pl.nsplit * (size_t)h * sizeof(float) : 0;
-}
+static inline size_t colsum_workspace_bytes(const ColPlan& pl, int64_t h) { return pl.nsplit > 1 ? (size_t)pl.nsplit * (size_t)h * sizeof(float) : 0; }
 
 // block-wide sum of two values; every thread gets the totals.  red must hold 2 * 16 floats.
 __device__ __forceinline__ void block_sum2(float& a, float& b, float* red) {
@@ -251,10 +258,9 @@ __global__ __launch_bounds__(1024) void ln_fwd_kernel(RowsParams P, const T* __r
 //              x and dy are read twice, the second time mostly out of the caches;
 //   many rows: G workgroups that walk through the rows together, each with the dgamma, dbeta sums of its rows in registers:
 //              x and dy are read once, and 2 G rows of fp32 partial sums are written and read back.
-// Bound: HBM and, below about 20 MB a tensor, the two or three memory round trips of a launch.  us before (896 threads a
-// row workgroup, slabs of 64 columns, always two reads) and now: 256 x 20480 15.3 -> 12.8, 512 x 12288 17.5 -> 12.8,
-// 1024 x 6144 18.3 -> 15.5, 2048 x 6144 27.2 -> 22.4, 8192 x 4096 75.6 -> 45.9, 4096 x 20480 188 -> 110 (4.6 TB/s of the
-// three tensors).
+// Bound: HBM and, below about 20 MB a tensor, the two or three memory round trips of a launch.  bf16, us, slabs of 64 columns beside 1024-thread row
+// workgroups (always two reads) and now: 256 x 20480 14.8 -> 10.3, 512 x 4096 9.4 -> 7.8, 512 x 12288 17.2 -> 12.1, 1024 x 6144 17.4 -> 13.3,
+// 2048 x 6144 26.4 -> 22.2, 8192 x 4096 58.1 -> 39.1, 4096 x 20480 190 -> 115 (4.4 TB/s of the three tensors).
 // ---------------------------------------------------------------------------------------------------
 template <typename T, int VPT>
 struct LnRow {  // a thread's share of a row: chunks threadIdx + u * blockDim
@@ -306,13 +312,13 @@ __global__ __launch_bounds__(NT) void ln_bwd_kernel(RowsParams P, const T* __res
                                                    float* __restrict__ dg_out, float* __restrict__ db_out, ColPlan pl) {
   __shared__ __attribute__((aligned(16))) float sb[8 * NT];
   if ((int64_t)blockIdx.x >= P.rows) {
-    const int block = (int)((int64_t)blockIdx.x - P.rows);
+    const int block = (int)((int64_t)blockIdx.x - P.rows), cb = block % pl.ncb, split = block / pl.ncb;
     LnBwdCols<T> op{P.h, dy, x, mean, rstd};
     float acc[2][8];
-    colsum_block<NT>(op, P.rows, P.h, pl, block, acc);
-    const int64_t at = (int64_t)(block / pl.ncb) * 2 * P.h;
+    colsum_block<NT>(op, P.rows, P.h, pl, cb, split, acc);
+    const int64_t at = (int64_t)split * 2 * P.h;
     float* const dst[2] = {dg_out + at, db_out + at};
-    colsum_store<NT, 2>(acc, sb, P.h, pl, block, dst);
+    colsum_store<NT, 2>(acc, sb, P.h, pl, cb, dst);
     return;
   }
   const int64_t r = blockIdx.x;
@@ -558,8 +564,8 @@ __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T*
 // ---------------------------------------------------------------------------------------------------
 // bias-dropout-add backward: dx = M dout/(1-p) with M regenerated from Philox; the residual branch's gradient is
 // dout itself and is not written.  Without dbias this is elementwise (one thread per 8 elements); with dbias a column-summing
-// pass (1024 x 6144: 9.0 + 2.7 us as slabs of 64 columns and a one-thread-a-column finish, 9.8
-// together now; 4096 x 20480: 113 -> 64 us).
+// pass (bf16, us, slabs of 64 columns on one or two workgroups a CU and now: 300 x 6144 8.3 -> 5.0, 1024 x 6144 9.4 -> 8.2, 4096 x 8192 31.6 -> 23.4,
+// 4096 x 20480 112 -> 63).
 // ---------------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void bda_bwd_kernel(RowsParams P, const T* __restrict__ dout, T* __restrict__ dx) {
@@ -736,10 +742,22 @@ static inline int ln_bwd_stream_groups(int64_t rows, int64_t h, bool bf16) {
   const int groups = nchunk <= 128 ? 1024 : nchunk <= 512 ? 512 : 256;
   return nchunk <= (bf16 ? 3584 : 2560) && rows >= (nchunk <= 2560 ? 8 : 16) * groups ? groups : 0;
 }
-static inline int ln_bwd_threads(int64_t h) { return h <= 8192 ? 256 : 512; }  // of a workgroup, where x and dy are read twice
+// x and dy read twice.  Rows wider than 28672: 1024 threads (four chunks a thread; eight of 512 threads: 1024 x 32768 61 / 70 us).
+static inline int ln_bwd_threads(int64_t h) { return h <= 8192 ? 256 : h <= 28672 ? 512 : 1024; }
+// Column sums in one split, us one / split: up to a few hundred rows (bf16 512 x 4096 7.7 / 8.9, fp32 300 x 6144 8.3 / 9.1; but fp32 512 x 3072 10.0 /
+// 8.7, bf16 512 x 6144 11.2 / 9.9), and wide rows at any count, as there are blocks enough for every CU (bf16 1024 x 16384 28.7 / 30.9), in wider
+// segments the wider they are (bf16 300 x 32768 by 8, 32 lanes 25.8 / 19.8); not beyond 85 MB, three of
+// which do not fit the last-level cache (2048 x 32768 141 / 128).
+static inline ColPlan ln_bwd_plan(int64_t rows, int64_t h, bool bf16) {
+  const int64_t nchunk = h >> 3, esz = bf16 ? 2 : 4;
+  int one = 0;
+  if (nchunk > 1024) one = rows * h * esz > 85000000 ? 0 : nchunk > 3584 ? 5 : nchunk > 2048 ? 4 : 3;
+  else if (rows <= one_split_rows(h, bf16 && nchunk <= 512 ? 512 : 384)) one = 3;
+  return col_plan(rows, h, esz, one, bf16 ? 768 : 512, 3, ln_bwd_threads(h));
+}
 
 size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {
-  const int groups = ln_bwd_stream_groups(rows, h, bf16), nsplit = groups ? groups : col_plan(rows, h, ln_bwd_threads(h)).nsplit;
+  const int groups = ln_bwd_stream_groups(rows, h, bf16), nsplit = groups ? groups : ln_bwd_plan(rows, h, bf16).nsplit;
   return nsplit > 1 ? (size_t)nsplit * 2 * (size_t)h * sizeof(float) : 256;
 }
 
@@ -771,7 +789,7 @@ static hipError_t ln_bwd_t(const RowsParams& P, const void* dy, const void* x, c
     return e != hipSuccess ? e : launch_colsum_finish(part, groups, 2 * P.h, P.h, dgamma, dbeta, st);
   }
   const int nt = ln_bwd_threads(P.h);
-  const ColPlan pl = col_plan(P.rows, P.h, nt);
+  const ColPlan pl = ln_bwd_plan(P.rows, P.h, half);
   float* dg_out = pl.nsplit == 1 ? dgamma : part;
   float* db_out = pl.nsplit == 1 ? dbeta : part + P.h;
   auto go = [&](auto kern) {
@@ -786,14 +804,15 @@ static hipError_t ln_bwd_t(const RowsParams& P, const void* dy, const void* x, c
       case 3: go(ln_bwd_kernel<T, 256, 3>); break;
       default: go(ln_bwd_kernel<T, 256, 4>); break;
     }
+  } else if (nt == 1024) {
+    go(ln_bwd_kernel<T, 1024, 4>);
   } else {
     switch (vpt) {
       case 3: go(ln_bwd_kernel<T, 512, 3>); break;
       case 4: go(ln_bwd_kernel<T, 512, 4>); break;
       case 5: go(ln_bwd_kernel<T, 512, 5>); break;
       case 6: go(ln_bwd_kernel<T, 512, 6>); break;
-      case 7: go(ln_bwd_kernel<T, 512, 7>); break;
-      default: go(ln_bwd_kernel<T, 512, 8>); break;
+      default: go(ln_bwd_kernel<T, 512, 7>); break;
     }
   }
   const hipError_t e = hipGetLastError();
@@ -849,8 +868,22 @@ hipError_t launch_bias_dropout_add_ln_fwd(const RowsParams& P, bool bf16, const 
               : bda_ln_t<float>(P, x, bias, resid, gamma, beta, out, y, mean, rstd, st);
 }
 
-size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h) { return colsum_workspace_bytes(rows, h); }
-size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h) { return colsum_workspace_bytes(rows, h); }
+// One split, us one / split: bias-dropout backward up to some hundred rows (bf16 512 x 6144 6.9 / 7.8, 700 x 6144 8.6 / 7.9; fp32 300 x 6144 7.0 / 8.3, 512 x
+// 4096 8.7 / 7.3) and on rows of 48 KB or more, whose blocks fill the chip by themselves (bf16 1024 x 32768 22.0 / 24.5, fp32 1024 x 12288 18.0 / 18.9).
+static ColPlan bda_bwd_plan(int64_t rows, int64_t h, bool bf16) {
+  const int64_t esz = bf16 ? 2 : 4;
+  const bool one = rows <= one_split_rows(h, bf16 ? 512 : 384) || (h * esz >= 49152 && rows * h * esz <= 144000000);
+  return col_plan(rows, h, esz, one ? 3 : 0, bf16 ? 768 : 512, 2);
+}
+// bias-GeLU backward, which does more on a row: up to 256 (300 x 4096 8.0 / 7.7), on wide rows a little further (fp32 512 x 16384 16.6 / 19.1, bf16 300 x 16384
+// 8.0 / 10.1, but bf16 512 x 25600 19.2 / 17.0); in bf16, whose rows are half as long, twice the workgroups or more (bf16 2048 x 10240
+// by 1040, 2080 workgroups 26.0 / 24.0; fp32 8192 x 4096 by 512, 2048 72.5 / 75.1).
+static ColPlan bias_gelu_bwd_plan(int64_t rows, int64_t h, bool bf16) {
+  const int64_t few = h >= 12288 ? (bf16 ? 320 : 640) : 256;
+  return col_plan(rows, h, bf16 ? 2 : 4, rows <= one_split_rows(h, few) ? 3 : 0, bf16 ? 2048 : 512, 3);
+}
+size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) { return colsum_workspace_bytes(bias_gelu_bwd_plan(rows, h, bf16), h); }
+size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) { return colsum_workspace_bytes(bda_bwd_plan(rows, h, bf16), h); }
 
 template <typename T>
 static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
@@ -858,7 +891,7 @@ static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, flo
     hipLaunchKernelGGL((bda_bwd_kernel<T>), dim3((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), dim3(256), 0, st, P, (const T*)dout, (T*)dx);
     return hipGetLastError();
   }
-  return launch_colsum(BdaBwdCols<T>{P, (const T*)dout, (T*)dx}, P.rows, P.h, dbias, (float*)ws, st);
+  return launch_colsum(BdaBwdCols<T>{P, (const T*)dout, (T*)dx}, P.rows, P.h, bda_bwd_plan(P.rows, P.h, sizeof(T) == 2), dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
@@ -886,8 +919,9 @@ static hipError_t bias_gelu_bwd_t(const RowsParams& P, const void* dy, const voi
     else hipLaunchKernelGGL((bias_gelu_bwd_kernel<T, false>), grid, block, 0, st, P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx);
     return hipGetLastError();
   }
-  if (bias) return launch_colsum(GeluBwdCols<T, true>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, dbias, (float*)ws, st);
-  return launch_colsum(GeluBwdCols<T, false>{P, (const T*)dy, (const T*)x, nullptr, (T*)dx, {}}, P.rows, P.h, dbias, (float*)ws, st);
+  const ColPlan pl = bias_gelu_bwd_plan(P.rows, P.h, sizeof(T) == 2);
+  if (bias) return launch_colsum(GeluBwdCols<T, true>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, pl, dbias, (float*)ws, st);
+  return launch_colsum(GeluBwdCols<T, false>{P, (const T*)dy, (const T*)x, nullptr, (T*)dx, {}}, P.rows, P.h, pl, dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_gelu_bwd(const RowsParams& P, bool bf16, const void* dy, const void* x, const void* bias, void* dx, float* dbias, void* ws,

@@ -219,6 +219,10 @@ def test_bias_gelu(rows, h, dtype, with_bias):
     (2048, 4104, "bf16"), (2049, 20480, "bf16"), (2048, 20480, "f32"), (4096, 28672, "bf16"),   # 512 threads: one chunk more than 512, widest rows
     (2047, 4104, "bf16"), (4095, 20488, "bf16"),                                                # one row too few for that
     (128, 520, "bf16"), (129, 520, "bf16"), (512, 12288, "bf16"), (513, 12288, "bf16"), (512, 12280, "bf16"), (700, 32768, "f32"),
+    (256, 1024, "bf16"), (257, 1024, "bf16"), (384, 2048, "f32"), (385, 2048, "f32"), (513, 4096, "bf16"), (385, 4160, "bf16"),  # one split or several: full last blocks
+    (320, 16384, "bf16"), (321, 16384, "bf16"), (641, 12352, "f32"), (600, 24576, "bf16"), (520, 20544, "bf16"),                # ... of wide rows
+    (300, 28680, "bf16"), (1500, 32768, "bf16"), (1000, 32768, "f32"),                                                          # 1024 threads a row; beyond the last-level cache
+    (33, 8, "bf16"), (140, 8, "f32"), (300, 72, "bf16"),                                                                         # a column block of one lane
 ])
 def test_column_sums(rows, h, dtype):
     """The passes that sum columns, on both sides of every line of their dispatch: rows split or not, x and dy of the LayerNorm
