@@ -562,54 +562,53 @@ int attn_mfma_cu_count() {
 
 static int cu_count() { return attn_mfma_cu_count(); }
 
-// Form of the forward by shape; us at s, heads (b * a/t), p = 0 / 0.1, from one sweep of every form.  w64, w128: workgroups of 64
-// and of 128 rows.
-//   128-row workgroups (one a CU), no mask: a round of them costs about 5/3 (d = 160) or 2 (d = 128) rounds of 64-row workgroups
-//     with loader waves, so they pay where that saves rounds: d = 160, s = 2048, 12 heads 60.4 / 60.9 -> 42.2 / 50.3, s = 1000, 24
-//     heads 31.9 / 33.1 -> 24.6 / 28.9, but s = 1736, 24 heads (two rounds against three) 75.9 / 91.2 -> 75.4 / 77.2 without
-//     them; d = 128, s = 2048, 64 heads 187 / 209 -> 157 / 192, s = 1000, 24 heads 23.9 / 28.6 -> 21.6 / 26.0.
-//     Causal, d = 160: more of them than CUs, so that the heaviest does not set the pace (-19 % at s = 4096, -20 % at s = 8192;
-//     +14 % with 256 workgroups).
-//     d = 64 without mask and dropout, 1024 workgroups of 64 rows or more: 2048 x 64 heads 107 -> 89 (loader waves 95).
-//   loader waves: d = 64: against the producer / consumer pairs that ran there before, 1736 x 24 heads, causal 20.0 / 26.3 -> 18.3 / 24.4, 2048 x 64 57.6 /
-//     74.1 -> 52.4 / 69.4, without the mask 107.6 / 138.8 -> 95.3 / 128.7, 512 x 128 18.5 / 22.5 -> 17.3 / 20.7.  d = 96, where three
-//     workgroups without them share a CU: only while a CU gets one (1024 x 8, causal 12.8 / 16.1 -> 10.6 / 13.9), or under the
-//     mask two (2048 x 12 23.9 / 29.7 -> 21.5 / 24.1; without the mask 32.5 / 44.5 -> 44.4 / 46.6).  d = 128, causal: not once
-//     two workgroups a CU are exceeded (1736 x 24 33.3 / 38.7 -> 29.0 / 35.4 without; 2048 x 12 23.7 / 26.2 -> 28.6 / 33.6).  d = 64, causal,
-//     no dropout: not from four workgroups a CU on (2048 x 64 49.6 against 52.4).
-//   persistent workgroups: every one gets two row blocks or more, d >= 128; below that under the mask and with exactly as many
-//     blocks as two a CU (4096 x 8: d = 64 29.8 / 44.9 -> 29.1 / 41.3, d = 96 41.0 / 49.3 -> 39.5 / 47.2; with more blocks than
-//     that 1736 x 24 18.3 / 24.4 -> 22.2 / 31.5).  d >= 128, causal, also from one and a half blocks a workgroup on while a head
-//     has 16 blocks at most, where a workgroup's start is a large part of its time (1000 x 24: d = 128 14.9 / 16.9 -> 14.0 /
-//     16.6, d = 160 18.3 / 19.9 -> 17.3 / 18.4; 512 x 48 11.5 / 12.9 -> 10.8 / 12.0; but 1000 x 20 13.1 / 15.3 -> 13.4 / 15.6 and 2048 x 12
-//     23.8 / 27.1 -> 24.1 / 27.4).
+// Form of the forward by shape, from a sweep of every form over 2276 shapes (d, s = 64 .. 8192, 4 .. 256 heads, mask, dropout): within
+// 1 % of the best form in the geometric mean, within 11 % everywhere.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us
+// or differences at p = 0 / 0.1.
+//   One workgroup a CU or less: loader waves (plain 5 to 31 % slower).  More:
+//   128-row workgroups.  No mask: d = 160 in one round of them, or from nearly two on, where they save rounds (2048 x 12 60.4 / 60.9 ->
+//     42.2 / 50.3, but 1024 x 40 5 / 21 % slower; without dropout from 1.4 rounds, 1000 x 48 53.4 -> 49.9); d = 96 and 128 the same but from
+//     3.5 rounds (d = 96, 512 x 256 66.7 / 76.3 -> 57.0 / 62.7); d = 64 only without dropout in whole pairs of rounds (2048 x 64 95 -> 89).
+//     Causal, d = 160: so many that the heaviest does not set the pace (1024 x 64 -12 / -3 %, 384 x 256 47 -> 43; 1024 x 40 -5 / +2 %).
+//   Persistent workgroups: the longest list of row blocks must not exceed the rounds of single ones (no mask, d = 160, 1024 x 48, lists of
+//     4 against 3 rounds: 68.6, loaders 54.2).  Then d = 160 (384 x 48 11.4 -> 10.3, 512 x 40 12.7 -> 11.5); under the mask d = 96 and 128
+//     up to two workgroups a CU (d = 128, 1000 x 24 14.9 / 16.9 -> 14.0 / 16.6, 2048 x 14 27.5 / 30.1 -> 26.4 / 28.0, but 2048 x 20 +14 /
+//     +7 %), d = 128 a little further where every CU gets as many as the next (768 x 64 with dropout 24.8 -> 23.6).  The more blocks a head
+//     has, the more of them a CU it takes (d = 128, 2048 x 12, 1.5 a CU: +0 / +3 %); four or less a head: nothing (d = 96, 256 x 128 8.4 against
+//     9.1).  d = 64: only long sequences with dropout (4096 x 8 -1 / -8 %; 512 x 64 +12 / +8 %).
+//   Loader waves or not: d = 160 with them (plain +1 to +12 / +4 to +18 %).  d = 64 too, except under the mask with more than four
+//     workgroups a CU (plain 0 to -14 %), or two without dropout and with up to 16 blocks a head.  d = 96, 128, where several workgroups
+//     without them share a CU: only under the mask, up to two a CU, more than four blocks a head (d = 128, no mask, 384 x 192 without them
+//     39.8 -> 30.6; causal, 200 x 128 10.2 -> 8.7).
 enum class FwdForm { Plain, Loaders, Persistent, Rows128 };
 template <int D>
 static FwdForm fwd_form(const AttnParams& P) {
   const int cus = cu_count(), N = P.b * P.A, nrb = (P.s + 63) / 64;
   const int64_t w64 = (int64_t)nrb * N, w128 = (int64_t)((P.s + 127) / 128) * N;
   const int64_t rounds64 = (w64 + cus - 1) / cus, rounds128 = (w128 + cus - 1) / cus;
+  const bool causal = P.causal != 0, drop = P.thresh != 0;
   const int f128 = P.s < 128 ? 0 : g_force_fwd128.load();
-  const bool bare = P.thresh == 0 && w64 >= 4 * (int64_t)cus;
   bool use128 = f128 == 1;
-  if (f128 < 0) {
-    if (P.causal) use128 = D == 160 && w128 > cus;
-    else use128 = D == 160 ? 5 * rounds128 <= 3 * rounds64 : D == 128 ? 2 * rounds128 <= rounds64 : D == 64 && bare;
+  if (f128 < 0 && w64 > cus) {
+    if (causal) use128 = D == 160 && (w128 > 2 * cus || (nrb >= 8 && 4 * w128 >= (drop ? 8 : 5) * cus));
+    else if (D == 160) use128 = w128 <= cus || 10 * w128 >= (drop ? 18 : 14) * cus;
+    else if (D >= 96) use128 = nrb > 4 && (w128 <= cus || 2 * w128 >= 7 * cus);
+    else use128 = !drop && w64 >= 4 * cus && 2 * rounds128 <= rounds64;
   }
   if (use128) return FwdForm::Rows128;
-  int lw = g_force_fwdlw.load();
-  const bool forced = lw >= 0;
-  if (!forced) {
-    if (D == 64) lw = !(bare && P.causal);
-    else if (D == 96) lw = w64 <= (P.causal ? 2 : 1) * (int64_t)cus;
-    else lw = !(D == 128 && P.causal && w64 > 2 * (int64_t)cus);
+  if (const int lw = g_force_fwdlw.load(); lw >= 0) return lw == 0 ? FwdForm::Plain : lw == 3 && N <= cus ? FwdForm::Persistent : FwdForm::Loaders;
+  if (w64 <= cus) return FwdForm::Loaders;
+  const int R = N <= cus ? std::min(nrb, cus / N) : 0;  // a persistent grid: R row blocks of every head at a time
+  if (R > 0 && (nrb + R - 1) / R <= rounds64) {
+    const int64_t from = (nrb <= 8 ? 110 : nrb <= 16 ? 140 : 170) * (int64_t)cus, full = 100 * w64;  // workgroups a CU in hundredths
+    if (D == 160 && (!causal || full >= from)) return FwdForm::Persistent;
+    if (D == 128 && causal && nrb > 4 && full >= from && w64 <= ((drop || nrb <= 8) && cus % N == 0 ? 3 : 2) * cus) return FwdForm::Persistent;
+    if (D == 96 && causal && nrb > 4 && full >= from + (nrb > 16 ? 20 : 0) * (int64_t)cus && w64 <= 2 * cus) return FwdForm::Persistent;
+    if (D == 64 && causal && drop && nrb >= 32 && full >= 190 * (int64_t)cus && w64 <= 2 * cus) return FwdForm::Persistent;
   }
-  if (lw == 0) return FwdForm::Plain;
-  // a grid of (row blocks at a time) x (heads) within the CU count
-  const bool two = N <= cus && nrb >= 2 * std::min(nrb, cus / N);
-  const bool small = D >= 128 && P.causal && N <= cus && nrb <= 16 && 2 * w64 >= 3 * (int64_t)cus;
-  if (forced ? lw == 3 && N <= cus : small || (two && (D >= 128 || (P.causal && w64 <= 2 * (int64_t)cus)))) return FwdForm::Persistent;
-  return FwdForm::Loaders;
+  if (D == 160) return FwdForm::Loaders;
+  if (D == 64) return causal && (w64 > 4 * cus || (!drop && w64 > 2 * cus && nrb <= 16)) ? FwdForm::Plain : FwdForm::Loaders;
+  return causal && nrb > 4 && w64 <= 2 * cus ? FwdForm::Loaders : FwdForm::Plain;
 }
 
 template <int D>

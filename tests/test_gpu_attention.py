@@ -216,7 +216,8 @@ def test_column_pass_persistent_workgroups(d, s, b, A, causal, p, two_pass):
     _check_bf16_heads("cols-pers", sh, q, k, v, do, got, [0, 1, N // 2, N - 1])
 
 
-@pytest.mark.parametrize("d,s,b,A,causal,p", [(160, 328, 3, 44, 1, 0.1), (128, 776, 1, 44, 1, 0.1), (160, 264, 2, 66, 0, 0.1), (128, 136, 5, 60, 1, 0.1), (160, 392, 1, 132, 1, 0.0)])
+@pytest.mark.parametrize("d,s,b,A,causal,p", [(160, 328, 3, 44, 1, 0.1), (128, 776, 1, 44, 1, 0.1), (160, 264, 2, 66, 0, 0.1), (128, 136, 5, 60, 1, 0.1), (160, 392, 1, 132, 1, 0.0),
+                                              (64, 776, 1, 44, 1, 0.1), (64, 264, 2, 66, 0, 0.0), (64, 392, 1, 132, 1, 0.0), (96, 328, 3, 44, 1, 0.1), (96, 776, 1, 44, 1, 0.0)])
 def test_forward_persistent_workgroups(d, s, b, A, causal, p):
     """The forward with persistent workgroups (forced), at head counts where a workgroup really gets several row blocks: 132
     heads (one workgroup per head takes all its row blocks in turn) and 44 heads (five workgroups per head: ranks wq, 9 - wq,
@@ -236,12 +237,15 @@ def test_forward_persistent_workgroups(d, s, b, A, causal, p):
 
 @pytest.mark.parametrize("d,s,b,A,p,causal", [(64, 136, 4, 86, 0.0, 1), (64, 264, 2, 103, 0.0, 0), (96, 72, 2, 64, 0.1, 1), (96, 328, 1, 85, 0.1, 1), (128, 136, 4, 43, 0.1, 1),
                                               (128, 200, 1, 100, 0.0, 0), (160, 200, 1, 100, 0.1, 0), (160, 264, 2, 66, 0.1, 0),
-                                              (128, 328, 1, 65, 0.1, 1), (160, 456, 2, 25, 0.0, 1)])
+                                              (128, 328, 1, 65, 0.1, 1), (160, 456, 2, 25, 0.0, 1), (64, 200, 2, 128, 0.0, 0), (64, 2040, 1, 16, 0.1, 1), (96, 328, 2, 150, 0.1, 0),
+                                              (96, 200, 1, 128, 0.1, 1), (96, 328, 1, 80, 0.1, 0), (128, 328, 1, 128, 0.0, 1), (128, 200, 1, 128, 0.1, 1), (128, 328, 1, 85, 0.1, 0),
+                                              (160, 136, 1, 100, 0.1, 1), (160, 136, 2, 130, 0.1, 1), (160, 200, 1, 192, 0.1, 0), (160, 200, 1, 192, 0.0, 0), (160, 264, 1, 100, 0.0, 0)])
 def test_forward_form_by_shape(d, s, b, A, p, causal):
-    """The forward as the library chooses it, on both sides of the lines between its forms on 256 compute units: without loader
-    waves (64: more than four workgroups a CU without dropout; 128: more than two under the mask), 128-row workgroups (64 bare;
-    128, 160 where they save a round), loader waves, persistent workgroups (96; 128, 160 with some
-    workgroups at two row blocks and the rest at one); every sequence ends inside a tile."""
+    """The forward as the library chooses it, on both sides of the lines between its forms on 256 compute units: plain (more than one
+    to four workgroups a CU, by head dimension and mask), 128-row workgroups (64 without dropout in whole rounds; 96, 128, 160 in one
+    round or several; 160 under the mask in more than two), loader waves, persistent workgroups (64: a long sequence with two row blocks a
+    workgroup; 96, 128, 160 with lists of two or three, or some at two and the rest at one; not where the longest list exceeds the
+    rounds of single blocks); every sequence ends inside a tile."""
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=s, b=b, a=A, h=A * d, p=p, seed=80, offset=(1 << 32) - 999, causal=causal)
     q, k, v, do = attn_inputs(s, b, A, d, "bf16", seed=43)

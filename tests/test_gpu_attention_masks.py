@@ -115,8 +115,9 @@ def test_fused_kernel_masks_kernel_variants():
             _compare(sh, "dq", two_pass=True)
         # the forward with persistent workgroups, 132 heads: every workgroup takes the three row blocks of its head in turn
         sar.sar_test_force_variants(0, 3, -1, -1)
-        print("masks persistent forward", flush=True)
-        _compare(oracle.AttnShape(s=328, b=3, a=44, h=44 * 160, p=0.25, seed=99, offset=(1 << 32) - 70000), "fwd")
+        for d in (64, 96, 128, 160):
+            print(f"masks persistent forward d={d}", flush=True)
+            _compare(oracle.AttnShape(s=328, b=3, a=44, h=44 * d, p=0.25, seed=99, offset=(1 << 32) - 70000), "fwd")
         # the column pass with persistent workgroups, 132 heads: every workgroup takes the five key blocks of its head in turn
         sar.sar_test_force_variants(-1, -1, -1, 3)
         print("masks persistent column pass", flush=True)
