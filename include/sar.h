@@ -265,14 +265,15 @@ sar_status bias_gelu_bwd(const sar_rows_desc* desc, const void* dy, const void* 
  * Test and measurement hook, not part of the method: forces kernel variants that the library otherwise picks by shape
  * (every variant computes the same result).  Each argument: -1 = the library's choice, 0 = off, 1 = on.
  *   fwd_128_rows      forward with 128 instead of 64 query rows per workgroup (needs s >= 128)
- *   fwd_loader_waves  forward (64-row workgroups) with four extra waves that only fetch K / V tiles (1; 2 means the same), or
- *                     3: as 1 with persistent workgroups, each working through a list of row blocks (used only when
- *                     b x heads does not exceed the number of compute units; otherwise 3 behaves as 1)
- *   dq_loader_waves   the same for the row pass of the recompute-twice backward
- *   dkdv_pipelined    form of the column pass: 0 plain (head dimension 64 and 96 only, otherwise it behaves as 2; 1 behaves as
- *                     0); 2 producer / consumer (two waves per SIMD: one computes scores, softmax, mask and dS, the other
- *                     accumulates dK, dV), one key block per workgroup; 3 the same with persistent workgroups that each take
- *                     several key blocks (only when b x heads does not exceed the number of compute units; otherwise as 2)
+ *   fwd_loader_waves  forward (64-row workgroups) with four extra waves that only fetch K / V tiles (1), or 3: as 1 with
+ *                     persistent workgroups, each working through a list of row blocks (used only when b x heads does not
+ *                     exceed the number of compute units; otherwise 3 behaves as 1).  2 is a form that no longer exists: as 1
+ *   dq_loader_waves   the same (0, 1) for the row pass of the recompute-twice backward
+ *   dkdv_pipelined    form of the column pass: 0 plain (head dimension 64, and 96 without dropout or in the recompute-twice
+ *                     backward; otherwise as 2); 2 producer / consumer (two waves per SIMD: one computes scores, softmax, mask and
+ *                     dS, the other accumulates dK, dV), one key block per workgroup; 3 the same with persistent workgroups that
+ *                     each take several key blocks (only when b x heads does not exceed the number of compute units; otherwise
+ *                     as 2).  1 is a form that no longer exists: as 0
  * Process-wide; not meant to be changed while another thread launches.
  */
 void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_loader_waves, int dkdv_pipelined);

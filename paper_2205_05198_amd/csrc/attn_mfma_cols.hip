@@ -1,12 +1,13 @@
 // bf16 attention core, backward column pass (dK, dV): which of its forms runs.
 #include "sar_internal.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace sar {
 
 // form of the column pass: -1 = the library's choice; 0 plain (d = 64, 96), 2 producer / consumer waves, 3 the same with
-// persistent workgroups (a forced form that does not exist falls back: 0 at d = 128, 160 to 2; 1 to 0; 3 to 2)
+// persistent workgroups (a forced form that does not exist falls back: 0 to 2 at d = 128, 160 and, with dropout and the tiles, at d = 96; 1 to 0; 3 to 2)
 static std::atomic<int> g_force_form{-1};
 void attn_mfma_force_dkdv_pipelined(int force) { g_force_form = force; }
 
@@ -15,21 +16,32 @@ hipError_t launch_attn_bwd_dkdv_mfma_small(const AttnParams& P, const void* q, c
 hipError_t launch_attn_bwd_dkdv_mfma_split(const AttnParams& P, const void* q, const void* k, const void* v, const float* lse, const void* dO,
                                            const float* delta, void* dk, void* dv, uint16_t* ds_ws, int pers, hipStream_t st);  // attn_mfma_cols_split.hip
 
-// the producer / consumer form, rather than the plain one?
+// The producer / consumer form, rather than the plain one?  From a sweep of both over 1140 shapes with and without the tiles (s = 64 .. 8192,
+// 4 .. 256 heads); s x heads, us, plain / this, p = 0.1 under the mask unless said otherwise; blocks: workgroups of 64 keys.
+//   d = 128, 160 have no plain form (s = 1000, 24 heads, whole backward: d = 128 54.6 / 40.2, d = 160 63.5 / 45.0).
+//   Up to one block a CU always this one (2048 x 12 39.7 / 26.6).  Above, two plain workgroups share a CU and start sooner:
+//   more than four blocks a CU: plain unless persistent workgroups come out even on full tiles (d = 64 512 x 192 36.0 / 40.7, but 384 x 256
+//     32.5 / 30.7; 1000 x 128, no mask, 138 / 147; d = 96 with the tiles without dropout 512 x 192 46.7 / 54.4, with it 58.8 / 55.8; d = 96 without
+//     the tiles not on short heads, 512 x 256 56.4 / 61.8);
+//   with the tiles to store also without mask and dropout on sequences that end inside a tile (d = 64 1000 x 24 29.0 / 30.1);
+//   without them also heads of four blocks or less from one and a half a CU on (200 x 192 13.6 / 15.4; six blocks: 384 x 96 12.9 / 14.6), and without
+//     dropout: no mask and more than one a CU (d = 96 1000 x 20 28.4 / 34.1), under the mask two (d = 64 1000 x 40 20.2 / 22.6);
+//     with dropout only d = 96, no mask, up to one and a half a CU (1000 x 20 33.2 / 35.3).
 static bool dkdv_split(const AttnParams& P, const uint16_t* ds_ws) {
   const int force = g_force_form.load();
-  // measured (once-form, us): 530B shard 78.6 / 80.2 / 69.6, 175B 70.4 / 60.5 / 48.1, 1T 98.3 / - / 90.0 for the plain, a software-
-  // pipelined one-wave form and this one;
-  // s = 1000, 24 heads, whole backward, plain / this: d = 128 54.6 / 40.2, d = 160 63.5 / 45.0 (without the tiles 54.0 / 45.2, 59.8 / 50.9)
-  if (P.d >= 128) return true;
+  const bool drop = P.thresh != 0, causal = P.causal != 0, ragged = P.s % 64 != 0;
+  if (P.d >= 128 || (P.d == 96 && ds_ws && drop)) return true;
   if (force >= 0) return force >= 2;
-  if (ds_ws && P.s % 64 == 0) return true;
-  // Without dropout, or without the tiles to store, two plain workgroups on a CU are as good once the launch keeps both busy.
-  // Whole backward at d = 64, plain / this, us: s = 2048, 12 heads, causal 58.5 / 47.5; no mask, s = 1000, 24 heads (384
-  // workgroups) 42.4 / 44.2; s = 2048, 64 heads 301 / 302 and (p = 0.1, persistent) 376 / 366; s = 1000, 24 heads, causal,
-  // p = 0.1, with tiles 37.9 / 30.5.  d = 96: 71.0 / 63.0, 52.1 / 55.6, 397 / 414, 481 / 474, 48.1 / 35.9.
-  const int64_t blocks = (int64_t)((P.s + 63) / 64) * P.b * P.A;
-  return P.thresh != 0 || blocks <= (P.causal ? 2 : 1) * attn_mfma_cu_count();
+  const int64_t nb = (P.s + 63) / 64, N = (int64_t)P.b * P.A, blocks = nb * N, cus = attn_mfma_cu_count();
+  const int64_t R = N <= cus ? std::min(nb, cus / N) : 0;  // key blocks of a head at a time, persistent
+  const bool even = R > 0 && (nb + R - 1) / R <= (blocks + cus - 1) / cus;
+  if (ds_ws && nb <= 4) return !(ragged && !drop && 2 * blocks > 5 * cus);
+  if (nb <= 4) return 2 * blocks < 3 * cus;
+  if (blocks > 4 * cus && (!even || ragged || (P.d == 96 && !ds_ws && nb <= 8))) return false;
+  if (ds_ws) return !(ragged && !drop && !causal && blocks > cus);
+  if (nb <= 6 && blocks > 2 * cus && 2 * blocks <= 5 * cus) return false;
+  if (drop) return !(P.d == 96 && ragged && !causal && blocks > cus && 2 * blocks <= 3 * cus);
+  return causal ? blocks <= 2 * cus || (P.d == 96 && !ragged) : blocks <= cus || (P.d == 64 && !ragged);
 }
 
 // persistent workgroups in the producer / consumer form: -1 the launcher decides by shape, 0 / 1 forced

@@ -257,8 +257,9 @@ static hipError_t bwd_dkdv_d(const AttnParams& P, const void* q, const void* k, 
                        (const uint16_t*)dO, delta, (uint16_t*)dk, (uint16_t*)dv, ds_ws);
   };
   if (ds_ws) {
-    if (P.thresh != 0) go(attn_bwd_dkdv_mfma_kernel<D, true, true>);
-    else go(attn_bwd_dkdv_mfma_kernel<D, false, true>);
+    if (P.thresh == 0) go(attn_bwd_dkdv_mfma_kernel<D, false, true>);
+    else if constexpr (D == 64) go(attn_bwd_dkdv_mfma_kernel<D, true, true>);  // d = 96 with dropout: the producer / consumer form at every shape
+    else return hipErrorInvalidValue;
   } else {
     if (P.thresh != 0) go(attn_bwd_dkdv_mfma_kernel<D, true, false>);
     else go(attn_bwd_dkdv_mfma_kernel<D, false, false>);

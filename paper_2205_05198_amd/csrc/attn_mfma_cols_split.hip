@@ -12,11 +12,20 @@ static hipError_t bwd_dkdv_split_d(const AttnParams& P, const void* q, const voi
                                    void* dk, void* dv, uint16_t* ds_ws, int pers, hipStream_t st) {
   const int N = P.b * P.A, nb = (P.s + 63) / 64;
   // Persistent workgroups (each takes several key blocks of its head, a heavy one then a light one, and overlaps a block's
-  // start with the end of the one before): needs (key blocks at a time) x (heads) workgroups within the CU count; chosen
-  // when every workgroup then gets at least two key blocks.
+  // start with the end of the one before): R key blocks of every head at a time, R x heads within the CU count.  Chosen where the longest
+  // list does not exceed the rounds of single blocks (us, single / persistent: d = 160, 1024 x 48 heads, no mask, lists of 4 against 3 rounds
+  // 83.8 / 94.8; 384 x 128, 3 against 3, 37.2 / 31.3).  Under the mask a list's blocks are not all heavy: every workgroup gets two or more
+  // (2048 x 12, some with one, 42.0 / 42.4), and a list may be one longer (1000 x 48 55.1 / 52.0), two at d = 128 and 160 (whose single blocks have
+  // a CU to themselves for longer); without it at d = 128, 160 one longer on heads of four blocks or less (256 x 192 35.3 / 30.6).
   const int cus = attn_mfma_cu_count();
   const int R = N <= cus ? std::min(nb, cus / N) : 0;
-  const bool use_pers = R > 0 && (pers == 1 || (pers < 0 && nb >= 2 * R));
+  const int64_t rounds = ((int64_t)nb * N + cus - 1) / cus;
+  bool use_pers = R > 0 && pers == 1;
+  if (R > 0 && pers < 0 && rounds > 1) {
+    const int64_t list = (nb + R - 1) / R;
+    if (P.causal) use_pers = nb >= 2 * R && list <= rounds + (D >= 128 ? 2 : 10 * R * N > 9 * cus ? 1 : 0);
+    else use_pers = list <= rounds + (D >= 128 && nb <= 4 ? 1 : 0);
+  }
   const unsigned grid = use_pers ? (unsigned)(R * N) : (unsigned)(nb * N);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, lse,

@@ -181,12 +181,12 @@ def test_forward_with_128_row_workgroups(d, s, causal):
     _check_bf16_heads("fwd128", sh, q, k, v, do, got, range(2))
 
 
-@pytest.mark.parametrize("lw", [0, 1, 2])
+@pytest.mark.parametrize("lw", [0, 1])
 @pytest.mark.parametrize("d,s,causal", [(64, 328, 1), (96, 200, 1), (160, 328, 1), (160, 200, 0), (128, 136, 1), (160, 40, 1)])
 def test_forward_with_and_without_loader_waves(d, s, causal, lw):
-    """The 64-row forward kernel and the dQ pass with (1: 8 waves) and without (0: 4 waves) their tile-fetching waves, and
-    the forward as producer / consumer wave pairs (2), each forced whatever the library would pick for the head dimension,
-    on ragged shapes (the last tile is fetched with clamped rows; s = 40: a single tile)."""
+    """The 64-row forward kernel and the dQ pass with (1: 8 waves) and without (0: 4 waves) their tile-fetching waves, forced
+    whatever the library would pick for the head dimension, on ragged shapes (the last tile is fetched with clamped rows; s = 40:
+    a single tile)."""
     import paper_2205_05198_amd as sar
     from gpu_util import run_attn
     sar.sar_test_force_variants(0, lw, lw)
@@ -294,22 +294,42 @@ def test_random_shapes_and_kernel_variants():
         _check_bf16_heads(f"sweep{case}", sh, q, k, v, do, got, range(b * A))
 
 
-@pytest.mark.parametrize("pipe", [0, 1, 2, 3])
-@pytest.mark.parametrize("two_pass", [False, True])
-@pytest.mark.parametrize("d,s,b,A,p,causal", [(160, 320, 1, 2, 0.1, 1), (128, 256, 2, 1, 0.25, 1), (160, 192, 1, 2, 0.1, 0), (128, 64, 1, 2, 0.0, 1), (160, 128, 1, 1, 0.0, 0),
-                                              (64, 320, 2, 1, 0.1, 1), (96, 192, 1, 2, 0.25, 0), (64, 64, 1, 1, 0.0, 1)])
-def test_column_pass_pipelined_and_plain(d, s, b, A, p, causal, two_pass, pipe):
-    """The column pass in its plain form (0), its software-pipelined form (1: three query-tile stages, K operands in
-    registers) and its producer / consumer form (2: two waves per SIMD), each forced, on sequences of one to five full
-    tiles: with and without the mask, with and without dropout, in both forms of the backward."""
+_COLUMN_SHAPES = [(160, 320, 1, 2, 0.1, 1), (128, 256, 2, 1, 0.25, 1), (160, 192, 1, 2, 0.1, 0), (128, 64, 1, 2, 0.0, 1), (160, 128, 1, 1, 0.0, 0),
+                  (64, 320, 2, 1, 0.1, 1), (96, 192, 1, 2, 0.25, 0), (64, 64, 1, 1, 0.0, 1), (96, 320, 1, 2, 0.0, 1), (64, 200, 1, 2, 0.1, 0)]
+
+
+@pytest.mark.parametrize("d,s,b,A,p,causal,two_pass,form", [
+    (*shape, two_pass, form) for shape in _COLUMN_SHAPES for two_pass in (False, True) for form in (0, 2, 3)
+    if form or shape[0] == 64 or (shape[0] == 96 and (two_pass or shape[4] == 0.0))])   # the others have no plain form
+def test_column_pass_forms(d, s, b, A, p, causal, two_pass, form):
+    """The column pass in its plain form (0: head dimensions 64 and 96) and its producer / consumer form with one key block a workgroup
+    (2) or persistent workgroups (3), each forced, on one to five tiles: with and without the mask, with and without dropout, in
+    both forms of the backward."""
     import paper_2205_05198_amd as sar
     from gpu_util import run_attn
-    sar.sar_test_force_variants(-1, -1, -1, pipe)
+    sar.sar_test_force_variants(-1, -1, -1, form)
     sh = oracle.AttnShape(s=s, b=b, a=A * 2, h=A * 2 * d, t=2, rank=1, p=p, seed=77, offset=(1 << 32) - 1000, causal=causal)
     q, k, v, do = attn_inputs(s, b, A, d, "bf16", seed=29)
-    print(f"column pass pipelined={pipe} d={d} s={s} causal={causal} p={p} two_pass={two_pass}", flush=True)
+    print(f"column pass form={form} d={d} s={s} causal={causal} p={p} two_pass={two_pass}", flush=True)
     got = run_attn(sh, "bf16", q, k, v, do, two_pass=two_pass)
-    _check_bf16_heads(f"cols-pipe{pipe}", sh, q, k, v, do, got, range(b * A))
+    _check_bf16_heads(f"cols-form{form}", sh, q, k, v, do, got, range(b * A))
+
+
+@pytest.mark.parametrize("two_pass", [False, True])
+@pytest.mark.parametrize("d,s,A,p,causal", [(64, 128, 192, 0.1, 1), (64, 384, 96, 0.1, 1), (64, 328, 256, 0.1, 1), (96, 320, 256, 0.1, 1), (96, 320, 256, 0.0, 0), (64, 328, 64, 0.0, 0),
+                                            (96, 328, 100, 0.0, 1), (96, 320, 120, 0.0, 1), (64, 200, 192, 0.0, 0), (160, 320, 100, 0.1, 0), (128, 192, 100, 0.1, 0),
+                                            (160, 328, 85, 0.1, 1), (64, 1000, 48, 0.1, 1), (96, 200, 66, 0.1, 0), (96, 328, 56, 0.1, 0)])
+def test_column_pass_form_by_shape(d, s, A, p, causal, two_pass):
+    """The column pass as the library chooses it, on both sides of the lines between its forms on 256 compute units: plain with dropout and
+    without (64, 96: more than four workgroups a CU, short heads, no mask), producer / consumer with one key block a workgroup (96 with
+    dropout and the tiles; 160 with lists of three against two rounds of single blocks) and persistent (128, 160; 64 with lists one
+    longer than the rounds under the mask; some workgroups with one block and the rest with two)."""
+    from gpu_util import run_attn
+    sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=p, seed=81, offset=(1 << 32) - 4321, causal=causal)
+    q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=47)
+    print(f"column pass by shape d={d} s={s} A={A} causal={causal} p={p} two_pass={two_pass}", flush=True)
+    got = run_attn(sh, "bf16", q, k, v, do, two_pass=two_pass)
+    _check_bf16_heads("cols-shape", sh, q, k, v, do, got, [0, 1, A // 2, A - 1])
 
 
 @pytest.mark.parametrize("pers", [2, 3])

@@ -104,11 +104,11 @@ def test_fused_kernel_masks_small(d, s, causal):
 
 
 def test_fused_kernel_masks_kernel_variants():
-    """The forward's other variants (128-row workgroups; without loader waves; producer / consumer pairs; persistent workgroups)
-    and the forms of the column pass draw the same mask."""
+    """The forward's other variants (128-row workgroups; without loader waves; with them; persistent workgroups) and the forms of the
+    column pass draw the same mask."""
     sh = oracle.AttnShape(s=328, b=1, a=4, h=4 * 160, t=2, rank=1, p=0.25, seed=99, offset=12345)
     try:
-        for variant in ((1, -1, -1, -1), (0, 0, 0, -1), (0, 1, 1, -1), (0, 2, -1, -1)):
+        for variant in ((1, -1, -1, -1), (0, 0, 0, -1), (0, 1, 1, -1)):
             sar.sar_test_force_variants(*variant)
             print(f"masks variants={variant}", flush=True)
             _compare(sh, "fwd")
@@ -125,14 +125,15 @@ def test_fused_kernel_masks_kernel_variants():
         for two_pass in (False, True):
             _compare(shp, "dv", two_pass)
         _compare(shp, "dq", False)
-        # the column pass in its three forms at a length of full tiles (s % 64 == 0), every head dimension (a form that does not
-        # exist at a head dimension falls back to the plain one)
+        # the column pass in its forms at a length of full tiles (s % 64 == 0), every head dimension; plain (0): 64, and 96 without the tiles
         for d in (64, 96, 128, 160):
             sh2 = oracle.AttnShape(s=320, b=1, a=4, h=4 * d, t=2, rank=1, p=0.25, seed=99, offset=(1 << 32) - 4000)
-            for pipe in (0, 1, 2, 3):
-                sar.sar_test_force_variants(-1, -1, -1, pipe)
-                print(f"masks column pass form={pipe} d={d}", flush=True)
+            for form in (0, 2, 3):
+                sar.sar_test_force_variants(-1, -1, -1, form)
                 for two_pass in (False, True):
+                    if form == 0 and (d >= 128 or (d == 96 and not two_pass)):
+                        continue
+                    print(f"masks column pass form={form} d={d}", flush=True)
                     _compare(sh2, "dv", two_pass)
                     _compare(sh2, "dq", two_pass)
     finally:
@@ -159,9 +160,9 @@ def test_fused_kernel_masks_530B_shard():
     _compare(sh, "dq", two_pass=True)
 
 
-def test_fused_kernel_masks_175B_shard_pipelined_column_pass():
-    """The 175B shard (s = 2048, 12 heads of 128), where the library picks the software-pipelined column pass: its mask and the
-    mask inside the dS tiles it stores, every head, low counter word overflowing inside head 5."""
+def test_fused_kernel_masks_175B_shard():
+    """The 175B shard (s = 2048, 12 heads of 128): the mask of the column pass and the mask inside the dS tiles it stores, every head,
+    low counter word overflowing inside head 5."""
     s, a, t, rank, d = 2048, 96, 8, 6, 128
     A = a // t
     first = (rank * A) * s * s // 8
