@@ -27,8 +27,9 @@
  *     Site 0 (softmax dropout): e = ((beta*a + rank*A + n)*s + i)*s + j.  Site 1 (bias-dropout-add):
  *     e = (row_offset + r)*h + c.  A shard therefore reproduces its slice of the unsharded mask.
  *   - Supported shapes: d in {64, 96, 128, 160} for bf16 (any multiple of 4 up to 256 for f32);
- *     s % 8 == 0; a % t == 0; h % a == 0; rows-kernels need h % 8 == 0 and h <= 32768.  Base pointers and
- *     row strides must be 16-byte aligned.  Anything else returns SAR_ERR_UNSUPPORTED / SAR_ERR_ALIGN.
+ *     s % 8 == 0 and s <= 32768 (f32, bf16 of other head dimensions, scale <= 0: 4864); a % t == 0; h % a == 0;
+ *     rows-kernels need h % 8 == 0 and h <= 32768.  Base pointers and row strides must be 16-byte aligned.
+ *     Anything else returns SAR_ERR_UNSUPPORTED / SAR_ERR_ALIGN.
  */
 #ifndef SAR_H_
 #define SAR_H_
@@ -201,7 +202,9 @@ typedef struct {
 sar_status ln_fwd(const sar_rows_desc* desc, const void* x, const void* gamma, const void* beta,
                   void* y, float* mean, float* rstd, void* stream);
 
-/* Bytes of scratch ln_bwd needs (per-workgroup partial sums of dgamma / dbeta). */
+/* Bytes of scratch ln_bwd needs: partial sums of dgamma and dbeta, 8 h bytes for each workgroup or row split that keeps some, 256
+ * where there are none.  Many rows: 1024 (h <= 1024), 512 (h <= 4096) or 256 of them, e.g. 12.6 MB at 2048 x 6144, 33.6 MB at
+ * 4096 x 16384, 42 MB at 4096 x 20480 in bf16; a few hundred rows or wide ones: none. */
 size_t ln_bwd_workspace(const sar_rows_desc* desc);
 
 /*

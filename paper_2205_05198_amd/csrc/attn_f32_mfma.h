@@ -291,7 +291,7 @@ __device__ __forceinline__ bool kept_pair(const AttnParams& P, int beta, int n, 
                             0u, P.key0, P.key1, P.thresh);
 }
 
-// Work of workgroup blockIdx: heaviest first, every other round of 256 (one workgroup a CU) the other way round, so that a CU that
+// Work of workgroup blockIdx: heaviest first, every other round of 256 (one workgroup for each CU of the chip) the other way round, so that a CU that
 // gets one of each round gets about the same work as the next (s = 1024, 24 heads, 768 workgroups: 196 -> 175 us for the whole
 // forward and backward).
 __device__ __forceinline__ int work_index() {
@@ -299,7 +299,9 @@ __device__ __forceinline__ int work_index() {
   return (b << 8) + ((b & 1) ? last - c : c);
 }
 
-// waves that share a SIMD: what the accumulators and the prefetched operands leave room for
+// Waves that share a SIMD: what the accumulators and the prefetched operands leave room for.  The column pass at M = 32, DT = 4 (head
+// dimensions 100 to 128) spills 10 to 23 registers with two waves and none with one, and is the faster with two (whole backward,
+// s = 1024, 24 heads of 128, causal: 257 us against 305; bf16, 104: 258 against 326).
 constexpr int waves_rows(int M, int DT) { return M == 16 ? (DT <= 2 ? 4 : DT <= 4 ? 3 : 2) : DT <= 2 ? 3 : 2; }
 constexpr int waves_cols(int M, int DT) { return M == 16 ? (DT <= 2 ? 3 : 2) : DT <= 4 ? 2 : 1; }
 
@@ -781,7 +783,7 @@ __global__ __launch_bounds__(64 * NWF) void attn_bwd_cols_few_kernel(AttnParams 
 // causal triangle better (us, forward and backward, M = 32 / 16: s = 128, 2 heads of 64 25.3 / 18.0; s = 1024, 8 heads of 128
 // 189 / 136; from there on equal, 512 x 64 heads 134 / 136, or slower for twice the operand reads, 1024 x 24 heads 175 / 186), and
 // where half of a block of 32 rows would be padding.
-inline bool narrow(const AttnParams& P) { return P.s <= 16 || (int64_t)((P.s + 31) / 32) * P.b * P.A < 512; }
+inline bool narrow(const AttnParams& P) { return P.s <= 16 || (int64_t)((P.s + 31) / 32) * P.b * P.A < 2 * (int64_t)attn_mfma_cu_count(); }
 
 // One wave a row: s <= 8 (backward, us, before / here: fp32, 1 head of 256 27.9 / 12.4, 2048 heads of 256 449 / 88, 2048 of 4 44.8 / 25.7); up to
 // s = 16 from head dimension 64 on, and 24 from 192 on, while there is at most one workgroup a CU (s = 16, 16 heads: d = 64

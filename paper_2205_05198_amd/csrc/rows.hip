@@ -734,9 +734,10 @@ hipError_t launch_ln_fwd(const RowsParams& P, bool bf16, const void* x, const vo
 
 // Workgroups of the form that reads x and dy once, 0 where the other one runs.  About 512 threads a CU; the narrower a row, the
 // fewer threads work on it and the more rows' partial sums there are.  From eight rows a workgroup on they cost less than the
-// second read (two reads / one, us: 1024 x 6144 15.4 / 17.1, 2048 x 6144 25.4 / 22.4, 8192 x 4096 59.7 / 45.9).  Rows wider than
-// 20480 leave no registers for a request ahead (bf16: from sixteen rows on, 2048 x 25600 90.9 / 99.8, 4096 x 25600 193 / 163),
-// and beyond 28672 no room for the sums.
+// second read (two reads / one, us, bf16: 8192 x 1024 20.8 / 20.5, 2048 x 6144 24.0 / 22.7, 8192 x 4096 54.1 / 38.9; fp32 2048 x 6144 41.0 / 30.8,
+// 4096 x 2048 30.8 / 23.3).  Rows wider than 20480 leave no registers for a request ahead (bf16: from sixteen rows on, 2048 x 25600 90.9 /
+// 99.8, 4096 x 25600 193 / 163; from 24576 on 13 registers spill, and it is the faster one all the same, 4096 x 28672 214 / 180), and beyond
+// 28672 there is no room for the sums.
 static inline int ln_bwd_stream_groups(int64_t rows, int64_t h, bool bf16) {
   const int64_t nchunk = h >> 3;
   const int groups = nchunk <= 128 ? 1024 : nchunk <= 512 ? 512 : 256;

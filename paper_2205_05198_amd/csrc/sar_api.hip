@@ -71,6 +71,9 @@ size_t delta_bytes(const sar::AttnParams& P) { return ((size_t)P.b * P.A * P.s *
 size_t ds_bytes(const sar::AttnParams& P) { return (size_t)P.b * P.A * (size_t)sar::ds_tiles_per_head(P) * sar::kDsTileElems * 2; }
 constexpr size_t kDsWorkspaceCap = 8ull << 30;  // above this attn_core_bwd_workspace asks for the two-pass backward's scratch only
 
+// Sequence length of every call that the bf16 matrix-core kernels do not take: at most 4864.  The stored baseline's one-wave-per-row kernels
+// keep whole score rows in LDS; the fp32 matrix-instruction kernels do not, but have the same line, within which their one-dimensional grids
+// stay below 2^32 threads for every number of heads.
 sar_status check_simple_limits(const sar::AttnParams& P) {
   if (sar::attn_simple_lds_bytes(P.s) > 160 * 1024) return fail(SAR_ERR_UNSUPPORTED, "s (%d) too long for this dtype / head dimension", P.s);
   return SAR_OK;
