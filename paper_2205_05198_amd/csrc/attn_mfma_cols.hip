@@ -22,7 +22,7 @@ hipError_t launch_attn_bwd_dkdv_mfma_split(const AttnParams& P, const void* q, c
 //   Up to one block a CU always this one (2048 x 12 39.7 / 26.6).  Above, two plain workgroups share a CU and start sooner:
 //   more than four blocks a CU: plain unless persistent workgroups come out even on full tiles (d = 64 512 x 192 36.0 / 40.7, but 384 x 256
 //     32.5 / 30.7; 1000 x 128, no mask, 138 / 147; d = 96 with the tiles without dropout 512 x 192 46.7 / 54.4, with it 58.8 / 55.8; d = 96 without
-//     the tiles not on short heads, 512 x 256 56.4 / 61.8);
+//     the tiles always, 512 x 256 56.4 / 61.8, 3712 x 24 without dropout 148 / 157);
 //   with the tiles to store also without mask and dropout on sequences that end inside a tile (d = 64 1000 x 24 29.0 / 30.1);
 //   without them also heads of four blocks or less from one and a half a CU on (200 x 192 13.6 / 15.4; six blocks: 384 x 96 12.9 / 14.6), and without
 //     dropout: no mask and more than one a CU (d = 96 1000 x 20 28.4 / 34.1), under the mask two (d = 64 1000 x 40 20.2 / 22.6);
@@ -37,7 +37,7 @@ static bool dkdv_split(const AttnParams& P, const uint16_t* ds_ws) {
   const bool even = R > 0 && (nb + R - 1) / R <= (blocks + cus - 1) / cus;
   if (ds_ws && nb <= 4) return !(ragged && !drop && 2 * blocks > 5 * cus);
   if (nb <= 4) return 2 * blocks < 3 * cus;
-  if (blocks > 4 * cus && (!even || ragged || (P.d == 96 && !ds_ws && nb <= 8))) return false;
+  if (blocks > 4 * cus && (!even || ragged || (P.d == 96 && !ds_ws))) return false;
   if (ds_ws) return !(ragged && !drop && !causal && blocks > cus);
   if (nb <= 6 && blocks > 2 * cus && 2 * blocks <= 5 * cus) return false;
   if (drop) return !(P.d == 96 && ragged && !causal && blocks > cus && 2 * blocks <= 3 * cus);

@@ -562,14 +562,16 @@ int attn_mfma_cu_count() {
 
 static int cu_count() { return attn_mfma_cu_count(); }
 
-// Form of the forward by shape, from a sweep of every form over 2276 shapes (d, s = 64 .. 8192, 4 .. 256 heads, mask, dropout): within
-// 1 % of the best form in the geometric mean, within 11 % everywhere.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us
-// or differences at p = 0 / 0.1.
+// Form of the forward by shape, from sweeps of every form over 3300 shapes (d, s = 64 .. 8192, 4 .. 256 heads, mask, dropout): within
+// 1 % of the best form in the geometric mean.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us or differences at
+// p = 0 / 0.1.
 //   One workgroup a CU or less: loader waves (plain 5 to 31 % slower).  More:
-//   128-row workgroups.  No mask: d = 160 in one round of them, or from nearly two on, where they save rounds (2048 x 12 60.4 / 60.9 ->
-//     42.2 / 50.3, but 1024 x 40 5 / 21 % slower; without dropout from 1.4 rounds, 1000 x 48 53.4 -> 49.9); d = 96 and 128 the same but from
-//     3.5 rounds (d = 96, 512 x 256 66.7 / 76.3 -> 57.0 / 62.7); d = 64 only without dropout in whole pairs of rounds (2048 x 64 95 -> 89).
-//     Causal, d = 160: so many that the heaviest does not set the pace (1024 x 64 -12 / -3 %, 384 x 256 47 -> 43; 1024 x 40 -5 / +2 %).
+//   128-row workgroups.  No mask: d = 160 in one round of them, then with dropout where they save two rounds of five (1024 x 64 -23 / -12 %, but
+//     1024 x 40, two rounds against three, +5 / +21 %), without it from 1.4 rounds and on long heads (1000 x 48 53.4 -> 49.9); d = 96 and 128 in
+//     one round and, on heads of up to 16 blocks, from 3.5 (d = 96, 512 x 256 66.7 / 76.3 -> 57.0 / 62.7, but 8192 x 14 at 0.1 554 -> 656);
+//     d = 64 only without dropout in whole pairs of rounds (2048 x 64 95 -> 89).  Causal, d = 160: so many that the heaviest does not set the
+//     pace, one and a half rounds with dropout and 1.25 without (1024 x 40 -5 / +2 %, 3712 x 17 at 0.1 136 -> 107), short heads two (384 x
+//     256 47 -> 43).
 //   Persistent workgroups: the longest list of row blocks must not exceed the rounds of single ones (no mask, d = 160, 1024 x 48, lists of
 //     4 against 3 rounds: 68.6, loaders 54.2).  Then d = 160 (384 x 48 11.4 -> 10.3, 512 x 40 12.7 -> 11.5); under the mask d = 96 and 128
 //     up to two workgroups a CU (d = 128, 1000 x 24 14.9 / 16.9 -> 14.0 / 16.6, 2048 x 14 27.5 / 30.1 -> 26.4 / 28.0, but 2048 x 20 +14 /
@@ -577,7 +579,8 @@ static int cu_count() { return attn_mfma_cu_count(); }
 //     has, the more of them a CU it takes (d = 128, 2048 x 12, 1.5 a CU: +0 / +3 %); four or less a head: nothing (d = 96, 256 x 128 8.4 against
 //     9.1).  d = 64: only long sequences with dropout (4096 x 8 -1 / -8 %; 512 x 64 +12 / +8 %).
 //   Loader waves or not: d = 160 with them (plain +1 to +12 / +4 to +18 %).  d = 64 too, except under the mask with more than four
-//     workgroups a CU (plain 0 to -14 %), or two without dropout and with up to 16 blocks a head.  d = 96, 128, where several workgroups
+//     workgroups a CU (plain 0 to -14 %), or two without dropout and with up to 16 blocks a head, and without either between two and 2.8 a
+//     CU (6000 x 6 105 -> 90).  d = 96, 128, where several workgroups
 //     without them share a CU: only under the mask, up to two a CU, more than four blocks a head (d = 128, no mask, 384 x 192 without them
 //     39.8 -> 30.6; causal, 200 x 128 10.2 -> 8.7).
 enum class FwdForm { Plain, Loaders, Persistent, Rows128 };
@@ -590,9 +593,10 @@ static FwdForm fwd_form(const AttnParams& P) {
   const int f128 = P.s < 128 ? 0 : g_force_fwd128.load();
   bool use128 = f128 == 1;
   if (f128 < 0 && w64 > cus) {
-    if (causal) use128 = D == 160 && (w128 > 2 * cus || (nrb >= 8 && 4 * w128 >= (drop ? 8 : 5) * cus));
-    else if (D == 160) use128 = w128 <= cus || 10 * w128 >= (drop ? 18 : 14) * cus;
-    else if (D >= 96) use128 = nrb > 4 && (w128 <= cus || 2 * w128 >= 7 * cus);
+    if (causal) use128 = D == 160 && (w128 > 2 * cus || (drop ? nrb >= 14 && 2 * w128 > 3 * cus : nrb >= 8 && 4 * w128 >= 5 * cus));
+    else if (D == 160 && drop) use128 = w128 <= cus || 5 * rounds128 < 3 * rounds64 || (5 * rounds128 == 3 * rounds64 && nrb <= 12);
+    else if (D == 160) use128 = w128 <= cus || 10 * w128 >= 14 * cus || nrb >= 40;
+    else if (D >= 96) use128 = nrb > 4 && (w128 <= cus || (2 * w128 >= 7 * cus && nrb <= 16));
     else use128 = !drop && w64 >= 4 * cus && 2 * rounds128 <= rounds64;
   }
   if (use128) return FwdForm::Rows128;
@@ -607,7 +611,10 @@ static FwdForm fwd_form(const AttnParams& P) {
     if (D == 64 && causal && drop && nrb >= 32 && full >= 190 * (int64_t)cus && w64 <= 2 * cus) return FwdForm::Persistent;
   }
   if (D == 160) return FwdForm::Loaders;
-  if (D == 64) return causal && (w64 > 4 * cus || (!drop && w64 > 2 * cus && nrb <= 16)) ? FwdForm::Plain : FwdForm::Loaders;
+  if (D == 64) {
+    const bool plain = causal ? w64 > 4 * cus || (!drop && w64 > 2 * cus && nrb <= 16) : !drop && w64 > 2 * cus && 10 * w64 < 28 * cus;
+    return plain ? FwdForm::Plain : FwdForm::Loaders;
+  }
   return causal && nrb > 4 && w64 <= 2 * cus ? FwdForm::Loaders : FwdForm::Plain;
 }
 

@@ -75,10 +75,10 @@ struct ColPlan {
   int lg, ncb, nsplit;  // lanes of a row segment (log2), column blocks, row splits
 };
 // one: lanes (log2) of a segment where a column block takes all of its rows, with no partial sums and no second launch (2.5 to 4 us); 0: rows
-// split over about `groups` workgroups.  Segments of 16 lanes then (bias-dropout backward, us, 8 / 16 / 64 lanes: bf16 8192 x 3072 19.7 / 19.3 /
+// split over about `groups` workgroups, in segments of 2^lg lanes: 16 (bias-dropout backward, us, 8 / 16 / 64 lanes: bf16 8192 x 3072 19.7 / 19.3 /
 // 20.5, fp32 4096 x 8192 - / 43.5 / 50.3), 32 on the widest rows, and 64 where the pass's tensors together do not fit the last-level cache
 // (bf16 4096 x 20480 - / 65.8 / 62.0; bias-GeLU backward of bf16 8192 x 8192 - / 87 / 80).
-static inline ColPlan col_plan(int64_t rows, int64_t h, int64_t esz, int one, int groups, int tensors, int nt = 256) {
+static inline ColPlan col_plan(int64_t rows, int64_t h, int64_t esz, int one, int groups, int lg, int tensors, int nt = 256) {
   const int64_t nchunk = h >> 3;
   ColPlan p{one, 0, 1};
   if (one) {
@@ -86,7 +86,7 @@ static inline ColPlan col_plan(int64_t rows, int64_t h, int64_t esz, int one, in
     return p;
   }
   const bool large = rows * h * esz * tensors > 288000000;
-  for (p.lg = large ? 6 : nchunk > 2560 ? 5 : 4; p.lg > 3; --p.lg) {  // the widest that leaves at most an eighth of the lanes without work
+  for (p.lg = large ? 6 : nchunk > 2560 ? 5 : lg; p.lg > 3; --p.lg) {  // the widest that leaves at most an eighth of the lanes without work
     const int64_t L = 1 << p.lg, used = (nchunk + L - 1) / L * L;
     if (used - nchunk <= nchunk / 8) break;
   }
@@ -754,7 +754,7 @@ static inline ColPlan ln_bwd_plan(int64_t rows, int64_t h, bool bf16) {
   int one = 0;
   if (nchunk > 1024) one = rows * h * esz > 85000000 ? 0 : nchunk > 3584 ? 5 : nchunk > 2048 ? 4 : 3;
   else if (rows <= one_split_rows(h, bf16 && nchunk <= 512 ? 512 : 384)) one = 3;
-  return col_plan(rows, h, esz, one, bf16 ? 768 : 512, 3, ln_bwd_threads(h));
+  return col_plan(rows, h, esz, one, bf16 ? 768 : 512, 4, 3, ln_bwd_threads(h));
 }
 
 size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {
@@ -874,14 +874,15 @@ hipError_t launch_bias_dropout_add_ln_fwd(const RowsParams& P, bool bf16, const 
 static ColPlan bda_bwd_plan(int64_t rows, int64_t h, bool bf16) {
   const int64_t esz = bf16 ? 2 : 4;
   const bool one = rows <= one_split_rows(h, bf16 ? 512 : 384) || (h * esz >= 49152 && rows * h * esz <= 144000000);
-  return col_plan(rows, h, esz, one ? 3 : 0, bf16 ? 768 : 512, 2);
+  return col_plan(rows, h, esz, one ? 3 : 0, bf16 ? 768 : 512, 4, 2);
 }
 // bias-GeLU backward, which does more on a row: up to 256 (300 x 4096 8.0 / 7.7), on wide rows a little further (fp32 512 x 16384 16.6 / 19.1, bf16 300 x 16384
 // 8.0 / 10.1, but bf16 512 x 25600 19.2 / 17.0); in bf16, whose rows are half as long, twice the workgroups or more (bf16 2048 x 10240
-// by 1040, 2080 workgroups 26.0 / 24.0; fp32 8192 x 4096 by 512, 2048 72.5 / 75.1).
+// by 1040, 2080 workgroups 26.0 / 24.0; fp32 8192 x 4096 by 512, 2048 72.5 / 75.1), in segments of 32 lanes (16, 32: 4096 x 6144 28.7 / 27.9; fp32
+// 8192 x 4096 72.5 / 77.8).
 static ColPlan bias_gelu_bwd_plan(int64_t rows, int64_t h, bool bf16) {
   const int64_t few = h >= 12288 ? (bf16 ? 320 : 640) : 256;
-  return col_plan(rows, h, bf16 ? 2 : 4, rows <= one_split_rows(h, few) ? 3 : 0, bf16 ? 2048 : 512, 3);
+  return col_plan(rows, h, bf16 ? 2 : 4, rows <= one_split_rows(h, few) ? 3 : 0, bf16 ? 2048 : 512, bf16 ? 5 : 4, 3);
 }
 size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) { return colsum_workspace_bytes(bias_gelu_bwd_plan(rows, h, bf16), h); }
 size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) { return colsum_workspace_bytes(bda_bwd_plan(rows, h, bf16), h); }

@@ -239,7 +239,8 @@ def test_forward_persistent_workgroups(d, s, b, A, causal, p):
                                               (128, 200, 1, 100, 0.0, 0), (160, 200, 1, 100, 0.1, 0), (160, 264, 2, 66, 0.1, 0),
                                               (128, 328, 1, 65, 0.1, 1), (160, 456, 2, 25, 0.0, 1), (64, 200, 2, 128, 0.0, 0), (64, 2040, 1, 16, 0.1, 1), (96, 328, 2, 150, 0.1, 0),
                                               (96, 200, 1, 128, 0.1, 1), (96, 328, 1, 80, 0.1, 0), (128, 328, 1, 128, 0.0, 1), (128, 200, 1, 128, 0.1, 1), (128, 328, 1, 85, 0.1, 0),
-                                              (160, 136, 1, 100, 0.1, 1), (160, 136, 2, 130, 0.1, 1), (160, 200, 1, 192, 0.1, 0), (160, 200, 1, 192, 0.0, 0), (160, 264, 1, 100, 0.0, 0)])
+                                              (160, 136, 1, 100, 0.1, 1), (160, 136, 2, 130, 0.1, 1), (160, 200, 1, 192, 0.1, 0), (160, 200, 1, 192, 0.0, 0), (160, 264, 1, 100, 0.0, 0),
+                                              (160, 904, 1, 50, 0.1, 1), (160, 2504, 1, 9, 0.0, 0), (64, 328, 1, 96, 0.0, 0)])
 def test_forward_form_by_shape(d, s, b, A, p, causal):
     """The forward as the library chooses it, on both sides of the lines between its forms on 256 compute units: plain (more than one
     to four workgroups a CU, by head dimension and mask), 128-row workgroups (64 without dropout in whole rounds; 96, 128, 160 in one
