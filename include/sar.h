@@ -236,7 +236,8 @@ sar_status bias_dropout_add_ln_fwd(const sar_rows_desc* desc, const void* x, con
                                    const void* gamma, const void* beta, void* out, void* y, float* mean, float* rstd,
                                    void* stream);
 
-/* Bytes of scratch bias_dropout_add_bwd needs when dbias is requested (row-split partial sums; may be 0). */
+/* Bytes of scratch bias_dropout_add_bwd needs when dbias is requested (row-split partial sums; may be 0).
+ * Where bias_gelu_bwd needs scratch too, bias_gelu_bwd_workspace answers the same, so that one buffer serves both. */
 size_t bias_dropout_add_bwd_workspace(const sar_rows_desc* desc);
 
 /*

@@ -884,8 +884,16 @@ static ColPlan bias_gelu_bwd_plan(int64_t rows, int64_t h, bool bf16) {
   const int64_t few = h >= 12288 ? (bf16 ? 320 : 640) : 256;
   return col_plan(rows, h, bf16 ? 2 : 4, rows <= one_split_rows(h, few) ? 3 : 0, bf16 ? 2048 : 512, bf16 ? 5 : 4, 3);
 }
-size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) { return colsum_workspace_bytes(bias_gelu_bwd_plan(rows, h, bf16), h); }
-size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) { return colsum_workspace_bytes(bda_bwd_plan(rows, h, bf16), h); }
+// Where both passes need scratch, one size for both, so that a buffer sized for either serves the other; none where a pass needs none.
+static inline size_t bias_bwd_workspace_bytes(const ColPlan& pl, const ColPlan& other, int64_t h) {
+  return pl.nsplit > 1 ? std::max(colsum_workspace_bytes(pl, h), colsum_workspace_bytes(other, h)) : 0;
+}
+size_t bias_gelu_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {
+  return bias_bwd_workspace_bytes(bias_gelu_bwd_plan(rows, h, bf16), bda_bwd_plan(rows, h, bf16), h);
+}
+size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {
+  return bias_bwd_workspace_bytes(bda_bwd_plan(rows, h, bf16), bias_gelu_bwd_plan(rows, h, bf16), h);
+}
 
 template <typename T>
 static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {

@@ -186,3 +186,15 @@ def test_bias_gelu_argument_errors(lib):
     assert lib.bias_gelu_bwd(ctypes.byref(big), p[0], p[1], p[2], p[3], p[4], p[5], need - 1, st) == -6
     assert lib.bias_gelu_bwd_workspace(None) == 0
 
+
+def test_bias_gradient_workspaces(lib):
+    """Where both bias gradients need scratch, a buffer sized by either function is large enough for the other pass."""
+    both = 0
+    for dtype in (binding.SAR_F32, binding.SAR_BF16):
+        for rows in (1, 37, 256, 300, 512, 700, 2048, 8192):
+            for h in (8, 256, 520, 3072, 6144, 10240, 16384, 32768):
+                d = ctypes.byref(sar.RowsDesc.make(rows, h, dtype=dtype))
+                sizes = {int(lib.bias_dropout_add_bwd_workspace(d)), int(lib.bias_gelu_bwd_workspace(d))} - {0}
+                assert len(sizes) <= 1, (dtype, rows, h, sizes)
+                both += len(sizes)
+    assert both > 60
