@@ -26,7 +26,10 @@ hipError_t launch_attn_bwd_dkdv_mfma_split(const AttnParams& P, const void* q, c
 //   with the tiles to store also without mask and dropout on sequences that end inside a tile (d = 64 1000 x 24 29.0 / 30.1);
 //   without them also heads of four blocks or less from one and a half a CU on (200 x 192 13.6 / 15.4; six blocks: 384 x 96 12.9 / 14.6), and without
 //     dropout: no mask and more than one a CU (d = 96 1000 x 20 28.4 / 34.1), under the mask two (d = 64 1000 x 40 20.2 / 22.6);
-//     with dropout only d = 96, no mask, up to one and a half a CU (1000 x 20 33.2 / 35.3).
+//     with dropout only d = 96, no mask, up to one and a half a CU (1000 x 20 33.2 / 35.3);
+//   heads of three to five blocks, one a CU: this one where persistent workgroups come out even, with dropout and no tiles (d = 96 256 x 210 48.9 / 45.6,
+//     no mask 60.9 / 56.9) or with the tiles under the mask (200 x 210 40.4 / 38.3); without dropout, mask and tiles the plain one on single blocks (d = 64
+//     64 x 320 12.5 / 14.0) and, where they do not come out even, up to eight (d = 64 320 x 180 37.6 / 41.8, but 2048 x 24 73.6 / 67.0).
 static bool dkdv_split(const AttnParams& P, const uint16_t* ds_ws) {
   const int force = g_force_form.load();
   const bool drop = P.thresh != 0, causal = P.causal != 0, ragged = P.s % 64 != 0;
@@ -35,13 +38,14 @@ static bool dkdv_split(const AttnParams& P, const uint16_t* ds_ws) {
   const int64_t nb = (P.s + 63) / 64, N = (int64_t)P.b * P.A, blocks = nb * N, cus = attn_mfma_cu_count();
   const int64_t R = N <= cus ? std::min(nb, cus / N) : 0;  // key blocks of a head at a time, persistent
   const bool even = R > 0 && (nb + R - 1) / R <= (blocks + cus - 1) / cus;
-  if (ds_ws && nb <= 4) return !(ragged && !drop && 2 * blocks > 5 * cus);
-  if (nb <= 4) return 2 * blocks < 3 * cus;
+  if (ds_ws && nb <= 4) return !(ragged && !drop && 2 * blocks > 5 * cus && !(causal && even));
+  if (!ds_ws && drop && even && R == 1 && N < cus && nb >= 3 && nb <= 5) return true;
+  if (nb <= 4) return 2 * blocks < 3 * cus && (nb > 1 || drop || causal || blocks <= cus);
   if (blocks > 4 * cus && (!even || ragged || (P.d == 96 && !ds_ws))) return false;
   if (ds_ws) return !(ragged && !drop && !causal && blocks > cus);
   if (nb <= 6 && blocks > 2 * cus && 2 * blocks <= 5 * cus) return false;
   if (drop) return !(P.d == 96 && ragged && !causal && blocks > cus && 2 * blocks <= 3 * cus);
-  return causal ? blocks <= 2 * cus || (P.d == 96 && !ragged) : blocks <= cus || (P.d == 64 && !ragged);
+  return causal ? blocks <= 2 * cus || (P.d == 96 && !ragged) : blocks <= cus || (P.d == 64 && !ragged && (even || nb > 8));
 }
 
 // persistent workgroups in the producer / consumer form: -1 the launcher decides by shape, 0 / 1 forced

@@ -562,17 +562,27 @@ int attn_mfma_cu_count() {
 
 static int cu_count() { return attn_mfma_cu_count(); }
 
-// Form of the forward by shape, from sweeps of every form over 3300 shapes (d, s = 64 .. 8192, 4 .. 256 heads, mask, dropout): within
-// 1 % of the best form in the geometric mean.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us or differences at
+// Form of the forward by shape, from sweeps of every form over 4256 shapes (d, s = 64 .. 8192, 4 .. 768 heads, mask, dropout): within
+// 0.5 % of the best form in the geometric mean.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us or differences at
 // p = 0 / 0.1.
 //   One workgroup a CU or less: loader waves (plain 5 to 31 % slower).  More:
+//   Heads of three to five blocks, one a CU: persistent workgroups where the lists are no longer than the rounds of single ones (d = 128 192 x 210
+//     17.8 / 18.1 -> 14.6 / 15.5, with the mask 16.2 / 16.9 -> 13.1 / 13.6; d = 160 192 x 210 -> 19.5 / 20.7, 128 rows 23.1 / 24.3, but four blocks
+//     without mask 256 x 210 32.1, 128 rows 29.4 with dropout).
 //   128-row workgroups.  No mask: d = 160 in one round of them, then with dropout where they save two rounds of five (1024 x 64 -23 / -12 %, but
-//     1024 x 40, two rounds against three, +5 / +21 %), without it from 1.4 rounds and on long heads (1000 x 48 53.4 -> 49.9); d = 96 and 128 in
-//     one round and, on heads of up to 16 blocks, from 3.5 (d = 96, 512 x 256 66.7 / 76.3 -> 57.0 / 62.7, but 8192 x 14 at 0.1 554 -> 656);
-//     d = 64 only without dropout in whole pairs of rounds (2048 x 64 95 -> 89).  Causal, d = 160: so many that the heaviest does not set the
+//     1024 x 40, two rounds against three, +5 / +21 %) or three of eight and heads are short (520 x 210 132 -> 101, but 3712 x 20 248 -> 277), on the
+//     shortest one of three (256 x 180 32.1 -> 27.9); without dropout from 1.4 rounds and on long heads (1000 x 48 53.4 -> 49.9), but not three
+//     blocks, a quarter of whose rows is padding, up to three rounds (136 x 272 26.1, 128 rows 30.6).  d = 96 and 128 in
+//     one round and, on heads of four (d = 128 256 x 384 37.3 -> 34.9) to 16 blocks, from three or 3.5 (d = 96, 512 x 256 66.7 / 76.3 -> 57.0 / 62.7,
+//     but 8192 x 14 at 0.1 554 -> 656; five blocks, a sixth of padding, from six: 320 x 320 37.4 -> 40.6, 320 x 512 69.9 -> 60.6).  d = 64, which holds
+//     two of them a CU, without dropout in whole pairs of rounds or from three (2048 x 64 95 -> 89, 256 x 210 14.7 -> 12.0, 520 x 512 96.6 -> 77.6, but
+//     512 x 96, 1.5 a CU, 13.0 -> 15.5; five blocks from six, 320 x 384 23.0 -> 25.8).
+//     Causal, d = 160: so many that the heaviest does not set the
 //     pace, one and a half rounds with dropout and 1.25 without (1024 x 40 -5 / +2 %, 3712 x 17 at 0.1 136 -> 107), short heads two (384 x
-//     256 47 -> 43).
-//   Persistent workgroups: the longest list of row blocks must not exceed the rounds of single ones (no mask, d = 160, 1024 x 48, lists of
+//     256 47 -> 43), three blocks never (136 x 272 22.7 / 23.1 -> 28.2 / 29.9).  d = 96, 128: from 5.5 rounds on heads of 12 blocks or more
+//     (1024 x 384 260 / 262 -> 179 / 196), six without dropout on those of six to ten in pairs, and d = 64 without dropout from nine, long ones 6.5
+//     (1024 x 210 70.6 -> 51.6, 520 x 384, 7.5, 35.3 -> 40.7).
+//   Persistent workgroups otherwise: the longest list of row blocks must not exceed the rounds of single ones (no mask, d = 160, 1024 x 48, lists of
 //     4 against 3 rounds: 68.6, loaders 54.2).  Then d = 160 (384 x 48 11.4 -> 10.3, 512 x 40 12.7 -> 11.5); under the mask d = 96 and 128
 //     up to two workgroups a CU (d = 128, 1000 x 24 14.9 / 16.9 -> 14.0 / 16.6, 2048 x 14 27.5 / 30.1 -> 26.4 / 28.0, but 2048 x 20 +14 /
 //     +7 %), d = 128 a little further where every CU gets as many as the next (768 x 64 with dropout 24.8 -> 23.6).  The more blocks a head
@@ -580,7 +590,7 @@ static int cu_count() { return attn_mfma_cu_count(); }
 //     9.1).  d = 64: only long sequences with dropout (4096 x 8 -1 / -8 %; 512 x 64 +12 / +8 %).
 //   Loader waves or not: d = 160 with them (plain +1 to +12 / +4 to +18 %).  d = 64 too, except under the mask with more than four
 //     workgroups a CU (plain 0 to -14 %), or two without dropout and with up to 16 blocks a head, and without either between two and 2.8 a
-//     CU (6000 x 6 105 -> 90).  d = 96, 128, where several workgroups
+//     CU (6000 x 6 105 -> 90), on heads of up to nine blocks from four on (136 x 768 21.8 -> 18.1).  d = 96, 128, where several workgroups
 //     without them share a CU: only under the mask, up to two a CU, more than four blocks a head (d = 128, no mask, 384 x 192 without them
 //     39.8 -> 30.6; causal, 200 x 128 10.2 -> 8.7).
 enum class FwdForm { Plain, Loaders, Persistent, Rows128 };
@@ -590,20 +600,42 @@ static FwdForm fwd_form(const AttnParams& P) {
   const int64_t w64 = (int64_t)nrb * N, w128 = (int64_t)((P.s + 127) / 128) * N;
   const int64_t rounds64 = (w64 + cus - 1) / cus, rounds128 = (w128 + cus - 1) / cus;
   const bool causal = P.causal != 0, drop = P.thresh != 0;
-  const int f128 = P.s < 128 ? 0 : g_force_fwd128.load();
+  const int f128 = P.s < 128 ? 0 : g_force_fwd128.load(), lw = g_force_fwdlw.load();
+  const int R = N <= cus ? std::min(nrb, cus / N) : 0;  // a persistent grid: R row blocks of every head at a time
+  const bool even = R > 0 && (nrb + R - 1) / R <= rounds64;
+  if (f128 < 0 && lw < 0 && w64 > cus && even && R == 1 && nrb >= 3 && nrb <= 5 &&
+      ((D == 128 && N < cus) || (D == 160 && (causal || nrb == 3))))
+    return FwdForm::Persistent;
   bool use128 = f128 == 1;
   if (f128 < 0 && w64 > cus) {
-    if (causal) use128 = D == 160 && (w128 > 2 * cus || (drop ? nrb >= 14 && 2 * w128 > 3 * cus : nrb >= 8 && 4 * w128 >= 5 * cus));
-    else if (D == 160 && drop) use128 = w128 <= cus || 5 * rounds128 < 3 * rounds64 || (5 * rounds128 == 3 * rounds64 && nrb <= 12);
-    else if (D == 160) use128 = w128 <= cus || 10 * w128 >= 14 * cus || nrb >= 40;
-    else if (D >= 96) use128 = nrb > 4 && (w128 <= cus || (2 * w128 >= 7 * cus && nrb <= 16));
-    else use128 = !drop && w64 >= 4 * cus && 2 * rounds128 <= rounds64;
+    if (causal) {
+      if (D == 160) {
+        use128 = nrb != 3 && (w128 > 2 * cus || (nrb == 2 && w128 == 2 * cus) || (drop ? nrb >= 14 && 2 * w128 > 3 * cus : nrb >= 8 && 4 * w128 >= 5 * cus));
+      } else if (D == 128) {
+        use128 = nrb >= 12 ? 2 * w128 >= 11 * cus : !drop && nrb >= 6 && nrb % 2 == 0 && w128 >= 6 * cus;
+      } else if (D == 96) {
+        use128 = nrb <= 64 && ((nrb >= 12 && 2 * w128 >= 11 * cus) || (!drop && nrb >= 6 && w128 >= (nrb % 2 == 0 ? 6 : 9) * cus));
+      } else {
+        use128 = !drop && ((nrb >= 6 && w128 >= 9 * cus) || (nrb >= 16 && 2 * w128 >= 13 * cus));
+      }
+    } else if (D == 160 && drop) {
+      use128 = w128 <= cus || 5 * rounds128 < 3 * rounds64 || (5 * rounds128 == 3 * rounds64 && nrb <= 12) || (8 * rounds128 <= 5 * rounds64 && nrb <= 16) ||
+               (3 * rounds128 <= 2 * rounds64 && nrb >= 3 && nrb <= 5);
+    } else if (D == 160) {
+      use128 = w128 <= cus || (10 * w128 >= 14 * cus && (nrb != 3 || w128 >= 3 * cus)) || nrb >= 40;
+    } else if (D >= 96) {
+      use128 = nrb >= 4 && ((nrb > 4 && w128 <= cus) || (2 * w128 >= (nrb == 5 ? 12 : nrb == 4 && D == 128 ? 6 : 7) * cus && nrb <= 16));
+    } else {
+      const int64_t pairs = (w128 + 2 * cus - 1) / (2 * cus);  // rounds of two workgroups a CU
+      use128 = !drop && nrb >= 4 && (w128 >= (nrb == 5 ? 6 : 3) * cus || 10 * w128 >= 16 * cus * pairs);
+    }
+    use128 = use128 && P.s >= 128;
   }
   if (use128) return FwdForm::Rows128;
-  if (const int lw = g_force_fwdlw.load(); lw >= 0) return lw == 0 ? FwdForm::Plain : lw == 3 && N <= cus ? FwdForm::Persistent : FwdForm::Loaders;
+  if (lw >= 0) return lw == 0 ? FwdForm::Plain : lw == 3 && N <= cus ? FwdForm::Persistent : FwdForm::Loaders;
   if (w64 <= cus) return FwdForm::Loaders;
-  const int R = N <= cus ? std::min(nrb, cus / N) : 0;  // a persistent grid: R row blocks of every head at a time
-  if (R > 0 && (nrb + R - 1) / R <= rounds64) {
+  if (D == 64 && !causal && !drop && nrb <= 9 && w64 > 4 * cus) return FwdForm::Plain;
+  if (even) {
     const int64_t from = (nrb <= 8 ? 110 : nrb <= 16 ? 140 : 170) * (int64_t)cus, full = 100 * w64;  // workgroups a CU in hundredths
     if (D == 160 && (!causal || full >= from)) return FwdForm::Persistent;
     if (D == 128 && causal && nrb > 4 && full >= from && w64 <= ((drop || nrb <= 8) && cus % N == 0 ? 3 : 2) * cus) return FwdForm::Persistent;

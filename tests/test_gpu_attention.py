@@ -240,12 +240,14 @@ def test_forward_persistent_workgroups(d, s, b, A, causal, p):
                                               (128, 328, 1, 65, 0.1, 1), (160, 456, 2, 25, 0.0, 1), (64, 200, 2, 128, 0.0, 0), (64, 2040, 1, 16, 0.1, 1), (96, 328, 2, 150, 0.1, 0),
                                               (96, 200, 1, 128, 0.1, 1), (96, 328, 1, 80, 0.1, 0), (128, 328, 1, 128, 0.0, 1), (128, 200, 1, 128, 0.1, 1), (128, 328, 1, 85, 0.1, 0),
                                               (160, 136, 1, 100, 0.1, 1), (160, 136, 2, 130, 0.1, 1), (160, 200, 1, 192, 0.1, 0), (160, 200, 1, 192, 0.0, 0), (160, 264, 1, 100, 0.0, 0),
-                                              (160, 904, 1, 50, 0.1, 1), (160, 2504, 1, 9, 0.0, 0), (64, 328, 1, 96, 0.0, 0)])
+                                              (160, 904, 1, 50, 0.1, 1), (160, 2504, 1, 9, 0.0, 0), (64, 328, 1, 96, 0.0, 0),
+                                              (128, 136, 1, 210, 0.1, 1), (160, 136, 2, 136, 0.0, 0), (160, 200, 1, 180, 0.1, 0), (64, 248, 1, 210, 0.0, 0), (64, 136, 2, 192, 0.0, 0),
+                                              (96, 776, 2, 108, 0.1, 1), (128, 360, 2, 256, 0.0, 1)])
 def test_forward_form_by_shape(d, s, b, A, p, causal):
     """The forward as the library chooses it, on both sides of the lines between its forms on 256 compute units: plain (more than one
     to four workgroups a CU, by head dimension and mask), 128-row workgroups (64 without dropout in whole rounds; 96, 128, 160 in one
-    round or several; 160 under the mask in more than two), loader waves, persistent workgroups (64: a long sequence with two row blocks a
-    workgroup; 96, 128, 160 with lists of two or three, or some at two and the rest at one; not where the longest list exceeds the
+    round or several; 160 under the mask in more than two, the others in six), loader waves, persistent workgroups (64: a long sequence with two
+    row blocks a workgroup; 128, 160: three blocks a head and nearly a head a unit; 96, 128, 160 with lists of two or three, or some at two and the rest at one; not where the longest list exceeds the
     rounds of single blocks); every sequence ends inside a tile."""
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=s, b=b, a=A, h=A * d, p=p, seed=80, offset=(1 << 32) - 999, causal=causal)
@@ -319,12 +321,13 @@ def test_column_pass_forms(d, s, b, A, p, causal, two_pass, form):
 @pytest.mark.parametrize("two_pass", [False, True])
 @pytest.mark.parametrize("d,s,A,p,causal", [(64, 128, 192, 0.1, 1), (64, 384, 96, 0.1, 1), (64, 328, 256, 0.1, 1), (96, 320, 256, 0.1, 1), (96, 320, 256, 0.0, 0), (64, 328, 64, 0.0, 0),
                                             (96, 328, 100, 0.0, 1), (96, 320, 120, 0.0, 1), (64, 200, 192, 0.0, 0), (160, 320, 100, 0.1, 0), (128, 192, 100, 0.1, 0),
-                                            (160, 328, 85, 0.1, 1), (64, 1000, 48, 0.1, 1), (96, 200, 66, 0.1, 0), (96, 328, 56, 0.1, 0)])
+                                            (160, 328, 85, 0.1, 1), (64, 1000, 48, 0.1, 1), (96, 200, 66, 0.1, 0), (96, 328, 56, 0.1, 0),
+                                            (96, 376, 180, 0.1, 1), (64, 264, 180, 0.0, 0), (96, 200, 210, 0.1, 0), (160, 376, 180, 0.1, 0), (64, 64, 320, 0.0, 0)])
 def test_column_pass_form_by_shape(d, s, A, p, causal, two_pass):
     """The column pass as the library chooses it, on both sides of the lines between its forms on 256 compute units: plain with dropout and
     without (64, 96: more than four workgroups a CU, short heads, no mask), producer / consumer with one key block a workgroup (96 with
     dropout and the tiles; 160 with lists of three against two rounds of single blocks) and persistent (128, 160; 64 with lists one
-    longer than the rounds under the mask; some workgroups with one block and the rest with two)."""
+    longer than the rounds under the mask; some workgroups with one block and the rest with two; nearly a head a unit with lists a third longer)."""
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=p, seed=81, offset=(1 << 32) - 4321, causal=causal)
     q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=47)
