@@ -748,13 +748,15 @@ static inline int ln_bwd_threads(int64_t h) { return h <= 8192 ? 256 : h <= 2867
 // Column sums in one split, us one / split: up to a few hundred rows (bf16 512 x 4096 7.7 / 8.9, fp32 300 x 6144 8.3 / 9.1; but fp32 512 x 3072 10.0 /
 // 8.7, bf16 512 x 6144 11.2 / 9.9), and wide rows at any count, as there are blocks enough for every CU (bf16 1024 x 16384 28.7 / 30.9), in wider
 // segments the wider they are (bf16 300 x 32768 by 8, 32 lanes 25.8 / 19.8); not beyond 85 MB, three of
-// which do not fit the last-level cache (2048 x 32768 141 / 128).
+// which do not fit the last-level cache (2048 x 32768 141 / 128), and not on rows of up to 12288 with many of them, where the blocks, 129 to 192, each
+// have a long chain (bf16 2000 x 8208 38.3 / 32.4, in segments of 16 lanes 34.5; 1500 x 10240 30.1 / 28.1; 900 x 8208 20.3 / 18.4; fp32 1500 x 9216 53.1 / 48.7, 1200 x
+// 8208 43.6 / 38.4, but 800 x 9216 26.5 / 29.3, bf16 900 x 9216 18.0 / 18.6).
 static inline ColPlan ln_bwd_plan(int64_t rows, int64_t h, bool bf16) {
   const int64_t nchunk = h >> 3, esz = bf16 ? 2 : 4;
   int one = 0;
-  if (nchunk > 1024) one = rows * h * esz > 85000000 ? 0 : nchunk > 3584 ? 5 : nchunk > 2048 ? 4 : 3;
+  if (nchunk > 1024) one = rows * h * esz > 85000000 || (nchunk <= 1536 && rows > (bf16 ? 800 : 1024)) ? 0 : nchunk > 3584 ? 5 : nchunk > 2048 ? 4 : 3;
   else if (rows <= one_split_rows(h, bf16 && nchunk <= 512 ? 512 : 384)) one = 3;
-  return col_plan(rows, h, esz, one, bf16 ? 768 : 512, 4, 3, ln_bwd_threads(h));
+  return col_plan(rows, h, esz, one, bf16 ? 768 : 512, bf16 && nchunk > 1024 ? 5 : 4, 3, ln_bwd_threads(h));
 }
 
 size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {

@@ -222,6 +222,7 @@ def test_bias_gelu(rows, h, dtype, with_bias):
     (256, 1024, "bf16"), (257, 1024, "bf16"), (384, 2048, "f32"), (385, 2048, "f32"), (513, 4096, "bf16"), (385, 4160, "bf16"),  # one split or several: full last blocks
     (320, 16384, "bf16"), (321, 16384, "bf16"), (641, 12352, "f32"), (600, 24576, "bf16"), (520, 20544, "bf16"),                # ... of wide rows
     (300, 28680, "bf16"), (1500, 32768, "bf16"), (1000, 32768, "f32"),                                                          # 1024 threads a row; beyond the last-level cache
+    (800, 8200, "bf16"), (801, 8200, "bf16"), (1501, 12288, "bf16"), (1500, 12296, "bf16"), (1024, 8208, "f32"), (1025, 8208, "f32"),  # LayerNorm backward: split on many rows
     (33, 8, "bf16"), (140, 8, "f32"), (300, 72, "bf16"),                                                                         # a column block of one lane
 ])
 def test_column_sums(rows, h, dtype):
