@@ -6,7 +6,7 @@
 // becomes a plain batched product over those tiles:
 //   1. attn_bwd_delta_kernel      delta_i = sum_x dO_ix O_ix                      (reads dO, O once)
 //   2. attn_bwd_dkdv_mfma_kernel  dK, dV, and dS tiles          (attn_mfma_cols_kernel.h, WDS = true)
-//   3. attn_bwd_dq_gemm_kernel    dQ = alpha dS K                                  (reads the tiles and K)
+//   3. attn_bwd_dq_gemm(128)_kernel dQ = alpha dS K                               (reads the tiles and K)
 // 5 contractions are executed instead of 7, and Philox and the exponentials run once per backward instead of twice.
 #include "attn_mfma_common.h"
 
@@ -178,6 +178,120 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm_kernel(AttnParams P, 
   lds_rows_to_global<D>(smem, dq + base + (int64_t)(rb * BM) * P.stride_s, gstride, P.s - rb * BM, tid);
 }
 
+// The same product for 128 query rows: 4 computing waves, one per 32 rows, each over all 64 keys of a tile (no partial sums to
+// merge), and 4 waves that fetch, now the dS tiles as well.  What bounds the 64-row form is the CU's path from the L2: loads into registers
+// come at 32 B a cycle and direct loads into LDS at 62 (measured, hits in the L2), so a 64 x 64 step at d = 160 takes 8 KB / 32 + 21 KB / 62 =
+// 600 cycles of it for 320 of matrix work.  Here dS goes through LDS and a K tile serves twice the rows: 300 cycles per 64 x 64.
+template <int D>
+__global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm128_kernel(AttnParams P, const uint16_t* __restrict__ k, const uint16_t* __restrict__ ds_ws,
+                                                                    uint16_t* __restrict__ dq) {
+  constexpr int BM = 128, BN = 64, KP = D + 8, DT = D / 32, NS = D == 64 ? 3 : 4, LA = NS - 1;
+  constexpr int TILE = BN * KP, STAGE = TILE + 2 * kDsTileElems;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[NS * STAGE];  // stage: K tile, dS tiles of the upper and lower 64 rows; afterwards the output tiles
+  const int N = P.b * P.A;
+  const int nb = (P.s + 63) / 64, nrb = (P.s + BM - 1) / BM;
+  const int rb = nrb - 1 - (int)(blockIdx.x / N);  // heaviest row blocks first
+  const int bn = blockIdx.x % N, beta = bn / P.A, n = bn % P.A;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 31, hh = lane >> 5;
+  const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a;
+  const int gstride = (int)P.stride_s;
+  const bool both = 2 * rb + 1 < nb;                          // the lower 64 rows exist
+  const int ntile = P.causal ? 2 * rb + (both ? 2 : 1) : nb;  // tiles of the block; under the mask the upper rows have one less
+  const int nt_up = P.causal ? 2 * rb + 1 : nb;
+  if (wave >= 4) {  // a loader
+    const int lw = wave - 4;
+    constexpr int KMIN = DmaMap<D>::NL / 4;  // fewest loads of a K tile per wave; a dS tile is two
+    const uint16_t* kg = k + base;
+    const uint16_t* dsh = ds_ws + (int64_t)bn * ds_tiles_per_head(P) * kDsTileElems;
+    DmaMap<D> map;
+    map.init(lw, lane, gstride, true);
+    auto fetch = [&](const int jt) __attribute__((always_inline)) {
+      const int left = P.s - jt * BN;
+      uint16_t* st = smem + (jt % NS) * STAGE;
+      if (left >= BN) dma_tile<D>(map, kg + (int64_t)(jt * BN) * gstride, st, lw);
+      else dma_tile_ragged<D>(map, kg + (int64_t)(jt * BN) * gstride, st, lw, lane, gstride, left);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (h ? both : jt < nt_up) {
+          const uint16_t* t = dsh + ds_tile_index(P, 2 * rb + h, jt) * kDsTileElems;
+#pragma unroll
+          for (int u = 0; u < 2; ++u) dma16(t + 512 * (lw + 4 * u), 16u * (uint32_t)lane, lds_addr(st + TILE + h * kDsTileElems) + 1024u * (uint32_t)(lw + 4 * u));
+        }
+    };
+    for (int jt = 0; jt < LA && jt < ntile; ++jt) fetch(jt);
+    for (int jt = 0; jt < ntile; ++jt) {
+      // tile jt has landed; the loads of the LA - 1 tiles after it may still be in flight (the last tile may hold one dS tile only)
+      if (both && jt + LA < ntile) dma_wait_keep<(LA - 1) * (KMIN + 4)>();
+      else if (LA > 2 && jt + 2 < ntile) dma_wait_keep<2 * (KMIN + 2)>();
+      else if (jt + 1 < ntile) dma_wait_keep<KMIN + 2>();
+      else dma_wait();
+      __syncthreads();  // top of step jt: its tile is there, and nobody reads the one before it any more
+      if (jt + LA < ntile) fetch(jt + LA);
+    }
+    __syncthreads();  // everybody is done with the last tile
+    __syncthreads();  // the output tiles are complete
+  } else {
+    const int half = wave >> 1, rg = wave & 1;
+    const bool mine = half == 0 || both;
+    const int it = 2 * rb + half, nt_w = half == 0 ? nt_up : ntile;
+    float16_t dqacc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) dqacc[dt][e] = 0.f;
+    for (int jt = 0; jt < ntile; ++jt) {
+      __syncthreads();
+      if (!mine || jt >= nt_w) continue;
+      const uint16_t* Ks = smem + (jt % NS) * STAGE;
+      const uint16_t* Ds = Ks + TILE + half * kDsTileElems + 2048 * rg + 8 * lane;  // key group g (16 keys) at + 512 g
+      constexpr int kAhead = 4, NF = 4 * DT;
+      bf16x8_t d[4], fr[kAhead];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) d[g] = ld_frag(Ds + 512 * g);
+#pragma unroll
+      for (int a = 0; a < kAhead; ++a) fr[a] = ld_frag_tr_perm(Ks, KP, 16 * (a / DT), 32 * (a % DT), lane);
+      if (P.causal && jt == it && rg == 0) {  // the upper right quarter of the diagonal tile lies above the diagonal
+        const u32x4_t zero = {0u, 0u, 0u, 0u};
+        d[2] = __builtin_bit_cast(bf16x8_t, zero);
+        d[3] = __builtin_bit_cast(bf16x8_t, zero);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        dqacc[f % DT] = mfma32(fr[f % kAhead], d[f / DT], dqacc[f % DT]);
+        if (f + kAhead < NF) fr[f % kAhead] = ld_frag_tr_perm(Ks, KP, 16 * ((f + kAhead) / DT), 32 * ((f + kAhead) % DT), lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();
+    if (mine) acc_to_lds_rows<DT>(smem + half * TILE, KP, 32 * rg + li, dqacc, P.scale, hh);
+    __syncthreads();
+  }
+  const int half = tid >> 8;  // threads 0 .. 255 copy rows 0 .. 63 out, the loaders rows 64 .. 127
+  lds_rows_to_global<D>(smem + half * TILE, dq + base + (int64_t)(rb * BM + 64 * half) * P.stride_s, gstride, P.s - rb * BM - 64 * half, tid & 255);
+}
+
+// The dQ product in blocks of 128 rows, rather than 64?  From both over 7818 shapes (s = 64 .. 8192, 1 .. 256 heads): 0.91 of the 64-row form's
+// time in the geometric mean of all, 0.65 to 0.85 where blocks are many (s x heads, us, 64 / 128 rows: d = 160 8192 x 16 under the mask 344 / 262, 1024 x 20
+// without 20.5 / 14.0; d = 96 2048 x 32 32.9 / 26.8).  A block of 128 rows takes about one and a half times as long as one of 64.  So: more 64-row blocks
+// than CUs, and without the mask rounds of blocks less by that; d = 64, which holds two of either a CU, not on long heads (7168 x 20 +5 %).
+// Under the mask the heaviest block, twice as long a chain as at 64 rows' rate, must not set the pace: the more tiles it has, the more blocks it takes to
+// hide it (d = 160 2048 x 16, one 128-row block a CU, 22.4 / 22.9; d = 128 2048 x 12 16.7 / 22.0).  `from`: 128-row blocks a CU, in hundredths.
+template <int D>
+static bool dq_rows128(const AttnParams& P) {
+  const int64_t cus = attn_mfma_cu_count(), N = (int64_t)P.b * P.A, nb = (P.s + 63) / 64, w64 = nb * N, w128 = (nb + 1) / 2 * N;
+  if (w64 <= cus) return false;
+  const int64_t r64 = (w64 + cus - 1) / cus, r128 = (w128 + cus - 1) / cus;
+  if (!P.causal) {
+    if (3 * r128 > 2 * r64 || (D == 128 && 3 * r128 == 2 * r64)) return false;
+    return D != 64 || (nb == 2 ? 100 * w128 >= 88 * cus : nb <= 24 || w128 > 6 * cus);
+  }
+  if (nb <= 6 && 3 * r128 > 2 * r64) return false;
+  constexpr int from[4][7] = {{65, 90, 113, 113, 125, 220, 300}, {50, 70, 80, 80, 105, 105, 113}, {60, 88, 101, 101, 113, 125, 150}, {50, 63, 70, 80, 105, 105, 105}};
+  const int len = (nb > 8) + (nb > 12) + (nb > 16) + (nb > 24) + (nb > 32) + (nb > 64);
+  return 100 * w128 >= from[D / 32 - 2][len] * cus;
+}
+
 template <int D>
 static hipError_t bwd_once_d(const AttnParams& P, const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq,
                              void* dk, void* dv, float* delta, uint16_t* ds_ws, int stages, hipStream_t st) {
@@ -191,8 +305,11 @@ static hipError_t bwd_once_d(const AttnParams& P, const void* q, const void* k, 
     if ((e = launch_attn_bwd_dkdv_mfma(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, st)) != hipSuccess) return e;
   }
   if (stages & 4) {
-    hipLaunchKernelGGL((attn_bwd_dq_gemm_kernel<D>), dim3((unsigned)(nb * N)), dim3(512), 0, st, P, (const uint16_t*)k, (const uint16_t*)ds_ws,
-                       (uint16_t*)dq);
+    auto go = [&](auto kern, int blocks) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)(blocks * N)), dim3(512), 0, st, P, (const uint16_t*)k, (const uint16_t*)ds_ws, (uint16_t*)dq);
+    };
+    if (dq_rows128<D>(P)) go(attn_bwd_dq_gemm128_kernel<D>, (nb + 1) / 2);
+    else go(attn_bwd_dq_gemm_kernel<D>, nb);
     e = hipGetLastError();
   }
   return e;

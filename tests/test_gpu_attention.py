@@ -354,6 +354,19 @@ def test_column_pass_producer_consumer_ragged(d, s, b, A, p, causal, two_pass, p
     _check_bf16_heads(f"cols-ragged{pers}", sh, q, k, v, do, got, sorted({0, 1, b * A // 2, b * A - 1}))
 
 
+@pytest.mark.parametrize("d,s,A,p,causal", [(160, 128, 160, 0.1, 1), (64, 72, 240, 0.0, 0), (128, 136, 100, 0.1, 1), (64, 328, 64, 0.1, 1), (160, 264, 120, 0.1, 0),
+                                            (96, 840, 36, 0.1, 1), (128, 520, 60, 0.0, 0), (96, 1024, 32, 0.1, 1), (160, 1000, 32, 0.1, 1)])
+def test_dq_product_in_blocks_of_128_rows(d, s, A, p, causal):
+    """The dQ product of the recompute-once backward where it runs in blocks of 128 rows (many blocks a compute unit): two to sixteen
+    tiles a block, with and without a lower half in the last block, sequences that end inside a tile, with and without the mask."""
+    from gpu_util import run_attn
+    sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=p, seed=83, offset=(1 << 32) - 99, causal=causal)
+    q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=53)
+    print(f"dq in 128 rows d={d} s={s} A={A} causal={causal} p={p}", flush=True)
+    got = run_attn(sh, "bf16", q, k, v, do, two_pass=False)
+    _check_bf16_heads("dq128", sh, q, k, v, do, got, [0, 1, A // 2, A - 1])
+
+
 def test_bf16_generic_path_other_head_dim():
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=72, b=1, a=2, h=2 * 40, p=0.1, seed=3)
