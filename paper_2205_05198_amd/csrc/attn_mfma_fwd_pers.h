@@ -17,12 +17,13 @@
 
 namespace sar {
 
+static constexpr float kSumLimit = 1.152921504606846976e18f;  // 2^60: sum of a lane's 16 probabilities of a tile above which the reference exponent moves
+
 template <int D, bool DROP>
 __global__ __launch_bounds__(512) void attn_fwd_pers_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                              const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse) {
   constexpr int BM = 64, BN = 64, KP = D + 8, KC = D / 16, DT = D / 32;
   constexpr int TILE = BN * KP;
-  constexpr float kRescale = 60.0f;  // the running reference exponent moves only when the row maximum grew by > 2^60
   constexpr int MGW = 64 * (16 * DT + 4);  // floats per row group in the merge buffer: DT accumulator tiles, (m, l) of both key halves
   __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TILE];
   __shared__ __attribute__((aligned(16))) float mgbuf[2 * MGW];     // the epilogue's buffers: partial outputs and statistics of the upper key half
@@ -183,7 +184,9 @@ __global__ __launch_bounds__(512) void attn_fwd_pers_kernel(AttnParams P, const 
       return ld_frag_tr_perm(Vs, KP, 32 * ks + 16 * (idx / DT), 32 * (idx % DT), lane);
     };
     float psum = 0.f;
+    // the probabilities that enter the product; with dropout rounded as they are formed (fewer registers), without after the last
     float pd[16];
+    union { uint32_t w[4]; bf16x8_t v; } pf[2];
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
       if (NEXT != 0) {
@@ -196,23 +199,44 @@ __global__ __launch_bounds__(512) void attn_fwd_pers_kernel(AttnParams P, const 
         const float pe = __builtin_amdgcn_exp2f(fmaf(st[e], sc2, -m_ref));
         psum += pe;
         pd[e] = (!DROP || keep_field(rnd[e >> 3], e & 7, P.thresh)) ? pe : 0.f;
+        if (DROP && (e & 1)) pf[e >> 3].w[(e & 7) >> 1] = pack_bf16x2(pd[e - 1], pd[e]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    // The running reference exponent moves only when a lane's sum says that a score exceeded it by about 2^60 (or is not finite):
+    // the tile's probabilities are then formed again against its maximum
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= kSumLimit)) != 0, 0)) {
+      const float m_new = fmaxf(m_ref, tile_max(st));
+      const float corr = __builtin_amdgcn_exp2f(m_ref - m_new);
+      m_ref = m_new;
+      l_run *= corr;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[dt][e] *= corr;
+      psum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(st[e], sc2, -m_ref));
+        psum += pe;
+        pd[e] = (!DROP || keep_field(rnd[e >> 3], e & 7, P.thresh)) ? pe : 0.f;
+        if (DROP && (e & 1)) pf[e >> 3].w[(e & 7) >> 1] = pack_bf16x2(pd[e - 1], pd[e]);
+      }
+    }
     l_run += psum;
-    bf16x8_t pf[2];
-    pf[0] = pack8(pd);
-    pf[1] = pack8(pd + 8);
+    if (!DROP) {
+      pf[0].v = pack8(pd);
+      pf[1].v = pack8(pd + 8);
+    }
     Philox4 rn[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
     if (DROP) {
       if (NEXT != 0) philox_begin(rn, rowG, jt + 1);
       else philox_begin(rn, rowG_n, 0);  // (drawn in vain after the last row block)
     }
     __builtin_amdgcn_sched_barrier(0);
-    float mt = 0.f;
 #pragma unroll
     for (int idx = 0; idx < NPV; ++idx) {
-      oacc[idx % DT] = mfma32(vfr[idx % kAhead], pf[idx / DT], oacc[idx % DT]);
+      oacc[idx % DT] = mfma32(vfr[idx % kAhead], pf[idx / DT].v, oacc[idx % DT]);
       if (idx + kAhead < NPV) vfr[idx % kAhead] = v_frag(idx + kAhead);
       if (NEXT == 2 && idx == 1) {  // the diagonal tile: keys beyond jlim are masked
         const int j0n = (jt + 1) * BN + 32 * ks;
@@ -220,7 +244,6 @@ __global__ __launch_bounds__(512) void attn_fwd_pers_kernel(AttnParams P, const 
         for (int e = 0; e < 16; ++e)
           if (j0n + 16 * (e >> 3) + 8 * hh + (e & 7) > jlim) stn[e] = -INFINITY;
       }
-      if (NEXT != 0 && idx == 2) mt = tile_max(stn);
       if (DROP) {
 #pragma unroll
         for (int u = (20 * idx) / NPV; u < (20 * (idx + 1)) / NPV; ++u) philox_round(rn[u & 1], P.key0, P.key1, u >> 1);
@@ -233,16 +256,6 @@ __global__ __launch_bounds__(512) void attn_fwd_pers_kernel(AttnParams P, const 
     rnd[1] = rn[1];
     if (NEXT != 0) {
       st = stn;
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_ref + kRescale) != 0, 0)) {
-        const float m_new = fmaxf(m_ref, mt);
-        const float corr = __builtin_amdgcn_exp2f(m_ref - m_new);
-        m_ref = m_new;
-        l_run *= corr;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) oacc[dt][e] *= corr;
-      }
     }
   };
 

@@ -29,7 +29,6 @@
 
 namespace sar {
 
-static constexpr float kLazyRescale = 60.0f;  // the running reference exponent moves only when the row maximum grew by > 2^60
 
 // ===================================================================================================
 // Forward.  Workgroup = 32 NRG query rows, 2 NRG waves: wave = (rg, ks), rg = 32-row group, ks = which 32 keys of
@@ -38,24 +37,32 @@ static constexpr float kLazyRescale = 60.0f;  // the running reference exponent 
 // row groups stop one tile before the two upper ones.
 // K and V tiles (both with swapped rows) go from global memory straight into LDS, two stages each.
 // The score tile and the Philox words run one step ahead of the rest: step j computes S_{j+1} between the exponentials and
-// keep decisions of tile j, then P_j V_j between the Philox rounds, the mask and the row maximum of tile j+1 (the order
+// keep decisions of tile j, then P_j V_j between the Philox rounds and the mask of tile j+1 (the order
 // is laid out by hand, see the step).  A wave issues in order, so a step costs the sum of its instructions' issue times
 // whichever pipe executes them: measured at d = 160 per 64 x 64 step, 1700 cycles = ~1130 of vector instructions
-// (16 exponentials at quarter rate are 256 of them, two Philox calls 320) + ~240 for issuing 20 matrix instructions +
+// (16 exponentials are 256 of them, two Philox calls 320) + ~240 for issuing 20 matrix instructions +
 // ~260 for 30 LDS reads + ~80 at the barrier; with the vector work removed the first half takes 562 cycles, with the
-// matrix work and its reads removed 627, both together 946.  The (rare) rescaling of the running maximum for tile j+1
-// is decided at the end of step j.
+// matrix work and its reads removed 627, both together 946 (with a row maximum a step, since replaced: fwd_by_max).
 // ===================================================================================================
 // DROP = false is the p = 0 variant: no random numbers are drawn at all.
 // LW (64-row workgroups only): four more waves, one per SIMD, that do nothing but fetch the K / V tiles.  A wave-wide
 // 16-byte load occupies its wave for about 64 cycles (16 bytes per cycle per SIMD; four SIMDs are the CU's 64 B/clk), so
 // 42 loads per step cost each computing wave some 650 cycles of a 2200-cycle step; in a wave of their own those cycles
 // run beside the arithmetic of the SIMD's other wave.  The price: every wave must fit half the register file.
+// How a step learns that the running reference exponent must move (by more than 2^60, which is rare): by the sums of the probabilities it forms
+// anyway, after which it forms the tile's again, or by the row maximum of the next tile, sixteen vector instructions a step.  The first keeps
+// the scores until the sum is known; where that costs a wave per SIMD its registers (d = 96 with dropout 166 -> 176, two instead of three; d = 64
+// without 124 -> 137) the maximum stays: 2048 x 64 at d = 96 174 against 184 us (183 held to 168 registers, with spills).  Elsewhere
+// the sum: d = 160 8192 x 16 424 -> 413, d = 64 2048 x 8 without dropout 15.2 -> 14.1.
+template <int D, bool DROP, int NRG, bool LW>
+constexpr bool fwd_by_max() { return NRG == 2 && !LW && (D == 96 ? DROP : D == 64 && !DROP); }
+
 template <int D, bool DROP, int NRG, bool LW = false>
-__global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0)) void attn_fwd_mfma_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+__global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0), D == 64 && (LW || (NRG == 4 && !DROP)) ? 4 : 1) void attn_fwd_mfma_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse) {
   constexpr int BM = 32 * NRG, BN = 64, KP = D + 8, KC = D / 16, DT = D / 32, NW = 2 * NRG;
   constexpr int TILE = BN * KP;
+  constexpr bool BYSUM = !fwd_by_max<D, DROP, NRG, LW>();
   __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TILE];
   uint16_t* Kst = smem;             // K tile jt lives in Kst + (jt & 1) * TILE
   uint16_t* Vst = smem + 2 * TILE;  // V tile jt lives in Vst + (jt & 1) * TILE
@@ -224,7 +231,9 @@ __global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0)) void attn_fwd_mfma_kern
       return ld_frag_tr_perm(Vs, KP, 32 * ks + 16 * (idx / DT), 32 * (idx % DT), lane);
     };
     float psum = 0.f;
+    // the probabilities that enter the product; with dropout rounded as they are formed (fewer registers), without after the last
     float pd[16];
+    union { uint32_t w[4]; bf16x8_t v; } pf[2];
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
       if (NEXT != 0) {
@@ -237,13 +246,35 @@ __global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0)) void attn_fwd_mfma_kern
         const float pe = __builtin_amdgcn_exp2f(fmaf(st[e], sc2, -m_ref));
         psum += pe;
         pd[e] = (!DROP || keep_field(rnd[e >> 3], e & 7, P.thresh)) ? pe : 0.f;
+        if (DROP && BYSUM && (e & 1)) pf[e >> 3].w[(e & 7) >> 1] = pack_bf16x2(pd[e - 1], pd[e]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    // The running reference exponent moves only when a lane's sum says that a score exceeded it by about 2^60 (or is not finite):
+    // the tile's probabilities are then formed again against its maximum
+    if (BYSUM && __builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= kSumLimit)) != 0, 0)) {
+      const float m_new = fmaxf(m_ref, tile_max(st));
+      const float corr = __builtin_amdgcn_exp2f(m_ref - m_new);
+      m_ref = m_new;
+      l_run *= corr;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[dt][e] *= corr;
+      psum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(st[e], sc2, -m_ref));
+        psum += pe;
+        pd[e] = (!DROP || keep_field(rnd[e >> 3], e & 7, P.thresh)) ? pe : 0.f;
+        if (DROP && BYSUM && (e & 1)) pf[e >> 3].w[(e & 7) >> 1] = pack_bf16x2(pd[e - 1], pd[e]);
+      }
+    }
     l_run += psum;
-    bf16x8_t pf[2];
-    pf[0] = pack8(pd);
-    pf[1] = pack8(pd + 8);
+    if (!DROP || !BYSUM) {
+      pf[0].v = pack8(pd);
+      pf[1].v = pack8(pd + 8);
+    }
     Philox4 rn[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
     if (DROP && NEXT != 0) philox_begin(rn, jt + 1);
     __builtin_amdgcn_sched_barrier(0);
@@ -251,7 +282,7 @@ __global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0)) void attn_fwd_mfma_kern
     float mt = 0.f;
 #pragma unroll
     for (int idx = 0; idx < NPV; ++idx) {
-      oacc[idx % DT] = mfma32(vfr[idx % kAhead], pf[idx / DT], oacc[idx % DT]);
+      oacc[idx % DT] = mfma32(vfr[idx % kAhead], pf[idx / DT].v, oacc[idx % DT]);
       if (idx + kAhead < NPV) vfr[idx % kAhead] = v_frag(idx + kAhead);
       if (NEXT == 2 && idx == 1) {  // the diagonal tile: keys beyond jlim are masked
         const int j0n = (jt + 1) * BN + 32 * ks;
@@ -259,7 +290,7 @@ __global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0)) void attn_fwd_mfma_kern
         for (int e = 0; e < 16; ++e)
           if (j0n + 16 * (e >> 3) + 8 * hh + (e & 7) > jlim) stn[e] = -INFINITY;
       }
-      if (NEXT != 0 && idx == 2) mt = tile_max(stn);
+      if (!BYSUM && NEXT != 0 && idx == 2) mt = tile_max(stn);
       if (DROP && NEXT != 0) {
 #pragma unroll
         for (int u = (20 * idx) / NPV; u < (20 * (idx + 1)) / NPV; ++u) philox_round(rn[u & 1], P.key0, P.key1, u >> 1);
@@ -273,8 +304,7 @@ __global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0)) void attn_fwd_mfma_kern
       st = stn;
       rnd[0] = rn[0];
       rnd[1] = rn[1];
-      // the running reference exponent only moves when the next tile's maximum exceeds it by more than 2^60
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_ref + kLazyRescale) != 0, 0)) {
+      if (!BYSUM && __builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_ref + 60.0f) != 0, 0)) {
         const float m_new = fmaxf(m_ref, mt);
         const float corr = __builtin_amdgcn_exp2f(m_ref - m_new);
         m_ref = m_new;

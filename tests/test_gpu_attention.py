@@ -354,6 +354,33 @@ def test_column_pass_producer_consumer_ragged(d, s, b, A, p, causal, two_pass, p
     _check_bf16_heads(f"cols-ragged{pers}", sh, q, k, v, do, got, sorted({0, 1, b * A // 2, b * A - 1}))
 
 
+@pytest.mark.parametrize("form", [(0, 0), (0, 1), (0, 3), (1, 0)])
+@pytest.mark.parametrize("d,s,p,causal", [(64, 320, 0.1, 1), (64, 320, 0.0, 0), (96, 328, 0.1, 1), (96, 320, 0.0, 1), (128, 200, 0.1, 0), (160, 392, 0.1, 1), (160, 320, 0.0, 0)])
+def test_forward_scores_that_grow_from_tile_to_tile(d, s, p, causal, form):
+    """Scores that rise by about 70 in powers of two (past the 60 that the running reference exponent leaves alone) from one tile of
+    64 keys to the next, and fall again from 0.57 s on: every form of the forward moves its reference exponent and rescales what it has.
+    Judged as any bf16 output; the scores, up to 200, are fp32 sums of d products (200 x 2^-24 x a few, far below one rounding of P)."""
+    import paper_2205_05198_amd as sar
+    from gpu_util import attn_scales, err_attn_bf16, run_attn
+    from paper_2205_05198_amd.workloads import to_dtype
+    sar.sar_test_force_variants(form[0], form[1], -1, -1)
+    A = 3
+    sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=p, seed=87, offset=17, causal=causal)
+    q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=59)
+    u = np.sign(np.random.default_rng(5).standard_normal(d))
+    j = np.arange(s)
+    ramp = np.minimum(j, 1.6 * s - 1.8 * j) / 64.0  # in tiles of keys
+    q = to_dtype((4.0 * u + q).astype(np.float32), "bf16")
+    k = to_dtype((k + ramp.reshape(s, 1, 1, 1) * u * (48.5 / (4.0 * np.sqrt(d)))).astype(np.float32), "bf16")
+    print(f"growing scores d={d} s={s} p={p} causal={causal} form={form}", flush=True)
+    got = run_attn(sh, "bf16", q, k, v, do)
+    f = oracle.attn_fwd(sh, q, k, v, materialise=True, heads=(0, A))
+    for n in range(A):
+        sc = attn_scales(sh, q, k, v, do, 0, n, f["P"][n], f["M"][n].astype(np.float64), f["D"][n])
+        assert err_attn_bf16(got["o"][:, 0, n], f["o"][:, 0, n], sc["o"]) <= 1.0, n
+        assert np.max(np.abs(got["lse"][0, n] - f["lse"][0, n])) < 2e-3 * (1.0 + np.max(np.abs(f["lse"][0, n])))
+
+
 @pytest.mark.parametrize("d,s,A,p,causal", [(160, 128, 160, 0.1, 1), (64, 72, 240, 0.0, 0), (128, 136, 100, 0.1, 1), (64, 328, 64, 0.1, 1), (160, 264, 120, 0.1, 0),
                                             (96, 840, 36, 0.1, 1), (128, 520, 60, 0.0, 0), (96, 1024, 32, 0.1, 1), (160, 1000, 32, 0.1, 1)])
 def test_dq_product_in_blocks_of_128_rows(d, s, A, p, causal):
