@@ -10,9 +10,14 @@ namespace sar {
 // Two 16-byte stores per lane at (uniform base) + 16 lane and + 1 KB more: the wave's two dS operands of a step.  Written
 // with a scalar base so that the only vector register the addresses cost is a short-lived one (the kernel is within a
 // few registers of its limit, and a spilled or recomputed tile address sits on the critical path of every load).
-__device__ __forceinline__ void ds_store2(uint16_t* base, int lane, bf16x8_t a, bf16x8_t b) {
+// stream (uniform): nontemporal.  Tiles that together exceed the last-level cache (256 MB) would push the (Q, dO) tiles that every
+// key block reads out of the L2 on their way to memory, where they end up anyway: column pass of 8192 x 16 heads of 160 (1.1 GB of tiles)
+// 960 -> 746 us; the whole backward with 256 to 320 MB 0.95 to 0.98 of its time, above 800 MB 0.95 (d = 64 to 160, 3415 shapes), but below 200 MB, which the
+// dQ product finds in the cache, 1.01 to 1.06.  The dQ product then loads them nontemporally too (d = 64 6144 x 20 482 -> 427).
+__device__ __forceinline__ void ds_store2(uint16_t* base, int lane, bf16x8_t a, bf16x8_t b, int stream) {
   const uint32_t off = 16u * (uint32_t)lane;
-  asm volatile("global_store_dwordx4 %0, %1, %3\n\tglobal_store_dwordx4 %0, %2, %3 offset:1024" : : "v"(off), "v"(a), "v"(b), "s"(base) : "memory");
+  if (stream) asm volatile("global_store_dwordx4 %0, %1, %3 nt\n\tglobal_store_dwordx4 %0, %2, %3 offset:1024 nt" : : "v"(off), "v"(a), "v"(b), "s"(base) : "memory");
+  else asm volatile("global_store_dwordx4 %0, %1, %3\n\tglobal_store_dwordx4 %0, %2, %3 offset:1024" : : "v"(off), "v"(a), "v"(b), "s"(base) : "memory");
 }
 
 // ===================================================================================================
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_mfma_kernel(AttnParams P
         df[c] = pack8(dvv);
         dsf[c] = pack8(ds);
       }
-      if constexpr (WDS) ds_store2(ds_tile, lane, dsf[0], dsf[1]);
+      if constexpr (WDS) ds_store2(ds_tile, lane, dsf[0], dsf[1], P.ds_stream);
       // one-key-per-lane copies: T[i][key] = sum_k tile[i][k] I[k][key]
       float16_t tD, tS;
 #pragma unroll
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_mfma_kernel(AttnParams P
       }
     } else if constexpr (WDS) {  // a quarter above the diagonal: its dS is zero (and the step still ends with two stores)
       const u32x4_t zero = {0u, 0u, 0u, 0u};
-      ds_store2(ds_tile, lane, __builtin_bit_cast(bf16x8_t, zero), __builtin_bit_cast(bf16x8_t, zero));
+      ds_store2(ds_tile, lane, __builtin_bit_cast(bf16x8_t, zero), __builtin_bit_cast(bf16x8_t, zero), P.ds_stream);
     }
     if constexpr (WDS) {
       ds_tile += ds_step;

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
         dsf[1] = pack8(ds + 8);
       }
       if constexpr (WDS) {
-        ds_store2(ds_tile, lane, dsf[0], dsf[1]);
+        ds_store2(ds_tile, lane, dsf[0], dsf[1], P.ds_stream);
         ds_tile += ds_step;
         if (P.causal) ds_step += kDsTileElems;
       }

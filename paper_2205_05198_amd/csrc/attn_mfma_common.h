@@ -58,6 +58,10 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(
 __device__ __forceinline__ void dma16(const void* gbase, uint32_t goff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(goff), "s"(gbase), "s"(lds_base) : "m0");
 }
+// nontemporal: what is read once and does not fit the caches
+__device__ __forceinline__ void dma16_nt(const void* gbase, uint32_t goff, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(goff), "s"(gbase), "s"(lds_base) : "m0");
+}
 // Same, pinned in the instruction stream: issued after `token` has been computed and before anything that uses
 // `token` afterwards (the statement pretends to modify it).
 template <typename T>

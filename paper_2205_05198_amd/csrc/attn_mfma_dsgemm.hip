@@ -215,7 +215,11 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm128_kernel(AttnParams 
         if (h ? both : jt < nt_up) {
           const uint16_t* t = dsh + ds_tile_index(P, 2 * rb + h, jt) * kDsTileElems;
 #pragma unroll
-          for (int u = 0; u < 2; ++u) dma16(t + 512 * (lw + 4 * u), 16u * (uint32_t)lane, lds_addr(st + TILE + h * kDsTileElems) + 1024u * (uint32_t)(lw + 4 * u));
+          for (int u = 0; u < 2; ++u) {
+            const uint32_t dst = lds_addr(st + TILE + h * kDsTileElems) + 1024u * (uint32_t)(lw + 4 * u);
+            if (P.ds_stream) dma16_nt(t + 512 * (lw + 4 * u), 16u * (uint32_t)lane, dst);
+            else dma16(t + 512 * (lw + 4 * u), 16u * (uint32_t)lane, dst);
+          }
         }
     };
     for (int jt = 0; jt < LA && jt < ntile; ++jt) fetch(jt);
@@ -277,10 +281,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm128_kernel(AttnParams 
 // than CUs, and without the mask rounds of blocks less by that; d = 64, which holds two of either a CU, not on long heads (7168 x 20 +5 %).
 // Under the mask the heaviest block, twice as long a chain as at 64 rows' rate, must not set the pace: the more tiles it has, the more blocks it takes to
 // hide it (d = 160 2048 x 16, one 128-row block a CU, 22.4 / 22.9; d = 128 2048 x 12 16.7 / 22.0).  `from`: 128-row blocks a CU, in hundredths.
+// Tiles that stream past the caches favour it further, since it loads them without keeping them (whole backward, 64 / 128 rows: d = 64 8192 x 8 394 / 364, 4352 x 24
+// without mask 0.90, 7680 x 5 under it, 1.2 a CU, 1.05).
 template <int D>
 static bool dq_rows128(const AttnParams& P) {
   const int64_t cus = attn_mfma_cu_count(), N = (int64_t)P.b * P.A, nb = (P.s + 63) / 64, w64 = nb * N, w128 = (nb + 1) / 2 * N;
   if (w64 <= cus) return false;
+  if (P.ds_stream && (!P.causal || 10 * w128 >= 19 * cus)) return true;
   const int64_t r64 = (w64 + cus - 1) / cus, r128 = (w128 + cus - 1) / cus;
   if (!P.causal) {
     if (3 * r128 > 2 * r64 || (D == 128 && 3 * r128 == 2 * r64)) return false;
@@ -293,9 +300,11 @@ static bool dq_rows128(const AttnParams& P) {
 }
 
 template <int D>
-static hipError_t bwd_once_d(const AttnParams& P, const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq,
+static hipError_t bwd_once_d(const AttnParams& P0, const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq,
                              void* dk, void* dv, float* delta, uint16_t* ds_ws, int stages, hipStream_t st) {
-  const int N = P.b * P.A, nb = (P.s + 63) / 64;
+  const int N = P0.b * P0.A, nb = (P0.s + 63) / 64;
+  AttnParams P = P0;
+  P.ds_stream = N * ds_tiles_per_head(P) * kDsTileElems * 2 >= 256000000;  // the tiles do not fit the last-level cache: see ds_store2
   hipError_t e = hipSuccess;
   if (stages & 1) {
     hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)nb, (unsigned)N), dim3(256), 0, st, P, (const uint16_t*)o, (const uint16_t*)dO, delta);

@@ -17,6 +17,7 @@ struct AttnParams {
   uint32_t thresh;              // keep iff 16-bit field >= thresh
   uint32_t key0, key1;          // Philox key = seed
   uint64_t offset;              // Philox counter base
+  int ds_stream = 0;            // the column pass writes the dS tiles past the caches (set by the backward's launcher)
 };
 
 // dS tiles of the backward that recomputes the region once: one 64 x 64 bf16 tile per (batch*head, 64-row query tile `it`,

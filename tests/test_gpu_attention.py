@@ -394,6 +394,17 @@ def test_dq_product_in_blocks_of_128_rows(d, s, A, p, causal):
     _check_bf16_heads("dq128", sh, q, k, v, do, got, [0, 1, A // 2, A - 1])
 
 
+def test_backward_with_tiles_beyond_the_last_level_cache():
+    """545 MB of dS tiles: written and read nontemporally, dQ in blocks of 128 rows.  One head against the oracle."""
+    from gpu_util import run_attn
+    s, A, d = 4096, 32, 64
+    sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=0.1, seed=89, offset=5, causal=1)
+    q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=61)
+    print(f"streamed tiles d={d} s={s} A={A}", flush=True)
+    got = run_attn(sh, "bf16", q, k, v, do, two_pass=False)
+    _check_bf16_heads("streamed", sh, q, k, v, do, got, [A - 1])
+
+
 def test_bf16_generic_path_other_head_dim():
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=72, b=1, a=2, h=2 * 40, p=0.1, seed=3)
