@@ -1,18 +1,22 @@
-// bf16 attention core, backward column pass (dK, dV) in its two-waves-per-SIMD form: the work of a (32 keys x 32 query rows)
-// block of every step is divided between a producing and a consuming wave that share a SIMD.
+// bf16 attention core, backward column pass (dK, dV) with three waves per SIMD: the work of a (32 keys x 32 query rows) block of every
+// step is divided between a producing, a consuming and a loading wave that share a SIMD.
 //
 // Why: a wave issues its instructions in order, so with one wave per SIMD a step of the column pass costs the sum of the issue
 // times of its vector instructions, matrix instructions, LDS reads and direct-to-LDS loads (about 3700 cycles at d = 160 for
 // 1400 cycles of matrix-pipe time and 1650 of vector-unit time), and a second wave of the same kind does not fit the register
-// file (two accumulator sets of d/32 x 16 registers plus the arithmetic's working set).  Divided in two, each half fits 256
-// registers, and the halves use different units:
+// file (two accumulator sets of d/32 x 16 registers plus the arithmetic's working set).  Divided in three, each part fits 168
+// registers, and the parts use different units:
 //   producer (waves 0..3)  S^T = K Q^T and dD^T = V dO^T with K and V operands held in registers, then the vector arithmetic:
-//                          P = exp2(alpha log2e S - LSE), Philox mask, D = M P / (1-p), dS = P (dD M / (1-p) - delta); the two
+//                          P = exp2(alpha log2e S - LSE), D = M P / (1-p), dS = P (dD M / (1-p) - delta); the two
 //                          results go, rounded to bf16, as row-major [32 rows][32 keys] tiles to an exchange buffer in LDS
 //                          (and, WDS, dS to the tiles that the dQ product reads);
 //   consumer (waves 4..7)  reads them one key per lane (transposing LDS reads) and accumulates dV^T += dO^T D (two of the
-//                          waves, one per 32 keys, over all 64 rows of the tile) or dK^T += Q^T dS (the other two), and
-//                          issues every direct-to-LDS load of the workgroup.
+//                          waves, one per 32 keys, over all 64 rows of the tile) or dK^T += Q^T dS (the other two);
+//   loader (waves 8..11)   issues every direct-to-LDS load of the workgroup, draws the dropout decisions of its pair's block one
+//                          tile ahead (sixteen bits a lane, through LDS) and copies dK out.
+// With loads and Philox rounds in the consumer's and the producer's streams instead (two waves per SIMD, 256 registers), us, before / now: 2048 x 16
+// heads of 160 57.4 / 54.4, 2048 x 32 of 96 84.2 / 80.8, 8192 x 16 of 160 763 / 716; over 3693 shapes 0.942 of the time, without dropout at d = 128 and 160
+// 0.91.  Long launches run at the card's power limit: 2048 x 16 of 160 takes 6 % fewer cycles at a 3 % lower clock.
 // The consumer works one tile behind the producer; (Q, dO) tiles live in three stages: tile m is loaded during step m-1, read
 // by the producer in step m and by the consumer in step m+1.  One workgroup barrier per step.
 // RAG: s is no multiple of 64 (the last tile's loads are clamped to the last row, and its rows and keys past the end get
@@ -24,7 +28,7 @@
 namespace sar {
 
 template <int D, bool DROP, bool WDS, bool PERS, bool RAG>
-__global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+__global__ __launch_bounds__(768, 1) void attn_bwd_dkdv_split_kernel(AttnParams P, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                                     const uint16_t* __restrict__ v, const float* __restrict__ lse,
                                                                     const uint16_t* __restrict__ dO, const float* __restrict__ delta,
                                                                     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, uint16_t* __restrict__ ds_ws) {
@@ -32,7 +36,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
   constexpr int TILE = 64 * KP;
   __shared__ __attribute__((aligned(16))) uint16_t smem[2 * NST * TILE];  // stage s: Q at 2 s TILE, dO at (2 s + 1) TILE; afterwards the epilogue's buffers
   __shared__ __attribute__((aligned(16))) uint16_t xb[2][4][4][512];      // exchange: [step parity][wave pair][D rows 0..15, D rows 16..31, dS likewise][16 rows x 32 keys]
-  __shared__ float lse_s[NST][BI], delta_s[NST][BI];
+  __shared__ float lse_s[2][BI], delta_s[2][BI];                          // of tile m in [m & 1]
+  __shared__ uint16_t keep_s[2][4][64];                                  // keep bits of a lane's 16 elements: [tile parity][wave pair][lane]
 
   const int N = P.b * P.A;
   const int nb = RAG ? (P.s + BN - 1) / BN : P.s / BN;
@@ -46,8 +51,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
   int kb = wq;
   const int bn = blockIdx.x % N, beta = bn / P.A, n = bn % P.A;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 31, hh = lane >> 5;
-  const bool producer = wave < 4;
-  const int w = wave & 3;  // the pair: waves w and w + 4 sit on SIMD w
+  const int w = wave & 3;  // the trio: waves w, w + 4 and w + 8 sit on SIMD w
   const int kgp = w & 1, is = w >> 1;
   const int64_t base = (int64_t)beta * P.stride_b + (int64_t)n * P.stride_a;
   const int gstride = (int)P.stride_s;
@@ -61,26 +65,30 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
   const uint16_t* qg = q + base;
   const uint16_t* dog = dO + base;
 
-  if (producer) {
+  auto stage_kv = [&](const DmaMap<D>& kvmap, const int kbs, const int sg) __attribute__((always_inline)) {  // four waves: K and V of key block kbs into stage sg
+    uint16_t* Kst = smem + sg * 2 * TILE;
+    const int64_t g0 = base + (int64_t)(kbs * BN) * gstride;
+    if (RAG && kbs == nb - 1) {
+      dma_tile_ragged<D>(kvmap, k + g0, Kst, w, lane, gstride, P.s - kbs * BN);
+      dma_tile_ragged<D>(kvmap, v + g0, Kst + TILE, w, lane, gstride, P.s - kbs * BN);
+    } else {
+      dma_tile<D>(kvmap, k + g0, Kst, w);
+      dma_tile<D>(kvmap, v + g0, Kst + TILE, w);
+    }
+  };
+
+  if (wave < 4) {
     // ---- K and V operands of this wave's 32 keys, for the whole kernel: lane li holds key jw0 + perm_row(li).  They come
     // through LDS (coalesced direct loads into the stage that tile it0 + 1 will take; rows swapped inside groups of 32):
     // fetched straight into registers, every lane reads 20 separate 16-byte pieces of its own row ----
     bf16x8_t kf[KC], vf[KC];
-    DmaMap<D> kvmap;
-    kvmap.init(w, lane, gstride, true);
-    {
-      uint16_t* Kst = smem + stage_of(it0 + 1) * 2 * TILE;
-      if (RAG && kb == nb - 1) {
-        dma_tile_ragged<D>(kvmap, k + base + (int64_t)(kb * BN) * gstride, Kst, w, lane, gstride, P.s - kb * BN);
-        dma_tile_ragged<D>(kvmap, v + base + (int64_t)(kb * BN) * gstride, Kst + TILE, w, lane, gstride, P.s - kb * BN);
-      } else {
-        dma_tile<D>(kvmap, k + base + (int64_t)(kb * BN) * gstride, Kst, w);
-        dma_tile<D>(kvmap, v + base + (int64_t)(kb * BN) * gstride, Kst + TILE, w);
-      }
+    if constexpr (!PERS) {  // (a loader of a persistent workgroup stages later blocks anyway; a second place costs scalar registers, 8192 x 16 of 160 694 -> 710 us)
+      DmaMap<D> kvmap;
+      kvmap.init(w, lane, gstride, true);
+      stage_kv(kvmap, kb, stage_of(it0 + 1));
       dma_wait();
-      __syncthreads();  // the K and V blocks are staged
     }
-    const uint64_t headG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s) * (uint64_t)(P.s >> 3);
+    __syncthreads();  // the K and V blocks are staged
     const float sc2 = P.scale * kLog2e;
     const float log2_keep_scale = __builtin_amdgcn_logf(P.keep_scale), inv_keep_scale = 1.0f / P.keep_scale;  // v_log_f32 is log2
     for (int j = 0;; ++j) {  // key blocks of this workgroup
@@ -114,18 +122,13 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
       for (int e = 0; e < 16; ++e) { st[e] = 0.f; dd[e] = 0.f; }
       const int i = m * BI + 32 * is + li;
       // lse2q: the row's LSE in log2 units minus log2 of 1/(1-p); dlq: delta (1-p)
-      const float lse2q = lse_s[sg][32 * is + li] * kLog2e - log2_keep_scale, dlq = delta_s[sg][32 * is + li] * inv_keep_scale;
+      const float lse2q = lse_s[m & 1][32 * is + li] * kLog2e - log2_keep_scale, dlq = delta_s[m & 1][32 * is + li] * inv_keep_scale;
       // The wave's instructions are ordered by hand so that its matrix instructions always have vector work of the same
       // wave beside them:
       //   1. S^T = K Q^T            between its matrix instructions: the two Philox calls of the tile (indices only);
       //   2. dD^T = V dO^T          between them: P = exp2(..), the keep decisions, D = P M / (1-p) (need S only);
       //   3. dS = P (dD M / (1-p) - delta), rounding to bf16.
-      Philox4 rnd[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-      if (DROP) {
-        const uint64_t rowG = headG + (uint64_t)i * (uint64_t)(P.s >> 3);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) rnd[c] = philox_start(rowG + (uint64_t)((jw0 + 16 * c + 8 * hh) >> 3), 0u);
-      }
+      const uint32_t keep = DROP ? keep_s[m & 1][w][lane] : 0u;
       constexpr int kAhead = 3;
       bf16x8_t qa[kAhead], da[kAhead];
 #pragma unroll
@@ -136,10 +139,6 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
         st = mfma32(kf[kc], qa[kc % kAhead], st);
         if (kc + kAhead < KC) qa[kc % kAhead] = ld_frag(qrow + 16 * (kc + kAhead));
         if (kc >= KC - kAhead) da[kc - (KC - kAhead)] = ld_frag(drow + 16 * (kc - (KC - kAhead)));
-        if (DROP) {
-#pragma unroll
-          for (int u = (20 * kc) / KC; u < (20 * (kc + 1)) / KC; ++u) philox_round(rnd[u & 1], P.key0, P.key1, u >> 1);
-        }
         __builtin_amdgcn_sched_barrier(0);
       }
       // the diagonal tile: keys j > i get probability exp2(-inf) = 0; RAG: rows and keys past the end as well
@@ -168,7 +167,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
           else if (o < 34) {
             const int c = o - 32;
             if (DROP) {
-              keep_select8(rnd[c], P.thresh, reinterpret_cast<const float(&)[8]>(pq[8 * c]), reinterpret_cast<float(&)[8]>(dvv[8 * c]));
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                dvv[8 * c + e] = __uint_as_float(__float_as_uint(pq[8 * c + e]) & (uint32_t)__builtin_amdgcn_sbfe((int)keep, 15 - (8 * c + e), 1));
             } else {
 #pragma unroll
               for (int e = 0; e < 8; ++e) dvv[8 * c + e] = pq[8 * c + e];
@@ -203,55 +204,18 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
       }
     }
     // The consumers' last step and epilogue.  The stage of the last tile becomes the output tiles; of the other two, the
-    // one after it takes the next key block's first (Q, dO) tile (fetched by the consumers), the one after that its K and V.
+    // one after it takes the next key block's first (Q, dO) tile, the one after that its K and V (fetched by the loaders).
     const int so = stage_of(nit - 1);
-    if (has_next) {
-      uint16_t* Kst = smem + ((so + 2) % NST) * 2 * TILE;
-      if (RAG && kb_n == nb - 1) {
-        dma_tile_ragged<D>(kvmap, k + base + (int64_t)(kb_n * BN) * gstride, Kst, w, lane, gstride, P.s - kb_n * BN);
-        dma_tile_ragged<D>(kvmap, v + base + (int64_t)(kb_n * BN) * gstride, Kst + TILE, w, lane, gstride, P.s - kb_n * BN);
-      } else {
-        dma_tile<D>(kvmap, k + base + (int64_t)(kb_n * BN) * gstride, Kst, w);
-        dma_tile<D>(kvmap, v + base + (int64_t)(kb_n * BN) * gstride, Kst + TILE, w);
-      }
-    }
     __syncthreads();  // the consumers are done with the last tile
-    if (has_next) dma_wait();
     __syncthreads();  // the output tiles are complete (and the next K and V blocks staged)
-    lds_rows_to_global<D>(smem + so * 2 * TILE, dk + base + (int64_t)(kb * BN) * P.stride_s, gstride, P.s - kb * BN, tid);
     if (!has_next) break;
     kb = kb_n;
     jw0 = kb * BN + kgp * 32;
     off = (so + 1) % NST;  // before it0 changes: stage_of(new it0) = off
     it0 = P.causal ? kb : 0;
     }  // key blocks
-  } else {
+  } else if (wave < 8) {
     // ---- consumer ----
-    DmaMap<D> map, last;  // last: RAG, the last tile's offsets
-    map.init(w, lane, gstride, false);
-    if constexpr (RAG) last.init(w, lane, gstride, false, P.s - (nit - 1) * BI);
-    auto fetch_to = [&](int it, int round, int sg) __attribute__((always_inline)) {  // rounds 0 .. 2 PER - 1 of tile `it`, into stage sg
-      constexpr int PER = DmaMap<D>::PER;
-      uint16_t* dst = smem + sg * 2 * TILE;
-      if constexpr (RAG) {
-        const int u = round < PER ? round : round - PER, l = w + 4 * u;
-        const uint16_t* src = (round < PER ? qg : dog) + (int64_t)(it * BI) * gstride;
-        if (u < PER - 1 || l < DmaMap<D>::NL)
-          dma16(src, it == nit - 1 ? last.goff[u] : map.goff[u], lds_addr(dst + (round < PER ? 0 : TILE)) + 1024u * (uint32_t)l);
-      } else if (round < PER) dma_one<D>(map, qg + (int64_t)(it * BI) * gstride, dst, w, round);
-      else dma_one<D>(map, dog + (int64_t)(it * BI) * gstride, dst + TILE, w, round - PER);
-    };
-    auto fetch_stats_to = [&](int it, int sg) __attribute__((always_inline)) {  // one float per row, straight into LDS
-      const int r = RAG ? min(lane, P.s - 1 - it * BI) : lane;
-      dma4(lse + (size_t)bn * P.s + it * BI + r, lds_addr(lse_s[sg]));
-      dma4(delta + (size_t)bn * P.s + it * BI + r, lds_addr(delta_s[sg]));
-    };
-    auto fetch = [&](int it, int round) __attribute__((always_inline)) { fetch_to(it, round, stage_of(it)); };
-    auto fetch_stats = [&](int it) __attribute__((always_inline)) { fetch_stats_to(it, stage_of(it)); };
-    constexpr int NR = 2 * DmaMap<D>::PER;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) fetch(it0, r);
-    if (w == 0) fetch_stats(it0);
     __syncthreads();  // the producers have staged K and V (they read them before the first barrier of the loop)
     // Consumer w = (kgp, role): role 0 accumulates dV^T of the pair of producers with key group kgp (both row halves of the
     // tile) from D and dO, role 1 dK^T from dS and Q.  One accumulator set per wave, complete at the end: no merging.
@@ -271,17 +235,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
     for (int m = it0; m <= nit; ++m) {
-      dma_wait();       // this wave's share of tile m has landed
-      __syncthreads();  // ... and everybody's; the producers have written exchange buffer (m - 1) & 1 and read tile m - 1
-      const bool more = m + 1 < nit;
-      if (more && w == 0) fetch_stats(m + 1);
-      if (m == it0) {  // nothing to consume yet
-        if (more) {
-#pragma unroll
-          for (int r = 0; r < NR; ++r) fetch(m + 1, r);
-        }
-        continue;
-      }
+      __syncthreads();  // the producers have written exchange buffer (m - 1) & 1
+      if (m == it0) continue;  // nothing to consume yet
       const int t = m - 1;
       const uint16_t* Ts = smem + stage_of(t) * 2 * TILE + (role ? 0 : TILE);  // Q for dK, dO for dV
       // one-key-per-lane operands straight from the exchange tiles (transposing LDS reads): slot e of lane (li, hh) <-> key li,
@@ -298,12 +253,6 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
           bT[h][X] = u.v;
         }
       }
-      if (more) { fetch(m + 1, 0); fetch(m + 1, 1); }
-      if (PERS && m == nit && has_next) {  // the next key block's first (Q, dO) tile and row statistics, into the stage after this one
-#pragma unroll
-        for (int r = 0; r < NR; ++r) fetch_to(it0_n, r, (so + 1) % NST);
-        if (w == 0) fetch_stats_to(it0_n, (so + 1) % NST);
-      }
       constexpr int kAhead = 3, NP = 4 * DT;
       bf16x8_t ta[kAhead];
       auto tr = [&](int p) __attribute__((always_inline)) {  // product p: rows 16 (p / DT) .. + 15 of the tile, columns 32 (p % DT) ..
@@ -316,13 +265,10 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
       for (int p = 0; p < NP; ++p) {
         acc[p % DT] = mfma32(ta[p % kAhead], bT[p / (2 * DT)][(p / DT) & 1], acc[p % DT]);
         if (p + kAhead < NP) ta[p % kAhead] = tr(p + kAhead);
-        // the rest of the next tile's loads, one after each of the first products: they have the rest of the step to land
-        if (more && 2 + p < NR) fetch(m + 1, 2 + p);
         __builtin_amdgcn_sched_barrier(0);
       }
-      static_assert(NR - 2 <= NP, "more load rounds than products");
     }
-    // ---- scale, round, rows through LDS (the producers' threads copy dK out, the consumers' dV) ----
+    // ---- scale, round, rows through LDS (the loaders' threads copy dK out, the consumers' dV) ----
     __syncthreads();  // every consumer is done with the last tile (the output tiles take its stage)
     acc_to_lds_rows<DT>(smem + (2 * so + (role ? 0 : 1)) * TILE, KP, 32 * kgp + li, acc, role ? P.scale : 1.0f, hh);
     __syncthreads();
@@ -332,6 +278,77 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
     off = (so + 1) % NST;  // before it0 changes: the new first tile's stage
     it0 = it0_n;
     }  // key blocks
+  } else {
+    // ---- loader: every direct load, and the keep bits of the tile after the one that the producers work on ----
+    DmaMap<D> map, last, kvmap;  // last: RAG, the last tile's offsets
+    map.init(w, lane, gstride, false);
+    if constexpr (RAG) last.init(w, lane, gstride, false, P.s - (nit - 1) * BI);
+    if (PERS) kvmap.init(w, lane, gstride, true);
+    const uint64_t headG = P.offset + (((uint64_t)beta * (uint64_t)P.a_global + (uint64_t)(P.head0 + n)) * (uint64_t)P.s) * (uint64_t)(P.s >> 3);
+    auto fetch = [&](const int it, const int sg) __attribute__((always_inline)) {  // tile `it` into stage sg
+      uint16_t* dst = smem + sg * 2 * TILE;
+      const uint16_t* qt = qg + (int64_t)(it * BI) * gstride;
+      const uint16_t* dt = dog + (int64_t)(it * BI) * gstride;
+      if (RAG && it == nit - 1) {
+        dma_tile<D>(last, qt, dst, w);
+        dma_tile<D>(last, dt, dst + TILE, w);
+      } else {
+        dma_tile<D>(map, qt, dst, w);
+        dma_tile<D>(map, dt, dst + TILE, w);
+      }
+      const int r = RAG ? min(lane, P.s - 1 - it * BI) : lane;  // one float per row, straight into LDS
+      if (w == 1) dma4(lse + (size_t)bn * P.s + it * BI + r, lds_addr(lse_s[it & 1]));
+      if (w == 2) dma4(delta + (size_t)bn * P.s + it * BI + r, lds_addr(delta_s[it & 1]));
+    };
+    auto draw = [&](const int it, const int j0) __attribute__((always_inline)) {  // keep bits of pair w's block of tile `it`, keys j0 ..
+      if constexpr (DROP) {
+        const uint64_t rowG = headG + (uint64_t)(it * BI + 32 * is + li) * (uint64_t)(P.s >> 3);
+        Philox4 rnd[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) rnd[c] = philox_start(rowG + (uint64_t)((j0 + 16 * c + 8 * hh) >> 3), 0u);
+#pragma unroll
+        for (int r = 0; r < 10; ++r) {
+          philox_round(rnd[0], P.key0, P.key1, r);
+          philox_round(rnd[1], P.key0, P.key1, r);
+        }
+        uint32_t b = keep_shift8(rnd[0], P.thresh, 0u);
+        b = keep_shift8(rnd[1], P.thresh, b);
+        keep_s[it & 1][w][lane] = (uint16_t)b;
+      }
+    };
+    if (PERS) stage_kv(kvmap, kb, stage_of(it0 + 1));
+    fetch(it0, stage_of(it0));
+    draw(it0, jw0);
+    dma_wait();
+    __syncthreads();  // K, V and the first tile are there
+    for (int j = 0;; ++j) {
+      const int kb_n = PERS ? block_of(j + 1) : nb;
+      const bool has_next = kb_n < nb;
+      const int so = stage_of(nit - 1);
+      for (int m = it0; m <= nit; ++m) {
+        __syncthreads();  // nobody reads tile m - 2 any more
+        if (m + 1 < nit) {
+          fetch(m + 1, stage_of(m + 1));
+          draw(m + 1, jw0);
+          dma_wait();
+        }
+      }
+      const int it0_n = P.causal ? kb_n : 0;
+      if (has_next) {  // the consumers are at the last tile: the other two stages take the next key block's first tile and its K, V
+        stage_kv(kvmap, kb_n, (so + 2) % NST);
+        fetch(it0_n, (so + 1) % NST);
+        draw(it0_n, kb_n * BN + kgp * 32);
+      }
+      __syncthreads();  // the consumers are done with the last tile
+      if (has_next) dma_wait();
+      __syncthreads();  // the output tiles are complete
+      lds_rows_to_global<D>(smem + so * 2 * TILE, dk + base + (int64_t)(kb * BN) * P.stride_s, gstride, P.s - kb * BN, tid - 512);
+      if (!has_next) break;
+      kb = kb_n;
+      jw0 = kb * BN + kgp * 32;
+      off = (so + 1) % NST;
+      it0 = it0_n;
+    }
   }
 }
 

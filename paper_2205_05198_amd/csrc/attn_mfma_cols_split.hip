@@ -1,5 +1,5 @@
-// bf16 attention core, backward column pass (dK, dV) in its producer / consumer form (two waves per SIMD, each within
-// 256 vector registers; compiled WITH -amdgpu-mfma-vgpr-form): every head dimension of the matrix-core path.
+// bf16 attention core, backward column pass (dK, dV) in its producer / consumer form (three waves per SIMD, each within
+// 168 vector registers; compiled WITH -amdgpu-mfma-vgpr-form): every head dimension of the matrix-core path.
 #include "attn_mfma_cols_split.h"
 
 #include <algorithm>
@@ -31,7 +31,7 @@ static hipError_t bwd_dkdv_split_d(const AttnParams& P, const void* q, const voi
   }
   const unsigned grid = use_pers ? (unsigned)(R * N) : (unsigned)(nb * N);
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, st, P, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, lse,
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(768), 0, st, P, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, lse,
                        (const uint16_t*)dO, delta, (uint16_t*)dk, (uint16_t*)dv, ds_ws);
   };
   auto with = [&](auto rag, auto persistent) {

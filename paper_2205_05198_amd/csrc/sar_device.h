@@ -150,6 +150,30 @@ __device__ __forceinline__ void keep_scale8(const Philox4& o, uint32_t T, float 
         "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3), "=&s"(m4), "=&s"(m5), "=&s"(m6), "=&s"(m7)
       : "v"(o.x), "v"(o.y), "v"(o.z), "v"(o.w), "s"(T), "v"(val));
 }
+// The eight decisions of a call shifted into b from the right, element 0 first (bit 7 of the result = element 0 kept): a compare
+// into a scalar register pair and an addition with carry each.
+__device__ __forceinline__ uint32_t keep_shift8(const Philox4& o, uint32_t T, uint32_t b) {
+  uint64_t m0, m1, m2, m3, m4, m5, m6, m7, cy;
+  asm("v_cmp_ge_u32_sdwa %1, %10, %14 src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %2, %10, %14 src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %3, %11, %14 src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %4, %11, %14 src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %5, %12, %14 src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %6, %12, %14 src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %7, %13, %14 src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %8, %13, %14 src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %1\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %2\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %3\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %4\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %5\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %6\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %7\n\t"
+      "v_addc_co_u32_e64 %0, %9, %0, %0, %8"
+      : "+&v"(b), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3), "=&s"(m4), "=&s"(m5), "=&s"(m6), "=&s"(m7), "=&s"(cy)
+      : "v"(o.x), "v"(o.y), "v"(o.z), "v"(o.w), "s"(T));
+  return b;
+}
 // keep bit of a single element e
 __device__ __forceinline__ uint32_t keep_bit1(uint64_t e, uint64_t offset, uint32_t site, uint32_t k0, uint32_t k1, uint32_t T) {
   uint32_t m = keep_bits8(offset + (e >> 3), site, k0, k1, T);
