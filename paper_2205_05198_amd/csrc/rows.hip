@@ -3,7 +3,23 @@
 #include "sar_device.h"
 #include "sar_internal.h"
 
+#include <type_traits>
+
 namespace sar {
+
+// 16 bytes to memory; STREAM: nontemporal.  A result that is large beside the caches is written past them: it would push out what is yet to be
+// read, and is itself gone before the next pass comes to it.  us, kept / past: bias-GeLU forward and backward 8192 x 8192 bf16 128 / 105, 4096 x 10240 75 / 67,
+// 8192 x 3072 44.2 / 43.7; dropout-add + LayerNorm forward and both backwards 4096 x 20480 316 / 300, 8192 x 6144 187 / 174, 4096 x 6144 92.9 / 89.9, but
+// 2048 x 6144 (25 MB a tensor) 53.2 / 54.2 and 16384 x 1024 (34 MB) 67 / 71.  A choice at run time inside one kernel cost more than it gave (512 x 20480 45 / 49).
+template <bool STREAM, typename V>
+__device__ __forceinline__ void store16(void* p, V v) {
+  typedef __attribute__((__vector_size__(16))) uint32_t raw_t;
+  const raw_t r = __builtin_bit_cast(raw_t, v);
+  if (STREAM) __builtin_nontemporal_store(r, reinterpret_cast<raw_t*>(p));
+  else *reinterpret_cast<raw_t*>(p) = r;
+}
+static inline bool rows_stream(int64_t rows, int64_t h, int64_t esz) { return rows * h * esz >= 48000000; }
+static inline bool gelu_stream(int64_t rows, int64_t h, int64_t esz) { return rows * h * esz >= 32000000; }  // nothing of it is read back by the other pass
 
 // 8 consecutive elements (one 16-byte access for bf16, two for fp32) <-> 8 floats
 template <typename T> struct Vec8;
@@ -17,13 +33,14 @@ template <> struct Vec8<uint16_t> {
       f[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
     }
   }
+  template <bool STREAM = false>
   static __device__ __forceinline__ void store(uint16_t* p, const float (&f)[8]) {
     uint4 u;
     u.x = pack_bf16x2(f[0], f[1]);
     u.y = pack_bf16x2(f[2], f[3]);
     u.z = pack_bf16x2(f[4], f[5]);
     u.w = pack_bf16x2(f[6], f[7]);
-    *reinterpret_cast<uint4*>(p) = u;
+    store16<STREAM>(p, u);
   }
 };
 template <> struct Vec8<float> {
@@ -31,9 +48,10 @@ template <> struct Vec8<float> {
     float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
     f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
   }
+  template <bool STREAM = false>
   static __device__ __forceinline__ void store(float* p, const float (&f)[8]) {
-    *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
-    *reinterpret_cast<float4*>(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
+    store16<STREAM>(p, make_float4(f[0], f[1], f[2], f[3]));
+    store16<STREAM>(p + 4, make_float4(f[4], f[5], f[6], f[7]));
   }
 };
 
@@ -368,7 +386,7 @@ __global__ __launch_bounds__(NT) void ln_bwd_kernel(RowsParams P, const T* __res
 }
 
 // many rows.  PF: the next row is requested before this one is worked on (where the registers allow it)
-template <typename T, int NT, int VPT, bool PF>
+template <typename T, int NT, int VPT, bool PF, bool STREAM>
 __global__ __launch_bounds__(NT, 2) void ln_bwd_stream_kernel(RowsParams P, const T* __restrict__ dy, const T* __restrict__ x,
                                                                      const float* __restrict__ mean, const float* __restrict__ rstd,
                                                                      const T* __restrict__ gamma, T* __restrict__ dx, float* __restrict__ part) {
@@ -446,7 +464,7 @@ __global__ __launch_bounds__(NT, 2) void ln_bwd_stream_kernel(RowsParams P, cons
         gr[u].get(g);
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = rs * (dv[e] * g[e] - c1 - (xv[e] - mu) * rs * c2);
-        Vec8<T>::store(dx + r * P.h + 8 * c, out);
+        Vec8<T>::template store<STREAM>(dx + r * P.h + 8 * c, out);
       }
     }
   }
@@ -496,7 +514,7 @@ __global__ __launch_bounds__(256) void bias_dropout_add_kernel(RowsParams P, con
 // The statistics are taken from `out` as it is stored (rounded to T), so that a later ln_bwd, which re-reads the
 // stored row, sees exactly the values mean and rstd belong to.
 // ---------------------------------------------------------------------------------------------------
-template <typename T, int VPT, bool HAS_BIAS>
+template <typename T, int VPT, bool HAS_BIAS, bool STREAM>
 __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T* __restrict__ x, const T* __restrict__ bias, const T* resid,
                                                          const T* __restrict__ gamma, const T* __restrict__ beta, T* out, T* __restrict__ y,
                                                          float* __restrict__ mean, float* __restrict__ rstd) {
@@ -520,7 +538,7 @@ __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T*
         const float xb = HAS_BIAS ? xv[q] + bv[q] : xv[q];
         ov[u][q] = Elem<T>::round(((keep >> q) & 1u) ? fmaf(xb, P.keep_scale, rv[q]) : rv[q]);
       }
-      Vec8<T>::store(out + r * P.h + 8 * c, ov[u]);
+      Vec8<T>::template store<STREAM>(out + r * P.h + 8 * c, ov[u]);
     }
   }
   // shift = the row's first element, held by thread 0: broadcast through LDS
@@ -555,7 +573,7 @@ __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T*
       Vec8<T>::load(beta + 8 * c, bt);
 #pragma unroll
       for (int q = 0; q < 8; ++q) o[q] = fmaf((ov[u][q] - mu) * rs, g[q], bt[q]);
-      Vec8<T>::store(y + r * P.h + 8 * c, o);
+      Vec8<T>::template store<STREAM>(y + r * P.h + 8 * c, o);
     }
   }
   if (threadIdx.x == 0) { mean[r] = mu; rstd[r] = rs; }
@@ -580,7 +598,7 @@ __global__ __launch_bounds__(256) void bda_bwd_kernel(RowsParams P, const T* __r
   Vec8<T>::store(dx + r * P.h + c, o);
 }
 
-template <typename T>
+template <typename T, bool STREAM>
 struct BdaBwdCols {
   static constexpr int kSums = 1;
   typedef Raw8<T> In;
@@ -603,7 +621,7 @@ struct BdaBwdCols {
       o[q] = ((keep >> q) & 1u) ? dv[q] * P.keep_scale : 0.f;
       acc[0][q] += o[q];
     }
-    Vec8<T>::store(dx + r * P.h + col, o);
+    Vec8<T>::template store<STREAM>(dx + r * P.h + col, o);
   }
 };
 
@@ -638,7 +656,7 @@ __device__ __forceinline__ float gelu_grad(float z) {
 
 // One chunk of 8 elements per thread; grid = (rows, chunks of a row / 256): no index division in the kernel (it cost
 // four instructions per element of a kernel that is bound by its vector arithmetic).  More chunks per thread were slower.
-template <typename T, bool HAS_BIAS>
+template <typename T, bool HAS_BIAS, bool STREAM>
 __global__ __launch_bounds__(256) void bias_gelu_fwd_kernel(RowsParams P, const T* __restrict__ x, const T* __restrict__ bias, T* __restrict__ y) {
   const int64_t c = ((int64_t)blockIdx.y * 256 + threadIdx.x) << 3;
   if (c >= P.h) return;
@@ -651,7 +669,7 @@ __global__ __launch_bounds__(256) void bias_gelu_fwd_kernel(RowsParams P, const 
     const float z = HAS_BIAS ? xv[q] + bv[q] : xv[q];
     o[q] = z * gelu_phi_cdf(z);
   }
-  Vec8<T>::store(y + at, o);
+  Vec8<T>::template store<STREAM>(y + at, o);
 }
 
 template <typename T, bool HAS_BIAS>
@@ -669,7 +687,7 @@ __global__ __launch_bounds__(256) void bias_gelu_bwd_kernel(RowsParams P, const 
   Vec8<T>::store(dx + at, o);
 }
 
-template <typename T, bool HAS_BIAS>
+template <typename T, bool HAS_BIAS, bool STREAM>
 struct GeluBwdCols {
   static constexpr int kSums = 1;
   struct In { Raw8<T> x, dy; };
@@ -697,7 +715,7 @@ struct GeluBwdCols {
       o[q] = dv[q] * gelu_grad(xv[q] + bv[q]);
       acc[0][q] += o[q];
     }
-    Vec8<T>::store(dx + r * P.h + col, o);
+    Vec8<T>::template store<STREAM>(dx + r * P.h + col, o);
   }
 };
 
@@ -774,18 +792,24 @@ static hipError_t ln_bwd_t(const RowsParams& P, const void* dy, const void* x, c
     auto go = [&](auto kern, int nt) {
       hipLaunchKernelGGL(kern, dim3(groups), dim3(nt), 0, st, P, (const T*)dy, (const T*)x, mean, rstd, (const T*)gamma, (T*)dx, part);
     };
-    if (nchunk <= 128) go(ln_bwd_stream_kernel<T, 128, 1, true>, 128);
-    else if (nchunk <= 256) go(ln_bwd_stream_kernel<T, 256, 1, true>, 256);
-    else if (nchunk <= 512) go(ln_bwd_stream_kernel<T, 256, 2, true>, 256);
+    auto with = [&](auto threads, auto vpt, auto ahead) {
+      constexpr int NT = decltype(threads)::value, VPT = decltype(vpt)::value;
+      constexpr bool PF = decltype(ahead)::value;
+      if (rows_stream(P.rows, P.h, sizeof(T))) go(ln_bwd_stream_kernel<T, NT, VPT, PF, true>, NT);
+      else go(ln_bwd_stream_kernel<T, NT, VPT, PF, false>, NT);
+    };
+    if (nchunk <= 128) with(std::integral_constant<int, 128>(), std::integral_constant<int, 1>(), std::integral_constant<bool, true>());
+    else if (nchunk <= 256) with(std::integral_constant<int, 256>(), std::integral_constant<int, 1>(), std::integral_constant<bool, true>());
+    else if (nchunk <= 512) with(std::integral_constant<int, 256>(), std::integral_constant<int, 2>(), std::integral_constant<bool, true>());
     else switch ((nchunk + 511) / 512) {
-      case 2: go(ln_bwd_stream_kernel<T, 512, 2, true>, 512); break;
-      case 3: go(ln_bwd_stream_kernel<T, 512, 3, true>, 512); break;
-      case 4: go(ln_bwd_stream_kernel<T, 512, 4, half>, 512); break;
-      case 5: go(ln_bwd_stream_kernel<T, 512, 5, half>, 512); break;
+      case 2: with(std::integral_constant<int, 512>(), std::integral_constant<int, 2>(), std::integral_constant<bool, true>()); break;
+      case 3: with(std::integral_constant<int, 512>(), std::integral_constant<int, 3>(), std::integral_constant<bool, true>()); break;
+      case 4: with(std::integral_constant<int, 512>(), std::integral_constant<int, 4>(), std::integral_constant<bool, half>()); break;
+      case 5: with(std::integral_constant<int, 512>(), std::integral_constant<int, 5>(), std::integral_constant<bool, half>()); break;
       default:
         if constexpr (half) {
-          if (nchunk <= 3072) go(ln_bwd_stream_kernel<T, 512, 6, false>, 512);
-          else go(ln_bwd_stream_kernel<T, 512, 7, false>, 512);
+          if (nchunk <= 3072) with(std::integral_constant<int, 512>(), std::integral_constant<int, 6>(), std::integral_constant<bool, false>());
+          else with(std::integral_constant<int, 512>(), std::integral_constant<int, 7>(), std::integral_constant<bool, false>());
         }
     }
     const hipError_t e = hipGetLastError();
@@ -851,8 +875,9 @@ static hipError_t bda_ln_t(const RowsParams& P, const void* x, const void* bias,
   int threads;
   const int vpt = pick_vpt(P.h, threads);
   dim3 grid((unsigned)P.rows), block(threads);
-#define SAR_BDA_LN(V, B) hipLaunchKernelGGL((bda_ln_fwd_kernel<T, V, B>), grid, block, 0, st, P, (const T*)x, (const T*)bias, (const T*)resid, \
+#define SAR_BDA_LN_S(V, B, S) hipLaunchKernelGGL((bda_ln_fwd_kernel<T, V, B, S>), grid, block, 0, st, P, (const T*)x, (const T*)bias, (const T*)resid, \
                                             (const T*)gamma, (const T*)beta, (T*)out, (T*)y, mean, rstd)
+#define SAR_BDA_LN(V, B) do { if (rows_stream(P.rows, P.h, sizeof(T))) SAR_BDA_LN_S(V, B, true); else SAR_BDA_LN_S(V, B, false); } while (0)
 #define SAR_BDA_LN_V(V) do { if (bias) SAR_BDA_LN(V, true); else SAR_BDA_LN(V, false); } while (0)
   switch (vpt) {
     case 1: SAR_BDA_LN_V(1); break;
@@ -862,6 +887,7 @@ static hipError_t bda_ln_t(const RowsParams& P, const void* x, const void* bias,
   }
 #undef SAR_BDA_LN_V
 #undef SAR_BDA_LN
+#undef SAR_BDA_LN_S
   return hipGetLastError();
 }
 
@@ -903,7 +929,9 @@ static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, flo
     hipLaunchKernelGGL((bda_bwd_kernel<T>), dim3((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), dim3(256), 0, st, P, (const T*)dout, (T*)dx);
     return hipGetLastError();
   }
-  return launch_colsum(BdaBwdCols<T>{P, (const T*)dout, (T*)dx}, P.rows, P.h, bda_bwd_plan(P.rows, P.h, sizeof(T) == 2), dbias, (float*)ws, st);
+  const ColPlan pl = bda_bwd_plan(P.rows, P.h, sizeof(T) == 2);
+  if (rows_stream(P.rows, P.h, sizeof(T))) return launch_colsum(BdaBwdCols<T, true>{P, (const T*)dout, (T*)dx}, P.rows, P.h, pl, dbias, (float*)ws, st);
+  return launch_colsum(BdaBwdCols<T, false>{P, (const T*)dout, (T*)dx}, P.rows, P.h, pl, dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
@@ -913,8 +941,9 @@ hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const voi
 template <typename T>
 static hipError_t bias_gelu_fwd_t(const RowsParams& P, const void* x, const void* bias, void* y, hipStream_t st) {
   dim3 grid((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), block(256);
-  if (bias) hipLaunchKernelGGL((bias_gelu_fwd_kernel<T, true>), grid, block, 0, st, P, (const T*)x, (const T*)bias, (T*)y);
-  else hipLaunchKernelGGL((bias_gelu_fwd_kernel<T, false>), grid, block, 0, st, P, (const T*)x, (const T*)bias, (T*)y);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)x, (const T*)bias, (T*)y); };
+  if (gelu_stream(P.rows, P.h, sizeof(T))) bias ? go(bias_gelu_fwd_kernel<T, true, true>) : go(bias_gelu_fwd_kernel<T, false, true>);
+  else bias ? go(bias_gelu_fwd_kernel<T, true, false>) : go(bias_gelu_fwd_kernel<T, false, false>);
   return hipGetLastError();
 }
 
@@ -932,8 +961,12 @@ static hipError_t bias_gelu_bwd_t(const RowsParams& P, const void* dy, const voi
     return hipGetLastError();
   }
   const ColPlan pl = bias_gelu_bwd_plan(P.rows, P.h, sizeof(T) == 2);
-  if (bias) return launch_colsum(GeluBwdCols<T, true>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, pl, dbias, (float*)ws, st);
-  return launch_colsum(GeluBwdCols<T, false>{P, (const T*)dy, (const T*)x, nullptr, (T*)dx, {}}, P.rows, P.h, pl, dbias, (float*)ws, st);
+  auto go = [&](auto has_bias, auto stream) {
+    return launch_colsum(GeluBwdCols<T, decltype(has_bias)::value, decltype(stream)::value>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, pl, dbias,
+                         (float*)ws, st);
+  };
+  if (gelu_stream(P.rows, P.h, sizeof(T))) return bias ? go(std::true_type(), std::true_type()) : go(std::false_type(), std::true_type());
+  return bias ? go(std::true_type(), std::false_type()) : go(std::false_type(), std::false_type());
 }
 
 hipError_t launch_bias_gelu_bwd(const RowsParams& P, bool bf16, const void* dy, const void* x, const void* bias, void* dx, float* dbias, void* ws,

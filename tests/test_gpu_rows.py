@@ -269,3 +269,13 @@ def test_column_sums(rows, h, dtype):
     else:
         assert bool(((dx.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-3 * ref.square().mean().sqrt()).all())
     close(c0, ref.sum(0), "f32")
+
+
+@pytest.mark.parametrize("rows,h,dtype", [(4096, 6152, "bf16"), (1600, 8200, "f32")])
+def test_results_written_past_the_caches(rows, h, dtype):
+    """Tensors of 50 MB and more, whose results are stored nontemporally: the same references as at every size, odd widths."""
+    test_layernorm(rows, h, dtype)
+    test_bias_dropout_add_ln_fwd(rows, h, dtype, 0.1, True)
+    test_bias_dropout_add_bwd(rows, h, dtype, 0.1)
+    test_bias_gelu(rows, h, dtype, True)
+    test_bias_gelu(rows, h, dtype, False)
