@@ -281,6 +281,13 @@ sar_status bias_gelu_bwd(const sar_rows_desc* desc, const void* dy, const void* 
  * Process-wide; not meant to be changed while another thread launches.
  */
 void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_loader_waves, int dkdv_pipelined);
+/*
+ * More of the same; the results are the same whichever runs.  Each argument: -1 = the library's choice by shape, 0 = off, 1 = on.
+ *   dq_128_rows       recompute-once backward: the dQ product in blocks of 128 instead of 64 query rows
+ *   ds_stream         recompute-once backward: the dS tiles written (and by the 128-row dQ product read) past the caches
+ *   row_stream        row passes: results written past the caches
+ */
+void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream);
 
 /*
  * Measurement hooks, not part of the method: the rates this GPU attains on the two rooflines that bound the kernels above.

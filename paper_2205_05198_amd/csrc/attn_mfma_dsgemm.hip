@@ -9,8 +9,16 @@
 //   3. attn_bwd_dq_gemm(128)_kernel dQ = alpha dS K                               (reads the tiles and K)
 // 5 contractions are executed instead of 7, and Philox and the exponentials run once per backward instead of twice.
 #include "attn_mfma_common.h"
+#include <atomic>
 
 namespace sar {
+
+// sar_test_force_forms (tests, measurements) overrides the choices: -1 = by shape, 0 / 1 = off / on
+static std::atomic<int> g_force_dq128{-1}, g_force_ds_stream{-1};
+void attn_mfma_force_bwd_once(int dq128, int ds_stream) {
+  g_force_dq128 = dq128;
+  g_force_ds_stream = ds_stream;
+}
 
 // ---------------------------------------------------------------------------------------------------
 // delta: one workgroup per 64 rows of one (batch, head).  Thread t takes the 16-byte chunks t, t + 256, ... of the
@@ -285,6 +293,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm128_kernel(AttnParams 
 // without mask 0.90, 7680 x 5 under it, 1.2 a CU, 1.05).
 template <int D>
 static bool dq_rows128(const AttnParams& P) {
+  if (const int force = g_force_dq128.load(); force >= 0) return force != 0;
   const int64_t cus = attn_mfma_cu_count(), N = (int64_t)P.b * P.A, nb = (P.s + 63) / 64, w64 = nb * N, w128 = (nb + 1) / 2 * N;
   if (w64 <= cus) return false;
   if (P.ds_stream && (!P.causal || 10 * w128 >= 19 * cus)) return true;
@@ -304,7 +313,8 @@ static hipError_t bwd_once_d(const AttnParams& P0, const void* q, const void* k,
                              void* dk, void* dv, float* delta, uint16_t* ds_ws, int stages, hipStream_t st) {
   const int N = P0.b * P0.A, nb = (P0.s + 63) / 64;
   AttnParams P = P0;
-  P.ds_stream = N * ds_tiles_per_head(P) * kDsTileElems * 2 >= 256000000;  // the tiles do not fit the last-level cache: see ds_store2
+  const int stream = g_force_ds_stream.load();
+  P.ds_stream = stream >= 0 ? stream != 0 : N * ds_tiles_per_head(P) * kDsTileElems * 2 >= 256000000;  // the tiles do not fit the last-level cache: see ds_store2
   hipError_t e = hipSuccess;
   if (stages & 1) {
     hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)nb, (unsigned)N), dim3(256), 0, st, P, (const uint16_t*)o, (const uint16_t*)dO, delta);

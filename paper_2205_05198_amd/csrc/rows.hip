@@ -3,6 +3,7 @@
 #include "sar_device.h"
 #include "sar_internal.h"
 
+#include <atomic>
 #include <type_traits>
 
 namespace sar {
@@ -18,8 +19,14 @@ __device__ __forceinline__ void store16(void* p, V v) {
   if (STREAM) __builtin_nontemporal_store(r, reinterpret_cast<raw_t*>(p));
   else *reinterpret_cast<raw_t*>(p) = r;
 }
-static inline bool rows_stream(int64_t rows, int64_t h, int64_t esz) { return rows * h * esz >= 48000000; }
-static inline bool gelu_stream(int64_t rows, int64_t h, int64_t esz) { return rows * h * esz >= 32000000; }  // nothing of it is read back by the other pass
+static std::atomic<int> g_force_stream{-1};  // sar_test_force_forms (tests, measurements)
+void rows_force_stream(int force) { g_force_stream = force; }
+static inline bool stream_from(int64_t bytes, int64_t least) {
+  const int force = g_force_stream.load(std::memory_order_relaxed);
+  return force >= 0 ? force != 0 : bytes >= least;
+}
+static inline bool rows_stream(int64_t rows, int64_t h, int64_t esz) { return stream_from(rows * h * esz, 48000000); }
+static inline bool gelu_stream(int64_t rows, int64_t h, int64_t esz) { return stream_from(rows * h * esz, 32000000); }  // nothing of it is read back by the other pass
 
 // 8 consecutive elements (one 16-byte access for bf16, two for fp32) <-> 8 floats
 template <typename T> struct Vec8;

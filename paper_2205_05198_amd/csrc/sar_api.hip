@@ -169,6 +169,11 @@ void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_load
   sar::attn_mfma_force_dkdv_pipelined(dkdv_pipelined);
 }
 
+void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream) {
+  sar::attn_mfma_force_bwd_once(dq_128_rows, ds_stream);
+  sar::rows_force_stream(row_stream);
+}
+
 // passes: two-pass backward, bit 0 = row pass, bit 1 = column pass.  stages (passes == 0): the backward that recomputes the
 // region once, bit 0 = delta, bit 1 = column pass + dS tiles, bit 2 = dQ from the tiles.  passes == 3 and stages == 7: the
 // whole backward, by whichever of the two the workspace allows.

@@ -74,9 +74,11 @@ hipError_t launch_attn_bwd_once_mfma(const AttnParams& P, const void* q, const v
 // test hook: force kernel variants (-1 = the library's choice, 0 / 1 = off / on)
 void attn_mfma_force_variants(int fwd128, int fwdlw, int dqlw);
 void attn_mfma_force_dkdv_pipelined(int force);
+void attn_mfma_force_bwd_once(int dq128, int ds_stream);
 int attn_mfma_cu_count();  // compute units of the current device, asked once
 
 // rows.hip: LayerNorm forward/backward and bias-dropout-add on [rows, h]
+void rows_force_stream(int force);  // test hook: results past the caches: -1 = by size, 0 / 1 = off / on
 hipError_t launch_ln_fwd(const RowsParams& P, bool bf16, const void* x, const void* gamma, const void* beta, void* y, float* mean,
                          float* rstd, hipStream_t st);
 size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16);

@@ -37,8 +37,10 @@ def _library_picks_variants():
     """Every test starts and ends with the library choosing its kernel variants."""
     import paper_2205_05198_amd as sar
     sar.sar_test_force_variants(-1, -1, -1, -1)
+    sar.sar_test_force_forms(-1, -1, -1)
     yield
     sar.sar_test_force_variants(-1, -1, -1, -1)
+    sar.sar_test_force_forms(-1, -1, -1)
 
 
 def _check_bf16_heads(tag, sh, q, k, v, do, got, heads, peaked=False):
@@ -384,14 +386,40 @@ def test_forward_scores_that_grow_from_tile_to_tile(d, s, p, causal, form):
 @pytest.mark.parametrize("d,s,A,p,causal", [(160, 128, 160, 0.1, 1), (64, 72, 240, 0.0, 0), (128, 136, 100, 0.1, 1), (64, 328, 64, 0.1, 1), (160, 264, 120, 0.1, 0),
                                             (96, 840, 36, 0.1, 1), (128, 520, 60, 0.0, 0), (96, 1024, 32, 0.1, 1), (160, 1000, 32, 0.1, 1)])
 def test_dq_product_in_blocks_of_128_rows(d, s, A, p, causal):
-    """The dQ product of the recompute-once backward where it runs in blocks of 128 rows (many blocks a compute unit): two to sixteen
+    """The dQ product of the recompute-once backward in blocks of 128 rows, at shapes of many blocks a compute unit: two to sixteen
     tiles a block, with and without a lower half in the last block, sequences that end inside a tile, with and without the mask."""
+    import paper_2205_05198_amd as sar
     from gpu_util import run_attn
+    sar.sar_test_force_forms(1, -1, -1)
     sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=p, seed=83, offset=(1 << 32) - 99, causal=causal)
     q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=53)
     print(f"dq in 128 rows d={d} s={s} A={A} causal={causal} p={p}", flush=True)
     got = run_attn(sh, "bf16", q, k, v, do, two_pass=False)
     _check_bf16_heads("dq128", sh, q, k, v, do, got, [0, 1, A // 2, A - 1])
+
+
+@pytest.mark.parametrize("rows128,stream,cols", [(0, 0, 2), (0, 1, 0), (0, 1, 3), (1, 0, 2), (1, 1, 0), (1, 1, 2), (1, 1, 3)])
+@pytest.mark.parametrize("d", [64, 96, 128, 160])
+@pytest.mark.parametrize("s,causal", [(8, 1), (64, 0), (128, 1), (200, 0), (264, 1), (320, 0)])
+def test_dq_product_forms(d, s, causal, rows128, stream, cols):
+    """The dQ product in blocks of 64 and of 128 rows on one to five tiles, with tiles that the column pass (plain: 0, producer /
+    consumer: 2, persistent: 3) wrote through the caches and past them.  All forms of one shape read the same tiles and add the same
+    products, those of 64 rows in two halves: dK, dV are the same bits, dQ differs by the order of fp32 sums, one rounding."""
+    import paper_2205_05198_amd as sar
+    from gpu_util import run_attn
+    p = 0.0 if cols == 0 else 0.1
+    sh = oracle.AttnShape(s=s, b=2, a=3, h=3 * d, p=p, seed=91, offset=(1 << 32) - 55, causal=causal)
+    q, k, v, do = attn_inputs(s, 2, 3, d, "bf16", seed=67)
+    print(f"dq forms rows128={rows128} stream={stream} cols={cols} d={d} s={s} causal={causal}", flush=True)
+    sar.sar_test_force_variants(-1, -1, -1, cols)
+    sar.sar_test_force_forms(0, 0, -1)
+    ref = run_attn(sh, "bf16", q, k, v, do, two_pass=False)
+    sar.sar_test_force_forms(rows128, stream, -1)
+    got = run_attn(sh, "bf16", q, k, v, do, two_pass=False)
+    assert np.array_equal(got["dk"], ref["dk"]) and np.array_equal(got["dv"], ref["dv"])
+    if not rows128:
+        assert np.array_equal(got["dq"], ref["dq"])
+    _check_bf16_heads("dq-forms", sh, q, k, v, do, got, [0, 5])
 
 
 def test_backward_with_tiles_beyond_the_last_level_cache():
