@@ -286,8 +286,9 @@ void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_load
  *   dq_128_rows       recompute-once backward: the dQ product in blocks of 128 instead of 64 query rows
  *   ds_stream         recompute-once backward: the dS tiles written (and by the 128-row dQ product read) past the caches
  *   row_stream        row passes: results written past the caches
+ *   cols_grid_blocks  (a number, or -1) producer / consumer column pass: most key blocks of one launch; more go in several
  */
-void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream);
+void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream, int cols_grid_blocks);
 
 /*
  * Measurement hooks, not part of the method: the rates this GPU attains on the two rooflines that bound the kernels above.

@@ -10,6 +10,9 @@ namespace sar {
 // persistent workgroups (a forced form that does not exist falls back: 0 to 2 at d = 128, 160 and, with dropout and the tiles, at d = 96; 1 to 0; 3 to 2)
 static std::atomic<int> g_force_form{-1};
 void attn_mfma_force_dkdv_pipelined(int force) { g_force_form = force; }
+// most key blocks of one launch of the producer / consumer form: <= 0 what a grid holds (tests force the division of a launch)
+static std::atomic<int> g_force_grid_blocks{-1};
+void attn_mfma_force_grid_blocks(int force) { g_force_grid_blocks = force; }
 
 hipError_t launch_attn_bwd_dkdv_mfma_small(const AttnParams& P, const void* q, const void* k, const void* v, const float* lse, const void* dO,
                                            const float* delta, void* dk, void* dv, uint16_t* ds_ws, hipStream_t st);  // attn_mfma_cols_small.hip
@@ -54,9 +57,39 @@ static int split_pers() {
   return force == 2 ? 0 : force == 3 ? 1 : -1;
 }
 
+// A grid holds fewer than 2^32 threads, with 768 a workgroup 5.6 million key blocks: more of them (65535 heads of 86 blocks and up) go in
+// two launches, each with half of the batches, or of one batch's heads.
+static constexpr int64_t kGridBlocks = ((1ll << 32) - 1) / 768;
+static hipError_t launch_split(const AttnParams& P, const void* q, const void* k, const void* v, const float* lse, const void* dO, const float* delta, void* dk,
+                               void* dv, uint16_t* ds_ws, int pers, hipStream_t st) {
+  const int64_t nb = (P.s + 63) / 64, N = (int64_t)P.b * P.A;
+  const int force = g_force_grid_blocks.load();
+  if (N == 1 || nb * N <= (force > 0 ? force : kGridBlocks)) return launch_attn_bwd_dkdv_mfma_split(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, pers, st);
+  AttnParams lo = P, hi = P;
+  int64_t at, n;  // elements and heads before the upper half
+  if (P.b > 1) {
+    lo.b = P.b / 2;
+    hi.b = P.b - lo.b;
+    at = lo.b * P.stride_b;
+    n = (int64_t)lo.b * P.A;
+    hi.offset += (uint64_t)lo.b * (uint64_t)P.a_global * (uint64_t)P.s * (uint64_t)(P.s >> 3);
+  } else {
+    lo.A = P.A / 2;
+    hi.A = P.A - lo.A;
+    hi.head0 += lo.A;
+    at = lo.A * P.stride_a;
+    n = lo.A;
+  }
+  if (const hipError_t e = launch_split(lo, q, k, v, lse, dO, delta, dk, dv, ds_ws, pers, st); e != hipSuccess) return e;
+  auto in = [&](const void* t) { return (const void*)((const uint16_t*)t + at); };
+  auto out = [&](void* t) { return (void*)((uint16_t*)t + at); };
+  return launch_split(hi, in(q), in(k), in(v), lse + n * P.s, in(dO), delta + n * P.s, out(dk), out(dv),
+                      ds_ws ? ds_ws + n * ds_tiles_per_head(P) * kDsTileElems : nullptr, pers, st);
+}
+
 hipError_t launch_attn_bwd_dkdv_mfma(const AttnParams& P, const void* q, const void* k, const void* v, const float* lse, const void* dO,
                                      const float* delta, void* dk, void* dv, uint16_t* ds_ws, hipStream_t st) {
-  if (dkdv_split(P, ds_ws)) return launch_attn_bwd_dkdv_mfma_split(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, split_pers(), st);
+  if (dkdv_split(P, ds_ws)) return launch_split(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, split_pers(), st);
   return launch_attn_bwd_dkdv_mfma_small(P, q, k, v, lse, dO, delta, dk, dv, ds_ws, st);
 }
 

@@ -169,7 +169,8 @@ void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_load
   sar::attn_mfma_force_dkdv_pipelined(dkdv_pipelined);
 }
 
-void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream) {
+void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream, int cols_grid_blocks) {
+  sar::attn_mfma_force_grid_blocks(cols_grid_blocks);
   sar::attn_mfma_force_bwd_once(dq_128_rows, ds_stream);
   sar::rows_force_stream(row_stream);
 }

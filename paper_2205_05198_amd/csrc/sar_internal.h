@@ -75,6 +75,7 @@ hipError_t launch_attn_bwd_once_mfma(const AttnParams& P, const void* q, const v
 void attn_mfma_force_variants(int fwd128, int fwdlw, int dqlw);
 void attn_mfma_force_dkdv_pipelined(int force);
 void attn_mfma_force_bwd_once(int dq128, int ds_stream);
+void attn_mfma_force_grid_blocks(int force);
 int attn_mfma_cu_count();  // compute units of the current device, asked once
 
 // rows.hip: LayerNorm forward/backward and bias-dropout-add on [rows, h]

@@ -37,10 +37,10 @@ def _library_picks_variants():
     """Every test starts and ends with the library choosing its kernel variants."""
     import paper_2205_05198_amd as sar
     sar.sar_test_force_variants(-1, -1, -1, -1)
-    sar.sar_test_force_forms(-1, -1, -1)
+    sar.sar_test_force_forms(-1, -1, -1, -1)
     yield
     sar.sar_test_force_variants(-1, -1, -1, -1)
-    sar.sar_test_force_forms(-1, -1, -1)
+    sar.sar_test_force_forms(-1, -1, -1, -1)
 
 
 def _check_bf16_heads(tag, sh, q, k, v, do, got, heads, peaked=False):
@@ -354,6 +354,53 @@ def test_column_pass_producer_consumer_ragged(d, s, b, A, p, causal, two_pass, p
     print(f"column pass ragged form={pers} d={d} s={s} b={b} A={A} causal={causal} p={p} two_pass={two_pass}", flush=True)
     got = run_attn(sh, "bf16", q, k, v, do, two_pass=two_pass)
     _check_bf16_heads(f"cols-ragged{pers}", sh, q, k, v, do, got, sorted({0, 1, b * A // 2, b * A - 1}))
+
+
+@pytest.mark.parametrize("d,p,causal,two_pass", [(128, 0.1, 1, False), (160, 0.0, 0, False), (64, 0.1, 0, True), (96, 0.25, 1, True)])
+@pytest.mark.parametrize("b,A,blocks", [(3, 5, 20), (3, 5, 7), (1, 7, 9), (2, 3, 1)])
+def test_column_pass_in_several_launches(b, A, blocks, d, p, causal, two_pass):
+    """The producer / consumer column pass divided over launches, by batches and then by heads: the same bits as in one launch (the
+    heads' mask, row statistics, tiles and outputs are those of their own place)."""
+    import paper_2205_05198_amd as sar
+    from gpu_util import run_attn
+    s = 200
+    sh = oracle.AttnShape(s=s, b=b, a=A * 2, h=A * 2 * d, t=2, rank=1, p=p, seed=101, offset=(1 << 32) - 5, causal=causal)
+    q, k, v, do = attn_inputs(s, b, A, d, "bf16", seed=71)
+    print(f"several launches b={b} A={A} blocks={blocks} d={d} p={p} causal={causal}", flush=True)
+    sar.sar_test_force_variants(-1, -1, -1, 2)
+    ref = run_attn(sh, "bf16", q, k, v, do, two_pass=two_pass)
+    sar.sar_test_force_forms(-1, -1, -1, blocks)
+    got = run_attn(sh, "bf16", q, k, v, do, two_pass=two_pass)
+    for nm in ("dq", "dk", "dv"):
+        assert np.array_equal(got[nm], ref[nm]), nm
+
+
+def test_column_pass_of_more_blocks_than_a_grid_holds():
+    """65535 batches of 86 key blocks, 5.6 million workgroups of 768 threads: more threads than the 2^32 of a grid, and within the entry point's
+    limits.  The batches share their memory (stride 0), so all of them write the same values: those of one batch alone."""
+    import torch
+    import paper_2205_05198_amd as sar
+    from paper_2205_05198_amd.binding import SAR_BF16
+    s, d, b = 5448, 128, 65535
+    g = torch.Generator(device="cuda").manual_seed(97)
+    q, k, v, do = (torch.randn(s, 1, 1, d, device="cuda", generator=g).to(torch.bfloat16) for _ in range(4))
+    o, dq, dk, dv, dk1, dv1 = (torch.empty_like(q) for _ in range(6))
+    one = sar.AttnDesc.packed(s, 1, 1, d, dtype=SAR_BF16, causal=1)
+    lse = torch.empty(1, 1, s, dtype=torch.float32, device="cuda")
+    ws = torch.empty(sar.attn_core_bwd_workspace_min(one), dtype=torch.uint8, device="cuda")
+    sar.attn_core_fwd(one, q, k, v, o, lse)
+    sar.attn_core_bwd_recompute_dq(one, q, k, v, o, lse, do, dq, ws)
+    sar.attn_core_bwd_recompute_dkdv(one, q, k, v, lse, do, dk1, dv1, ws)
+    many = sar.AttnDesc.packed(s, b, 1, d, dtype=SAR_BF16, causal=1)
+    many.stride_s, many.stride_b = d, 0
+    delta = ws.view(torch.float32)[:s].repeat(b)
+    ws = torch.empty(sar.attn_core_bwd_workspace_min(many), dtype=torch.uint8, device="cuda")
+    ws.view(torch.float32)[:delta.numel()] = delta
+    lse = lse.expand(b, 1, s).contiguous()
+    print(f"column pass of {b} x {(s + 63) // 64} blocks", flush=True)
+    sar.attn_core_bwd_recompute_dkdv(many, q, k, v, lse, do, dk, dv, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dk, dk1) and torch.equal(dv, dv1)
 
 
 @pytest.mark.parametrize("form", [(0, 0), (0, 1), (0, 3), (1, 0)])
