@@ -274,20 +274,24 @@ sar_status bias_gelu_bwd(const sar_rows_desc* desc, const void* dy, const void* 
  *                     exceed the number of compute units; otherwise 3 behaves as 1).  2 is a form that no longer exists: as 1
  *   dq_loader_waves   the same (0, 1) for the row pass of the recompute-twice backward
  *   dkdv_pipelined    form of the column pass: 0 plain (head dimension 64, and 96 without dropout or in the recompute-twice
- *                     backward; otherwise as 2); 2 producer / consumer (two waves per SIMD: one computes scores, softmax, mask and
- *                     dS, the other accumulates dK, dV), one key block per workgroup; 3 the same with persistent workgroups that
+ *                     backward; otherwise as 2); 2 producer / consumer (three waves per SIMD: one computes scores, softmax and dS, one
+ *                     accumulates dK, dV, one fetches the tiles and draws the mask), one key block per workgroup; 3 the same with persistent workgroups that
  *                     each take several key blocks (only when b x heads does not exceed the number of compute units; otherwise
  *                     as 2).  1 is a form that no longer exists: as 0
  * Process-wide; not meant to be changed while another thread launches.
  */
 void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_loader_waves, int dkdv_pipelined);
 /*
- * More of the same; the results are the same whichever runs.  Each argument: -1 = the library's choice by shape, 0 = off, 1 = on.
+ * sar_test_chosen_forms: which forms a call of the bf16 matrix-core kernels would run (host only), into forms[3]: the forward's (0 plain, 1 loader
+ *   waves, 2 persistent, 3 128 rows), the column pass's (0 plain, 2 producer / consumer, 3 persistent; with_tiles: of the recompute-once backward, else of the
+ *   recompute-twice one) and the dQ product's of the former (0 / 1: 64 / 128 rows, + 2: tiles past the caches); -1: the call takes other kernels.
+ * sar_test_force_forms: more to force; the results are the same whichever runs.  Each argument: -1 = the library's choice by shape, 0 = off, 1 = on.
  *   dq_128_rows       recompute-once backward: the dQ product in blocks of 128 instead of 64 query rows
  *   ds_stream         recompute-once backward: the dS tiles written (and by the 128-row dQ product read) past the caches
  *   row_stream        row passes: results written past the caches
  *   cols_grid_blocks  (a number, or -1) producer / consumer column pass: most key blocks of one launch; more go in several
  */
+void sar_test_chosen_forms(const sar_attn_desc* desc, int with_tiles, int* forms);
 void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream, int cols_grid_blocks);
 
 /*

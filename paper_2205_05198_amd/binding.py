@@ -122,6 +122,7 @@ def load_library():
         "attn_core_bwd_workspace_min": (sz, [ad]),
         "attn_core_bwd_recompute_stages": (ctypes.c_int, [ad, ctypes.c_int, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]),
         "sar_test_force_variants": (None, [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]),
+        "sar_test_chosen_forms": (None, [ad, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]),
         "sar_test_force_forms": (None, [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]),
         "attn_core_bwd_noalloc_max_bytes": (sz, []),
         "attn_core_bwd_recompute_noalloc": (ctypes.c_int, [ad, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]),
@@ -157,7 +158,7 @@ def load_library():
 
 
 EXPORTS = ["attn_core_fwd", "attn_core_bwd_workspace", "attn_core_bwd_workspace_min", "attn_core_bwd_recompute",
-           "attn_core_bwd_recompute_stages", "sar_test_force_variants", "sar_test_force_forms", "attn_core_bwd_noalloc_max_bytes",
+           "attn_core_bwd_recompute_stages", "sar_test_force_variants", "sar_test_chosen_forms", "sar_test_force_forms", "attn_core_bwd_noalloc_max_bytes",
            "attn_core_bwd_recompute_noalloc", "attn_core_bwd_recompute_dq",
            "attn_core_bwd_recompute_dkdv", "attn_core_fwd_stored",
            "attn_core_bwd_stored", "attn_core_saved_bytes", "attn_core_small_buffer_bytes", "attn_core_philox_count",
@@ -248,6 +249,13 @@ def attn_core_bwd_workspace_min(desc: AttnDesc) -> int:
 
 def sar_test_force_variants(fwd_128_rows: int = -1, fwd_loader_waves: int = -1, dq_loader_waves: int = -1, dkdv_pipelined: int = -1):
     load_library().sar_test_force_variants(fwd_128_rows, fwd_loader_waves, dq_loader_waves, dkdv_pipelined)
+
+
+def sar_test_chosen_forms(desc: AttnDesc, with_tiles: int = 1):
+    """(forward, column pass, dQ product) as in the header."""
+    forms = (ctypes.c_int * 3)()
+    load_library().sar_test_chosen_forms(ctypes.byref(desc), with_tiles, forms)
+    return tuple(forms)
 
 
 def sar_test_force_forms(dq_128_rows: int = -1, ds_stream: int = -1, row_stream: int = -1, cols_grid_blocks: int = -1):

@@ -308,13 +308,23 @@ static bool dq_rows128(const AttnParams& P) {
   return 100 * w128 >= from[D / 32 - 2][len] * cus;
 }
 
+static bool ds_past_caches(const AttnParams& P) {  // the tiles do not fit the last-level cache: see ds_store2
+  const int force = g_force_ds_stream.load();
+  return force >= 0 ? force != 0 : (int64_t)P.b * P.A * ds_tiles_per_head(P) * kDsTileElems * 2 >= 256000000;
+}
+
+int attn_mfma_dq_form(const AttnParams& P0) {
+  AttnParams P = P0;
+  P.ds_stream = ds_past_caches(P);
+  return (P.d == 64 ? dq_rows128<64>(P) : P.d == 96 ? dq_rows128<96>(P) : P.d == 128 ? dq_rows128<128>(P) : dq_rows128<160>(P)) + 2 * P.ds_stream;
+}
+
 template <int D>
 static hipError_t bwd_once_d(const AttnParams& P0, const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq,
                              void* dk, void* dv, float* delta, uint16_t* ds_ws, int stages, hipStream_t st) {
   const int N = P0.b * P0.A, nb = (P0.s + 63) / 64;
   AttnParams P = P0;
-  const int stream = g_force_ds_stream.load();
-  P.ds_stream = stream >= 0 ? stream != 0 : N * ds_tiles_per_head(P) * kDsTileElems * 2 >= 256000000;  // the tiles do not fit the last-level cache: see ds_store2
+  P.ds_stream = ds_past_caches(P);
   hipError_t e = hipSuccess;
   if (stages & 1) {
     hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((unsigned)nb, (unsigned)N), dim3(256), 0, st, P, (const uint16_t*)o, (const uint16_t*)dO, delta);

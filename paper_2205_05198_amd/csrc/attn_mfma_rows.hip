@@ -680,6 +680,10 @@ static FwdForm fwd_form(const AttnParams& P) {
   return causal && nrb > 4 && w64 <= 2 * cus ? FwdForm::Loaders : FwdForm::Plain;
 }
 
+int attn_mfma_fwd_form(const AttnParams& P) {
+  return (int)(P.d == 64 ? fwd_form<64>(P) : P.d == 96 ? fwd_form<96>(P) : P.d == 128 ? fwd_form<128>(P) : fwd_form<160>(P));
+}
+
 template <int D>
 static hipError_t fwd_d(const AttnParams& P, const void* q, const void* k, const void* v, void* o, float* lse, hipStream_t st) {
   const int N = P.b * P.A, nrb = (P.s + 63) / 64;

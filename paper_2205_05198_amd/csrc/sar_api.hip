@@ -175,6 +175,14 @@ void sar_test_force_forms(int dq_128_rows, int ds_stream, int row_stream, int co
   sar::rows_force_stream(row_stream);
 }
 
+void sar_test_chosen_forms(const sar_attn_desc* desc, int with_tiles, int* forms) {
+  sar::AttnParams P;
+  const bool mfma = check_attn_desc(desc, &P) == SAR_OK && use_mfma(desc, P);
+  forms[0] = mfma ? sar::attn_mfma_fwd_form(P) : -1;
+  forms[1] = mfma ? sar::attn_mfma_cols_form(P, with_tiles != 0) : -1;
+  forms[2] = mfma ? sar::attn_mfma_dq_form(P) : -1;
+}
+
 // passes: two-pass backward, bit 0 = row pass, bit 1 = column pass.  stages (passes == 0): the backward that recomputes the
 // region once, bit 0 = delta, bit 1 = column pass + dS tiles, bit 2 = dQ from the tiles.  passes == 3 and stages == 7: the
 // whole backward, by whichever of the two the workspace allows.

@@ -76,6 +76,11 @@ void attn_mfma_force_variants(int fwd128, int fwdlw, int dqlw);
 void attn_mfma_force_dkdv_pipelined(int force);
 void attn_mfma_force_bwd_once(int dq128, int ds_stream);
 void attn_mfma_force_grid_blocks(int force);
+// the forms that a call would run: forward 0 plain, 1 loader waves, 2 persistent, 3 128 rows; column pass 0 plain, 2 producer / consumer, 3 persistent;
+// dQ product 0 / 1 64 / 128 rows, + 2 with tiles past the caches
+int attn_mfma_fwd_form(const AttnParams& P);
+int attn_mfma_cols_form(const AttnParams& P, bool tiles);
+int attn_mfma_dq_form(const AttnParams& P);
 int attn_mfma_cu_count();  // compute units of the current device, asked once
 
 // rows.hip: LayerNorm forward/backward and bias-dropout-add on [rows, h]

@@ -198,3 +198,40 @@ def test_bias_gradient_workspaces(lib):
                 assert len(sizes) <= 1, (dtype, rows, h, sizes)
                 both += len(sizes)
     assert both > 60
+
+
+def _forms(lib, s, heads, d, p, causal, tiles=1):
+    """(forward, column pass, dQ product) that a call runs on 256 compute units."""
+    if not lib_has_256_units():
+        pytest.skip("the lines between the forms are drawn for 256 compute units")
+    return binding.sar_test_chosen_forms(binding.AttnDesc.packed(s, 1, heads, heads * d, p=p, causal=causal), tiles)
+
+
+def lib_has_256_units():
+    import torch
+    return not torch.cuda.is_available() or torch.cuda.get_device_properties(0).multi_processor_count == 256
+
+
+def test_forms_of_other_kernels(lib):
+    assert binding.sar_test_chosen_forms(binding.AttnDesc.packed(128, 1, 2, 160, dtype=binding.SAR_BF16)) == (-1, -1, -1)      # d = 80
+    assert binding.sar_test_chosen_forms(binding.AttnDesc.packed(128, 1, 2, 128, dtype=binding.SAR_F32)) == (-1, -1, -1)
+
+
+# s, heads, d, p, causal, with the tiles -> the column pass: 0 plain, 2 producer / consumer, 3 persistent
+COLUMN_FORMS = [
+    (64, 256, 64, 0.1, 1, 0, 2), (64, 320, 64, 0.1, 1, 0, 0), (64, 320, 64, 0.1, 1, 1, 0), (64, 320, 96, 0.1, 1, 1, 2), (64, 512, 128, 0.1, 1, 1, 2),   # one block a head
+    (128, 160, 64, 0.1, 1, 1, 0), (128, 160, 64, 0.1, 0, 0, 0), (128, 160, 64, 0.1, 0, 1, 3), (128, 160, 128, 0.1, 1, 1, 3),                            # two
+    (192, 160, 64, 0.1, 1, 1, 0), (256, 128, 64, 0.1, 1, 1, 3), (320, 64, 64, 0.1, 1, 0, 3), (320, 192, 64, 0.1, 1, 0, 0), (256, 80, 64, 0.1, 1, 1, 3),
+    (512, 128, 64, 0.1, 1, 1, 3), (768, 40, 64, 0.1, 1, 1, 3), (768, 160, 64, 0.1, 1, 1, 0), (1024, 192, 64, 0.1, 1, 1, 0), (2048, 40, 64, 0.1, 1, 1, 2),   # lists even or not
+    (768, 80, 96, 0.1, 1, 0, 3), (512, 256, 96, 0.1, 1, 0, 0), (512, 256, 96, 0.1, 0, 0, 3), (512, 256, 96, 0.1, 1, 1, 3), (1024, 96, 96, 0.1, 1, 0, 0),
+    (512, 256, 64, 0.1, 1, 0, 3), (2048, 300, 64, 0.0, 1, 0, 0), (2432, 300, 64, 0.1, 1, 0, 2), (2432, 300, 64, 0.1, 0, 0, 2), (1280, 300, 64, 0.1, 0, 0, 2),
+    (512, 128, 96, 0.1, 1, 1, 3), (2048, 32, 96, 0.1, 1, 1, 3), (2048, 12, 128, 0.1, 1, 1, 2), (2048, 16, 160, 0.1, 1, 1, 3), (8192, 16, 160, 0.1, 1, 1, 3),
+    (1000, 24, 128, 0.1, 1, 0, 3), (1000, 23, 128, 0.1, 1, 0, 2), (248, 128, 160, 0.1, 0, 1, 3), (384, 179, 128, 0.1, 0, 1, 3), (256, 160, 128, 0.1, 1, 1, 2), (256, 160, 128, 0.1, 0, 1, 3),
+    (512, 40, 128, 0.1, 1, 1, 3), (512, 36, 128, 0.1, 1, 1, 2), (1000, 48, 128, 0.1, 1, 1, 3),
+]
+
+
+@pytest.mark.parametrize("s,heads,d,p,causal,tiles,want", COLUMN_FORMS)
+def test_column_pass_form(lib, s, heads, d, p, causal, tiles, want):
+    """The form of the column pass on both sides of its lines, as measured: the faster one."""
+    assert _forms(lib, s, heads, d, p, causal, tiles)[1] == want

@@ -326,10 +326,8 @@ def test_column_pass_forms(d, s, b, A, p, causal, two_pass, form):
                                             (160, 328, 85, 0.1, 1), (64, 1000, 48, 0.1, 1), (96, 200, 66, 0.1, 0), (96, 328, 56, 0.1, 0),
                                             (96, 376, 180, 0.1, 1), (64, 264, 180, 0.0, 0), (96, 200, 210, 0.1, 0), (160, 376, 180, 0.1, 0), (64, 64, 320, 0.0, 0)])
 def test_column_pass_form_by_shape(d, s, A, p, causal, two_pass):
-    """The column pass as the library chooses it, on both sides of the lines between its forms on 256 compute units: plain with dropout and
-    without (64, 96: more than four workgroups a CU, short heads, no mask), producer / consumer with one key block a workgroup (96 with
-    dropout and the tiles; 160 with lists of three against two rounds of single blocks) and persistent (128, 160; 64 with lists one
-    longer than the rounds under the mask; some workgroups with one block and the rest with two; nearly a head a unit with lists a third longer)."""
+    """The column pass as the library chooses it: plain with dropout and without, producer / consumer with one key block a workgroup and
+    persistent, on short and long lists of blocks (which form runs where: test_column_pass_form of the host tests)."""
     from gpu_util import run_attn
     sh = oracle.AttnShape(s=s, b=1, a=A, h=A * d, p=p, seed=81, offset=(1 << 32) - 4321, causal=causal)
     q, k, v, do = attn_inputs(s, 1, A, d, "bf16", seed=47)
