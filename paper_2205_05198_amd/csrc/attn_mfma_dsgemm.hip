@@ -10,6 +10,7 @@
 // 5 contractions are executed instead of 7, and Philox and the exponentials run once per backward instead of twice.
 #include "attn_mfma_common.h"
 #include <atomic>
+#include <cmath>
 
 namespace sar {
 
@@ -283,29 +284,26 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm128_kernel(AttnParams 
   lds_rows_to_global<D>(smem + half * TILE, dq + base + (int64_t)(rb * BM + 64 * half) * P.stride_s, gstride, P.s - rb * BM - 64 * half, tid & 255);
 }
 
-// The dQ product in blocks of 128 rows, rather than 64?  From both over 7818 shapes (s = 64 .. 8192, 1 .. 256 heads): 0.91 of the 64-row form's
-// time in the geometric mean of all, 0.65 to 0.85 where blocks are many (s x heads, us, 64 / 128 rows: d = 160 8192 x 16 under the mask 344 / 262, 1024 x 20
-// without 20.5 / 14.0; d = 96 2048 x 32 32.9 / 26.8).  A block of 128 rows takes about one and a half times as long as one of 64.  So: more 64-row blocks
-// than CUs, and without the mask rounds of blocks less by that; d = 64, which holds two of either a CU, not on long heads (7168 x 20 +5 %).
-// Under the mask the heaviest block, twice as long a chain as at 64 rows' rate, must not set the pace: the more tiles it has, the more blocks it takes to
-// hide it (d = 160 2048 x 16, one 128-row block a CU, 22.4 / 22.9; d = 128 2048 x 12 16.7 / 22.0).  `from`: 128-row blocks a CU, in hundredths.
-// Tiles that stream past the caches favour it further, since it loads them without keeping them (whole backward, 64 / 128 rows: d = 64 8192 x 8 394 / 364, 4352 x 24
-// without mask 0.90, 7680 x 5 under it, 1.2 a CU, 1.05).
+// The dQ product in blocks of 128 rows, rather than 64?  From both over 18317 shapes (s = 64 .. 8192, 1 .. 512 heads, more 64-row blocks than CUs), where this
+// rule takes 1.001 times the faster one's time in the geometric mean, 1.002 in the worst group.  All blocks together take 0.6 to 0.85 of the 64-row form's time, as a K
+// tile serves twice the rows; but one block is a chain one and a half times as long, and where the CUs get few of them the longest sets the pace.  s x heads, us, 64 / 128 rows:
+//   Up to one 64-row block a CU: 64 (blocks of 128 would leave half of the CUs empty).
+//   Without the mask, where all blocks are as long: 128 (d = 160 768 x 22, half a block a CU, 18.0 / 11.9; d = 128 768 x 24 13.8 / 11.2; d = 96 1024 x 80 48.1 /
+//     41.1; d = 64 2048 x 64 124 / 100), but heads of three blocks, a quarter of whose rows is padding, where that costs a second round (d >= 96 1.02 to 1.11).
+//   Under the mask the more tiles the heaviest block has, the more blocks a CU it takes to hide it: from a + b log2(nb / 8) hundredths of a 128-row block a CU
+//     (nb tiles; d = 160 1024 x 20, 0.62 a CU, 11.3 / 12.0, 768 x 32, 0.75, 11.0 / 10.5, 2048 x 16, 1.0, 22.0 / 21.5; d = 128 2048 x 12, 0.75, 15.5 / 21.8, 2048 x 16
+//     18.6 / 22.4, 2048 x 20, 1.25, 25.7 / 23.4, 4096 x 24, 3, 122 / 93; d = 96 2048 x 16 16.7 / 17.7, 1024 x 32, 1.0, 11.6 / 11.2; d = 64 2048 x 16, 1.0, 14.2 / 16.9, 2048 x
+//     20, 1.25, 19.3 / 19.1).  d = 64 holds two blocks a CU: where heads are a multiple of eight, so that a die keeps its heads' K in its L2, 4096 x 16 are all resident at
+//     once at either size (51 / 60, but 17 heads 68 / 63).
 template <int D>
 static bool dq_rows128(const AttnParams& P) {
   if (const int force = g_force_dq128.load(); force >= 0) return force != 0;
-  const int64_t cus = attn_mfma_cu_count(), N = (int64_t)P.b * P.A, nb = (P.s + 63) / 64, w64 = nb * N, w128 = (nb + 1) / 2 * N;
-  if (w64 <= cus) return false;
-  if (P.ds_stream && (!P.causal || 10 * w128 >= 19 * cus)) return true;
-  const int64_t r64 = (w64 + cus - 1) / cus, r128 = (w128 + cus - 1) / cus;
-  if (!P.causal) {
-    if (3 * r128 > 2 * r64 || (D == 128 && 3 * r128 == 2 * r64)) return false;
-    return D != 64 || (nb == 2 ? 100 * w128 >= 88 * cus : nb <= 24 || w128 > 6 * cus);
-  }
-  if (nb <= 6 && 3 * r128 > 2 * r64) return false;
-  constexpr int from[4][7] = {{65, 90, 113, 113, 125, 220, 300}, {50, 70, 80, 80, 105, 105, 113}, {60, 88, 101, 101, 113, 125, 150}, {50, 63, 70, 80, 105, 105, 105}};
-  const int len = (nb > 8) + (nb > 12) + (nb > 16) + (nb > 24) + (nb > 32) + (nb > 64);
-  return 100 * w128 >= from[D / 32 - 2][len] * cus;
+  const int64_t cus = attn_mfma_cu_count(), N = (int64_t)P.b * P.A, nb = (P.s + 63) / 64, w128 = (nb + 1) / 2 * N;
+  if (nb * N <= cus || (D >= 96 && nb == 3 && w128 > cus && 4 * w128 <= 5 * cus)) return false;
+  if (!P.causal) return true;
+  constexpr float a = D == 160 ? 49.f : D == 64 ? 70.f : 64.f;
+  const float b = D == 160 ? 18.f : D != 64 ? 20.f : N % 8 == 0 ? 45.f : 28.f;
+  return 100.f * (float)w128 >= (a + b * (std::log2((float)nb) - 3.f)) * (float)cus;
 }
 
 static bool ds_past_caches(const AttnParams& P) {  // the tiles do not fit the last-level cache: see ds_store2

@@ -217,6 +217,21 @@ def test_forms_of_other_kernels(lib):
     assert binding.sar_test_chosen_forms(binding.AttnDesc.packed(128, 1, 2, 128, dtype=binding.SAR_F32)) == (-1, -1, -1)
 
 
+# s, heads, d, causal -> the dQ product: 0 in blocks of 64 rows, 1 of 128 (+ 2: tiles past the caches)
+DQ_FORMS = [
+    (2048, 8, 160, 1, 0), (512, 40, 128, 0, 1), (768, 22, 160, 0, 1), (520, 60, 128, 0, 1), (2048, 20, 64, 0, 1), (320, 192, 64, 0, 1), (192, 128, 64, 0, 1),
+    (192, 130, 64, 0, 1), (192, 130, 128, 0, 0), (192, 161, 128, 0, 1), (192, 130, 96, 1, 0),
+    (1024, 20, 160, 1, 0), (768, 32, 160, 1, 1), (2048, 16, 160, 1, 1), (2048, 13, 160, 1, 0), (2048, 12, 128, 1, 0), (2048, 16, 128, 1, 0), (2048, 20, 128, 1, 1), (320, 192, 128, 1, 1),
+    (2048, 16, 96, 1, 0), (1024, 32, 96, 1, 1), (2048, 32, 96, 1, 1), (2048, 16, 64, 1, 0), (2048, 21, 64, 1, 1), (4096, 16, 64, 1, 2), (4096, 17, 64, 1, 3), (8192, 16, 160, 1, 3),
+]
+
+
+@pytest.mark.parametrize("s,heads,d,causal,want", DQ_FORMS)
+def test_dq_product_form(lib, s, heads, d, causal, want):
+    """The dQ product in blocks of 64 or of 128 rows, on both sides of its lines, as measured: the faster one."""
+    assert _forms(lib, s, heads, d, 0.1, causal)[2] == want
+
+
 # s, heads, d, p, causal, with the tiles -> the column pass: 0 plain, 2 producer / consumer, 3 persistent
 COLUMN_FORMS = [
     (64, 256, 64, 0.1, 1, 0, 2), (64, 320, 64, 0.1, 1, 0, 0), (64, 320, 64, 0.1, 1, 1, 0), (64, 320, 96, 0.1, 1, 1, 2), (64, 512, 128, 0.1, 1, 1, 2),   # one block a head
