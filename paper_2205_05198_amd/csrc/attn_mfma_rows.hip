@@ -592,6 +592,52 @@ int attn_mfma_cu_count() {
 
 static int cu_count() { return attn_mfma_cu_count(); }
 
+// 128-row workgroups in the forward?  From every form over 14380 shapes (s = 64 .. 8192, 1 .. 512 heads, more 64-row workgroups than CUs), each change of line
+// confirmed with both forms in turn, each warmed up by itself (6899 shapes, where this rule takes 0.86 of the time of the one before it).  w128: 128-row workgroups a CU; us,
+// 64 rows / 128 rows, p = 0.1 unless said otherwise.
+//   A K / V tile serves twice the rows.  What that is worth depends on where the tiles come from: a die (of eight) works on the heads n = its number modulo eight where the heads are a
+//   multiple of eight, on all of them otherwise (up to 96 at a time, three workgroups on each of its 32 CUs), and once their K and V are several times its 4 MB L2, tiles come from the
+//   last-level cache, whose rate bounds the 64-row forms (d = 96 2048 x 192, no mask, 19 MB a die, 907 / 548; 4096 x 85 of 128 178 MB 1601 / 1077; 3840 x 128 of 96 without dropout 1878 / 838).
+//   d = 96, 128 (several 64-row workgroups share a CU).  No mask: heads of six blocks or more whose last round is at least 0.8 full, from w128 = 1.5 (1.6 .. 2 0.85 to 0.98, 2.5 .. 3 0.75 to
+//     0.98, but 2 .. 2.5 up to 1.2), beyond 2.2 only above 8 MB a die (d = 128 2048 x 34 at 2.1 66 / 67), and at any fullness above 36 MB from 2.5 (2048 x 55 of 128 253 / 190); d = 96 up
+//     to 16 blocks from 3.5 (1024 x 128 98 / 97, others up to 1.34 slower without); five blocks, a sixth of padding, from 6, four from 3 (d = 128) and 3.5; one round of more than four.
+//     Under the mask, where the heaviest workgroup must not set the pace: above 20 MB a die from w128 = 1.5 (d = 128 1024 x 83 0.88, 4096 x 21 161 / 145, but 4096 x 20 127 / 133) or 2.5 (d = 96 2048 x 65 131 /
+//     107, 4096 x 25 169 / 151), above 7.5 in any case (0.92 to 0.98 at least), d = 96 with 12 to 24 blocks above 5.5 (1024 x 192 108 / 95); from nine blocks a head on, without
+//     dropout and an even number also six and eight above 5.5.
+//   d = 160 (one workgroup a CU).  No mask: one round; from 1.5 (0.66 to 0.9), 1.4 without dropout, heads no multiple of eight from 1.25 (768 x 59 61 / 48, but 512 x 80 31.7 / 36.1); three blocks, a
+//     quarter of padding, from 3.  Under the mask above 2; from 1.25 on heads of seven blocks or more where they are no multiple of eight (1024 x 47 49.0 / 35.5, but 1024 x 40 29.1 / 29.6) or there is no dropout,
+//     else above 1.5 from 14 blocks (0.85 to 0.93); three blocks never, five from 3.
+//   d = 64, which holds two of them a CU: never with dropout (1.04 to 1.8).  Without it, no mask: whole pairs of rounds or from 3 (2048 x 64 95 / 89, 256 x 210 14.7 / 12.0, but 512 x 96 13.0 / 15.5; five
+//     blocks from 6); under the mask from 5.5 on heads of nine blocks or more (0.87 to 0.95), 3.5 of 25 (0.90 to 0.98), 6 of six.
+template <int D>
+static bool fwd_rows128(const AttnParams& P) {
+  const int64_t cus = cu_count(), N = (int64_t)P.b * P.A, nrb = (P.s + 63) / 64, w128 = (P.s + 127) / 128 * N;
+  const bool drop = P.thresh != 0, apart = N % 8 != 0;
+  const int64_t w = 100 * w128 / cus;  // hundredths of a 128-row workgroup a CU
+  const int64_t kv = (apart ? std::min<int64_t>(N, 96) : N / 8) * P.s * (4 * D);  // bytes of the K and V that one die works on
+  if (D == 160) {
+    if (w128 <= cus) return !P.causal;
+    if (nrb == 3 || (nrb == 5 && P.causal)) return w >= 300 && (nrb != 3 || !P.causal);
+    if (w128 > 2 * cus || (nrb == 2 && w128 == 2 * cus)) return true;
+    if (P.causal) return apart || !drop ? w >= 125 && nrb >= (drop ? 7 : 8) : w > 150 && nrb >= 14;
+    return w >= 150 || (w >= (apart ? 125 : 140) && (!drop || (apart && nrb <= 12))) || (!drop && nrb >= 40);
+  }
+  if (D == 64) {
+    if (drop) return false;
+    if (P.causal) return nrb >= 9 ? w >= (nrb >= 25 ? 350 : 550) : nrb >= 6 && w >= 600;
+    const int64_t pairs = (w128 + 2 * cus - 1) / (2 * cus);  // rounds of two workgroups a CU
+    return nrb >= 4 && (w >= (nrb == 5 ? 600 : 300) || 10 * w128 >= 16 * cus * pairs);
+  }
+  if (P.causal) {
+    if (nrb < (drop || D == 96 ? 9 : 6)) return !drop && (nrb == 6 || nrb == 8) && w >= 550;
+    return w > 750 || (kv > 20000000 && w > (D == 96 ? 250 : 150)) || (D == 96 && nrb >= 12 && nrb <= 24 && w >= 550);
+  }
+  if (w128 <= cus || nrb <= 5) return w128 <= cus ? nrb > 4 : w >= (nrb == 5 ? 600 : D == 128 ? 300 : 350) && nrb >= 4;
+  if (D == 96 && nrb <= 16 && w >= 350) return true;
+  if (w > 150 && w >= 80 * ((w128 + cus - 1) / cus)) return w <= 220 || kv > 8000000;
+  return w > 250 && kv > 36000000;
+}
+
 // Form of the forward by shape, from sweeps of every form over 4256 shapes (d, s = 64 .. 8192, 4 .. 768 heads, mask, dropout): within
 // 0.5 % of the best form in the geometric mean.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us or differences at
 // p = 0 / 0.1.
@@ -599,19 +645,7 @@ static int cu_count() { return attn_mfma_cu_count(); }
 //   Heads of three to five blocks, one a CU: persistent workgroups where the lists are no longer than the rounds of single ones (d = 128 192 x 210
 //     17.8 / 18.1 -> 14.6 / 15.5, with the mask 16.2 / 16.9 -> 13.1 / 13.6; d = 160 192 x 210 -> 19.5 / 20.7, 128 rows 23.1 / 24.3, but four blocks
 //     without mask 256 x 210 32.1, 128 rows 29.4 with dropout).
-//   128-row workgroups.  No mask: d = 160 in one round of them, then with dropout where they save two rounds of five (1024 x 64 -23 / -12 %, but
-//     1024 x 40, two rounds against three, +5 / +21 %) or three of eight and heads are short (520 x 210 132 -> 101, but 3712 x 20 248 -> 277), on the
-//     shortest one of three (256 x 180 32.1 -> 27.9); without dropout from 1.4 rounds and on long heads (1000 x 48 53.4 -> 49.9), but not three
-//     blocks, a quarter of whose rows is padding, up to three rounds (136 x 272 26.1, 128 rows 30.6).  d = 96 and 128 in
-//     one round and, on heads of four (d = 128 256 x 384 37.3 -> 34.9) to 16 blocks, from three or 3.5 (d = 96, 512 x 256 66.7 / 76.3 -> 57.0 / 62.7,
-//     but 8192 x 14 at 0.1 554 -> 656; five blocks, a sixth of padding, from six: 320 x 320 37.4 -> 40.6, 320 x 512 69.9 -> 60.6).  d = 64, which holds
-//     two of them a CU, without dropout in whole pairs of rounds or from three (2048 x 64 95 -> 89, 256 x 210 14.7 -> 12.0, 520 x 512 96.6 -> 77.6, but
-//     512 x 96, 1.5 a CU, 13.0 -> 15.5; five blocks from six, 320 x 384 23.0 -> 25.8).
-//     Causal, d = 160: so many that the heaviest does not set the
-//     pace, one and a half rounds with dropout and 1.25 without (1024 x 40 -5 / +2 %, 3712 x 17 at 0.1 136 -> 107), short heads two (384 x
-//     256 47 -> 43), three blocks never (136 x 272 22.7 / 23.1 -> 28.2 / 29.9).  d = 96, 128: from 5.5 rounds on heads of 12 blocks or more
-//     (1024 x 384 260 / 262 -> 179 / 196), six without dropout on those of six to ten in pairs, and d = 64 without dropout from nine, long ones 6.5
-//     (1024 x 210 70.6 -> 51.6, 520 x 384, 7.5, 35.3 -> 40.7).
+//   128-row workgroups: fwd_rows128.
 //   Persistent workgroups otherwise: the longest list of row blocks must not exceed the rounds of single ones (no mask, d = 160, 1024 x 48, lists of
 //     4 against 3 rounds: 68.6, loaders 54.2).  Then d = 160 (384 x 48 11.4 -> 10.3, 512 x 40 12.7 -> 11.5); under the mask d = 96 and 128
 //     up to two workgroups a CU (d = 128, 1000 x 24 14.9 / 16.9 -> 14.0 / 16.6, 2048 x 14 27.5 / 30.1 -> 26.4 / 28.0, but 2048 x 20 +14 /
@@ -627,8 +661,7 @@ enum class FwdForm { Plain, Loaders, Persistent, Rows128 };
 template <int D>
 static FwdForm fwd_form(const AttnParams& P) {
   const int cus = cu_count(), N = P.b * P.A, nrb = (P.s + 63) / 64;
-  const int64_t w64 = (int64_t)nrb * N, w128 = (int64_t)((P.s + 127) / 128) * N;
-  const int64_t rounds64 = (w64 + cus - 1) / cus, rounds128 = (w128 + cus - 1) / cus;
+  const int64_t w64 = (int64_t)nrb * N, rounds64 = (w64 + cus - 1) / cus;
   const bool causal = P.causal != 0, drop = P.thresh != 0;
   const int f128 = P.s < 128 ? 0 : g_force_fwd128.load(), lw = g_force_fwdlw.load();
   const int R = N <= cus ? std::min(nrb, cus / N) : 0;  // a persistent grid: R row blocks of every head at a time
@@ -636,31 +669,7 @@ static FwdForm fwd_form(const AttnParams& P) {
   if (f128 < 0 && lw < 0 && w64 > cus && even && R == 1 && nrb >= 3 && nrb <= 5 &&
       ((D == 128 && N < cus) || (D == 160 && (causal || nrb == 3))))
     return FwdForm::Persistent;
-  bool use128 = f128 == 1;
-  if (f128 < 0 && w64 > cus) {
-    if (causal) {
-      if (D == 160) {
-        use128 = nrb != 3 && (w128 > 2 * cus || (nrb == 2 && w128 == 2 * cus) || (drop ? nrb >= 14 && 2 * w128 > 3 * cus : nrb >= 8 && 4 * w128 >= 5 * cus));
-      } else if (D == 128) {
-        use128 = nrb >= 12 ? 2 * w128 >= 11 * cus : !drop && nrb >= 6 && nrb % 2 == 0 && w128 >= 6 * cus;
-      } else if (D == 96) {
-        use128 = nrb <= 64 && ((nrb >= 12 && 2 * w128 >= 11 * cus) || (!drop && nrb >= 6 && w128 >= (nrb % 2 == 0 ? 6 : 9) * cus));
-      } else {
-        use128 = !drop && ((nrb >= 6 && w128 >= 9 * cus) || (nrb >= 16 && 2 * w128 >= 13 * cus));
-      }
-    } else if (D == 160 && drop) {
-      use128 = w128 <= cus || 5 * rounds128 < 3 * rounds64 || (5 * rounds128 == 3 * rounds64 && nrb <= 12) || (8 * rounds128 <= 5 * rounds64 && nrb <= 16) ||
-               (3 * rounds128 <= 2 * rounds64 && nrb >= 3 && nrb <= 5);
-    } else if (D == 160) {
-      use128 = w128 <= cus || (10 * w128 >= 14 * cus && (nrb != 3 || w128 >= 3 * cus)) || nrb >= 40;
-    } else if (D >= 96) {
-      use128 = nrb >= 4 && ((nrb > 4 && w128 <= cus) || (2 * w128 >= (nrb == 5 ? 12 : nrb == 4 && D == 128 ? 6 : 7) * cus && nrb <= 16));
-    } else {
-      const int64_t pairs = (w128 + 2 * cus - 1) / (2 * cus);  // rounds of two workgroups a CU
-      use128 = !drop && nrb >= 4 && (w128 >= (nrb == 5 ? 6 : 3) * cus || 10 * w128 >= 16 * cus * pairs);
-    }
-    use128 = use128 && P.s >= 128;
-  }
+  const bool use128 = f128 >= 0 ? f128 == 1 : P.s >= 128 && w64 > cus && fwd_rows128<D>(P);
   if (use128) return FwdForm::Rows128;
   if (lw >= 0) return lw == 0 ? FwdForm::Plain : lw == 3 && N <= cus ? FwdForm::Persistent : FwdForm::Loaders;
   if (w64 <= cus) return FwdForm::Loaders;

@@ -217,6 +217,25 @@ def test_forms_of_other_kernels(lib):
     assert binding.sar_test_chosen_forms(binding.AttnDesc.packed(128, 1, 2, 128, dtype=binding.SAR_F32)) == (-1, -1, -1)
 
 
+# s, heads, d, p, causal -> the forward: 0 plain, 1 loader waves, 2 persistent, 3 128 rows
+FORWARD_FORMS = [
+    (2048, 8, 96, 0.1, 1, 1), (120, 300, 160, 0.1, 0, 1), (192, 210, 128, 0.1, 0, 2), (512, 128, 64, 0.0, 0, 3), (512, 128, 64, 0.1, 0, 1),   # few; short; the two at d = 64
+    (2048, 192, 96, 0.1, 0, 3), (3840, 128, 96, 0.0, 0, 3), (2048, 55, 128, 0.1, 0, 3), (2048, 34, 128, 0.1, 0, 0), (768, 80, 96, 0.1, 0, 3), (1024, 128, 96, 0.1, 0, 3),
+    (1024, 80, 128, 0.1, 0, 0), (320, 300, 96, 0.1, 0, 0), (320, 512, 96, 0.1, 0, 3), (256, 200, 128, 0.1, 0, 2), (256, 260, 128, 0.1, 0, 0), (256, 400, 128, 0.1, 0, 3),                       # no mask
+    (1024, 83, 128, 0.1, 1, 3), (1024, 80, 128, 0.1, 1, 0), (4096, 21, 128, 0.1, 1, 3), (2048, 65, 96, 0.1, 1, 3), (2048, 33, 96, 0.1, 1, 0), (1024, 192, 96, 0.1, 1, 3),
+    (1024, 160, 96, 0.1, 1, 0), (2048, 128, 128, 0.1, 1, 3), (2048, 112, 128, 0.1, 1, 0), (512, 512, 128, 0.0, 1, 3), (512, 384, 128, 0.0, 1, 0), (512, 512, 128, 0.1, 1, 0),                   # the mask
+    (2048, 32, 96, 0.1, 1, 0), (2048, 12, 128, 0.1, 1, 1), (2048, 16, 160, 0.1, 1, 2), (8192, 16, 160, 0.1, 1, 3), (1000, 24, 128, 0.1, 1, 2),
+    (1024, 47, 160, 0.1, 1, 3), (1024, 40, 160, 0.1, 1, 2), (768, 59, 160, 0.1, 0, 3), (512, 80, 160, 0.1, 0, 2), (192, 250, 160, 0.1, 1, 2), (192, 260, 160, 0.1, 1, 1),
+    (1600, 72, 64, 0.0, 1, 3), (1600, 64, 64, 0.0, 1, 0), (1600, 64, 64, 0.1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("s,heads,d,p,causal,want", FORWARD_FORMS)
+def test_forward_form(lib, s, heads, d, p, causal, want):
+    """The form of the forward, on both sides of the lines of its 128-row workgroups and at sizes in use: the faster one, as measured."""
+    assert _forms(lib, s, heads, d, p, causal)[0] == want
+
+
 # s, heads, d, causal -> the dQ product: 0 in blocks of 64 rows, 1 of 128 (+ 2: tiles past the caches)
 DQ_FORMS = [
     (2048, 8, 160, 1, 0), (512, 40, 128, 0, 1), (768, 22, 160, 0, 1), (520, 60, 128, 0, 1), (2048, 20, 64, 0, 1), (320, 192, 64, 0, 1), (192, 128, 64, 0, 1),
