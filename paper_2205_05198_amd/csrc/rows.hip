@@ -4,14 +4,10 @@
 #include "sar_internal.h"
 
 #include <atomic>
-#include <type_traits>
 
 namespace sar {
 
-// 16 bytes to memory; STREAM: nontemporal.  A result that is large beside the caches is written past them: it would push out what is yet to be
-// read, and is itself gone before the next pass comes to it.  us, kept / past: bias-GeLU forward and backward 8192 x 8192 bf16 128 / 105, 4096 x 10240 75 / 67,
-// 8192 x 3072 44.2 / 43.7; dropout-add + LayerNorm forward and both backwards 4096 x 20480 316 / 300, 8192 x 6144 187 / 174, 4096 x 6144 92.9 / 89.9, but
-// 2048 x 6144 (25 MB a tensor) 53.2 / 54.2 and 16384 x 1024 (34 MB) 67 / 71.  A choice at run time inside one kernel cost more than it gave (512 x 20480 45 / 49).
+// 16 bytes to memory; STREAM: nontemporal
 template <bool STREAM, typename V>
 __device__ __forceinline__ void store16(void* p, V v) {
   typedef __attribute__((__vector_size__(16))) uint32_t raw_t;
@@ -19,14 +15,6 @@ __device__ __forceinline__ void store16(void* p, V v) {
   if (STREAM) __builtin_nontemporal_store(r, reinterpret_cast<raw_t*>(p));
   else *reinterpret_cast<raw_t*>(p) = r;
 }
-static std::atomic<int> g_force_stream{-1};  // sar_test_force_forms (tests, measurements)
-void rows_force_stream(int force) { g_force_stream = force; }
-static inline bool stream_from(int64_t bytes, int64_t least) {
-  const int force = g_force_stream.load(std::memory_order_relaxed);
-  return force >= 0 ? force != 0 : bytes >= least;
-}
-static inline bool rows_stream(int64_t rows, int64_t h, int64_t esz) { return stream_from(rows * h * esz, 48000000); }
-static inline bool gelu_stream(int64_t rows, int64_t h, int64_t esz) { return stream_from(rows * h * esz, 32000000); }  // nothing of it is read back by the other pass
 
 // 8 consecutive elements (one 16-byte access for bf16, two for fp32) <-> 8 floats
 template <typename T> struct Vec8;
@@ -393,7 +381,7 @@ __global__ __launch_bounds__(NT) void ln_bwd_kernel(RowsParams P, const T* __res
 }
 
 // many rows.  PF: the next row is requested before this one is worked on (where the registers allow it)
-template <typename T, int NT, int VPT, bool PF, bool STREAM>
+template <typename T, int NT, int VPT, bool PF>
 __global__ __launch_bounds__(NT, 2) void ln_bwd_stream_kernel(RowsParams P, const T* __restrict__ dy, const T* __restrict__ x,
                                                                      const float* __restrict__ mean, const float* __restrict__ rstd,
                                                                      const T* __restrict__ gamma, T* __restrict__ dx, float* __restrict__ part) {
@@ -471,7 +459,7 @@ __global__ __launch_bounds__(NT, 2) void ln_bwd_stream_kernel(RowsParams P, cons
         gr[u].get(g);
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = rs * (dv[e] * g[e] - c1 - (xv[e] - mu) * rs * c2);
-        Vec8<T>::template store<STREAM>(dx + r * P.h + 8 * c, out);
+        Vec8<T>::store(dx + r * P.h + 8 * c, out);
       }
     }
   }
@@ -521,7 +509,7 @@ __global__ __launch_bounds__(256) void bias_dropout_add_kernel(RowsParams P, con
 // The statistics are taken from `out` as it is stored (rounded to T), so that a later ln_bwd, which re-reads the
 // stored row, sees exactly the values mean and rstd belong to.
 // ---------------------------------------------------------------------------------------------------
-template <typename T, int VPT, bool HAS_BIAS, bool STREAM>
+template <typename T, int VPT, bool HAS_BIAS>
 __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T* __restrict__ x, const T* __restrict__ bias, const T* resid,
                                                          const T* __restrict__ gamma, const T* __restrict__ beta, T* out, T* __restrict__ y,
                                                          float* __restrict__ mean, float* __restrict__ rstd) {
@@ -545,7 +533,7 @@ __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T*
         const float xb = HAS_BIAS ? xv[q] + bv[q] : xv[q];
         ov[u][q] = Elem<T>::round(((keep >> q) & 1u) ? fmaf(xb, P.keep_scale, rv[q]) : rv[q]);
       }
-      Vec8<T>::template store<STREAM>(out + r * P.h + 8 * c, ov[u]);
+      Vec8<T>::store(out + r * P.h + 8 * c, ov[u]);
     }
   }
   // shift = the row's first element, held by thread 0: broadcast through LDS
@@ -580,7 +568,7 @@ __global__ __launch_bounds__(1024) void bda_ln_fwd_kernel(RowsParams P, const T*
       Vec8<T>::load(beta + 8 * c, bt);
 #pragma unroll
       for (int q = 0; q < 8; ++q) o[q] = fmaf((ov[u][q] - mu) * rs, g[q], bt[q]);
-      Vec8<T>::template store<STREAM>(y + r * P.h + 8 * c, o);
+      Vec8<T>::store(y + r * P.h + 8 * c, o);
     }
   }
   if (threadIdx.x == 0) { mean[r] = mu; rstd[r] = rs; }
@@ -605,7 +593,7 @@ __global__ __launch_bounds__(256) void bda_bwd_kernel(RowsParams P, const T* __r
   Vec8<T>::store(dx + r * P.h + c, o);
 }
 
-template <typename T, bool STREAM>
+template <typename T>
 struct BdaBwdCols {
   static constexpr int kSums = 1;
   typedef Raw8<T> In;
@@ -628,7 +616,7 @@ struct BdaBwdCols {
       o[q] = ((keep >> q) & 1u) ? dv[q] * P.keep_scale : 0.f;
       acc[0][q] += o[q];
     }
-    Vec8<T>::template store<STREAM>(dx + r * P.h + col, o);
+    Vec8<T>::store(dx + r * P.h + col, o);
   }
 };
 
@@ -694,7 +682,7 @@ __global__ __launch_bounds__(256) void bias_gelu_bwd_kernel(RowsParams P, const 
   Vec8<T>::store(dx + at, o);
 }
 
-template <typename T, bool HAS_BIAS, bool STREAM>
+template <typename T, bool HAS_BIAS>
 struct GeluBwdCols {
   static constexpr int kSums = 1;
   struct In { Raw8<T> x, dy; };
@@ -722,7 +710,7 @@ struct GeluBwdCols {
       o[q] = dv[q] * gelu_grad(xv[q] + bv[q]);
       acc[0][q] += o[q];
     }
-    Vec8<T>::template store<STREAM>(dx + r * P.h + col, o);
+    Vec8<T>::store(dx + r * P.h + col, o);
   }
 };
 
@@ -799,24 +787,18 @@ static hipError_t ln_bwd_t(const RowsParams& P, const void* dy, const void* x, c
     auto go = [&](auto kern, int nt) {
       hipLaunchKernelGGL(kern, dim3(groups), dim3(nt), 0, st, P, (const T*)dy, (const T*)x, mean, rstd, (const T*)gamma, (T*)dx, part);
     };
-    auto with = [&](auto threads, auto vpt, auto ahead) {
-      constexpr int NT = decltype(threads)::value, VPT = decltype(vpt)::value;
-      constexpr bool PF = decltype(ahead)::value;
-      if (rows_stream(P.rows, P.h, sizeof(T))) go(ln_bwd_stream_kernel<T, NT, VPT, PF, true>, NT);
-      else go(ln_bwd_stream_kernel<T, NT, VPT, PF, false>, NT);
-    };
-    if (nchunk <= 128) with(std::integral_constant<int, 128>(), std::integral_constant<int, 1>(), std::integral_constant<bool, true>());
-    else if (nchunk <= 256) with(std::integral_constant<int, 256>(), std::integral_constant<int, 1>(), std::integral_constant<bool, true>());
-    else if (nchunk <= 512) with(std::integral_constant<int, 256>(), std::integral_constant<int, 2>(), std::integral_constant<bool, true>());
+    if (nchunk <= 128) go(ln_bwd_stream_kernel<T, 128, 1, true>, 128);
+    else if (nchunk <= 256) go(ln_bwd_stream_kernel<T, 256, 1, true>, 256);
+    else if (nchunk <= 512) go(ln_bwd_stream_kernel<T, 256, 2, true>, 256);
     else switch ((nchunk + 511) / 512) {
-      case 2: with(std::integral_constant<int, 512>(), std::integral_constant<int, 2>(), std::integral_constant<bool, true>()); break;
-      case 3: with(std::integral_constant<int, 512>(), std::integral_constant<int, 3>(), std::integral_constant<bool, true>()); break;
-      case 4: with(std::integral_constant<int, 512>(), std::integral_constant<int, 4>(), std::integral_constant<bool, half>()); break;
-      case 5: with(std::integral_constant<int, 512>(), std::integral_constant<int, 5>(), std::integral_constant<bool, half>()); break;
+      case 2: go(ln_bwd_stream_kernel<T, 512, 2, true>, 512); break;
+      case 3: go(ln_bwd_stream_kernel<T, 512, 3, true>, 512); break;
+      case 4: go(ln_bwd_stream_kernel<T, 512, 4, half>, 512); break;
+      case 5: go(ln_bwd_stream_kernel<T, 512, 5, half>, 512); break;
       default:
         if constexpr (half) {
-          if (nchunk <= 3072) with(std::integral_constant<int, 512>(), std::integral_constant<int, 6>(), std::integral_constant<bool, false>());
-          else with(std::integral_constant<int, 512>(), std::integral_constant<int, 7>(), std::integral_constant<bool, false>());
+          if (nchunk <= 3072) go(ln_bwd_stream_kernel<T, 512, 6, false>, 512);
+          else go(ln_bwd_stream_kernel<T, 512, 7, false>, 512);
         }
     }
     const hipError_t e = hipGetLastError();
@@ -882,9 +864,8 @@ static hipError_t bda_ln_t(const RowsParams& P, const void* x, const void* bias,
   int threads;
   const int vpt = pick_vpt(P.h, threads);
   dim3 grid((unsigned)P.rows), block(threads);
-#define SAR_BDA_LN_S(V, B, S) hipLaunchKernelGGL((bda_ln_fwd_kernel<T, V, B, S>), grid, block, 0, st, P, (const T*)x, (const T*)bias, (const T*)resid, \
+#define SAR_BDA_LN(V, B) hipLaunchKernelGGL((bda_ln_fwd_kernel<T, V, B>), grid, block, 0, st, P, (const T*)x, (const T*)bias, (const T*)resid, \
                                             (const T*)gamma, (const T*)beta, (T*)out, (T*)y, mean, rstd)
-#define SAR_BDA_LN(V, B) do { if (rows_stream(P.rows, P.h, sizeof(T))) SAR_BDA_LN_S(V, B, true); else SAR_BDA_LN_S(V, B, false); } while (0)
 #define SAR_BDA_LN_V(V) do { if (bias) SAR_BDA_LN(V, true); else SAR_BDA_LN(V, false); } while (0)
   switch (vpt) {
     case 1: SAR_BDA_LN_V(1); break;
@@ -894,7 +875,6 @@ static hipError_t bda_ln_t(const RowsParams& P, const void* x, const void* bias,
   }
 #undef SAR_BDA_LN_V
 #undef SAR_BDA_LN
-#undef SAR_BDA_LN_S
   return hipGetLastError();
 }
 
@@ -936,20 +916,36 @@ static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, flo
     hipLaunchKernelGGL((bda_bwd_kernel<T>), dim3((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), dim3(256), 0, st, P, (const T*)dout, (T*)dx);
     return hipGetLastError();
   }
-  const ColPlan pl = bda_bwd_plan(P.rows, P.h, sizeof(T) == 2);
-  if (rows_stream(P.rows, P.h, sizeof(T))) return launch_colsum(BdaBwdCols<T, true>{P, (const T*)dout, (T*)dx}, P.rows, P.h, pl, dbias, (float*)ws, st);
-  return launch_colsum(BdaBwdCols<T, false>{P, (const T*)dout, (T*)dx}, P.rows, P.h, pl, dbias, (float*)ws, st);
+  return launch_colsum(BdaBwdCols<T>{P, (const T*)dout, (T*)dx}, P.rows, P.h, bda_bwd_plan(P.rows, P.h, sizeof(T) == 2), dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
   return bf16 ? bda_bwd_t<uint16_t>(P, dout, dx, dbias, ws, st) : bda_bwd_t<float>(P, dout, dx, dbias, ws, st);
 }
 
+// Which results are written past the caches?  What the pair of a pass and the reader of its result takes decides, not the pass alone: in a loop over one set of buffers,
+// where nobody reads the results, storing those of every pass past the caches from 32 or 48 MB on makes the passes up to 15 % faster (their inputs stay in the last-level cache for the next
+// round), but a reader then finds them in memory.  us, kept / past, pass and reader together, inputs not in the cache unless said otherwise (bf16; 34 / 50 / 67 / 100 / 168 MB a tensor):
+//   bias_gelu_fwd, x just written by a matrix product, y read by one of 2048 columns   148 / 148, 179 / 177, 242 / 238, 285 / 284, 472 / 465 (201 MB 492 / 481, but 268 MB 803 / 808), read by a copy
+//     45 / 48, 62 / 66, 82 / 80, 122 / 120, 210 / 196 (268 MB 349 / 337)
+//   bias_gelu_bwd, dx read by a matrix product   137 / 138, 163 / 166, 218 / 220, 256 / 262, 432 / 440, by a copy 34 / 37, 48 / 51, 67 / 67, 107 / 102, 162 / 167
+//   bias_dropout_add_bwd, likewise   130 / 132, 152 / 154, 205 / 207, 234 / 235, 390 / 399; copy 27 / 30, 38 / 42, 48 / 53, 76 / 79, 127 / 129
+//   ln_bwd, dx read by a copy (as by the pass before it)   40 / 43, 59 / 62, 74 / 76, 115 / 109, 169 / 170
+//   bias_dropout_add_ln_fwd, out and y, y read by a matrix product   141 / 142, 171 / 171, 228 / 230, 273 / 273, 461 / 459
+// and a whole MLP block, forward and backward with its products, all of them past the caches, at nine shapes between 0.986 and 1.005 of the time kept.  So only the forward of
+// the bias-GeLU, whose input a product has just left in the cache, between 64 MB, from where it gains with either reader, and the cache's 256 MB.
+static std::atomic<int> g_force_stream{-1};  // sar_test_force_forms (tests, measurements)
+void rows_force_stream(int force) { g_force_stream = force; }
+static inline bool gelu_fwd_stream(int64_t bytes) {
+  const int force = g_force_stream.load(std::memory_order_relaxed);
+  return force >= 0 ? force != 0 : bytes >= 64000000 && bytes < 256000000;
+}
+
 template <typename T>
 static hipError_t bias_gelu_fwd_t(const RowsParams& P, const void* x, const void* bias, void* y, hipStream_t st) {
   dim3 grid((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), block(256);
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)x, (const T*)bias, (T*)y); };
-  if (gelu_stream(P.rows, P.h, sizeof(T))) bias ? go(bias_gelu_fwd_kernel<T, true, true>) : go(bias_gelu_fwd_kernel<T, false, true>);
+  if (gelu_fwd_stream(P.rows * P.h * (int64_t)sizeof(T))) bias ? go(bias_gelu_fwd_kernel<T, true, true>) : go(bias_gelu_fwd_kernel<T, false, true>);
   else bias ? go(bias_gelu_fwd_kernel<T, true, false>) : go(bias_gelu_fwd_kernel<T, false, false>);
   return hipGetLastError();
 }
@@ -968,12 +964,8 @@ static hipError_t bias_gelu_bwd_t(const RowsParams& P, const void* dy, const voi
     return hipGetLastError();
   }
   const ColPlan pl = bias_gelu_bwd_plan(P.rows, P.h, sizeof(T) == 2);
-  auto go = [&](auto has_bias, auto stream) {
-    return launch_colsum(GeluBwdCols<T, decltype(has_bias)::value, decltype(stream)::value>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, pl, dbias,
-                         (float*)ws, st);
-  };
-  if (gelu_stream(P.rows, P.h, sizeof(T))) return bias ? go(std::true_type(), std::true_type()) : go(std::false_type(), std::true_type());
-  return bias ? go(std::true_type(), std::false_type()) : go(std::false_type(), std::false_type());
+  if (bias) return launch_colsum(GeluBwdCols<T, true>{P, (const T*)dy, (const T*)x, (const T*)bias, (T*)dx, {}}, P.rows, P.h, pl, dbias, (float*)ws, st);
+  return launch_colsum(GeluBwdCols<T, false>{P, (const T*)dy, (const T*)x, nullptr, (T*)dx, {}}, P.rows, P.h, pl, dbias, (float*)ws, st);
 }
 
 hipError_t launch_bias_gelu_bwd(const RowsParams& P, bool bf16, const void* dy, const void* x, const void* bias, void* dx, float* dbias, void* ws,

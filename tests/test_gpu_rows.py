@@ -271,11 +271,24 @@ def test_column_sums(rows, h, dtype):
     close(c0, ref.sum(0), "f32")
 
 
-@pytest.mark.parametrize("rows,h,dtype", [(4096, 6152, "bf16"), (1600, 8200, "f32")])
-def test_results_written_past_the_caches(rows, h, dtype):
-    """Tensors of 50 MB and more, whose results are stored nontemporally: the same references as at every size, odd widths."""
-    test_layernorm(rows, h, dtype)
-    test_bias_dropout_add_ln_fwd(rows, h, dtype, 0.1, True)
-    test_bias_dropout_add_bwd(rows, h, dtype, 0.1)
-    test_bias_gelu(rows, h, dtype, True)
-    test_bias_gelu(rows, h, dtype, False)
+@pytest.mark.parametrize("rows,h,dtype,with_bias", [(37, 1032, "bf16", True), (37, 1032, "f32", True), (5, 8, "bf16", False), (5, 8, "f32", False), (300, 12800, "bf16", False),
+                                                    (4096, 8200, "bf16", True)])
+def test_results_written_past_the_caches(rows, h, dtype, with_bias):
+    """The forward of the bias-GeLU with y stored nontemporally, in all its instantiations, forced and (67 MB) as its size has it: the reference of every
+    size, and the bits of ordinary stores."""
+    from gpu_util import DT
+    by_size = rows * h * (2 if dtype == "bf16" else 4) >= 64e6
+    try:
+        sar.sar_test_force_forms(-1, -1, -1 if by_size else 1, -1)
+        test_bias_gelu(rows, h, dtype, with_bias)
+        tdt, code = DT[dtype]
+        g = torch.Generator(device="cuda").manual_seed(rows)
+        x, bias = torch.randn(rows, h, device="cuda", generator=g).to(tdt), torch.randn(h, device="cuda", generator=g).to(tdt) if with_bias else None
+        y = [torch.full_like(x, float("nan")) for _ in range(2)]
+        for stream in (0, 1):
+            sar.sar_test_force_forms(-1, -1, stream, -1)
+            sar.bias_gelu_fwd(sar.RowsDesc.make(rows, h, dtype=code), x, bias, y[stream])
+        torch.cuda.synchronize()
+        assert torch.equal(y[0], y[1])
+    finally:
+        sar.sar_test_force_forms(-1, -1, -1, -1)
