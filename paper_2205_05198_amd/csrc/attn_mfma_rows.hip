@@ -54,6 +54,7 @@ namespace sar {
 // the scores until the sum is known; where that costs a wave per SIMD its registers (d = 96 with dropout 166 -> 176, two instead of three; d = 64
 // without 124 -> 137) the maximum stays: 2048 x 64 at d = 96 174 against 184 us (183 held to 168 registers, with spills).  Elsewhere
 // the sum: d = 160 8192 x 16 424 -> 413, d = 64 2048 x 8 without dropout 15.2 -> 14.1.
+// d = 64 with loader waves, or with 128 rows without dropout: held to 128 registers, four waves a SIMD (126 and 128 used, no spills).
 template <int D, bool DROP, int NRG, bool LW>
 constexpr bool fwd_by_max() { return NRG == 2 && !LW && (D == 96 ? DROP : D == 64 && !DROP); }
 
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(128 * NRG + (LW ? 256 : 0), D == 64 && (LW || (NRG 
     }
     // The running reference exponent moves only when a lane's sum says that a score exceeded it by about 2^60 (or is not finite):
     // the tile's probabilities are then formed again against its maximum
-    if (BYSUM && __builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= kSumLimit)) != 0, 0)) {
+    if (BYSUM && (!first_tile_skips<D, DROP>() || jt > 0) && __builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= kSumLimit)) != 0, 0)) {
       const float m_new = fmaxf(m_ref, tile_max(st));
       const float corr = __builtin_amdgcn_exp2f(m_ref - m_new);
       m_ref = m_new;
