@@ -17,6 +17,9 @@
 // With loads and Philox rounds in the consumer's and the producer's streams instead (two waves per SIMD, 256 registers), us, before / now: 2048 x 16
 // heads of 160 57.4 / 54.4, 2048 x 32 of 96 84.2 / 80.8, 8192 x 16 of 160 763 / 716; over 3693 shapes 0.942 of the time, without dropout at d = 128 and 160
 // 0.91.  Long launches run at the card's power limit: 2048 x 16 of 160 takes 6 % fewer cycles at a 3 % lower clock.
+// At 168 registers five persistent instantiations with dropout spill one to three of them, reloaded once a key block, outside the steps: d = 128 and 160 on
+// ragged sequences, d = 160 on full tiles without the dS tiles.  A launch of one to three tiles a block with more than one block a CU starts its second round later than
+// with eight waves (d = 128, 160 without dropout, 64 x 300 to 490 heads, +0.4 of 11 to 14 us).
 // The consumer works one tile behind the producer; (Q, dO) tiles live in three stages: tile m is loaded during step m-1, read
 // by the producer in step m and by the consumer in step m+1.  One workgroup barrier per step.
 // RAG: s is no multiple of 64 (the last tile's loads are clamped to the last row, and its rows and keys past the end get
@@ -125,8 +128,8 @@ __global__ __launch_bounds__(768, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
       const float lse2q = lse_s[m & 1][32 * is + li] * kLog2e - log2_keep_scale, dlq = delta_s[m & 1][32 * is + li] * inv_keep_scale;
       // The wave's instructions are ordered by hand so that its matrix instructions always have vector work of the same
       // wave beside them:
-      //   1. S^T = K Q^T            between its matrix instructions: the two Philox calls of the tile (indices only);
-      //   2. dD^T = V dO^T          between them: P = exp2(..), the keep decisions, D = P M / (1-p) (need S only);
+      //   1. S^T = K Q^T            alone (the tile's keep decisions come from the loader, sixteen bits a lane);
+      //   2. dD^T = V dO^T          between its matrix instructions: P = exp2(..), D = P M / (1-p) (need S only);
       //   3. dS = P (dD M / (1-p) - delta), rounding to bf16.
       const uint32_t keep = DROP ? keep_s[m & 1][w][lane] : 0u;
       constexpr int kAhead = 3;
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(768, 1) void attn_bwd_dkdv_split_kernel(AttnParams 
     }  // key blocks
   } else if (wave < 8) {
     // ---- consumer ----
-    __syncthreads();  // the producers have staged K and V (they read them before the first barrier of the loop)
+    __syncthreads();  // K and V are staged, by the producers or, persistent, the loaders (the producers read them before the first barrier of the loop)
     // Consumer w = (kgp, role): role 0 accumulates dV^T of the pair of producers with key group kgp (both row halves of the
     // tile) from D and dO, role 1 dK^T from dS and Q.  One accumulator set per wave, complete at the end: no merging.
     const int role = is;

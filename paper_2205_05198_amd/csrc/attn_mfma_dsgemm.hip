@@ -291,18 +291,18 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_gemm128_kernel(AttnParams 
 //   Without the mask, where all blocks are as long: 128 (d = 160 768 x 22, half a block a CU, 18.0 / 11.9; d = 128 768 x 24 13.8 / 11.2; d = 96 1024 x 80 48.1 /
 //     41.1; d = 64 2048 x 64 124 / 100), but heads of three blocks, a quarter of whose rows is padding, where that costs a second round (d >= 96 1.02 to 1.11).
 //   Under the mask the more tiles the heaviest block has, the more blocks a CU it takes to hide it: from a + b log2(nb / 8) hundredths of a 128-row block a CU
-//     (nb tiles; d = 160 1024 x 20, 0.62 a CU, 11.3 / 12.0, 768 x 32, 0.75, 11.0 / 10.5, 2048 x 16, 1.0, 22.0 / 21.5; d = 128 2048 x 12, 0.75, 15.5 / 21.8, 2048 x 16
-//     18.6 / 22.4, 2048 x 20, 1.25, 25.7 / 23.4, 4096 x 24, 3, 122 / 93; d = 96 2048 x 16 16.7 / 17.7, 1024 x 32, 1.0, 11.6 / 11.2; d = 64 2048 x 16, 1.0, 14.2 / 16.9, 2048 x
-//     20, 1.25, 19.3 / 19.1).  d = 64 holds two blocks a CU: where heads are a multiple of eight, so that a die keeps its heads' K in its L2, 4096 x 16 are all resident at
-//     once at either size (51 / 60, but 17 heads 68 / 63).
+//     (nb tiles; d = 160 1024 x 20, 0.62 a CU, 11.3 / 12.0, 768 x 32, 0.75, 11.0 / 10.5, in the whole backward after the forward 56.6 / 55.0; d = 128 2048 x 12, 0.75, 15.5 / 21.8,
+//     2048 x 16 18.6 / 22.4, 2048 x 20, 1.25, 25.7 / 23.4, 4096 x 24, 3, 122 / 93; d = 96 2048 x 16 16.7 / 17.7, 1024 x 32, 1.0, 11.6 / 11.2; d = 64 2048 x 16, 1.0, 14.2 / 16.9, 4096 x
+//     20, 2.5, 74.7 / 68.4).  Where heads are a multiple of eight a die keeps their K in its L2, which helps the 64-row form: larger b (d = 160 2048 x 16, 1.0, 22.0 / 21.5 by itself but in the
+//     whole layer's step 260.9 / 264.4; d = 64, two blocks a CU, 4096 x 16, 2.0, 51 / 60, but 17 heads 68 / 63).
 template <int D>
 static bool dq_rows128(const AttnParams& P) {
   if (const int force = g_force_dq128.load(); force >= 0) return force != 0;
   const int64_t cus = attn_mfma_cu_count(), N = (int64_t)P.b * P.A, nb = (P.s + 63) / 64, w128 = (nb + 1) / 2 * N;
   if (nb * N <= cus || (D >= 96 && nb == 3 && w128 > cus && 4 * w128 <= 5 * cus)) return false;
   if (!P.causal) return true;
-  constexpr float a = D == 160 ? 49.f : D == 64 ? 70.f : 64.f;
-  const float b = D == 160 ? 18.f : D != 64 ? 20.f : N % 8 == 0 ? 45.f : 28.f;
+  constexpr float a = D == 160 ? 49.f : D == 64 ? 70.f : 64.f, b_even[4] = {45.f, 20.f, 24.f, 26.f}, b_odd[4] = {28.f, 20.f, 20.f, 18.f};
+  const float b = N % 8 == 0 ? b_even[D / 32 - 2] : b_odd[D / 32 - 2];
   return 100.f * (float)w128 >= (a + b * (std::log2((float)nb) - 3.f)) * (float)cus;
 }
 

@@ -240,7 +240,7 @@ def test_forward_form(lib, s, heads, d, p, causal, want):
 DQ_FORMS = [
     (2048, 8, 160, 1, 0), (512, 40, 128, 0, 1), (768, 22, 160, 0, 1), (520, 60, 128, 0, 1), (2048, 20, 64, 0, 1), (320, 192, 64, 0, 1), (192, 128, 64, 0, 1),
     (192, 130, 64, 0, 1), (192, 130, 128, 0, 0), (192, 161, 128, 0, 1), (192, 130, 96, 1, 0),
-    (1024, 20, 160, 1, 0), (768, 32, 160, 1, 1), (2048, 16, 160, 1, 1), (2048, 13, 160, 1, 0), (2048, 12, 128, 1, 0), (2048, 16, 128, 1, 0), (2048, 20, 128, 1, 1), (320, 192, 128, 1, 1),
+    (1024, 20, 160, 1, 0), (768, 32, 160, 1, 1), (2048, 16, 160, 1, 0), (2048, 17, 160, 1, 1), (2048, 13, 160, 1, 0), (2048, 12, 128, 1, 0), (2048, 16, 128, 1, 0), (2048, 20, 128, 1, 1), (320, 192, 128, 1, 1),
     (2048, 16, 96, 1, 0), (1024, 32, 96, 1, 1), (2048, 32, 96, 1, 1), (2048, 16, 64, 1, 0), (2048, 21, 64, 1, 1), (4096, 16, 64, 1, 2), (4096, 17, 64, 1, 3), (8192, 16, 160, 1, 3),
 ]
 
