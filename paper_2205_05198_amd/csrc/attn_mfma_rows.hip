@@ -24,6 +24,7 @@
 // No s x s tensor is ever written; the dropout mask is regenerated from (seed, offset) in all three.
 #include "attn_mfma_common.h"
 #include <atomic>
+#include <numeric>
 #include <type_traits>
 #include "attn_mfma_fwd_pers.h"
 
@@ -593,35 +594,42 @@ int attn_mfma_cu_count() {
 
 static int cu_count() { return attn_mfma_cu_count(); }
 
-// 128-row workgroups in the forward?  From every form over 14380 shapes (s = 64 .. 8192, 1 .. 512 heads, more 64-row workgroups than CUs), each change of line
-// confirmed with both forms in turn, each warmed up by itself (6899 shapes, where this rule takes 0.86 of the time of the one before it).  w128: 128-row workgroups a CU; us,
-// 64 rows / 128 rows, p = 0.1 unless said otherwise.
-//   A K / V tile serves twice the rows.  What that is worth depends on where the tiles come from: a die (of eight) works on the heads n = its number modulo eight where the heads are a
-//   multiple of eight, on all of them otherwise (up to 96 at a time, three workgroups on each of its 32 CUs), and once their K and V are several times its 4 MB L2, tiles come from the
-//   last-level cache, whose rate bounds the 64-row forms (d = 96 2048 x 192, no mask, 19 MB a die, 907 / 548; 4096 x 85 of 128 178 MB 1601 / 1077; 3840 x 128 of 96 without dropout 1878 / 838).
-//   d = 96, 128 (several 64-row workgroups share a CU).  No mask: heads of six blocks or more whose last round is at least 0.8 full, from w128 = 1.5 (1.6 .. 2 0.85 to 0.98, 2.5 .. 3 0.75 to
-//     0.98, but 2 .. 2.5 up to 1.2), beyond 2.2 only above 8 MB a die (d = 128 2048 x 34 at 2.1 66 / 67), and at any fullness above 36 MB from 2.5 (2048 x 55 of 128 253 / 190); d = 96 up
-//     to 16 blocks from 3.5 (1024 x 128 98 / 97, others up to 1.34 slower without); five blocks, a sixth of padding, from 6, four from 3 (d = 128) and 3.5; one round of more than four.
-//     Under the mask, where the heaviest workgroup must not set the pace: above 20 MB a die from w128 = 1.5 (d = 128 1024 x 83 0.88, 4096 x 21 161 / 145, but 4096 x 20 127 / 133) or 2.5 (d = 96 2048 x 65 131 /
-//     107, 4096 x 25 169 / 151), above 7.5 in any case (0.92 to 0.98 at least), d = 96 with 12 to 24 blocks above 5.5 (1024 x 192 108 / 95); from nine blocks a head on, without
-//     dropout and an even number also six and eight above 5.5.
-//   d = 160 (one workgroup a CU).  No mask: one round; from 1.5 (0.66 to 0.9), 1.4 without dropout, heads no multiple of eight from 1.25 (768 x 59 61 / 48, but 512 x 80 31.7 / 36.1); three blocks, a
-//     quarter of padding, from 3.  Under the mask above 2; from 1.25 on heads of seven blocks or more where they are no multiple of eight (1024 x 47 49.0 / 35.5, but 1024 x 40 29.1 / 29.6) or there is no dropout,
-//     else above 1.5 from 14 blocks (0.85 to 0.93); three blocks never, five from 3.
+// 128-row workgroups in the forward?  From every form over 14380 shapes (s = 64 .. 8192, 1 .. 512 heads, more 64-row workgroups than CUs); most changes of line
+// confirmed with both forms in turn, each warmed up by itself (6899 shapes, where d = 96 and 128 are within 0.7 % of the faster of the two on average, d = 160 within 2.2 %).
+// w128: 128-row workgroups a CU; us, 64 rows / 128 rows, p = 0.1 unless said otherwise.
+//   A K / V tile serves twice the rows.  What that is worth depends on where the tiles come from.  Workgroup i runs on die i % 8 and works on head i % N, so a die meets N / gcd(N, 8) heads.  With
+//   few of them its workgroups walk the same heads side by side and one read from the last-level cache serves them all; with many, and K and V together past the die's 4 MB L2, each tile comes from the
+//   last-level cache again, whose rate then bounds the 64-row forms (d = 96, no mask, 2048 x 192, 24 heads and 19 MB a die, 907 / 548; d = 128 4096 x 85, 178 MB, 1601 / 1077; but d = 96 5824 x 18, 9 heads
+//   and 20 MB, 405 / 501).
+//   d = 96, 128 (several 64-row workgroups share a CU): from w128 = 1.5, where a die meets enough heads and their K and V are large enough.
+//     Heads: with dropout, whose arithmetic slows the walk, 16 (d = 96: 6 to 16 heads up to 1.24, 20 on 0.62 to 0.81; d = 128 under the mask 12, there long sequences only), without it 6 (d = 96) or 10, under the mask 10
+//     or 12 (d = 96, 6 to 10 heads 0.97 to 1.18, 10 to 13 above 3072 rows 0.82 to 0.87).
+//     K and V a die: no mask 6 / 10 MB (d = 96 / 128), under the mask, where the heaviest workgroup must not set the pace, 11 / 22 MB (d = 128 22 to 30 MB 0.91 to 0.98, 10 to 17 MB 1.02 to 1.1), d = 96 with dropout 9 (1024 x
+//     192 108 / 95), 18 with less than 20 heads (16 to 20 heads below it 1.0 to 1.17).  No mask below 16 / 22 MB, d = 96 with dropout up to w128 = 2.4: only where the last round is at least 0.8 full (w128 2 .. 2.3 up to 1.25,
+//     1.75 .. 2 0.83).
+//     No mask, five blocks a head, a sixth of padding, from 6, four from 3 (d = 128) and 3.5; one round of more than four.  Under the mask nine blocks on; without dropout also six and eight (d = 96 from 5.5; d = 128
+//     512 x 404 89 / 77, but seven, 448 x 463, 81 / 86).
+//   d = 160 (one workgroup a CU; many: 16 heads a die).  No mask: one round; from 1.1 on many heads (0.80 to 0.93); on fewer from 1.6 with dropout (0.86; 1.5 .. 1.6 1.01 to 1.16), above 2 with the last round at least
+//     0.8 full (1.00 to 1.14 where not), without dropout from 1.5 (0.97 to 0.76) or 1.25 of 30 blocks (0.94); three blocks, a quarter of padding, from 3.  Under the mask above 2; many heads of seven (dropout) or eight blocks
+//     on from 1.05 (0.78 to 0.93); fewer heads of 30 from 1.4 with dropout (0.94; 14 to 30 blocks 1.03 to 1.08, above 1.5 0.87 to 1.1), of 14 from 1.25 without (0.89 to 0.96); three blocks never, five from 3.
 //   d = 64, which holds two of them a CU: never with dropout (1.04 to 1.8).  Without it, no mask: whole pairs of rounds or from 3 (2048 x 64 95 / 89, 256 x 210 14.7 / 12.0, but 512 x 96 13.0 / 15.5; five
 //     blocks from 6); under the mask from 5.5 on heads of nine blocks or more (0.87 to 0.95), 3.5 of 25 (0.90 to 0.98), 6 of six.
 template <int D>
 static bool fwd_rows128(const AttnParams& P) {
   const int64_t cus = cu_count(), N = (int64_t)P.b * P.A, nrb = (P.s + 63) / 64, w128 = (P.s + 127) / 128 * N;
-  const bool drop = P.thresh != 0, apart = N % 8 != 0;
-  const int64_t w = 100 * w128 / cus;  // hundredths of a 128-row workgroup a CU
-  const int64_t kv = (apart ? std::min<int64_t>(N, 96) : N / 8) * P.s * (4 * D);  // bytes of the K and V that one die works on
+  const bool drop = P.thresh != 0;
+  const int64_t w = 100 * w128 / cus;                            // hundredths of a 128-row workgroup a CU
+  const bool full = w >= 80 * ((w128 + cus - 1) / cus);          // the last round at least 0.8 full, spread over all rounds
+  const int64_t heads = N / std::gcd(N, (int64_t)8);             // that one die meets
+  const int64_t kv = heads * P.s * (4 * D);                      // bytes of their K and V
   if (D == 160) {
+    const bool many = heads >= 16;
     if (w128 <= cus) return !P.causal;
     if (nrb == 3 || (nrb == 5 && P.causal)) return w >= 300 && (nrb != 3 || !P.causal);
-    if (w128 > 2 * cus || (nrb == 2 && w128 == 2 * cus)) return true;
-    if (P.causal) return apart || !drop ? w >= 125 && nrb >= (drop ? 7 : 8) : w > 150 && nrb >= 14;
-    return w >= 150 || (w >= (apart ? 125 : 140) && (!drop || (apart && nrb <= 12))) || (!drop && nrb >= 40);
+    if (nrb == 2 && w128 >= 2 * cus) return true;
+    if (w128 > 2 * cus) return many || P.causal || !drop || full;
+    if (P.causal) return many ? w >= 105 && nrb >= (drop ? 7 : 8) : nrb >= 14 && w >= (!drop ? 125 : nrb >= 30 ? 140 : 151);
+    return w >= (many ? 110 : drop ? 160 : nrb >= 30 ? 125 : 150);
   }
   if (D == 64) {
     if (drop) return false;
@@ -629,14 +637,15 @@ static bool fwd_rows128(const AttnParams& P) {
     const int64_t pairs = (w128 + 2 * cus - 1) / (2 * cus);  // rounds of two workgroups a CU
     return nrb >= 4 && (w >= (nrb == 5 ? 600 : 300) || 10 * w128 >= 16 * cus * pairs);
   }
+  const int64_t from = D == 96 ? (drop ? 16 : P.causal ? 10 : 6) : P.causal ? 12 : drop ? 16 : 10;
+  const bool fetched = w > 150 && heads >= from;  // the 64-row forms' tiles come from the last-level cache, given kv
   if (P.causal) {
-    if (nrb < (drop || D == 96 ? 9 : 6)) return !drop && (nrb == 6 || nrb == 8) && w >= 550;
-    return w > 750 || (kv > 20000000 && w > (D == 96 ? 250 : 150)) || (D == 96 && nrb >= 12 && nrb <= 24 && w >= 550);
+    if (nrb < 9 && (drop || (nrb != 6 && nrb != 8))) return false;
+    if (nrb < 9 && D == 96) return w >= 550;
+    return fetched && kv > (D == 128 ? 22000000 : !drop ? 11000000 : heads >= 20 ? 9000000 : 18000000);
   }
   if (w128 <= cus || nrb <= 5) return w128 <= cus ? nrb > 4 : w >= (nrb == 5 ? 600 : D == 128 ? 300 : 350) && nrb >= 4;
-  if (D == 96 && nrb <= 16 && w >= 350) return true;
-  if (w > 150 && w >= 80 * ((w128 + cus - 1) / cus)) return w <= 220 || kv > 8000000;
-  return w > 250 && kv > 36000000;
+  return fetched && kv > (D == 96 ? 6000000 : 10000000) && (full || (kv > (D == 96 ? 16000000 : 22000000) && (D == 128 || !drop || w > 240)));
 }
 
 // Form of the forward by shape, from sweeps of every form over 4256 shapes (d, s = 64 .. 8192, 4 .. 768 heads, mask, dropout): within
