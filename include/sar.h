@@ -288,7 +288,7 @@ void sar_test_force_variants(int fwd_128_rows, int fwd_loader_waves, int dq_load
  * sar_test_force_forms: more to force; the results are the same whichever runs.  Each argument: -1 = the library's choice by shape, 0 = off, 1 = on.
  *   dq_128_rows       recompute-once backward: the dQ product in blocks of 128 instead of 64 query rows
  *   ds_stream         recompute-once backward: the dS tiles written (and by the 128-row dQ product read) past the caches
- *   row_stream        bias_gelu_fwd: y written past the caches
+ *   row_stream        bias_gelu_fwd: y, bias_dropout_add_bwd with dbias: dx written past the caches
  *   cols_grid_blocks  (a number, or -1) producer / consumer column pass: most key blocks of one launch; more go in several
  */
 void sar_test_chosen_forms(const sar_attn_desc* desc, int with_tiles, int* forms);

@@ -648,8 +648,8 @@ static bool fwd_rows128(const AttnParams& P) {
   return fetched && kv > (D == 96 ? 6000000 : 10000000) && (full || (kv > (D == 96 ? 16000000 : 22000000) && (D == 128 || !drop || w > 240)));
 }
 
-// Form of the forward by shape, from sweeps of every form over 4256 shapes (d, s = 64 .. 8192, 4 .. 768 heads, mask, dropout): within
-// 0.5 % of the best form in the geometric mean.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us or differences at
+// Form of the forward by shape: the 64-row forms from sweeps of each over 4256 shapes (d, s = 64 .. 8192, 4 .. 768 heads, mask, dropout), within
+// 0.5 % of the best of them in the geometric mean.  w64, w128: workgroups of 64 and of 128 rows; below s x heads, us or differences at
 // p = 0 / 0.1.
 //   One workgroup a CU or less: loader waves (plain 5 to 31 % slower).  More:
 //   Heads of three to five blocks, one a CU: persistent workgroups where the lists are no longer than the rounds of single ones (d = 128 192 x 210

@@ -593,7 +593,7 @@ __global__ __launch_bounds__(256) void bda_bwd_kernel(RowsParams P, const T* __r
   Vec8<T>::store(dx + r * P.h + c, o);
 }
 
-template <typename T>
+template <typename T, bool STREAM>
 struct BdaBwdCols {
   static constexpr int kSums = 1;
   typedef Raw8<T> In;
@@ -616,7 +616,7 @@ struct BdaBwdCols {
       o[q] = ((keep >> q) & 1u) ? dv[q] * P.keep_scale : 0.f;
       acc[0][q] += o[q];
     }
-    Vec8<T>::store(dx + r * P.h + col, o);
+    Vec8<T>::template store<STREAM>(dx + r * P.h + col, o);
   }
 };
 
@@ -910,42 +910,46 @@ size_t bda_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16) {
   return bias_bwd_workspace_bytes(bda_bwd_plan(rows, h, bf16), bias_gelu_bwd_plan(rows, h, bf16), h);
 }
 
-template <typename T>
-static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
-  if (!dbias) {
-    hipLaunchKernelGGL((bda_bwd_kernel<T>), dim3((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), dim3(256), 0, st, P, (const T*)dout, (T*)dx);
-    return hipGetLastError();
-  }
-  return launch_colsum(BdaBwdCols<T>{P, (const T*)dout, (T*)dx}, P.rows, P.h, bda_bwd_plan(P.rows, P.h, sizeof(T) == 2), dbias, (float*)ws, st);
-}
-
-hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
-  return bf16 ? bda_bwd_t<uint16_t>(P, dout, dx, dbias, ws, st) : bda_bwd_t<float>(P, dout, dx, dbias, ws, st);
-}
-
 // Which results are written past the caches?  What the pair of a pass and the reader of its result takes decides, not the pass alone: in a loop over one set of buffers,
 // where nobody reads the results, storing those of every pass past the caches from 32 or 48 MB on makes the passes up to 15 % faster (their inputs stay in the last-level cache for the next
 // round), but a reader then finds them in memory.  us, kept / past, pass and reader together, inputs not in the cache unless said otherwise (bf16; 34 / 50 / 67 / 100 / 168 MB a tensor):
 //   bias_gelu_fwd, x just written by a matrix product, y read by one of 2048 columns   148 / 148, 179 / 177, 242 / 238, 285 / 284, 472 / 465 (201 MB 492 / 481, but 268 MB 803 / 808), read by a copy
 //     45 / 48, 62 / 66, 82 / 80, 122 / 120, 210 / 196 (268 MB 349 / 337)
 //   bias_gelu_bwd, dx read by a matrix product   137 / 138, 163 / 166, 218 / 220, 256 / 262, 432 / 440, by a copy 34 / 37, 48 / 51, 67 / 67, 107 / 102, 162 / 167
-//   bias_dropout_add_bwd, likewise   130 / 132, 152 / 154, 205 / 207, 234 / 235, 390 / 399; copy 27 / 30, 38 / 42, 48 / 53, 76 / 79, 127 / 129
+//   bias_dropout_add_bwd with dbias, likewise   130 / 132, 152 / 154, 205 / 207, 234 / 235, 390 / 399; copy 27 / 30, 38 / 42, 48 / 53, 76 / 79, 127 / 129; dout just written (by a product) 67 / 100 /
+//     134 / 168 / 200 MB: 247 / 244, 292 / 291, 429 / 419, 477 / 473, 498 / 488, copy 91 / 84, 126 / 124, 190 / 173, 217 / 202, 257 / 236 (268 MB 816 / 821, 355 / 355)
 //   ln_bwd, dx read by a copy (as by the pass before it)   40 / 43, 59 / 62, 74 / 76, 115 / 109, 169 / 170
 //   bias_dropout_add_ln_fwd, out and y, y read by a matrix product   141 / 142, 171 / 171, 228 / 230, 273 / 273, 461 / 459
-// and a whole MLP block, forward and backward with its products, all of them past the caches, at nine shapes between 0.986 and 1.005 of the time kept.  So only the forward of
-// the bias-GeLU, whose input a product has just left in the cache, between 64 MB, from where it gains with either reader, and the cache's 256 MB.
+// and a whole MLP block, forward and backward with its products, all of them past the caches, at nine shapes between 0.986 and 1.005 of the time kept.  So only below
+// the cache's 256 MB, and where the input has just been written: the forward of the bias-GeLU from 40 MB, from where it gains with the product that reads its y in an MLP (42 MB 126 / 124, 116 / 114, 254 / 254, 50 MB
+// above; with a copy from 64 MB), and bias_dropout_add_bwd, whose dout the pass before has written, from 64 MB, from where it gains with either reader (42 and 50 MB with a product 0.98 to 1.01).
 static std::atomic<int> g_force_stream{-1};  // sar_test_force_forms (tests, measurements)
 void rows_force_stream(int force) { g_force_stream = force; }
-static inline bool gelu_fwd_stream(int64_t bytes) {
+static inline bool result_stream(int64_t bytes, int64_t least) {
   const int force = g_force_stream.load(std::memory_order_relaxed);
-  return force >= 0 ? force != 0 : bytes >= 64000000 && bytes < 256000000;
+  return force >= 0 ? force != 0 : bytes >= least && bytes < 256000000;
+}
+
+template <typename T>
+static hipError_t bda_bwd_t(const RowsParams& P, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
+  if (!dbias) {
+    hipLaunchKernelGGL((bda_bwd_kernel<T>), dim3((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), dim3(256), 0, st, P, (const T*)dout, (T*)dx);
+    return hipGetLastError();
+  }
+  const ColPlan pl = bda_bwd_plan(P.rows, P.h, sizeof(T) == 2);
+  if (result_stream(P.rows * P.h * (int64_t)sizeof(T), 64000000)) return launch_colsum(BdaBwdCols<T, true>{P, (const T*)dout, (T*)dx}, P.rows, P.h, pl, dbias, (float*)ws, st);
+  return launch_colsum(BdaBwdCols<T, false>{P, (const T*)dout, (T*)dx}, P.rows, P.h, pl, dbias, (float*)ws, st);
+}
+
+hipError_t launch_bias_dropout_add_bwd(const RowsParams& P, bool bf16, const void* dout, void* dx, float* dbias, void* ws, hipStream_t st) {
+  return bf16 ? bda_bwd_t<uint16_t>(P, dout, dx, dbias, ws, st) : bda_bwd_t<float>(P, dout, dx, dbias, ws, st);
 }
 
 template <typename T>
 static hipError_t bias_gelu_fwd_t(const RowsParams& P, const void* x, const void* bias, void* y, hipStream_t st) {
   dim3 grid((unsigned)P.rows, (unsigned)(((P.h >> 3) + 255) / 256)), block(256);
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, P, (const T*)x, (const T*)bias, (T*)y); };
-  if (gelu_fwd_stream(P.rows * P.h * (int64_t)sizeof(T))) bias ? go(bias_gelu_fwd_kernel<T, true, true>) : go(bias_gelu_fwd_kernel<T, false, true>);
+  if (result_stream(P.rows * P.h * (int64_t)sizeof(T), 40000000)) bias ? go(bias_gelu_fwd_kernel<T, true, true>) : go(bias_gelu_fwd_kernel<T, false, true>);
   else bias ? go(bias_gelu_fwd_kernel<T, true, false>) : go(bias_gelu_fwd_kernel<T, false, false>);
   return hipGetLastError();
 }

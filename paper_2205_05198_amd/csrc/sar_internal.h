@@ -84,7 +84,7 @@ int attn_mfma_dq_form(const AttnParams& P);
 int attn_mfma_cu_count();  // compute units of the current device, asked once
 
 // rows.hip: LayerNorm forward/backward and bias-dropout-add on [rows, h]
-void rows_force_stream(int force);  // test hook: bias_gelu_fwd's y past the caches: -1 = by size, 0 / 1 = off / on
+void rows_force_stream(int force);  // test hook: bias_gelu_fwd's y, bias_dropout_add_bwd's dx (with dbias) past the caches: -1 = by size, 0 / 1 = off / on
 hipError_t launch_ln_fwd(const RowsParams& P, bool bf16, const void* x, const void* gamma, const void* beta, void* y, float* mean,
                          float* rstd, hipStream_t st);
 size_t ln_bwd_workspace_bytes(int64_t rows, int64_t h, bool bf16);

@@ -274,13 +274,15 @@ def test_column_sums(rows, h, dtype):
 @pytest.mark.parametrize("rows,h,dtype,with_bias", [(37, 1032, "bf16", True), (37, 1032, "f32", True), (5, 8, "bf16", False), (5, 8, "f32", False), (300, 12800, "bf16", False),
                                                     (4096, 8200, "bf16", True)])
 def test_results_written_past_the_caches(rows, h, dtype, with_bias):
-    """The forward of the bias-GeLU with y stored nontemporally, in all its instantiations, forced and (67 MB) as its size has it: the reference of every
-    size, and the bits of ordinary stores."""
+    """The forward of the bias-GeLU with y, and the backward of the dropout-add with dx stored nontemporally, in all their instantiations, forced and (67 MB) as their
+    size has it: the reference of every size, and the bits of ordinary stores."""
     from gpu_util import DT
     by_size = rows * h * (2 if dtype == "bf16" else 4) >= 64e6
     try:
         sar.sar_test_force_forms(-1, -1, -1 if by_size else 1, -1)
         test_bias_gelu(rows, h, dtype, with_bias)
+        if rows * h < 10 ** 7:
+            test_bias_dropout_add_bwd(rows, h, dtype, 0.1)
         tdt, code = DT[dtype]
         g = torch.Generator(device="cuda").manual_seed(rows)
         x, bias = torch.randn(rows, h, device="cuda", generator=g).to(tdt), torch.randn(h, device="cuda", generator=g).to(tdt) if with_bias else None
@@ -288,7 +290,13 @@ def test_results_written_past_the_caches(rows, h, dtype, with_bias):
         for stream in (0, 1):
             sar.sar_test_force_forms(-1, -1, stream, -1)
             sar.bias_gelu_fwd(sar.RowsDesc.make(rows, h, dtype=code), x, bias, y[stream])
+        desc = sar.RowsDesc.make(rows, h, dtype=code, p=0.1, seed=5)
+        ws = torch.empty(max(16, sar.bias_dropout_add_bwd_workspace(desc)), dtype=torch.uint8, device="cuda")
+        dx, dbias = [torch.full_like(x, float("nan")) for _ in range(3)], [torch.empty(h, dtype=torch.float32, device="cuda") for _ in range(3)]
+        for i, stream in enumerate((0, 1, -1)):
+            sar.sar_test_force_forms(-1, -1, stream, -1)
+            sar.bias_dropout_add_bwd(desc, x, dx[i], dbias[i], ws)
         torch.cuda.synchronize()
-        assert torch.equal(y[0], y[1])
+        assert torch.equal(y[0], y[1]) and all(torch.equal(dx[0], dx[i]) and torch.equal(dbias[0], dbias[i]) for i in (1, 2))
     finally:
         sar.sar_test_force_forms(-1, -1, -1, -1)
